@@ -46,7 +46,7 @@ struct cake_ctx {
           *t_part = nullptr;
     int32_t* t_tok = nullptr;
     void* static_scratch = nullptr;   // this device's copy of the file-scope scratch array (set by cake_create)
-    GemmSplitWs split{};       // parts and ticket counters of the split-K GEMMs (bf16 models; compute stream only)
+    GemmSplitWs split{};       // float32 parts and ticket counters of launches that split K or keys (compute stream only)
     void* q_stage = nullptr;   // device staging for quantised page images: a ring of image slots (cake_create)
     size_t q_stage_bytes = 0;
     // second hop of a file-backed store: two pinned buffers of one DMA piece each
@@ -180,6 +180,9 @@ static hipError_t gemm(cake_ctx* c, int epi, const void* a, const void* w, const
 static hipError_t attention(cake_ctx* c, const void* q, void* out, int tok_begin, int rows, const KvView& kv) {
     if (c->m.dtype == CAKE_BF16 && c->tun.kernel_path == 0 && attention_mfma_supported(kv.head_dim, kv.page_tokens))
         return launch_attention_mfma(q, out, c->m.n_q_heads, tok_begin, rows, kv, c->cs, c->tun.attn_variant);
+    if (c->m.dtype == CAKE_F32 && c->tun.kernel_path == 0 && attention_f32_supported(q, out, kv))
+        return launch_attention_f32((const float*)q, (float*)out, c->m.n_q_heads, tok_begin, rows, kv, c->cs, c->split.part,
+                                    c->split.part_bytes);
     return launch_attention_generic(c->m.dtype, q, out, c->m.n_q_heads, tok_begin, rows, kv, c->cs);
 }
 
@@ -519,7 +522,7 @@ int32_t cake_create(cake_ctx** out, const cake_model_desc* model, const cake_wei
     ok = ok && hipMalloc(&c->act, R * m.ffn_dim * e) == hipSuccess;
     ok = ok && hipMalloc((void**)&c->rope_cs, R * m.head_dim * 4) == hipSuccess;
     ok = ok && hipMalloc((void**)&c->d_ids, size_t(max_tokens) * 4) == hipSuccess;
-    if (m.dtype == CAKE_BF16) {
+    {
         // room for 256 workgroups' float32 tiles of 256 x 256, less for a small model
         const size_t rows_up = (R + 255) / 256 * 256;
         c->split.part_bytes = std::min<size_t>(size_t(64) << 20, 8 * rows_up * std::max<size_t>(m.d_model, nqkv) * 4);

@@ -37,6 +37,16 @@ hipError_t launch_gemm_generic(int dtype, int epi, const void* a, const void* w,
 hipError_t launch_attention_generic(int dtype, const void* q, void* out, int n_q, int tok_begin,
                                     int rows, const KvView& kv, hipStream_t st);
 
+// ---- float32 on the matrix cores ----
+// part (or null): workspace for the key ranges of a launch with few queries; launches sharing it must not overlap.
+bool attention_f32_supported(const void* q, const void* out, const KvView& kv);
+hipError_t launch_attention_f32(const float* q, float* out, int n_q, int tok_begin, int rows, const KvView& kv,
+                                hipStream_t st, float* part, size_t part_bytes);
+// Adds up the key ranges of a split attention launch: part[split][head][row][head_dim + 2] (O, reference of
+// the exponentials, row sum) -> out[row][head][head_dim].
+hipError_t launch_attention_merge(int dtype, int head_dim, const float* part, void* out, int n_q, int rows, int splits,
+                                  hipStream_t st);
+
 // ---- MFMA kernels (bf16) ----
 bool gemm_mfma_supported(int epi, int M, int N, int K);
 // Workspace of the split-K GEMMs: float32 parts of the tiles in flight, and one ticket counter per

@@ -1,0 +1,76 @@
+"""Attention kernels whose keys may be divided among workgroups, through cake_op_attention against the oracle: the
+edges of query and key tiles, short and long prefixes (one key range and many), grouped queries, both head sizes,
+and values that a query must not see."""
+import numpy as np
+import pytest
+
+import synth_inputs as si
+from oracle import store as ostore
+from oracle import transformer as otf
+
+pytestmark = pytest.mark.gpu
+
+
+def _case(kind, hd, n_q, n_kv, tok_begin, rows, pt, seed=0, attn_variant=0):
+    """(engine, q on the GPU, q / K / V as the kernel sees them in float64)."""
+    import torch
+    import paper_2410_03065_amd as cake
+    shape = si.ModelShape("attn-splits", 1, 256, n_q, n_kv, hd, 512, 64, kind, rope_theta=500000.0)
+    T = tok_begin + rows
+    n_log = (T + pt - 1) // pt
+    bt = np.random.default_rng(3).permutation(n_log).astype(np.int32)
+    eng = cake.Engine(shape, None, max_tokens=n_log * pt, max_chunk=min(1024, n_log * pt), page_tokens=pt, block_table=bt)
+    eng.set_tuning(attn_variant=attn_variant)
+    rng = np.random.default_rng(seed + rows)
+    cache = otf.KVCache(1, T, n_kv, hd)
+    cache.k[0] = otf.round_storage(rng.standard_normal((T, n_kv, hd)) * 1.5, kind)
+    cache.v[0] = otf.round_storage(rng.standard_normal((T, n_kv, hd)), kind)
+    eng.set_store(ostore.pack_store(cache, pt, kind))
+    eng.load_chunk(0, T)
+    q = otf.round_storage(rng.standard_normal((rows, n_q, hd)), kind)
+    Q = torch.from_numpy(q.transpose(1, 0, 2).astype(np.float32).copy()).cuda().to(eng.tdtype)
+    return eng, Q, q, cache.k[0], cache.v[0]
+
+
+def _check(kind, eng, Q, q, k, v, tok_begin, tol):
+    rows, n_q, hd = q.shape
+    got = eng.op_attention(Q, 0, tok_begin).float().cpu().numpy().reshape(rows, n_q, hd)
+    want = otf.attention(q, k, v, np.arange(tok_begin, tok_begin + rows), np.arange(tok_begin + rows))
+    err = float(np.abs(got - want).max() / np.abs(want).max())
+    print("attention %s: largest error %.2e of the largest value" % (kind, err))
+    assert err < tol, err
+
+
+# float32: a score is a sum of hd products (error below hd * 2^-24 of a magnitude of at most about 30 here), it acts
+# in the exponent, and the result is a weighted mean: 64 * 6e-8 * 5 = 2e-5
+@pytest.mark.parametrize("hd,n_q,n_kv", [(64, 4, 4), (128, 8, 2)])
+@pytest.mark.parametrize("tok_begin,rows,pt", [(0, 1, 64), (0, 33, 64), (31, 32, 64), (300, 95, 128), (1792, 256, 128), (6001, 7, 256)])
+def test_attention_f32(hd, n_q, n_kv, tok_begin, rows, pt):
+    _check("f32", *_case("f32", hd, n_q, n_kv, tok_begin, rows, pt), tok_begin, 2e-5)
+
+
+def _poisoned(kind, hd, n_q, n_kv, tok_begin, rows, pt, bad_row, tol):
+    """A NaN in V of row `bad_row` of the chunk, and NaNs in the page slots past its last token: the rows before
+    `bad_row` are unaffected, it and the rows after it become NaN."""
+    import torch
+    eng, Q, q, k, v = _case(kind, hd, n_q, n_kv, tok_begin, rows, pt)
+    T = tok_begin + rows
+    pages = eng.pool[0].view(eng.kv.n_physical_pages, 2, -1)
+    bt = eng.block_table_host
+    vt = pages[:, 1].view(-1, n_kv, hd, pt)
+    p, t = divmod(tok_begin + bad_row, pt)
+    vt[int(bt[p]), :, 0, t] = float("nan")
+    if T % pt:
+        vt[int(bt[T // pt]), :, :, T % pt:] = float("nan")
+        pages[:, 0].view(-1, n_kv, pt, hd)[int(bt[T // pt]), :, T % pt:] = float("inf")
+    torch.cuda.synchronize()
+    got = eng.op_attention(Q, 0, tok_begin).float().cpu().numpy().reshape(rows, n_q, hd)
+    want = otf.attention(q, k, v, np.arange(tok_begin, T), np.arange(T))
+    clean = got.copy()
+    clean[bad_row:, :, 0] = want[bad_row:, :, 0]
+    assert np.isnan(got[bad_row:, :, 0]).all()
+    assert float(np.abs(clean - want).max() / np.abs(want).max()) < tol
+
+
+def test_attention_f32_hidden_values_do_not_leak():
+    _poisoned("f32", 64, 4, 2, 200, 77, 128, 50, 2e-5)
