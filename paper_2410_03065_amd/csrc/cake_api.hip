@@ -174,13 +174,15 @@ static hipError_t gemm(cake_ctx* c, int epi, const void* a, const void* w, const
     if (c->m.dtype == CAKE_BF16 && c->tun.kernel_path == 0 && gemm_mfma_supported(epi, M, N, K))
         return launch_gemm_mfma(epi, a, w, w2, out, M, N, K, c->cs, c->tun.gemm_config - 1, c->split.part ? &c->split : nullptr,
                                 c->tun.gemm_ksplit);
+    if (c->m.dtype == CAKE_F32 && c->tun.kernel_path == 0 && ((uintptr_t(a) | uintptr_t(w) | uintptr_t(w2)) & 15) == 0)
+        return launch_gemm_f32(epi, (const float*)a, (const float*)w, (const float*)w2, (float*)out, M, N, K, c->cs);
     return launch_gemm_generic(c->m.dtype, epi, a, w, w2, out, M, N, K, c->cs);
 }
 
 static hipError_t attention(cake_ctx* c, const void* q, void* out, int tok_begin, int rows, const KvView& kv) {
     if (c->m.dtype == CAKE_BF16 && c->tun.kernel_path == 0 && attention_mfma_supported(kv.head_dim, kv.page_tokens))
         return launch_attention_mfma(q, out, c->m.n_q_heads, tok_begin, rows, kv, c->cs, c->tun.attn_variant);
-    if (c->m.dtype == CAKE_F32 && c->tun.kernel_path == 0 && attention_f32_supported(q, out, kv))
+    if (c->m.dtype == CAKE_F32 && c->tun.kernel_path == 0 && attention_f32_supported(q, tok_begin + rows, kv))
         return launch_attention_f32((const float*)q, (float*)out, c->m.n_q_heads, tok_begin, rows, kv, c->cs, c->split.part,
                                     c->split.part_bytes);
     return launch_attention_generic(c->m.dtype, q, out, c->m.n_q_heads, tok_begin, rows, kv, c->cs);

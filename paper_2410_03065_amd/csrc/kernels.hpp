@@ -39,9 +39,11 @@ hipError_t launch_attention_generic(int dtype, const void* q, void* out, int n_q
 
 // ---- float32 on the matrix cores ----
 // part (or null): workspace for the key ranges of a launch with few queries; launches sharing it must not overlap.
-bool attention_f32_supported(const void* q, const void* out, const KvView& kv);
+bool attention_f32_supported(const void* q, int n_keys, const KvView& kv);
 hipError_t launch_attention_f32(const float* q, float* out, int n_q, int tok_begin, int rows, const KvView& kv,
                                 hipStream_t st, float* part, size_t part_bytes);
+hipError_t launch_gemm_f32(int epi, const float* a, const float* w, const float* w2, float* out, int M, int N, int K,
+                           hipStream_t st);
 // Adds up the key ranges of a split attention launch: part[split][head][row][head_dim + 2] (O, reference of
 // the exponentials, row sum) -> out[row][head][head_dim].
 hipError_t launch_attention_merge(int dtype, int head_dim, const float* part, void* out, int n_q, int rows, int splits,

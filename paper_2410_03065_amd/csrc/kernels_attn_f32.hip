@@ -26,7 +26,7 @@ typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 //
 // What bounds it: the float32 matrix rate where there are enough queries; for the few queries of a small model's
 // chunk the number of waves, hence the key ranges (launch_attention_f32).  256 rows x 4 heads x 64 against 2048
-// keys: 19 us with the merge, against 352 us for one wave per row and query head with a lane per key, whose 64
+// keys: 17 us with the merge, against 352 us for one wave per row and query head with a lane per key, whose 64
 // lanes each walked a key row of their own (one cache line per lane and load).
 // =====================================================================================
 constexpr int FQ = 32, FK = 32;
@@ -228,9 +228,10 @@ hipError_t launch_attention_merge(int dtype, int head_dim, const float* part, vo
     return hipGetLastError();
 }
 
-// 16-byte reads of q and of the pages
-bool attention_f32_supported(const void* q, const void* out, const KvView& kv) {
-    return (kv.head_dim == 64 || kv.head_dim == 128) && kv.page_tokens % 64 == 0 && ((uintptr_t(q) | uintptr_t(out) | uintptr_t(kv.pool)) & 15) == 0;
+// 16-byte reads of q and of the pages.  Below one key tile the kernel with a wave per row and head is as fast or
+// faster (16 heads x 64, us: 8 rows of 8 keys 3.9 against 6.3, 24 of 24 5.3 against 6.1, 32 of 32 6.0 against 5.8).
+bool attention_f32_supported(const void* q, int n_keys, const KvView& kv) {
+    return n_keys >= FK && (kv.head_dim == 64 || kv.head_dim == 128) && kv.page_tokens % 64 == 0 && ((uintptr_t(q) | uintptr_t(kv.pool)) & 15) == 0;
 }
 
 // Key ranges: enough workgroups for two per CU, as long as every wave of a range still has two tiles to overlap

@@ -1,0 +1,161 @@
+// Float32 GEMM on the matrix cores: out[M][N] = a[M][K] * w[N][K]^T and the same epilogues as the bf16 GEMMs
+// (the projections of a float32 model, Sec. 3).  Any M and N, K a multiple of 4.
+//
+// MFMA used: v_mfma_f32_16x16x4_f32.  For D[16x16] += A[16x4] * B[4x16] lane l supplies A[l%16][l/16] and
+// B[l/16][l%16] and holds D[4*(l/16) + v][l%16] in accumulator register v (0..3).  Both operands use the same
+// permutation of K, so a lane reads 16 bytes of its row (elements 16b + 4*(l/16) .. + 3) for four MFMAs.
+//
+// A wave owns T x T MFMA tiles; the four waves of a workgroup stand SP x SP over the output (SP = 1 or 2) or, where
+// SP = 1, divide K among them, 16 * KB elements at a time, and add up through LDS.  Operands go straight to
+// registers, the next 16 * KB elements of K on their way while the present ones are multiplied.
+//
+// What bounds it: for the products of a small model's chunk the number of waves and the latency of a walk along K,
+// so the tile shrinks until the grid fills the chip and K is divided (256 rows of the tiny model, us a launch:
+// 256 -> 768 18 -> 7, 256 -> 688 twice with SwiGLU 35 -> 9.5, 688 -> 256 48 -> 5); for large products the float32
+// matrix rate, fed from L2 through tiles of 64 x 64 per wave (1024 x 4096 x 4096: 492 -> 323 us, 106 TFLOP/s, both
+// against the 64 x 64 tiles on the vector ALUs of the generic kernel).
+#include "kernels.hpp"
+
+namespace cake {
+
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
+
+template <int T, int SP, int EPI>
+__global__ void __launch_bounds__(256)
+gemm_f32_kernel(const float* __restrict__ a, const float* __restrict__ w, const float* __restrict__ w2, float* __restrict__ out,
+                int M, int N, int K, int tiles_m) {
+    constexpr int KW = SP == 1 ? 4 : 1;              // waves that divide K
+    constexpr int NM = EPI == EPI_SWIGLU ? 2 : 1;    // weight matrices
+    constexpr int KB = NM * T > 4 ? 1 : 2;           // 16-deep blocks per trip (one where 64 x 64 twice fill the registers)
+    constexpr int BT = 16 * T * SP;                  // rows and columns of the workgroup's tile
+    __shared__ float4 parts[KW > 1 ? (KW - 1) * NM * T * T * 64 : 1];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int l16 = lane & 15, lq = lane >> 4;
+    const int kw = SP == 1 ? wave : 0, wm = SP == 1 ? 0 : wave >> 1, wn = SP == 1 ? 0 : wave & 1;
+    const int m0 = (blockIdx.x % tiles_m) * BT + wm * 16 * T, n0 = (blockIdx.x / tiles_m) * BT + wn * 16 * T;
+
+    const float *ap[T], *wp[NM][T];
+#pragma unroll
+    for (int i = 0; i < T; ++i) {
+        ap[i] = a + size_t(min(m0 + 16 * i + l16, M - 1)) * K + 4 * lq;
+        wp[0][i] = w + size_t(min(n0 + 16 * i + l16, N - 1)) * K + 4 * lq;
+        if constexpr (NM == 2) wp[1][i] = w2 + size_t(min(n0 + 16 * i + l16, N - 1)) * K + 4 * lq;
+    }
+    auto ld = [&](const float* p, int k) { return k + 4 * lq < K ? *(const float4*)(p + k) : make_float4(0.f, 0.f, 0.f, 0.f); };
+    auto load = [&](float4 (&av)[T][KB], float4 (&wv)[NM][T][KB], int k0) {
+#pragma unroll
+        for (int b = 0; b < KB; ++b) {
+#pragma unroll
+            for (int i = 0; i < T; ++i) av[i][b] = ld(ap[i], k0 + 16 * b);
+#pragma unroll
+            for (int n = 0; n < NM; ++n)
+#pragma unroll
+                for (int j = 0; j < T; ++j) wv[n][j][b] = ld(wp[n][j], k0 + 16 * b);
+        }
+    };
+    f32x4 acc[NM][T][T];
+#pragma unroll
+    for (int n = 0; n < NM; ++n)
+#pragma unroll
+        for (int i = 0; i < T; ++i)
+#pragma unroll
+            for (int j = 0; j < T; ++j) acc[n][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto mul = [&](const float4 (&av)[T][KB], const float4 (&wv)[NM][T][KB]) {
+#pragma unroll
+        for (int b = 0; b < KB; ++b)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int n = 0; n < NM; ++n)
+#pragma unroll
+                    for (int i = 0; i < T; ++i)
+#pragma unroll
+                        for (int j = 0; j < T; ++j)
+                            acc[n][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(((const float*)&av[i][b])[e], ((const float*)&wv[n][j][b])[e],
+                                                                                acc[n][i][j], 0, 0, 0);
+    };
+    float4 av[2][T][KB], wv[2][NM][T][KB];
+    int k = 16 * KB * kw;
+    constexpr int STEP = 16 * KB * KW;
+    if (k < K) load(av[0], wv[0], k);
+    for (; k < K; k += 2 * STEP) {   // two trips unrolled, so that the two register sets alternate without copies
+        if (k + STEP < K) load(av[1], wv[1], k + STEP);
+        mul(av[0], wv[0]);
+        if (k + STEP >= K) break;
+        if (k + 2 * STEP < K) load(av[0], wv[0], k + 2 * STEP);
+        mul(av[1], wv[1]);
+    }
+    if constexpr (KW > 1) {   // waves 1 .. 3 hand their sums to wave 0, which adds them in that order
+        if (wave > 0) {
+#pragma unroll
+            for (int n = 0; n < NM; ++n)
+#pragma unroll
+                for (int i = 0; i < T; ++i)
+#pragma unroll
+                    for (int j = 0; j < T; ++j) {
+                        const f32x4 v = acc[n][i][j];
+                        parts[(((wave - 1) * NM + n) * T * T + i * T + j) * 64 + lane] = make_float4(v[0], v[1], v[2], v[3]);
+                    }
+        }
+        __syncthreads();
+        if (wave > 0) return;
+#pragma unroll
+        for (int p = 0; p < KW - 1; ++p)
+#pragma unroll
+            for (int n = 0; n < NM; ++n)
+#pragma unroll
+                for (int i = 0; i < T; ++i)
+#pragma unroll
+                    for (int j = 0; j < T; ++j) {
+                        const float4 v = parts[((p * NM + n) * T * T + i * T + j) * 64 + lane];
+                        acc[n][i][j][0] += v.x; acc[n][i][j][1] += v.y; acc[n][i][j][2] += v.z; acc[n][i][j][3] += v.w;
+                    }
+    }
+#pragma unroll
+    for (int i = 0; i < T; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int row = m0 + 16 * i + 4 * lq + v;
+            if (row >= M) continue;
+#pragma unroll
+            for (int j = 0; j < T; ++j) {
+                const int col = n0 + 16 * j + l16;
+                if (col >= N) continue;
+                float* o = out + size_t(row) * N + col;
+                const float x = acc[0][i][j][v];
+                if constexpr (EPI == EPI_STORE_F32) *o = x;
+                else if constexpr (EPI == EPI_RESIDUAL_F32) *o += x;
+                else *o = x / (1.0f + expf(-x)) * acc[1][i][j][v];
+            }
+        }
+}
+
+template <int T, int SP, int EPI>
+static hipError_t launch_t(const float* a, const float* w, const float* w2, float* out, int M, int N, int K, hipStream_t st) {
+    constexpr int BT = 16 * T * SP;
+    const int tiles_m = (M + BT - 1) / BT, tiles_n = (N + BT - 1) / BT;
+    hipLaunchKernelGGL((gemm_f32_kernel<T, SP, EPI>), dim3(tiles_m * tiles_n), dim3(256), 0, st, a, w, w2, out, M, N, K, tiles_m);
+    return hipGetLastError();
+}
+
+// The largest tile whose grid still gives most CUs a workgroup: 128 x 128 (64 x 64 per wave); 64 x 64, 32 x 32 or
+// 16 x 16 with the waves dividing K.  (512 x 4096 x 1024: 58 us on 64 x 64 tiles, 78 on 32 x 32, 72 generic.)
+template <int EPI>
+static hipError_t launch_epi(const float* a, const float* w, const float* w2, float* out, int M, int N, int K, hipStream_t st) {
+    auto tiles = [&](long t) { return ((M + t - 1) / t) * ((N + t - 1) / t); };
+    if (tiles(128) >= 192) return launch_t<4, 2, EPI>(a, w, w2, out, M, N, K, st);
+    if (tiles(64) >= 160) return launch_t<4, 1, EPI>(a, w, w2, out, M, N, K, st);
+    if (tiles(32) >= 160) return launch_t<2, 1, EPI>(a, w, w2, out, M, N, K, st);
+    return launch_t<1, 1, EPI>(a, w, w2, out, M, N, K, st);
+}
+
+hipError_t launch_gemm_f32(int epi, const float* a, const float* w, const float* w2, float* out, int M, int N, int K, hipStream_t st) {
+    if (M <= 0 || N <= 0) return hipSuccess;
+    if (K <= 0 || (K & 3)) return hipErrorInvalidValue;
+    if (epi == EPI_STORE_F32) return launch_epi<EPI_STORE_F32>(a, w, w2, out, M, N, K, st);
+    if (epi == EPI_RESIDUAL_F32) return launch_epi<EPI_RESIDUAL_F32>(a, w, w2, out, M, N, K, st);
+    if (epi == EPI_SWIGLU) return launch_epi<EPI_SWIGLU>(a, w, w2, out, M, N, K, st);
+    return hipErrorInvalidValue;
+}
+
+}  // namespace cake

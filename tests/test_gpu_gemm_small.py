@@ -1,0 +1,45 @@
+"""GEMM kernels for few rows and for float32 models, through the C ABI's op calls against a float64 product: every
+tile of the dispatch, with rows, columns and K that end inside one."""
+import numpy as np
+import pytest
+
+import synth_inputs as si
+
+pytestmark = pytest.mark.gpu
+
+
+def _products(kind, M, N, K):
+    """max |error| / max |value| of the three epilogues (SwiGLU: largest error over 2^-8 resp. 2^-17 of each value)."""
+    import torch
+    import paper_2410_03065_amd as cake
+    shape = si.ModelShape("gemm-small", 1, 256, 4, 4, 64, 512, 64, kind)
+    eng = cake.Engine(shape, None, max_tokens=1024, max_chunk=1024, page_tokens=64)
+    g = torch.Generator(device="cuda").manual_seed(M * 7 + N + K)
+    mk = lambda r, c, std: (torch.randn(r, c, device="cuda", generator=g) * std).to(eng.tdtype)
+    a, w, w2 = mk(M, K, 1.0), mk(N, K, 0.05), mk(N, K, 0.05)
+    x0 = torch.randn(M, N, device="cuda", generator=g)
+    want = a.double() @ w.double().t().contiguous()
+    up = a.double() @ w2.double().t().contiguous()
+    x = x0.clone()
+    torch.cuda.synchronize()       # the engine's streams do not wait for torch's
+    rel = lambda got, ref: float((got.double() - ref).abs().max() / ref.abs().max())
+    plain = rel(eng.op_gemm(a, w), want)
+    again = torch.equal(eng.op_gemm(a, w), eng.op_gemm(a, w))
+    residual = rel(eng.op_gemm_residual(a, w, x), x0.double() + want)
+    ref = torch.nn.functional.silu(want) * up
+    got = eng.op_gemm_swiglu(a, w, w2).double()
+    bound = (2.0 ** -17 if kind == "f32" else 2.0 ** -8 * 1.01) * ref.abs() + 1e-6 * ref.abs().max()
+    return plain, residual, float(((got - ref).abs() / bound).max()), again
+
+
+# float32 sums over K: 2e-6 of the largest value up to K = 256 and in proportion beyond (a bound of K * 2^-24 on a
+# sum's relative error, taken at the spread of these operands)
+@pytest.mark.parametrize("M,N,K", [
+    (1, 5, 8), (17, 15, 40), (256, 256, 256), (33, 1376, 72),         # 16 x 16 tiles, K in fewer and more pieces than waves
+    (256, 768, 256), (500, 321, 104),                                 # 32 x 32
+    (1000, 1300, 136), (1024, 3072, 96),                              # 64 x 64 and 128 x 128
+])
+def test_gemm_f32(M, N, K):
+    plain, residual, swiglu, again = _products("f32", M, N, K)
+    tol = 2e-6 * max(1, K / 256)
+    assert plain < tol and residual < tol and swiglu < 1.0 and again, (plain, residual, swiglu, again)
