@@ -76,6 +76,11 @@ bool attention_mfma_supported(int head_dim, int page_tokens);
 hipError_t launch_attention_mfma(const void* q, void* out, int n_q, int tok_begin, int rows,
                                  const KvView& kv, hipStream_t st, int variant = 0);
 
+// bf16, head_dim 64; part as for launch_attention_f32
+bool attention_hd64_supported(const void* q, const void* out, int n_keys, const KvView& kv);
+hipError_t launch_attention_hd64(const void* q, void* out, int n_q, int tok_begin, int rows, const KvView& kv,
+                                 hipStream_t st, float* part, size_t part_bytes);
+
 bool decode_attention_mfma_supported(int dtype, int head_dim, int page_tokens, int r);
 hipError_t launch_decode_attention_mfma(const float* q, float* part, int n_q, int n_keys, int tiles_per_split,
                                         int n_splits, const KvView& kv, hipStream_t st);

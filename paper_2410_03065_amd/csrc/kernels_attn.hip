@@ -6,6 +6,8 @@
 // MFMA shape used throughout: v_mfma_f32_32x32x16_bf16.  For D[32x32] += A[32x16] * B[16x32]
 // lane l supplies A[l%32][8*(l/32) .. +7] and B[8*(l/32) .. +7][l%32], and holds
 // D[8*(v/4) + 4*(l/32) + v%4][l%32] in accumulator register v (0..15).
+#include <algorithm>
+#include <cfloat>
 #include <type_traits>
 
 #include "kernels.hpp"
@@ -15,6 +17,7 @@ namespace cake {
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
@@ -683,6 +686,251 @@ attention_mfma8_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, i
 }
 
 // =====================================================================================
+// Head dimension 64: eight waves as above (QW x 32 queries, the two wave halves on alternate 64-key tiles), K and
+// V^T tiles of 8 KB in two LDS slots per half, filled one pair ahead by direct loads.
+//
+// Nothing is rounded that the one-wave-per-row kernel keeps in float32: the softmax scale stays out of Q (it is
+// applied in the exponent's multiply-add) and a probability enters the second product as the sum of two bf16 values
+// (the nearest, and the nearest to what that leaves: 16 bits), so P V takes two MFMAs per tile instead of one.
+//
+// What bounds it: the vector work per score (exponential, running sum, two conversions and a subtraction) against
+// 24 MFMAs per 64 x 32 scores.  Two workgroups share a CU, so that four waves per SIMD cover each other's waits.
+// 512 rows x 32 heads (8 KV heads) against 2048 keys: 35 us, against 5203 us for the one-wave-per-row kernel; 1024 rows
+// against 31K keys 493 us (519 TFLOP/s, 780 with the doubled P V), 556 while the registers held one workgroup per CU.
+// =====================================================================================
+constexpr int H64_TILE = AK * 64 * 2, H64_GROUP = 4 * H64_TILE, H64_TABLE = 2 * H64_GROUP;
+
+template <int QW>
+__global__ void __launch_bounds__(128 * QW)
+attention_hd64_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, float* __restrict__ part, int n_q, int tok_begin,
+                      int rows, KvView kv, int pairs_per_split) {
+    constexpr int HD = 64, AQW = 32 * QW, PER = 8 / QW;
+    extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave8 = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = wave8 % QW, grp = wave8 / QW;
+    const int lrow = lane & 31, lhalf = lane >> 5;
+    const int G = kv.n_kv, r = n_q / G;
+    int g, rest;   // workgroups that share a KV head go to the same XCD
+    if ((G & 7) == 0) {
+        const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3, gpx = G >> 3;
+        g = xcd + 8 * (idx % gpx);
+        rest = idx / gpx;
+    } else {
+        g = blockIdx.x % G;
+        rest = blockIdx.x / G;
+    }
+    const int h = g * r + rest % r, q0 = (rest / r) * AQW, split = blockIdx.y;
+    const int pt = kv.page_tokens;
+    const int my_pos = tok_begin + min(q0 + wave * 32 + lrow, rows - 1);
+    const int wave_first_pos = tok_begin + min(q0 + wave * 32, rows - 1);
+    const int wg_last_pos = tok_begin + min(q0 + AQW, rows) - 1;
+    const int n_tiles = wg_last_pos / AK + 1;
+    const int pair_lo = split * pairs_per_split, pair_hi = min(pair_lo + pairs_per_split, (n_tiles + 1) >> 1);
+    const int first_masked = (wave_first_pos + 1) / AK;   // first tile with a key some query of this wave must not see
+
+    bf16x8 qreg[HD / 16];
+    {
+        const bf16_t* qp = q + (size_t(h) * rows + (my_pos - tok_begin)) * HD + 8 * lhalf;
+#pragma unroll
+        for (int ks = 0; ks < HD / 16; ++ks) qreg[ks] = *(const bf16x8*)(qp + 16 * ks);
+    }
+    // wave-load j of a tile covers its rows 8j .. 8j + 7 (128 B each); chunk c of row x is stored at c ^ ((x >> 1) & 7)
+    unsigned koff[PER], voff[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int row = 8 * (wave + QW * i) + (lane >> 3), c = (lane & 7) ^ ((row >> 1) & 7);
+        koff[i] = unsigned(row * HD + c * 8) * 2u;
+        voff[i] = unsigned(row * pt + c * 8) * 2u;
+    }
+    unsigned long long* pg_lds = (unsigned long long*)(lds + H64_TABLE);
+    {
+        const size_t layer_base = size_t(kv.layer) * kv.n_physical_pages;
+        const size_t page_bytes = kv.page_elems() * 2, k_head = size_t(g) * pt * HD * 2;
+        for (int i = tid; i <= wg_last_pos / pt; i += 128 * QW) pg_lds[i] = (layer_base + kv.block_table[i]) * page_bytes + k_head;
+    }
+    __syncthreads();
+    const unsigned long long k_to_v = (size_t(G - g) * pt * HD + size_t(g) * HD * pt) * 2;
+    unsigned char* ring = lds + grp * H64_GROUP;          // slot s: K at 2 s tiles, V^T right after it
+    auto page_of = [&](int key0) {                        // K block of head g in the page of a key (wave-uniform)
+        const unsigned long long off = pg_lds[key0 / pt];
+        const unsigned long long lo = (unsigned)__builtin_amdgcn_readfirstlane((int)unsigned(off));
+        const unsigned long long hi = (unsigned)__builtin_amdgcn_readfirstlane((int)unsigned(off >> 32));
+        return (const char*)kv.pool + ((hi << 32) | lo);
+    };
+    auto issue = [&](int pair) {
+        const int tile = min(2 * pair + grp, n_tiles - 1);   // a tile past the end re-reads the last one (it is masked)
+        const char* page = page_of(tile * AK);
+        const size_t in_page0 = size_t(tile * AK % pt);
+        const char *kp = page + in_page0 * (HD * 2), *vp = page + k_to_v + in_page0 * 2;
+        unsigned char* sa = ring + (pair & 1) * 2 * H64_TILE;
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
+            __builtin_amdgcn_global_load_lds((const CAKE_GLOBAL_AS void*)(kp + koff[i]), (CAKE_LDS_AS void*)(sa + (wave + QW * i) * 1024), 16, 0, 0);
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
+            __builtin_amdgcn_global_load_lds((const CAKE_GLOBAL_AS void*)(vp + voff[i]), (CAKE_LDS_AS void*)(sa + H64_TILE + (wave + QW * i) * 1024), 16, 0, 0);
+    };
+    const int sk = sigma16(lrow & 15), sv = (lrow >> 1) & 7;
+    int kaddr[HD / 16], vaddr[4];
+#pragma unroll
+    for (int ks = 0; ks < HD / 16; ++ks) kaddr[ks] = (16 * (lrow >> 4) + sk) * 128 + (((2 * ks + lhalf) ^ ((sk >> 1) & 7)) << 4);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) vaddr[j] = H64_TILE + lrow * 128 + (((2 * j + lhalf) ^ sv) << 4);
+
+    const f32x16 zero16 = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+    f32x16 o[2] = {zero16, zero16};
+    float m_run = -FLT_MAX, l_part = 0.f;
+    const float sl2 = 0.125f * 1.4426950408889634f;   // 1/sqrt(64) * log2(e)
+    constexpr float RESCALE_LOG2 = 6.0f;              // the reference follows the running maximum lazily, as above
+
+    unsigned left_out = 0;   // tiles, counted from first_masked (a wave has at most four there)
+
+    if (pair_lo < pair_hi) issue(pair_lo);
+    for (int pair = pair_lo; pair < pair_hi; ++pair) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        if (pair + 1 < pair_hi) issue(pair + 1);
+        const unsigned char* st = ring + (pair & 1) * 2 * H64_TILE;
+        const int tile = 2 * pair + grp;
+        f32x16 s[2];
+#pragma unroll
+        for (int ks = 0; ks < HD / 16; ++ks)
+#pragma unroll
+            for (int t = 0; t < 2; ++t) s[t] = mfma32(*(const bf16x8*)(st + t * 32 * 128 + kaddr[ks]), qreg[ks], ks == 0 ? zero16 : s[t]);
+        const bool masked = tile >= first_masked;   // also a tile past the end
+        if (masked) {
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    if (tile * AK + 32 * t + (v & 7) + 8 * lhalf + 16 * (v >> 3) > my_pos) s[t][v] = -INFINITY;
+        }
+        float mx = s[0][0];
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) mx = fmaxf(mx, s[t][v]);
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * sl2;
+        if (__builtin_amdgcn_ballot_w64(mx > m_run + RESCALE_LOG2) != 0) {
+            const float m_new = fmaxf(m_run, mx), corr = __builtin_amdgcn_exp2f(m_run - m_new);
+            m_run = m_new;
+            l_part *= corr;
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) o[t][v] *= corr;
+        }
+        if (masked) {
+            // A hidden key's probability is 0, but 0 * V is not where V holds an infinity or a NaN (a later token's, or
+            // what a page held before): such a tile is left for the loop below.
+            unsigned bad = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    const u32x4 w = *(const u32x4*)(st + t * 32 * 128 + vaddr[j]);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) bad |= unsigned((w[e] & 0x7F80u) == 0x7F80u) | unsigned((w[e] & 0x7F800000u) == 0x7F800000u);
+                }
+            if (__builtin_amdgcn_ballot_w64(bad != 0) != 0) {
+                left_out |= tile < n_tiles ? 1u << (tile - first_masked) : 0u;
+                continue;
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            bf16x8 p_hi, p_lo;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float x = __builtin_amdgcn_exp2f(__builtin_fmaf(s[j >> 1][8 * (j & 1) + i], sl2, -m_run));
+                l_part += x;
+                p_hi[i] = bf16_t(x);
+                p_lo[i] = bf16_t(x - float(p_hi[i]));
+            }
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const bf16x8 v = *(const bf16x8*)(st + t * 32 * 128 + vaddr[j]);
+                o[t] = mfma32(v, p_hi, o[t]);
+                o[t] = mfma32(v, p_lo, o[t]);
+            }
+        }
+    }
+
+    // Diagonal tiles with an infinity or a NaN in V: key by key, over the keys a query sees, straight from the page
+    // (wave-uniform bases and one lane offset, so that this loop costs the one above no registers).
+#pragma unroll 1
+    for (; left_out != 0; left_out &= left_out - 1) {
+        const int key0 = (first_masked + __builtin_ctz(left_out)) * AK;
+        const char* page = page_of(key0);
+        const unsigned in_page0 = unsigned(key0 % pt);
+#pragma unroll 1
+        for (int key = 0; key < AK; ++key) {
+            const char* kp = page + size_t(in_page0 + key) * (HD * 2);
+            const char* vp = page + k_to_v + size_t(in_page0 + key) * 2;
+            float d = 0.f;   // this half-wave's 8 of every 16 elements, then the other's
+#pragma unroll
+            for (int ks = 0; ks < HD / 16; ++ks) {
+                const bf16x8 kk = *(const bf16x8*)(kp + 32 * ks + unsigned(16 * lhalf));
+#pragma unroll
+                for (int e = 0; e < 8; ++e) d = __builtin_fmaf(float(kk[e]), float(qreg[ks][e]), d);
+            }
+            d += __shfl_xor(d, 32, 64);
+            if (key0 + key > my_pos) continue;
+            const float m_new = fmaxf(m_run, d * sl2), corr = __builtin_amdgcn_exp2f(m_run - m_new);
+            const float x = __builtin_amdgcn_exp2f(__builtin_fmaf(d, sl2, -m_new));
+            m_run = m_new;
+            l_part = l_part * corr + (lhalf == 0 ? x : 0.f);
+            const unsigned lane_row = unsigned(8 * lhalf * pt);
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const char* row = vp + size_t(32 * t + 8 * (v >> 2) + (v & 3)) * pt * 2;
+                    o[t][v] = __builtin_fmaf(x, float(*(const bf16_t*)(row + lane_row)), o[t][v] * corr);
+                }
+        }
+    }
+
+    // merge the two key halves: the second parks (O, l, reference) in LDS, the first combines and stores
+    __syncthreads();
+    float* park = (float*)lds + size_t(wave) * 34 * 64 + lane;
+    const float l_tot = l_part + __shfl_xor(l_part, 32, 64);
+    if (grp == 1) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) park[(16 * t + v) * 64] = o[t][v];
+        park[32 * 64] = l_tot;
+        park[33 * 64] = m_run;
+    }
+    __syncthreads();
+    const int row = q0 + wave * 32 + lrow;
+    if (grp == 1 || row >= rows) return;
+    const float m_b = park[33 * 64], m = fmaxf(m_run, m_b);
+    const float ca = __builtin_amdgcn_exp2f(m_run - m), cb = __builtin_amdgcn_exp2f(m_b - m);
+    const float den = l_tot * ca + park[32 * 64] * cb, inv = part ? 1.0f : 1.0f / den;
+    float* pp = part + ((size_t(split) * n_q + h) * rows + row) * (HD + 2);
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int v4 = 0; v4 < 4; ++v4) {
+            float x[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[e] = (o[t][4 * v4 + e] * ca + park[(16 * t + 4 * v4 + e) * 64] * cb) * inv;
+            const int d = t * 32 + 8 * v4 + 4 * lhalf;
+            if (part) {
+                *(float2*)(pp + d) = make_float2(x[0], x[1]);
+                *(float2*)(pp + d + 2) = make_float2(x[2], x[3]);
+            } else {
+                *(bf16x4*)(out + (size_t(row) * n_q + h) * HD + d) = bf16x4{bf16_t(x[0]), bf16_t(x[1]), bf16_t(x[2]), bf16_t(x[3])};
+            }
+        }
+    if (part && lhalf == 0) *(float2*)(pp + HD) = make_float2(m * 0.6931471805599453f, den);
+}
+
+// =====================================================================================
 // One-token attention on the matrix cores (first-token step; bf16 pages, head_dim 128).
 //
 // The "queries" of a workgroup are the r query heads that share KV head g, all at the same
@@ -880,6 +1128,46 @@ hipError_t launch_attention_mfma(const void* q, void* out, int n_q, int tok_begi
                                n_q, tok_begin, rows, kv, q_tiles);
     }
     return hipGetLastError();
+}
+
+// Head dimension 64, 16-byte reads of q, the pages and the result; with fewer keys than 24 the one-wave-per-row kernel
+// is as fast or faster (32 heads, us: 8 rows of 8 keys 5.6 here, 4.3 there; 16: 5.6, 5.2; 24: 5.6, 5.9).  Queries per workgroup by the rows there are; key
+// ranges until two workgroups per CU, as long as a range keeps four tile pairs and the parts fit the workspace.
+bool attention_hd64_supported(const void* q, const void* out, int n_keys, const KvView& kv) {
+    const size_t table = 8 * (size_t(n_keys - 1) / kv.page_tokens + 1);
+    return n_keys >= 24 && kv.head_dim == 64 && kv.page_tokens % AK == 0 && ((uintptr_t(q) | uintptr_t(out) | uintptr_t(kv.pool)) & 15) == 0 &&
+           H64_TABLE + table <= 160 * 1024;
+}
+
+template <int QW>
+static hipError_t launch_hd64(const bf16_t* q, bf16_t* out, int n_q, int tok_begin, int rows, const KvView& kv, hipStream_t st,
+                              float* part, size_t part_bytes) {
+    const int q_tiles = (rows + 32 * QW - 1) / (32 * QW), n_pairs = (tok_begin + rows - 1) / (2 * AK) + 1;
+    const int lds = H64_TABLE + 8 * ((tok_begin + rows - 1) / kv.page_tokens + 1);
+    static bool attr_set = false;   // one flag per instantiation
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute((const void*)attention_hd64_kernel<QW>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    int splits = std::max(1, std::min(512 / std::max(1, q_tiles * n_q), n_pairs / 4));
+    const size_t one = size_t(n_q) * rows * 66 * sizeof(float);
+    splits = part ? int(std::min<size_t>(splits, std::max<size_t>(1, part_bytes / one))) : 1;
+    const int per = (n_pairs + splits - 1) / splits;
+    splits = (n_pairs + per - 1) / per;
+    hipLaunchKernelGGL(attention_hd64_kernel<QW>, dim3(q_tiles * n_q, splits), dim3(128 * QW), lds, st, q, out, splits > 1 ? part : nullptr,
+                       n_q, tok_begin, rows, kv, per);
+    hipError_t e = hipGetLastError();
+    return e != hipSuccess || splits == 1 ? e : launch_attention_merge(1, 64, part, out, n_q, rows, splits, st);
+}
+
+hipError_t launch_attention_hd64(const void* q, void* out, int n_q, int tok_begin, int rows, const KvView& kv, hipStream_t st,
+                                 float* part, size_t part_bytes) {
+    if (rows <= 0) return hipSuccess;
+    const bf16_t* Q = (const bf16_t*)q;
+    if (rows <= 32) return launch_hd64<1>(Q, (bf16_t*)out, n_q, tok_begin, rows, kv, st, part, part_bytes);
+    if (rows <= 64) return launch_hd64<2>(Q, (bf16_t*)out, n_q, tok_begin, rows, kv, st, part, part_bytes);
+    return launch_hd64<4>(Q, (bf16_t*)out, n_q, tok_begin, rows, kv, st, part, part_bytes);
 }
 
 }  // namespace cake

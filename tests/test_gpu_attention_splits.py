@@ -74,3 +74,17 @@ def _poisoned(kind, hd, n_q, n_kv, tok_begin, rows, pt, bad_row, tol):
 
 def test_attention_f32_hidden_values_do_not_leak():
     _poisoned("f32", 64, 4, 2, 200, 77, 128, 50, 2e-5)
+
+
+# bf16, heads of 64: the scores and the probabilities keep float32's precision (16 bits in the second product), so what
+# is left is the rounding of the result to 8 significant bits (in [1, 2) the values lie 2^-7 apart: at most half of
+# that, 2^-8 of a value), and 2^-15 for the probabilities and the sums
+@pytest.mark.parametrize("n_q,n_kv", [(4, 4), (8, 2), (16, 8)])
+@pytest.mark.parametrize("tok_begin,rows,pt", [(0, 1, 64), (0, 33, 64), (63, 32, 64), (64, 65, 128), (300, 95, 128), (1000, 256, 128),
+                                               (6001, 7, 256), (4000, 129, 256)])
+def test_attention_bf16_hd64(n_q, n_kv, tok_begin, rows, pt):
+    _check("bf16", *_case("bf16", 64, n_q, n_kv, tok_begin, rows, pt), tok_begin, 2.0 ** -8 + 2.0 ** -15)
+
+
+def test_attention_bf16_hd64_hidden_values_do_not_leak():
+    _poisoned("bf16", 64, 4, 2, 200, 77, 128, 50, 2.0 ** -8 + 2.0 ** -15)
