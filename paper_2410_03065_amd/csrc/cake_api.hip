@@ -181,7 +181,8 @@ static hipError_t gemm(cake_ctx* c, int epi, const void* a, const void* w, const
 
 static hipError_t attention(cake_ctx* c, const void* q, void* out, int tok_begin, int rows, const KvView& kv) {
     if (c->m.dtype == CAKE_BF16 && c->tun.kernel_path == 0 && attention_mfma_supported(kv.head_dim, kv.page_tokens))
-        return launch_attention_mfma(q, out, c->m.n_q_heads, tok_begin, rows, kv, c->cs, c->tun.attn_variant);
+        return launch_attention_mfma(q, out, c->m.n_q_heads, tok_begin, rows, kv, c->cs, c->tun.attn_variant, c->split.part,
+                                     c->split.part_bytes);
     if (c->m.dtype == CAKE_BF16 && c->tun.kernel_path == 0 && attention_hd64_supported(q, out, tok_begin + rows, kv))
         return launch_attention_hd64(q, out, c->m.n_q_heads, tok_begin, rows, kv, c->cs, c->split.part, c->split.part_bytes);
     if (c->m.dtype == CAKE_F32 && c->tun.kernel_path == 0 && attention_f32_supported(q, tok_begin + rows, kv))

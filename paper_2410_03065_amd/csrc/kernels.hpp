@@ -71,10 +71,10 @@ void gemm_mfma_plan(int epi, int M, int N, int K, int cfg_override, const GemmSp
 // MFMA-only yardstick kernel: out holds workgroups * 8 floats; see kernels_gemm.hip.
 hipError_t launch_mfma_rate(float* out, int workgroups, int iters, hipStream_t st);
 bool attention_mfma_supported(int head_dim, int page_tokens);
-// variant: 0 = eight-wave kernel, 128 or 64 queries per workgroup by grid size; 1 = four-wave kernel;
-// 2 / 3 = eight-wave kernel with 128 / 64 queries per workgroup (testing).
+// variant: 0 = eight-wave kernel, 128, 64 or 32 queries per workgroup and the key ranges by a cost model; 1 = four-wave
+// kernel; 2 / 3 = eight-wave kernel with 128 / 64 queries per workgroup (testing).  part as for launch_attention_f32.
 hipError_t launch_attention_mfma(const void* q, void* out, int n_q, int tok_begin, int rows,
-                                 const KvView& kv, hipStream_t st, int variant = 0);
+                                 const KvView& kv, hipStream_t st, int variant, float* part, size_t part_bytes);
 
 // bf16, head_dim 64; part as for launch_attention_f32
 bool attention_hd64_supported(const void* q, const void* out, int n_keys, const KvView& kv);

@@ -362,40 +362,55 @@ constexpr int A8_RING = 2 * A_KBYTES;        // one ring slot: group A's tile th
 constexpr int A8_VBASE = 2 * A8_RING;        // V^T ring after the K ring
 constexpr int A8_TABLE = 4 * A8_RING;        // page offsets after both rings
 
-// QW = query waves per half (4: 128 queries per workgroup; 2: 64 queries, for launches whose
-// 128-query grid would leave CUs idle, e.g. 512-token chunks of a 32-head model).
-template <int QW>
+// The r query heads that share a KV head are laid side by side: query number x of KV head g is row x / r of head
+// g r + x % r, so a workgroup's queries fill up across heads (137 rows of four heads: five tiles of 128 instead of
+// eight).  QW = query waves per half: 128, 64 or 32 queries per workgroup.
+//
+// Launches with too few query tiles for the chip divide the keys as well: blockIdx.y takes `pairs_per_split` pairs of
+// key tiles and leaves its unnormalised result in `part` for attention_merge_kernel (SPLIT, an instantiation of its
+// own: the unsplit loop's code stays as it is).
+template <int QW, bool SPLIT>
 __global__ void __launch_bounds__(128 * QW)
-attention_mfma8_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, int n_q, int tok_begin, int rows,
-                       KvView kv, int q_tiles) {
+attention_mfma8_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, float* __restrict__ part, int n_q, int tok_begin,
+                       int rows, KvView kv, int pairs_per_split) {
     constexpr int AQW = 32 * QW;        // queries per workgroup
     constexpr int PER = 16 / QW;        // wave-loads per wave per K (or V^T) tile
-    constexpr int KP = QW >= 4 ? 1 : 4 / QW;   // period after which the K swizzle term of a wave's loads repeats
+    constexpr int KP = QW >= 4 ? 1 : 4 / QW;   // period after which the K swizzle term of a wave's loads repeats,
+    constexpr int VP = QW >= 2 ? 1 : 2;        // and the V^T term
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave8 = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wave = wave8 % QW, grp = wave8 / QW;
     const int lrow = lane & 31, lhalf = lane >> 5;
     const int G = kv.n_kv, r = n_q / G;
-    int g, rest;
+    int g, q0;
     if ((G & 7) == 0) {
         const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3, gpx = G >> 3;
         g = xcd + 8 * (idx % gpx);
-        rest = idx / gpx;
+        q0 = idx / gpx * AQW;
     } else {
         g = blockIdx.x % G;
-        rest = blockIdx.x / G;
+        q0 = blockIdx.x / G * AQW;
     }
-    const int h = g * r + rest % r;
-    const int q0 = (rest / r) * AQW;
     const int pt = kv.page_tokens;
 
-    const int my_row = min(q0 + wave * 32 + lrow, rows - 1);
+    const int n_queries = rows * r, my_query = min(q0 + wave * 32 + lrow, n_queries - 1);
+    const int my_row = my_query / r, h = g * r + (my_query - my_row * r);
     const int my_pos = tok_begin + my_row;
-    const int wave_first_pos = tok_begin + min(q0 + wave * 32, rows - 1);
-    const int wg_last_pos = tok_begin + min(q0 + AQW, rows) - 1;
+    const int wave_first_pos = tok_begin + min(q0 + wave * 32, n_queries - 1) / r;
+    const int wg_last_pos = tok_begin + (min(q0 + AQW, n_queries) - 1) / r;
     const int n_tiles = wg_last_pos / AK + 1;
-    const int n_pairs = (n_tiles + 1) >> 1;
+    const int pair_lo = SPLIT ? blockIdx.y * pairs_per_split : 0;
+    const int n_pairs = SPLIT ? min(pair_lo + pairs_per_split, (n_tiles + 1) >> 1) : (n_tiles + 1) >> 1;
+    const bool is_query = q0 + wave * 32 + lrow < n_queries;
+    float* my_part = SPLIT ? part + ((size_t(blockIdx.y) * n_q + h) * rows + my_row) * (AHD + 2) : nullptr;
+    if (SPLIT && pair_lo >= n_pairs) {   // a range wholly above this workgroup's diagonal
+        if (grp == 0 && is_query) {
+            for (int d = lhalf * (AHD / 2); d < (lhalf + 1) * (AHD / 2); d += 2) *(float2*)(my_part + d) = make_float2(0.f, 0.f);
+            if (lhalf == 0) *(float2*)(my_part + AHD) = make_float2(-FLT_MAX, 0.f);
+        }
+        return;
+    }
     const int first_masked = (wave_first_pos + 1) / AK;   // first tile with a key some query of this wave must not see
 
     bf16x8 qreg[AHD / 16];
@@ -412,17 +427,18 @@ attention_mfma8_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, i
     }
     // lane offsets of this wave's K / V^T wave-loads of a tile: load i covers 1 KB = key rows
     // 4j .. 4j+3 (V^T: head-dim rows 8j .. 8j+7) with j = wave + QW*i.  The swizzle term of the K
-    // rows repeats every KP loads, that of the V^T rows with every load, so the other loads are a
+    // rows repeats every KP loads, that of the V^T rows every VP loads, so the other loads are a
     // wave-uniform distance from these.
-    unsigned koffp[KP], voff0;
+    unsigned koffp[KP], voffp[VP];
 #pragma unroll
     for (int i = 0; i < KP; ++i) {
         int krow = 4 * (wave + QW * i) + (lane >> 4), kpos = lane & 15;
         koffp[i] = unsigned(krow * AHD + ((kpos ^ (krow & 15)) << 3)) * 2u;
     }
-    {
-        int vrow = 8 * wave + (lane >> 3), vpos = lane & 7;
-        voff0 = unsigned(vrow * pt + ((vpos ^ ((vrow >> 1) & 7)) << 3)) * 2u;
+#pragma unroll
+    for (int i = 0; i < VP; ++i) {
+        int vrow = 8 * (wave + QW * i) + (lane >> 3), vpos = lane & 7;
+        voffp[i] = unsigned(vrow * pt + ((vpos ^ ((vrow >> 1) & 7)) << 3)) * 2u;
     }
     const int last_page = wg_last_pos / pt;
     unsigned long long* pg_lds = (unsigned long long*)(lds + A8_TABLE);
@@ -458,7 +474,7 @@ attention_mfma8_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, i
         unsigned char* sa = lds + A8_VBASE + (pair & 1) * A8_RING + grp * A_KBYTES;
 #pragma unroll
         for (int i = 0; i < PER; ++i)
-            __builtin_amdgcn_global_load_lds((const CAKE_GLOBAL_AS void*)(vp + size_t(i) * (8 * QW) * pt * 2 + voff0),
+            __builtin_amdgcn_global_load_lds((const CAKE_GLOBAL_AS void*)(vp + size_t(i / VP) * (8 * QW * VP) * pt * 2 + voffp[i % VP]),
                                              (CAKE_LDS_AS void*)(sa + (wave + QW * i) * 1024), 16, 0, 0);
     };
 
@@ -487,14 +503,14 @@ attention_mfma8_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, i
     float corr_cur = 1.f, delta_cur = 0.f;
     bool moved_cur = false;
     constexpr float RESCALE_LOG2 = 6.0f;
-    auto mask_tile = [&](f32x16* s, int tile) {
+    auto mask_tile = [&](f32x16* s, int tile, int last_visible) {
         const int key0 = tile * AK;
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 int key = key0 + 32 * t + (v & 7) + 8 * lhalf + 16 * (v >> 3);
-                if (key > my_pos) s[t][v] = -INFINITY;
+                if (key > last_visible) s[t][v] = -INFINITY;
             }
     };
     auto part_max = [&](const f32x16* s, int part, float acc) {
@@ -566,7 +582,8 @@ attention_mfma8_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, i
         asm volatile("" ::"v"(l_part));
         __builtin_amdgcn_sched_barrier(0);
         const int next_tile = 2 * (i + 1) + grp;
-        if (next_tile >= first_masked) mask_tile(s_nxt, next_tile);   // also blanks tiles past the end
+        // blanks tiles past the end, and what was formed from a stale slot after the range's last pair
+        if (next_tile >= first_masked || (SPLIT && i + 1 >= n_pairs)) mask_tile(s_nxt, next_tile, !SPLIT || i + 1 < n_pairs ? my_pos : -1);
         float raw;
         read_v(opb, 1);
 #pragma unroll
@@ -603,11 +620,11 @@ attention_mfma8_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, i
         }
     };
 
-    // prologue: K(0), V(0), K(1) in flight; K(0) landed; scores and reference of the first tile
-    issue_k(0);
-    issue_v(0);
-    if (n_pairs > 1) {
-        issue_k(1);
+    // prologue: K, V of the first pair and K of the second in flight; K landed; scores and reference of the first tile
+    issue_k(pair_lo);
+    issue_v(pair_lo);
+    if (pair_lo + 1 < n_pairs) {
+        issue_k(pair_lo + 1);
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * PER));
     } else {
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER));
@@ -615,7 +632,7 @@ attention_mfma8_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, i
     __builtin_amdgcn_s_barrier();
     f32x16 s_a[2], s_b[2];
     {
-        const unsigned char* stk = lds;
+        const unsigned char* stk = lds + (pair_lo & 1) * A8_RING;
 #pragma unroll
         for (int ks = 0; ks < AHD / 16; ++ks)
 #pragma unroll
@@ -624,7 +641,7 @@ attention_mfma8_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, i
                 s_a[t] = mfma32(a, qreg[ks], ks == 0 ? zero16 : s_a[t]);
             }
     }
-    if (grp >= first_masked) mask_tile(s_a, grp);
+    if (2 * pair_lo + grp >= first_masked) mask_tile(s_a, 2 * pair_lo + grp, my_pos);
     {
         // the first tile fixes the reference exactly; a row that sees none of its keys (possible for
         // the second wave half only) keeps reference 0 and contributes nothing
@@ -640,7 +657,7 @@ attention_mfma8_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, i
 #pragma unroll
         for (int v = 0; v < 16; ++v) negm[v] = -m_run;
     }
-    for (int i = 0; i < n_pairs; i += 2) {
+    for (int i = pair_lo; i < n_pairs; i += 2) {
         step(i, s_a, s_b);
         if (i + 1 < n_pairs) step(i + 1, s_b, s_a);
     }
@@ -665,10 +682,21 @@ attention_mfma8_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, i
         const float ca = __builtin_amdgcn_exp2f(m_run - m), cb = __builtin_amdgcn_exp2f(m_b - m);
         float l_mine = l_part * ca + l_b * cb;
         const float l_tot = l_mine + __shfl_xor(l_mine, 32, 64);
+        if constexpr (SPLIT) {
+            if (is_query) {
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+#pragma unroll
+                    for (int v = 0; v < 16; v += 2)
+                        *(float2*)(my_part + t * 32 + 8 * (v >> 2) + 4 * lhalf + (v & 3)) =
+                            make_float2(o[t][v] * ca + park[(16 * t + v) * 64] * cb, o[t][v + 1] * ca + park[(16 * t + v + 1) * 64] * cb);
+                if (lhalf == 0) *(float2*)(my_part + AHD) = make_float2(l_tot > 0.f ? m * 0.6931471805599453f : -FLT_MAX, l_tot);
+            }
+            return;
+        }
         const float inv = 1.0f / l_tot;
-        const int row = q0 + wave * 32 + lrow;
-        if (row < rows) {
-            bf16_t* op = out + size_t(row) * n_q * AHD + h * AHD;
+        if (is_query) {
+            bf16_t* op = out + size_t(my_row) * n_q * AHD + h * AHD;
 #pragma unroll
             for (int t = 0; t < 4; ++t)
 #pragma unroll
@@ -1093,41 +1121,76 @@ bool attention_mfma_supported(int head_dim, int page_tokens) {
     return head_dim == AHD && page_tokens % AK == 0;
 }
 
-hipError_t launch_attention_mfma(const void* q, void* out, int n_q, int tok_begin, int rows, const KvView& kv,
-                                 hipStream_t st, int variant) {
-    if (rows <= 0) return hipSuccess;
-    static bool attr_set = false;
-    constexpr int LDS_MAX = 160 * 1024;
-    const int table = 8 * ((tok_begin + rows - 1) / kv.page_tokens + 1);   // one 8-byte page offset per logical page
-    const int q_tiles = (rows + AQ - 1) / AQ;
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void*)attention_mfma_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_MAX);
-        if (e == hipSuccess) e = hipFuncSetAttribute((const void*)attention_mfma8_kernel<4>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_MAX);
-        if (e == hipSuccess) e = hipFuncSetAttribute((const void*)attention_mfma8_kernel<2>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_MAX);
-        if (e != hipSuccess) return e;
-        attr_set = true;
+// How a launch is divided: queries per workgroup (32 qw) and key ranges, by the time of the busiest CU.  A pair of key
+// tiles takes a workgroup (one per CU) about 1.98 us with 128 queries and 1.40 with 64 or fewer (512 rows x 32 heads
+// over 8000 keys and 1024 over 15360, measured), a workgroup about 9 us beyond its pairs (one pair: 10.4); key ranges
+// cost the merge kernel and their parts' way through memory (about 4 bytes per ps each way).  32 heads on 8 KV heads,
+// us undivided and divided, merge included: 8 rows at 4000 keys 55 and 15, 39 rows at 14000 174 and 28, 137 rows at
+// 4000 46 and 28; 509 rows of 32 KV heads at 7003 90 and 79.
+constexpr int A_LDS_MAX = 160 * 1024;
+struct AttnPlan { int qw, splits; };
+static AttnPlan attn_plan(int n_q, int n_kv, int tok_begin, int rows, size_t part_bytes, int force_qw) {
+    static const struct { int qw; double pair_us; } kinds[3] = {{4, 1.98}, {2, 1.40}, {1, 1.40}};
+    const int n_pairs = (tok_begin + rows - 1) / (2 * AK) + 1;
+    const double one = double(n_q) * rows * (AHD + 2) * sizeof(float);
+    AttnPlan best{4, 1};
+    double best_us = 1e30;
+    for (const auto& k : kinds) {
+        if (force_qw && k.qw != force_qw) continue;
+        const long wgs = (long(rows) * (n_q / n_kv) + 32 * k.qw - 1) / (32 * k.qw) * n_kv;
+        for (int s = 1; s <= 32 && s <= n_pairs; ++s) {
+            if (s > 1 && s * one > double(part_bytes)) break;
+            const int per = (n_pairs + s - 1) / s;
+            if ((n_pairs + per - 1) / per != s) continue;
+            double us = double((wgs * s + 255) / 256) * (per * k.pair_us + 9.0);
+            if (s > 1) us = (us + 4.5 + 2.0 * s * one / 4.0e6) * 1.05;
+            if (us < best_us) { best_us = us; best = AttnPlan{k.qw, s}; }
+        }
     }
+    return best;
+}
+
+template <int QW>
+static hipError_t launch_mfma8(const bf16_t* q, bf16_t* out, float* part, int n_q, int tok_begin, int rows, const KvView& kv, int splits,
+                               int lds, hipStream_t st) {
+    const int r = n_q / kv.n_kv, q_tiles = (rows * r + 32 * QW - 1) / (32 * QW);
+    const int n_pairs = (tok_begin + rows - 1) / (2 * AK) + 1, per = (n_pairs + splits - 1) / splits;
+    auto kern = splits > 1 ? attention_mfma8_kernel<QW, true> : attention_mfma8_kernel<QW, false>;
+    static bool attr_set[2] = {false, false};
+    if (!attr_set[splits > 1]) {
+        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, A_LDS_MAX);
+        if (e != hipSuccess) return e;
+        attr_set[splits > 1] = true;
+    }
+    hipLaunchKernelGGL(kern, dim3(q_tiles * kv.n_kv, splits), dim3(128 * QW), lds, st, q, out, part, n_q, tok_begin, rows, kv, per);
+    hipError_t e = hipGetLastError();
+    return e != hipSuccess || splits == 1 ? e : launch_attention_merge(1, AHD, part, out, n_q, rows, splits, st);
+}
+
+hipError_t launch_attention_mfma(const void* q, void* out, int n_q, int tok_begin, int rows, const KvView& kv,
+                                 hipStream_t st, int variant, float* part, size_t part_bytes) {
+    if (rows <= 0) return hipSuccess;
+    const int table = 8 * ((tok_begin + rows - 1) / kv.page_tokens + 1);   // one 8-byte page offset per logical page
     if (variant == 1) {
-        const int LDS = A_STAGES * A_STAGE + table;
-        if (LDS > LDS_MAX) return hipErrorInvalidValue;
+        const int LDS = A_STAGES * A_STAGE + table, q_tiles = (rows + AQ - 1) / AQ;
+        if (LDS > A_LDS_MAX) return hipErrorInvalidValue;
+        static bool attr_set = false;
+        if (!attr_set) {
+            hipError_t e = hipFuncSetAttribute((const void*)attention_mfma_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, A_LDS_MAX);
+            if (e != hipSuccess) return e;
+            attr_set = true;
+        }
         hipLaunchKernelGGL(attention_mfma_kernel, dim3(q_tiles * n_q), dim3(256), LDS, st, (const bf16_t*)q, (bf16_t*)out, n_q,
                            tok_begin, rows, kv, q_tiles);
-    } else {
-        const int LDS = A8_TABLE + table;
-        if (LDS > LDS_MAX) return hipErrorInvalidValue;
-        // 64-query workgroups (four waves, one per SIMD: about 0.85 of the eight-wave kernel's rate per CU) when
-        // they shorten the busiest CU's work: rounds of workgroups over 256 CUs times queries per workgroup
-        const int q_tiles64 = (rows + 63) / 64;
-        const long rounds128 = (long(q_tiles) * n_q + 255) / 256, rounds64 = (long(q_tiles64) * n_q + 255) / 256;
-        const bool small_wins = q_tiles64 > q_tiles && double(rounds64) * 64 / 0.85 < double(rounds128) * 128;
-        if (variant == 3 || (variant == 0 && small_wins))
-            hipLaunchKernelGGL(attention_mfma8_kernel<2>, dim3(q_tiles64 * n_q), dim3(256), LDS, st, (const bf16_t*)q, (bf16_t*)out,
-                               n_q, tok_begin, rows, kv, q_tiles64);
-        else
-            hipLaunchKernelGGL(attention_mfma8_kernel<4>, dim3(q_tiles * n_q), dim3(512), LDS, st, (const bf16_t*)q, (bf16_t*)out,
-                               n_q, tok_begin, rows, kv, q_tiles);
+        return hipGetLastError();
     }
-    return hipGetLastError();
+    const int LDS = A8_TABLE + table;
+    if (LDS > A_LDS_MAX) return hipErrorInvalidValue;
+    const AttnPlan plan = attn_plan(n_q, kv.n_kv, tok_begin, rows, part ? part_bytes : 0, variant == 2 ? 4 : variant == 3 ? 2 : 0);
+    const bf16_t* Q = (const bf16_t*)q;
+    if (plan.qw == 4) return launch_mfma8<4>(Q, (bf16_t*)out, part, n_q, tok_begin, rows, kv, plan.splits, LDS, st);
+    if (plan.qw == 2) return launch_mfma8<2>(Q, (bf16_t*)out, part, n_q, tok_begin, rows, kv, plan.splits, LDS, st);
+    return launch_mfma8<1>(Q, (bf16_t*)out, part, n_q, tok_begin, rows, kv, plan.splits, LDS, st);
 }
 
 // Head dimension 64, 16-byte reads of q, the pages and the result; with fewer keys than 24 the one-wave-per-row kernel

@@ -201,9 +201,10 @@ attention_merge_kernel(const float* __restrict__ part, T* __restrict__ out, int 
     const float* p = part + size_t(item) * (HD + 2);
     const size_t step = size_t(n_q) * rows * (HD + 2);
     float m = p[HD];
+#pragma unroll 8
     for (int s = 1; s < splits; ++s) m = fmaxf(m, p[s * step + HD]);
     float den = 0.f, x0 = 0.f, x1 = 0.f;
-#pragma unroll 4
+#pragma unroll 8
     for (int s = 0; s < splits; ++s) {
         const float2 ml = *(const float2*)(p + s * step + HD), o = *(const float2*)(p + s * step + d);
         const float w = __expf(ml.x - m);

@@ -88,3 +88,13 @@ def test_attention_bf16_hd64(n_q, n_kv, tok_begin, rows, pt):
 
 def test_attention_bf16_hd64_hidden_values_do_not_leak():
     _poisoned("bf16", 64, 4, 2, 200, 77, 128, 50, 2.0 ** -8 + 2.0 ** -15)
+
+
+# bf16, heads of 128: the result, each probability and the scaled query are rounded to bf16; 2^-7 of the largest value
+# covers the three (tests/test_gpu_ops.py::test_attention).  Query heads of a KV head are laid side by side, so a tile of
+# queries ends inside a row's heads (r = 3) and a workgroup's rows inside a key tile.
+@pytest.mark.parametrize("n_q,n_kv", [(4, 4), (6, 2), (32, 8), (8, 1)])
+@pytest.mark.parametrize("tok_begin,rows,pt", [(0, 1, 64), (0, 33, 64), (63, 32, 64), (300, 95, 128), (1000, 256, 128), (6001, 7, 256),
+                                               (4000, 129, 256), (9000, 43, 64)])
+def test_attention_bf16_hd128(n_q, n_kv, tok_begin, rows, pt):
+    _check("bf16", *_case("bf16", 128, n_q, n_kv, tok_begin, rows, pt), tok_begin, 2.0 ** -7)
