@@ -37,11 +37,16 @@ hipError_t launch_gemm_generic(int dtype, int epi, const void* a, const void* w,
 hipError_t launch_attention_generic(int dtype, const void* q, void* out, int n_q, int tok_begin,
                                     int rows, const KvView& kv, hipStream_t st);
 
+// Where an attention launch may leave the parts of its key ranges: float32 workspace (part null: never divide the keys);
+// launches sharing it must not overlap.  range_keys > 0: the keys are divided into ranges of that many whatever the
+// number of rows, so that a token's result does not depend on the step it is computed in; 0: by a cost model.
+struct AttnWs { float* part; size_t bytes; int range_keys; };
+
 // ---- float32 on the matrix cores ----
 // part (or null): workspace for the key ranges of a launch with few queries; launches sharing it must not overlap.
 bool attention_f32_supported(const void* q, int n_keys, const KvView& kv);
 hipError_t launch_attention_f32(const float* q, float* out, int n_q, int tok_begin, int rows, const KvView& kv,
-                                hipStream_t st, float* part, size_t part_bytes);
+                                hipStream_t st, const AttnWs& ws);
 hipError_t launch_gemm_f32(int epi, const float* a, const float* w, const float* w2, float* out, int M, int N, int K,
                            hipStream_t st);
 // Adds up the key ranges of a split attention launch: part[split][head][row][head_dim + 2] (O, reference of
@@ -72,14 +77,14 @@ void gemm_mfma_plan(int epi, int M, int N, int K, int cfg_override, const GemmSp
 hipError_t launch_mfma_rate(float* out, int workgroups, int iters, hipStream_t st);
 bool attention_mfma_supported(int head_dim, int page_tokens);
 // variant: 0 = eight-wave kernel, 128, 64 or 32 queries per workgroup and the key ranges by a cost model; 1 = four-wave
-// kernel; 2 / 3 = eight-wave kernel with 128 / 64 queries per workgroup (testing).  part as for launch_attention_f32.
+// kernel; 2 / 3 = eight-wave kernel with 128 / 64 queries per workgroup (testing).
 hipError_t launch_attention_mfma(const void* q, void* out, int n_q, int tok_begin, int rows,
-                                 const KvView& kv, hipStream_t st, int variant, float* part, size_t part_bytes);
+                                 const KvView& kv, hipStream_t st, int variant, const AttnWs& ws);
 
-// bf16, head_dim 64; part as for launch_attention_f32
+// bf16, head_dim 64
 bool attention_hd64_supported(const void* q, const void* out, int n_keys, const KvView& kv);
 hipError_t launch_attention_hd64(const void* q, void* out, int n_q, int tok_begin, int rows, const KvView& kv,
-                                 hipStream_t st, float* part, size_t part_bytes);
+                                 hipStream_t st, const AttnWs& ws);
 
 bool decode_attention_mfma_supported(int dtype, int head_dim, int page_tokens, int r);
 hipError_t launch_decode_attention_mfma(const float* q, float* part, int n_q, int n_keys, int tiles_per_split,

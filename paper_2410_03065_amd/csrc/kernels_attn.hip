@@ -1128,23 +1128,25 @@ bool attention_mfma_supported(int head_dim, int page_tokens) {
 // us undivided and divided, merge included: 8 rows at 4000 keys 55 and 15, 39 rows at 14000 174 and 28, 137 rows at
 // 4000 46 and 28; 509 rows of 32 KV heads at 7003 90 and 79.
 constexpr int A_LDS_MAX = 160 * 1024;
-struct AttnPlan { int qw, splits; };
-static AttnPlan attn_plan(int n_q, int n_kv, int tok_begin, int rows, size_t part_bytes, int force_qw) {
+struct AttnPlan { int qw, splits, per; };   // 32 qw queries per workgroup, key ranges of `per` pairs
+static AttnPlan attn_plan(int n_q, int n_kv, int tok_begin, int rows, const AttnWs& ws, int force_qw) {
     static const struct { int qw; double pair_us; } kinds[3] = {{4, 1.98}, {2, 1.40}, {1, 1.40}};
     const int n_pairs = (tok_begin + rows - 1) / (2 * AK) + 1;
     const double one = double(n_q) * rows * (AHD + 2) * sizeof(float);
-    AttnPlan best{4, 1};
+    const int fixed = ws.range_keys / (2 * AK);   // pairs per range where the caller fixes it (and the parts fit)
+    const bool use_fixed = fixed > 0 && ws.part && double((n_pairs + fixed - 1) / fixed) * one <= double(ws.bytes);
+    AttnPlan best{4, 1, n_pairs};
     double best_us = 1e30;
     for (const auto& k : kinds) {
         if (force_qw && k.qw != force_qw) continue;
         const long wgs = (long(rows) * (n_q / n_kv) + 32 * k.qw - 1) / (32 * k.qw) * n_kv;
-        for (int s = 1; s <= 32 && s <= n_pairs; ++s) {
-            if (s > 1 && s * one > double(part_bytes)) break;
-            const int per = (n_pairs + s - 1) / s;
+        for (int s = 1; s <= (use_fixed ? n_pairs : 32) && s <= n_pairs; ++s) {
+            if (s > 1 && (!ws.part || s * one > double(ws.bytes))) break;
+            const int per = use_fixed ? fixed : (n_pairs + s - 1) / s;
             if ((n_pairs + per - 1) / per != s) continue;
             double us = double((wgs * s + 255) / 256) * (per * k.pair_us + 9.0);
             if (s > 1) us = (us + 4.5 + 2.0 * s * one / 4.0e6) * 1.05;
-            if (us < best_us) { best_us = us; best = AttnPlan{k.qw, s}; }
+            if (us < best_us) { best_us = us; best = AttnPlan{k.qw, s, per}; }
         }
     }
     return best;
@@ -1152,9 +1154,8 @@ static AttnPlan attn_plan(int n_q, int n_kv, int tok_begin, int rows, size_t par
 
 template <int QW>
 static hipError_t launch_mfma8(const bf16_t* q, bf16_t* out, float* part, int n_q, int tok_begin, int rows, const KvView& kv, int splits,
-                               int lds, hipStream_t st) {
+                               int per, int lds, hipStream_t st) {
     const int r = n_q / kv.n_kv, q_tiles = (rows * r + 32 * QW - 1) / (32 * QW);
-    const int n_pairs = (tok_begin + rows - 1) / (2 * AK) + 1, per = (n_pairs + splits - 1) / splits;
     auto kern = splits > 1 ? attention_mfma8_kernel<QW, true> : attention_mfma8_kernel<QW, false>;
     static bool attr_set[2] = {false, false};
     if (!attr_set[splits > 1]) {
@@ -1168,7 +1169,7 @@ static hipError_t launch_mfma8(const bf16_t* q, bf16_t* out, float* part, int n_
 }
 
 hipError_t launch_attention_mfma(const void* q, void* out, int n_q, int tok_begin, int rows, const KvView& kv,
-                                 hipStream_t st, int variant, float* part, size_t part_bytes) {
+                                 hipStream_t st, int variant, const AttnWs& ws) {
     if (rows <= 0) return hipSuccess;
     const int table = 8 * ((tok_begin + rows - 1) / kv.page_tokens + 1);   // one 8-byte page offset per logical page
     if (variant == 1) {
@@ -1186,11 +1187,11 @@ hipError_t launch_attention_mfma(const void* q, void* out, int n_q, int tok_begi
     }
     const int LDS = A8_TABLE + table;
     if (LDS > A_LDS_MAX) return hipErrorInvalidValue;
-    const AttnPlan plan = attn_plan(n_q, kv.n_kv, tok_begin, rows, part ? part_bytes : 0, variant == 2 ? 4 : variant == 3 ? 2 : 0);
+    const AttnPlan plan = attn_plan(n_q, kv.n_kv, tok_begin, rows, ws, variant == 2 ? 4 : variant == 3 ? 2 : 0);
     const bf16_t* Q = (const bf16_t*)q;
-    if (plan.qw == 4) return launch_mfma8<4>(Q, (bf16_t*)out, part, n_q, tok_begin, rows, kv, plan.splits, LDS, st);
-    if (plan.qw == 2) return launch_mfma8<2>(Q, (bf16_t*)out, part, n_q, tok_begin, rows, kv, plan.splits, LDS, st);
-    return launch_mfma8<1>(Q, (bf16_t*)out, part, n_q, tok_begin, rows, kv, plan.splits, LDS, st);
+    if (plan.qw == 4) return launch_mfma8<4>(Q, (bf16_t*)out, ws.part, n_q, tok_begin, rows, kv, plan.splits, plan.per, LDS, st);
+    if (plan.qw == 2) return launch_mfma8<2>(Q, (bf16_t*)out, ws.part, n_q, tok_begin, rows, kv, plan.splits, plan.per, LDS, st);
+    return launch_mfma8<1>(Q, (bf16_t*)out, ws.part, n_q, tok_begin, rows, kv, plan.splits, plan.per, LDS, st);
 }
 
 // Head dimension 64, 16-byte reads of q, the pages and the result; with fewer keys than 24 the one-wave-per-row kernel
@@ -1204,7 +1205,8 @@ bool attention_hd64_supported(const void* q, const void* out, int n_keys, const 
 
 template <int QW>
 static hipError_t launch_hd64(const bf16_t* q, bf16_t* out, int n_q, int tok_begin, int rows, const KvView& kv, hipStream_t st,
-                              float* part, size_t part_bytes) {
+                              const AttnWs& ws) {
+    float* part = ws.part;
     const int q_tiles = (rows + 32 * QW - 1) / (32 * QW), n_pairs = (tok_begin + rows - 1) / (2 * AK) + 1;
     const int lds = H64_TABLE + 8 * ((tok_begin + rows - 1) / kv.page_tokens + 1);
     static bool attr_set = false;   // one flag per instantiation
@@ -1213,11 +1215,12 @@ static hipError_t launch_hd64(const bf16_t* q, bf16_t* out, int n_q, int tok_beg
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    int splits = std::max(1, std::min(512 / std::max(1, q_tiles * n_q), n_pairs / 4));
+    const int fixed = ws.range_keys / (2 * AK);
+    const int want = fixed ? (n_pairs + fixed - 1) / fixed : std::max(1, std::min(512 / std::max(1, q_tiles * n_q), n_pairs / 4));
     const size_t one = size_t(n_q) * rows * 66 * sizeof(float);
-    splits = part ? int(std::min<size_t>(splits, std::max<size_t>(1, part_bytes / one))) : 1;
-    const int per = (n_pairs + splits - 1) / splits;
-    splits = (n_pairs + per - 1) / per;
+    const int room = part ? std::max(1, int(std::min<size_t>(size_t(want), ws.bytes / one))) : 1;
+    const int per = fixed && room >= want ? fixed : (n_pairs + room - 1) / room;
+    const int splits = (n_pairs + per - 1) / per;
     hipLaunchKernelGGL(attention_hd64_kernel<QW>, dim3(q_tiles * n_q, splits), dim3(128 * QW), lds, st, q, out, splits > 1 ? part : nullptr,
                        n_q, tok_begin, rows, kv, per);
     hipError_t e = hipGetLastError();
@@ -1225,12 +1228,12 @@ static hipError_t launch_hd64(const bf16_t* q, bf16_t* out, int n_q, int tok_beg
 }
 
 hipError_t launch_attention_hd64(const void* q, void* out, int n_q, int tok_begin, int rows, const KvView& kv, hipStream_t st,
-                                 float* part, size_t part_bytes) {
+                                 const AttnWs& ws) {
     if (rows <= 0) return hipSuccess;
     const bf16_t* Q = (const bf16_t*)q;
-    if (rows <= 32) return launch_hd64<1>(Q, (bf16_t*)out, n_q, tok_begin, rows, kv, st, part, part_bytes);
-    if (rows <= 64) return launch_hd64<2>(Q, (bf16_t*)out, n_q, tok_begin, rows, kv, st, part, part_bytes);
-    return launch_hd64<4>(Q, (bf16_t*)out, n_q, tok_begin, rows, kv, st, part, part_bytes);
+    if (rows <= 32) return launch_hd64<1>(Q, (bf16_t*)out, n_q, tok_begin, rows, kv, st, ws);
+    if (rows <= 64) return launch_hd64<2>(Q, (bf16_t*)out, n_q, tok_begin, rows, kv, st, ws);
+    return launch_hd64<4>(Q, (bf16_t*)out, n_q, tok_begin, rows, kv, st, ws);
 }
 
 }  // namespace cake

@@ -238,15 +238,17 @@ bool attention_f32_supported(const void* q, int n_keys, const KvView& kv) {
 // Key ranges: enough workgroups for two per CU, as long as every wave of a range still has two tiles to overlap
 // (the next tile's keys are read while this one is worked on) and the parts fit the workspace.
 hipError_t launch_attention_f32(const float* q, float* out, int n_q, int tok_begin, int rows, const KvView& kv, hipStream_t st,
-                                float* part, size_t part_bytes) {
+                                const AttnWs& ws) {
     if (rows <= 0) return hipSuccess;
+    float* part = ws.part;
     const int q_tiles = (rows + FQ - 1) / FQ, n_tiles = (tok_begin + rows - 1) / FK + 1;
-    int splits = std::max(1, std::min(512 / std::max(1, q_tiles * n_q), n_tiles / 8));
+    const int want = ws.range_keys ? (n_tiles * FK + ws.range_keys - 1) / ws.range_keys
+                                   : std::max(1, std::min(512 / std::max(1, q_tiles * n_q), n_tiles / 8));
     const size_t one = size_t(n_q) * rows * (kv.head_dim + 2) * sizeof(float);
-    if (!part) splits = 1;
-    else splits = int(std::min<size_t>(splits, std::max<size_t>(1, part_bytes / one)));
-    const int per = (n_tiles + splits - 1) / splits;
-    splits = (n_tiles + per - 1) / per;
+    const int room = part ? int(std::min<size_t>(size_t(want), ws.bytes / one)) : 1;
+    const bool fixed = ws.range_keys && room >= want;
+    const int per = fixed ? ws.range_keys / FK : (n_tiles + std::max(1, room) - 1) / std::max(1, room);
+    const int splits = (n_tiles + per - 1) / per;
     const dim3 grid(q_tiles, n_q, splits), block(256);
     float* p = splits > 1 ? part : nullptr;
     if (kv.head_dim == 64) hipLaunchKernelGGL(attention_f32_kernel<64>, grid, block, 0, st, q, out, p, n_q, tok_begin, rows, kv, per);

@@ -98,3 +98,19 @@ def test_attention_bf16_hd64_hidden_values_do_not_leak():
                                                (4000, 129, 256), (9000, 43, 64)])
 def test_attention_bf16_hd128(n_q, n_kv, tok_begin, rows, pt):
     _check("bf16", *_case("bf16", 128, n_q, n_kv, tok_begin, rows, pt), tok_begin, 2.0 ** -7)
+
+
+@pytest.mark.parametrize("kind,hd,n_q,n_kv", [("bf16", 128, 8, 2), ("bf16", 128, 8, 8), ("bf16", 64, 8, 2), ("f32", 64, 4, 4)])
+def test_attention_of_a_model_of_few_heads_does_not_depend_on_the_step(kind, hd, n_q, n_kv):
+    """Rows computed in one call, in pieces of 128, 64 and 32 and at another length of the prefix: the same bits (a
+    prompt's KV must not show where the compute side's last claim ended)."""
+    import torch
+    begin, rows = 3072, 512
+    eng, Q, *_ = _case(kind, hd, n_q, n_kv, begin, rows, 128)
+    whole = eng.op_attention(Q, 0, begin)
+    for piece in (256, 128, 64, 32):
+        for r in range(0, rows, piece):
+            q = Q[:, r:r + piece].contiguous()
+            torch.cuda.synchronize()
+            part = eng.op_attention(q, 0, begin + r)
+            assert torch.equal(part, whole[r:r + piece]), (piece, r)
