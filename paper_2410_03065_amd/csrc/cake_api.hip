@@ -47,8 +47,8 @@ struct cake_ctx {
     int32_t* t_tok = nullptr;
     void* static_scratch = nullptr;   // this device's copy of the file-scope scratch array (set by cake_create)
     GemmSplitWs split{};       // float32 parts and ticket counters of launches that split K or keys (compute stream only)
-    void* q_stage = nullptr;   // device staging for quantised page images: a ring of image slots (cake_create)
     int attn_range_keys = 0;   // fixed key ranges of the attention launches of a model of few heads, else 0 (see AttnWs)
+    void* q_stage = nullptr;   // device staging for quantised page images: a ring of image slots (cake_create)
     size_t q_stage_bytes = 0;
     // second hop of a file-backed store: two pinned buffers of one DMA piece each
     void* f_stage[2] = {nullptr, nullptr};
@@ -181,8 +181,8 @@ static hipError_t gemm(cake_ctx* c, int epi, const void* a, const void* w, const
 }
 
 static hipError_t attention(cake_ctx* c, const void* q, void* out, int tok_begin, int rows, const KvView& kv) {
-    if (c->m.dtype == CAKE_BF16 && c->tun.kernel_path == 0 && attention_mfma_supported(kv.head_dim, kv.page_tokens))
     const AttnWs ws{c->split.part, c->split.part_bytes, c->attn_range_keys};
+    if (c->m.dtype == CAKE_BF16 && c->tun.kernel_path == 0 && attention_mfma_supported(kv.head_dim, kv.page_tokens))
         return launch_attention_mfma(q, out, c->m.n_q_heads, tok_begin, rows, kv, c->cs, c->tun.attn_variant, ws);
     if (c->m.dtype == CAKE_BF16 && c->tun.kernel_path == 0 && attention_hd64_supported(q, out, tok_begin + rows, kv))
         return launch_attention_hd64(q, out, c->m.n_q_heads, tok_begin, rows, kv, c->cs, ws);
@@ -533,6 +533,9 @@ int32_t cake_create(cake_ctx** out, const cake_model_desc* model, const cake_wei
         c->split.part_bytes = std::min<size_t>(size_t(64) << 20, 8 * rows_up * std::max<size_t>(m.d_model, nqkv) * 4);
         c->split.n_counters = 1024;
         ok = ok && hipMalloc((void**)&c->split.part, c->split.part_bytes) == hipSuccess;
+        ok = ok && hipMalloc((void**)&c->split.counters, size_t(c->split.n_counters) * 4) == hipSuccess;
+        ok = ok && hipMemset(c->split.counters, 0, size_t(c->split.n_counters) * 4) == hipSuccess;
+    }
     {
         // A model of few heads divides its keys in every launch.  It does so into the same ranges however many rows a
         // step has, so that the chunk a token is computed in does not show in its bits: the shortest power of two
@@ -542,9 +545,6 @@ int32_t cake_create(cake_ctx** out, const cake_model_desc* model, const cake_wei
         if (m.n_q_heads <= (f32 ? 4 : 16))
             for (c->attn_range_keys = f32 ? 256 : 1024; (max_tokens + c->attn_range_keys - 1) / c->attn_range_keys * row > c->split.part_bytes;)
                 if ((c->attn_range_keys *= 2) >= max_tokens) break;
-    }
-        ok = ok && hipMalloc((void**)&c->split.counters, size_t(c->split.n_counters) * 4) == hipSuccess;
-        ok = ok && hipMemset(c->split.counters, 0, size_t(c->split.n_counters) * 4) == hipSuccess;
     }
     {
         // staging of the load path, so that no load allocates: device room for the 8-bit images (the largest
