@@ -225,7 +225,8 @@ typedef struct {
 /* Creates a context on the current device: copies the layer table, allocates the
  * activation workspace for chunks of up to max_chunk tokens, a device buffer for
  * max_tokens token ids and the staging of the load path (device room for the 8-bit page
- * images of max_chunk tokens; two pinned buffers of one DMA piece for file-backed stores),
+ * images of max_chunk tokens; two pinned buffers of one DMA piece for file-backed stores; with
+ * head weights, a pinned buffer for the first-token step's logits),
  * and starts the load worker.  Loads allocate nothing; a page of more than max_chunk tokens
  * cannot be loaded from a quantised store.  compute_stream / copy_stream: hipStream_t, default priority.
  * Errors: CAKE_E_INVAL (shape not supported), CAKE_E_NOMEM, CAKE_E_HIP. */

@@ -42,8 +42,10 @@ struct cake_ctx {
     // first-token step (one row, float32 throughout); null unless the weights carry final_norm and lm_head
     const float* final_norm = nullptr;
     const void* lm_head = nullptr;
-    float *t_h = nullptr, *t_q = nullptr, *t_qr = nullptr, *t_ao = nullptr, *t_act = nullptr, *t_logits = nullptr,
-          *t_part = nullptr;
+    float *t_qr = nullptr, *t_ao = nullptr, *t_act = nullptr, *t_logits = nullptr, *t_part = nullptr;
+    double* t_cs = nullptr;           // rotary (cos, sin) of the token's position
+    ArgmaxWs* t_argmax = nullptr;
+    float* t_host = nullptr;          // pinned: the logits and the token of cake_first_token on their way to the caller
     int32_t* t_tok = nullptr;
     void* static_scratch = nullptr;   // this device's copy of the file-scope scratch array (set by cake_create)
     GemmSplitWs split{};       // float32 parts and ticket counters of launches that split K or keys (compute stream only)
@@ -246,33 +248,30 @@ static int enqueue_prefill(cake_ctx* c, int tok_begin, int rows, const cake_kv* 
     return CAKE_OK;
 }
 
-// Enqueues the first-token step for a prompt of n_tokens whose KV is complete; the last token's id
-// is already in c->d_ids[n_tokens-1].  The cache is read, never written.
-static int enqueue_first_token(cake_ctx* c, int n_tokens, const cake_kv* kv) {
+// Enqueues the first-token step for a prompt of n_tokens whose KV is complete and whose last token is `last_id`
+// (checked against the vocabulary by the callers).  The cache is read, never written.  token: where the result goes,
+// device or pinned; logits_host: pinned memory for the logits, or null.
+static int enqueue_first_token(cake_ctx* c, int n_tokens, int last_id, const cake_kv* kv, int32_t* token, float* logits_host) {
     const cake_model_desc& m = c->m;
     const uint64_t d = m.d_model, hq = uint64_t(m.n_q_heads) * m.head_dim, hkv = uint64_t(m.n_kv_heads) * m.head_dim;
     const uint64_t ff = m.ffn_dim, e = esize(c), T = n_tokens;
-    const int pos = n_tokens - 1;
-    HIP_TRY(c, launch_embed(m.dtype, c->embed, c->d_ids + pos, c->x, 1, d, m.vocab, c->cs));
+    HIP_TRY(c, launch_token_begin(m.dtype, c->embed, last_id, c->x, d, c->t_cs, m.head_dim, n_tokens - 1, m.rope_theta, c->cs));
     for (int l = 0; l < m.n_layers; ++l) {
         const cake_layer_weights& w = c->layers[l];
         KvView view = make_view(c, kv, l);
-        HIP_TRY(c, launch_rmsnorm(CAKE_F32, c->x, w.attn_norm, c->t_h, 1, d, m.rms_eps, c->cs));
         KLAUNCH(c, CAKE_K_GEMV, 2 * hq * d, hq * d * e,                 // the W_Q rows only: K and V of the token are cached
-                launch_gemv(m.dtype, 0, c->t_h, w.wqkv, nullptr, c->t_q, hq, d, c->cs));
-        HIP_TRY(c, launch_rope_token(c->t_q, c->t_qr, m.n_q_heads, m.head_dim, pos, m.rope_theta, c->cs));
+                launch_gemv(m.dtype, 3, {w.attn_norm, m.rms_eps}, c->x, w.wqkv, nullptr, c->t_qr, hq, d, c->cs, c->t_cs, m.head_dim));
         KLAUNCH(c, CAKE_K_DECODE_ATTN, 4 * hq * T, 2 * hkv * T * e,
                 launch_decode_attention(m.dtype, c->t_qr, c->t_ao, c->t_part, m.n_q_heads, n_tokens, view, c->cs,
                                         c->tun.kernel_path == 1));
-        KLAUNCH(c, CAKE_K_GEMV, 2 * d * hq, d * hq * e, launch_gemv(m.dtype, 1, c->t_ao, w.wo, nullptr, c->x, d, hq, c->cs));
-        HIP_TRY(c, launch_rmsnorm(CAKE_F32, c->x, w.ffn_norm, c->t_h, 1, d, m.rms_eps, c->cs));
-        KLAUNCH(c, CAKE_K_GEMV, 4 * ff * d, 2 * ff * d * e, launch_gemv(m.dtype, 2, c->t_h, w.w_gate, w.w_up, c->t_act, ff, d, c->cs));
-        KLAUNCH(c, CAKE_K_GEMV, 2 * d * ff, d * ff * e, launch_gemv(m.dtype, 1, c->t_act, w.w_down, nullptr, c->x, d, ff, c->cs));
+        KLAUNCH(c, CAKE_K_GEMV, 2 * d * hq, d * hq * e, launch_gemv(m.dtype, 1, {nullptr, 0.f}, c->t_ao, w.wo, nullptr, c->x, d, hq, c->cs));
+        KLAUNCH(c, CAKE_K_GEMV, 4 * ff * d, 2 * ff * d * e,
+                launch_gemv(m.dtype, 2, {w.ffn_norm, m.rms_eps}, c->x, w.w_gate, w.w_up, c->t_act, ff, d, c->cs));
+        KLAUNCH(c, CAKE_K_GEMV, 2 * d * ff, d * ff * e, launch_gemv(m.dtype, 1, {nullptr, 0.f}, c->t_act, w.w_down, nullptr, c->x, d, ff, c->cs));
     }
-    HIP_TRY(c, launch_rmsnorm(CAKE_F32, c->x, c->final_norm, c->t_h, 1, d, m.rms_eps, c->cs));
     KLAUNCH(c, CAKE_K_GEMV, 2 * uint64_t(m.vocab) * d, uint64_t(m.vocab) * d * e,
-            launch_gemv(m.dtype, 0, c->t_h, c->lm_head, nullptr, c->t_logits, m.vocab, d, c->cs));
-    HIP_TRY(c, launch_argmax(c->t_logits, m.vocab, c->t_tok, c->cs));
+            launch_gemv(m.dtype, 0, {c->final_norm, m.rms_eps}, c->x, c->lm_head, nullptr, c->t_logits, m.vocab, d, c->cs));
+    HIP_TRY(c, launch_argmax(c->t_logits, m.vocab, c->t_argmax, token, logits_host, c->cs));
     return CAKE_OK;
 }
 
@@ -558,14 +557,15 @@ int32_t cake_create(cake_ctx** out, const cake_model_desc* model, const cake_wei
     if (weights->final_norm && weights->lm_head) {
         c->final_norm = weights->final_norm;
         c->lm_head = weights->lm_head;
-        ok = ok && hipMalloc((void**)&c->t_h, size_t(m.d_model) * 4) == hipSuccess;
-        ok = ok && hipMalloc((void**)&c->t_q, hq * 4) == hipSuccess;
+        ok = ok && hipMalloc((void**)&c->t_cs, size_t(m.head_dim) * sizeof(double)) == hipSuccess;
+        ok = ok && hipMalloc((void**)&c->t_argmax, sizeof(ArgmaxWs)) == hipSuccess && hipMemset(c->t_argmax, 0, sizeof(ArgmaxWs)) == hipSuccess;
         ok = ok && hipMalloc((void**)&c->t_qr, hq * 4) == hipSuccess;
         ok = ok && hipMalloc((void**)&c->t_ao, hq * 4) == hipSuccess;
         ok = ok && hipMalloc((void**)&c->t_act, size_t(m.ffn_dim) * 4) == hipSuccess;
         ok = ok && hipMalloc((void**)&c->t_logits, size_t(m.vocab) * 4) == hipSuccess;
         ok = ok && hipMalloc((void**)&c->t_part, decode_attention_workspace_bytes(m.n_q_heads, m.head_dim)) == hipSuccess;
         ok = ok && hipMalloc((void**)&c->t_tok, 4) == hipSuccess;
+        ok = ok && hipHostMalloc((void**)&c->t_host, (size_t(m.vocab) + 1) * 4, hipHostMallocDefault) == hipSuccess;
     }
     if (!ok) {
         (void)hipGetLastError();
@@ -587,9 +587,10 @@ int32_t cake_destroy(cake_ctx* c) {
     if (c->cs || c->ls) (void)hipDeviceSynchronize();
     (void)hipFree(c->x); (void)hipFree(c->h); (void)hipFree(c->qkv); (void)hipFree(c->q);
     (void)hipFree(c->ao); (void)hipFree(c->act); (void)hipFree(c->rope_cs); (void)hipFree(c->d_ids);
-    (void)hipFree(c->t_h); (void)hipFree(c->t_q); (void)hipFree(c->t_qr); (void)hipFree(c->t_ao);
+    (void)hipFree(c->t_cs); (void)hipFree(c->t_argmax); (void)hipFree(c->t_qr); (void)hipFree(c->t_ao);
     (void)hipFree(c->t_act); (void)hipFree(c->t_logits); (void)hipFree(c->t_part); (void)hipFree(c->t_tok);
     (void)hipFree(c->q_stage); (void)hipFree(c->split.part); (void)hipFree(c->split.counters);
+    if (c->t_host) (void)hipHostFree(c->t_host);
     for (int i = 0; i < 2; ++i)
         if (c->f_stage[i]) (void)hipHostFree(c->f_stage[i]);
     for (hipEvent_t e : c->prof_events) (void)hipEventDestroy(e);
@@ -788,15 +789,14 @@ int32_t cake_first_token(cake_ctx* c, const int32_t* token_ids, int32_t n_tokens
     if (rc != CAKE_OK) return rc;
     const int32_t last = token_ids[n_tokens - 1];
     if (last < 0 || last >= c->m.vocab) return fail(c, CAKE_E_INVAL, "last token id outside the vocabulary");
-    HIP_TRY(c, hipMemcpyAsync(c->d_ids + (n_tokens - 1), &token_ids[n_tokens - 1], 4, hipMemcpyHostToDevice, c->cs));
     HIP_TRY(c, hipEventRecord(c->ev_a, c->cs));
-    rc = enqueue_first_token(c, n_tokens, kv);
+    int32_t* tok_host = (int32_t*)(c->t_host + c->m.vocab);
+    rc = enqueue_first_token(c, n_tokens, last, kv, tok_host, logits_out ? c->t_host : nullptr);
     if (rc != CAKE_OK) return rc;
     HIP_TRY(c, hipEventRecord(c->ev_b, c->cs));
-    HIP_TRY(c, hipMemcpyAsync(token_out, c->t_tok, 4, hipMemcpyDeviceToHost, c->cs));
-    if (logits_out)
-        HIP_TRY(c, hipMemcpyAsync(logits_out, c->t_logits, size_t(c->m.vocab) * 4, hipMemcpyDeviceToHost, c->cs));
     HIP_TRY(c, hipStreamSynchronize(c->cs));
+    *token_out = *tok_host;
+    if (logits_out) memcpy(logits_out, c->t_host, size_t(c->m.vocab) * 4);
     if (device_ns_out) {
         float ms = 0.f;
         HIP_TRY(c, hipEventElapsedTime(&ms, c->ev_a, c->ev_b));
@@ -1044,8 +1044,8 @@ int32_t cake_adaptive_serve(cake_ctx* c, cake_request* reqs, int32_t n_reqs, int
         for (const Part& p : parts) {
             const int32_t* ids = p.req < 0 ? c->tr_ids.data() : reqs[p.req].token_ids + p.first;
             const cake_kv* pkv = p.req < 0 ? &c->tr_kv : reqs[p.req].kv;
-            if (hipMemcpyAsync(c->d_ids + p.first, ids, size_t(p.count) * 4, hipMemcpyHostToDevice, c->cs) != hipSuccess) { hard = CAKE_E_HIP; break; }
-            int rc = p.decode ? enqueue_first_token(c, reqs[p.req].n_tokens, pkv) : enqueue_prefill(c, p.first, p.count, pkv);
+            if (!p.decode && hipMemcpyAsync(c->d_ids + p.first, ids, size_t(p.count) * 4, hipMemcpyHostToDevice, c->cs) != hipSuccess) { hard = CAKE_E_HIP; break; }
+            int rc = p.decode ? enqueue_first_token(c, reqs[p.req].n_tokens, ids[0], pkv, c->t_tok, nullptr) : enqueue_prefill(c, p.first, p.count, pkv);
             if (rc != CAKE_OK) { hard = rc; break; }
             // the token leaves the device before the next decode part overwrites it (one stream)
             if (p.decode && hipMemcpyAsync(&ft_tok[p.req], c->t_tok, 4, hipMemcpyDeviceToHost, c->cs) != hipSuccess) { hard = CAKE_E_HIP; break; }

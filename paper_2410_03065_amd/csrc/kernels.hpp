@@ -43,7 +43,6 @@ hipError_t launch_attention_generic(int dtype, const void* q, void* out, int n_q
 struct AttnWs { float* part; size_t bytes; int range_keys; };
 
 // ---- float32 on the matrix cores ----
-// part (or null): workspace for the key ranges of a launch with few queries; launches sharing it must not overlap.
 bool attention_f32_supported(const void* q, int n_keys, const KvView& kv);
 hipError_t launch_attention_f32(const float* q, float* out, int n_q, int tok_begin, int rows, const KvView& kv,
                                 hipStream_t st, const AttnWs& ws);
@@ -97,15 +96,23 @@ hipError_t launch_quant_page(int dtype, void* image, const KvView& kv, int phys_
                              hipStream_t st);
 
 // ---- first-token step (one row of activations: matrix-vector products, one-token attention) ----
-// out[n] (mode 0: =, 1: +=) sum_k x[k] w[n][k]; mode 2: out[n] = silu(x.w[n]) * (x.w2[n]).  x, out float32.
-hipError_t launch_gemv(int dtype, int mode, const float* x, const void* w, const void* w2, float* out,
-                       int N, int K, hipStream_t st);
-hipError_t launch_rope_token(const float* qin, float* qout, int n_heads, int head_dim, int pos,
-                             float theta, hipStream_t st);
+// h = x (gain null: mode 1 only) or its RMSNorm (gain, eps; modes 0, 2, 3): out[n] (mode 0: =, 1: +=) sum_k h[k] w[n][k];
+// mode 2: out[n] = silu(h.w[n]) * (h.w2[n]); mode 3: mode 0 with adjacent rows of a head rotated by cs[head_dim / 2]
+// (cos, sin).  x, out float32.
+struct GemvNorm { const float* gain; float eps; };
+hipError_t launch_gemv(int dtype, int mode, const GemvNorm& nm, const float* x, const void* w, const void* w2, float* out,
+                       int N, int K, hipStream_t st, const double* cs = nullptr, int head_dim = 0);
+// x = row `id` of the embedding table; cs[head_dim / 2] = (cos, sin) of the rotary pairs at position pos.
+hipError_t launch_token_begin(int dtype, const void* table, int id, float* x, int d, double* cs, int head_dim, int pos,
+                              float theta, hipStream_t st);
 size_t decode_attention_workspace_bytes(int n_q, int head_dim);
 // generic_only: keep to the vector-ALU kernel (testing)
 hipError_t launch_decode_attention(int dtype, const float* q, float* out, float* part, int n_q,
                                    int n_keys, const KvView& kv, hipStream_t st, bool generic_only = false);
-hipError_t launch_argmax(const float* v, int n, int32_t* result, hipStream_t st);
+// Device memory of launch_argmax; counter is zero between launches.
+constexpr int ARGMAX_BLOCKS = 128;
+struct ArgmaxWs { unsigned long long best[ARGMAX_BLOCKS]; unsigned counter; };
+// host: null, or pinned memory for a copy of the n values.
+hipError_t launch_argmax(const float* v, int n, ArgmaxWs* ws, int32_t* result, float* host, hipStream_t st);
 
 }  // namespace cake

@@ -7,6 +7,7 @@
 // The paper counts the time to first token up to "the generation of the first token" (Sec. 5.1,
 // Metrics); the prefill it describes (Sec. 3) ends with that token's logits.
 #include <algorithm>
+#include <type_traits>
 
 #include "kernels.hpp"
 
@@ -66,80 +67,205 @@ template <> struct Ld16<bf16_t> {
 }  // namespace
 
 // ------------------------------------------------------------------ matrix-vector product
-// out[n] (op)= sum_k x[k] * w[n][k]; one wave per output row, 16-byte loads, 1 KB of the row per
-// wave-instruction.  MODE 0: store; 1: add into out (residual stream); 2: silu(x.w[n]) * (x.w2[n]).
-template <typename T, int MODE>
-__global__ void __launch_bounds__(256) gemv_kernel(const float* __restrict__ x, const T* __restrict__ w,
-                                                   const T* __restrict__ w2, float* __restrict__ out, int N, int K) {
-    constexpr int E = Ld16<T>::N;
-    const int lane = threadIdx.x & 63;
-    const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (row >= N) return;
-    const T* wr = w + size_t(row) * K;
-    const T* wr2 = MODE == 2 ? w2 + size_t(row) * K : nullptr;
-    float acc = 0.f, acc2 = 0.f;
-#pragma unroll 4
-    for (int k = lane * E; k + E <= K; k += 64 * E) {
-        float wf[E], xf[E];
-        Ld16<T>::load(wr + k, wf);
+// out[n] (op)= sum_k h[k] * w[n][k], where h is x itself or its RMSNorm (NORM: h = x / sqrt(mean(x^2) + eps) * gain).
+// MODE 0: store; 1: add into out (residual stream); 2: silu(h.w[n]) * (h.w2[n]); 3: store with the rotary embedding of
+// the token applied, rows 2i and 2i+1 of a head being a pair.
+//
+// One wave takes RB consecutive rows, 16-byte loads, 1 KB of a row per wave-instruction.  The weights are read once
+// from HBM and bound the kernel: U pieces of every row are loaded before the first is used.  The norm needs no pass of
+// its own: the squares are summed beside the products, the sums scaled at the end; and a wave holds both rows of a
+// rotary pair.  Where x is normed and long enough to be worth a barrier, the workgroup stages x times the gain in LDS
+// behind the first weight loads (STAGED: 2048 to 16K elements), otherwise every wave reads both from the caches.
+// One row per wave (two for a rotary pair; four where there are 16K rows and more).  us for the Llama3-8B shape: W_q
+// with norm and rotation 9.8 (norm 4.3, product 7.7 and rotation 4.5 as three launches), gate/up with norm 42 (4.3 and
+// 41), LM head 171 (4.3 and 182); two rows per wave took 23.1 instead of 22.7 for the down product, and a second set of
+// loads in flight 26.
+template <typename T, int MODE, int RB, bool NORM, bool STAGED>
+__global__ void __launch_bounds__(256) gemv_kernel(const float* __restrict__ x, const float* __restrict__ gain, float eps,
+                                                   const T* __restrict__ w, const T* __restrict__ w2, float* __restrict__ out, int N,
+                                                   int K, const double2* __restrict__ cs, int head_dim) {
+    constexpr int E = Ld16<T>::N, NM = MODE == 2 ? 2 : 1;
+    constexpr int U = RB * NM >= 4 ? 2 : 4, PIECE = 64 * E;   // pieces in flight per row
+    extern __shared__ __attribute__((aligned(16))) float xs[];
+    __shared__ float ss_part[4];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int row0 = (blockIdx.x * 4 + wave) * RB;
+    const T* wr[NM][RB];
+#pragma unroll
+    for (int r = 0; r < RB; ++r) {
+        wr[0][r] = w + size_t(min(row0 + r, N - 1)) * K;
+        if constexpr (NM == 2) wr[1][r] = w2 + size_t(min(row0 + r, N - 1)) * K;
+    }
+    struct Set { uint4 raw[U][NM][RB]; };
+    // whole sets in one go, the last one piece by piece (wave-uniform choices)
+    auto load_piece = [&](Set& st, int u, int k) {
+#pragma unroll
+        for (int m = 0; m < NM; ++m)
+#pragma unroll
+            for (int r = 0; r < RB; ++r) st.raw[u][m][r] = Ld16<T>::raw(wr[m][r] + k);
+    };
+    auto load = [&](Set& st, int k0) {
+        if (k0 + U * PIECE <= K) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) load_piece(st, u, k0 + u * PIECE + lane * E);
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int k = k0 + u * PIECE + lane * E;
+                if (k0 + (u + 1) * PIECE <= K) load_piece(st, u, k);   // without a test per lane
+                else if (k < K) load_piece(st, u, k);
+            }
+        }
+    };
+    float acc[NM][RB] = {}, ss = 0.f;
+    auto multiply_piece = [&](const Set& st, int u, int k) {
+        float xf[E];
 #pragma unroll
         for (int e = 0; e < E; e += 4) {
-            const float4 xv = *(const float4*)(x + k + e);
+            const float4 xv = STAGED ? *(const float4*)(xs + k + e) : *(const float4*)(x + k + e);
             xf[e] = xv.x; xf[e + 1] = xv.y; xf[e + 2] = xv.z; xf[e + 3] = xv.w;
+            if constexpr (NORM && !STAGED) {
+                const float4 gv = *(const float4*)(gain + k + e);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) ss = __builtin_fmaf(xf[e + i], xf[e + i], ss);
+                xf[e] *= gv.x; xf[e + 1] *= gv.y; xf[e + 2] *= gv.z; xf[e + 3] *= gv.w;
+            }
         }
 #pragma unroll
-        for (int e = 0; e < E; ++e) acc = __builtin_fmaf(wf[e], xf[e], acc);
-        if (MODE == 2) {
-            Ld16<T>::load(wr2 + k, wf);
+        for (int m = 0; m < NM; ++m)
 #pragma unroll
-            for (int e = 0; e < E; ++e) acc2 = __builtin_fmaf(wf[e], xf[e], acc2);
+            for (int r = 0; r < RB; ++r) {
+                float wf[E];
+                Ld16<T>::unpack(st.raw[u][m][r], wf);
+#pragma unroll
+                for (int e = 0; e < E; ++e) acc[m][r] = __builtin_fmaf(wf[e], xf[e], acc[m][r]);
+            }
+    };
+    auto multiply = [&](const Set& st, int k0) {
+        if (k0 + U * PIECE <= K) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) multiply_piece(st, u, k0 + u * PIECE + lane * E);
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int k = k0 + u * PIECE + lane * E;
+                if (k0 + (u + 1) * PIECE <= K) multiply_piece(st, u, k);
+                else if (k < K) multiply_piece(st, u, k);
+            }
         }
+    };
+    Set set;
+    load(set, 0);
+    if constexpr (STAGED) {
+        for (int k = threadIdx.x * 4; k < K; k += 1024) {
+            float4 v = *(const float4*)(x + k);
+            if constexpr (NORM) {
+                const float4 g = *(const float4*)(gain + k);
+                ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+                v.x *= g.x; v.y *= g.y; v.z *= g.z; v.w *= g.w;
+            }
+            *(float4*)(xs + k) = v;
+        }
+        if constexpr (NORM) {
+            ss = wsum(ss);
+            if (lane == 0) ss_part[wave] = ss;
+        }
+        __syncthreads();
+        if constexpr (NORM) ss = ss_part[0] + ss_part[1] + ss_part[2] + ss_part[3];
     }
-    acc = wsum(acc);
-    if (MODE == 2) acc2 = wsum(acc2);
-    if (lane == 0) {
-        if (MODE == 0) out[row] = acc;
-        else if (MODE == 1) out[row] += acc;
-        else out[row] = acc / (1.0f + __expf(-acc)) * acc2;
+    if (row0 >= N) return;
+    for (int k0 = 0; k0 < K; k0 += U * PIECE) {
+        multiply(set, k0);
+        load(set, k0 + U * PIECE);
+    }
+    float norm = 1.0f;
+    if constexpr (NORM) norm = 1.0f / sqrtf((STAGED ? ss : wsum(ss)) / float(K) + eps);
+#pragma unroll
+    for (int m = 0; m < NM; ++m)
+#pragma unroll
+        for (int r = 0; r < RB; ++r) acc[m][r] = wsum(acc[m][r]) * norm;
+    if (lane != 0) return;
+#pragma unroll
+    for (int r = 0; r < RB; ++r) {
+        const int row = row0 + r;
+        if (row >= N) break;
+        if constexpr (MODE == 0) out[row] = acc[0][r];
+        else if constexpr (MODE == 1) out[row] += acc[0][r];
+        else if constexpr (MODE == 2) out[row] = acc[0][r] / (1.0f + __expf(-acc[0][r])) * acc[1][r];
+        else if ((r & 1) == 0) {   // N and the head dimension are even
+            const double2 c = cs[(row % head_dim) / 2];
+            out[row] = float(acc[0][r] * c.x - acc[0][r + 1] * c.y);
+            out[row + 1] = float(acc[0][r] * c.y + acc[0][r + 1] * c.x);
+        }
     }
 }
 
-hipError_t launch_gemv(int dtype, int mode, const float* x, const void* w, const void* w2, float* out, int N, int K,
-                       hipStream_t st) {
-    if (N <= 0) return hipSuccess;
-    if (K % (dtype == 0 ? 4 : 8) || mode < 0 || mode > 2) return hipErrorInvalidValue;
-    dim3 grid((N + 3) / 4), block(256);
-#define CAKE_GEMV(T, MODE) \
-    hipLaunchKernelGGL((gemv_kernel<T, MODE>), grid, block, 0, st, x, (const T*)w, (const T*)w2, out, N, K)
-    if (dtype == 0) {
-        if (mode == 0) CAKE_GEMV(float, 0); else if (mode == 1) CAKE_GEMV(float, 1); else CAKE_GEMV(float, 2);
-    } else {
-        if (mode == 0) CAKE_GEMV(bf16_t, 0); else if (mode == 1) CAKE_GEMV(bf16_t, 1); else CAKE_GEMV(bf16_t, 2);
+template <typename T, int MODE, bool NORM>
+static hipError_t gemv_launch(const GemvNorm& nm, const float* x, const void* w, const void* w2, float* out, int N, int K,
+                              const double* cs, int head_dim, hipStream_t st) {
+    constexpr int RB_MIN = MODE == 3 ? 2 : 1;
+#define CAKE_GEMV(RB, STAGED, LDS)                                                                                        \
+    hipLaunchKernelGGL((gemv_kernel<T, MODE, RB, NORM, STAGED>), dim3((N + 4 * RB - 1) / (4 * RB)), dim3(256), LDS, st, x, \
+                       nm.gain, nm.eps, (const T*)w, (const T*)w2, out, N, K, (const double2*)cs, head_dim)
+    const size_t lds = size_t(K) * sizeof(float);
+    if constexpr (NORM) {
+        if (K >= 2048 && lds <= 65000) {
+            if (N >= 16384 && MODE == 0) CAKE_GEMV(4, true, lds);
+            else CAKE_GEMV(RB_MIN, true, lds);
+            return hipGetLastError();
+        }
     }
+    if (N >= 16384 && MODE == 0) CAKE_GEMV(4, false, 0);
+    else CAKE_GEMV(RB_MIN, false, 0);
 #undef CAKE_GEMV
     return hipGetLastError();
 }
 
-// ------------------------------------------------------------------ rotary on one token's queries
-// q[h][2i], q[h][2i+1] rotated by pos * theta^(-2i/hd); the angle is formed in double precision
-// like the prefill's table.
-__global__ void rope_token_kernel(const float* __restrict__ qin, float* __restrict__ qout, int n_pairs, int half,
-                                  int pos, double log2_theta) {
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= n_pairs) return;
-    const int pair = idx % half;
-    const double inv_freq = exp2(-(double(pair) / double(half)) * log2_theta);
-    double s, c;
-    sincos(double(pos) * inv_freq, &s, &c);
-    const float2 v = ((const float2*)qin)[idx];
-    ((float2*)qout)[idx] = make_float2(float(v.x * c - v.y * s), float(v.x * s + v.y * c));
+hipError_t launch_gemv(int dtype, int mode, const GemvNorm& nm, const float* x, const void* w, const void* w2, float* out, int N,
+                       int K, hipStream_t st, const double* cs, int head_dim) {
+    if (N <= 0) return hipSuccess;
+    if (K % (dtype == 0 ? 4 : 8) || mode < 0 || mode > 3 || (mode == 3 && (!cs || !nm.gain)) || (mode == 1 && nm.gain)) return hipErrorInvalidValue;
+#define CAKE_GEMV(MODE, NORM)                                                                              \
+    return dtype == 0 ? gemv_launch<float, MODE, NORM>(nm, x, w, w2, out, N, K, cs, head_dim, st)          \
+                      : gemv_launch<bf16_t, MODE, NORM>(nm, x, w, w2, out, N, K, cs, head_dim, st)
+    if (mode == 1) CAKE_GEMV(1, false);
+    if (mode == 3) CAKE_GEMV(3, true);
+    if (!nm.gain) return hipErrorInvalidValue;   // the step's other products all follow a norm
+    if (mode == 2) CAKE_GEMV(2, true);
+    CAKE_GEMV(0, true);
+#undef CAKE_GEMV
 }
 
-hipError_t launch_rope_token(const float* qin, float* qout, int n_heads, int head_dim, int pos, float theta,
-                             hipStream_t st) {
-    const int half = head_dim / 2, n = n_heads * half;
-    hipLaunchKernelGGL(rope_token_kernel, dim3((n + 255) / 256), dim3(256), 0, st, qin, qout, n, half, pos,
-                       log2(double(theta)));
+// ------------------------------------------------------------------ what every layer of the step starts from
+// x = the token's embedding row (grid.x - 1 workgroups of 1024 elements), and the rotary pairs' (cos, sin) of its
+// position in double precision like the prefill's table (the last workgroup).
+template <typename T>
+__global__ void __launch_bounds__(256) token_begin_kernel(const T* __restrict__ table, int id, float* __restrict__ x, int d,
+                                                          double2* __restrict__ cs, int half, int pos, double log2_theta) {
+    if (blockIdx.x == gridDim.x - 1) {
+        for (int pair = threadIdx.x; pair < half; pair += 256) {
+            const double inv_freq = exp2(-(double(pair) / double(half)) * log2_theta);
+            double s, c;
+            sincos(double(pos) * inv_freq, &s, &c);
+            cs[pair] = make_double2(c, s);
+        }
+        return;
+    }
+    const T* src = table + size_t(id) * d;
+    const int lo = blockIdx.x * 1024;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int c = lo + threadIdx.x + 256 * i;
+        if (c < d) x[c] = float(src[c]);
+    }
+}
+
+hipError_t launch_token_begin(int dtype, const void* table, int id, float* x, int d, double* cs, int head_dim, int pos, float theta,
+                              hipStream_t st) {
+    const dim3 grid((d + 1023) / 1024 + 1), block(256);
+    const double l2 = log2(double(theta));
+    if (dtype == 0) hipLaunchKernelGGL(token_begin_kernel<float>, grid, block, 0, st, (const float*)table, id, x, d, (double2*)cs, head_dim / 2, pos, l2);
+    else hipLaunchKernelGGL(token_begin_kernel<bf16_t>, grid, block, 0, st, (const bf16_t*)table, id, x, d, (double2*)cs, head_dim / 2, pos, l2);
     return hipGetLastError();
 }
 
@@ -370,34 +496,69 @@ hipError_t launch_decode_attention(int dtype, const float* q, float* out, float*
 }
 
 // ------------------------------------------------------------------ argmax over the logits
-// result[0] = index of the largest value (the lowest index among equal values).
-__global__ void __launch_bounds__(1024) argmax_kernel(const float* __restrict__ v, int n, int32_t* __restrict__ result) {
-    __shared__ float bv[16];
-    __shared__ int bi[16];
-    float best = -INFINITY;
-    int idx = 0x7fffffff;
-    for (int i = threadIdx.x; i < n; i += 1024) {
-        const float x = v[i];
-        if (x > best || (x == best && i < idx)) { best = x; idx = i; }
-    }
+// result[0] = index of the largest value (the lowest index among equal values); `host`, if given, gets a copy of the
+// values (pinned memory: a copy by the copy engine into the caller's pageable buffer takes 88 us for 32 000 and 241 us
+// for 128 256 values, writing them here and copying on the CPU 28 and 41 with the wait).  Workgroups take 1024-element pieces in
+// turn and leave their best in `best`; the one that draws the last ticket looks those through and puts the counter back.
+// (One workgroup over 128 256 logits took 56 us, most of it waiting for one load after another.)
+__device__ __forceinline__ void argmax_take(float x, int i, float* best, int* idx) {
+    if (x > *best || (x == *best && i < *idx)) { *best = x; *idx = i; }
+}
+__device__ __forceinline__ void argmax_wave(float* best, int* idx) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
-        const float ob = __shfl_xor(best, o, 64);
-        const int oi = __shfl_xor(idx, o, 64);
-        if (ob > best || (ob == best && oi < idx)) { best = ob; idx = oi; }
-    }
-    if ((threadIdx.x & 63) == 0) { bv[threadIdx.x >> 6] = best; bi[threadIdx.x >> 6] = idx; }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < 16; ++w)
-            if (bv[w] > best || (bv[w] == best && bi[w] < idx)) { best = bv[w]; idx = bi[w]; }
-        result[0] = idx;
+        const float ob = __shfl_xor(*best, o, 64);
+        const int oi = __shfl_xor(*idx, o, 64);
+        argmax_take(ob, oi, best, idx);
     }
 }
 
-hipError_t launch_argmax(const float* v, int n, int32_t* result, hipStream_t st) {
+__global__ void __launch_bounds__(256) argmax_kernel(const float* __restrict__ v, int n, unsigned long long* __restrict__ best_of,
+                                                     unsigned* __restrict__ counter, int32_t* __restrict__ result,
+                                                     float* __restrict__ host) {
+    __shared__ float bv[4];
+    __shared__ int bi[4];
+    __shared__ unsigned ticket;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    float best = -INFINITY;
+    int idx = 0x7fffffff;
+    for (int base = blockIdx.x * 1024; base < n; base += gridDim.x * 1024)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int at = base + threadIdx.x + 256 * i;
+            if (at < n) {
+                const float x = v[at];
+                if (host) host[at] = x;
+                argmax_take(x, at, &best, &idx);
+            }
+        }
+    argmax_wave(&best, &idx);
+    if (lane == 0) { bv[wave] = best; bi[wave] = idx; }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < 4; ++w) argmax_take(bv[w], bi[w], &best, &idx);
+        __hip_atomic_store(&best_of[blockIdx.x], (unsigned long long)(unsigned)idx << 32 | __float_as_uint(best), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+        ticket = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (ticket != gridDim.x - 1 || wave != 0) return;
+    best = -INFINITY;
+    idx = 0x7fffffff;
+    for (int b = lane; b < int(gridDim.x); b += 64) {
+        const unsigned long long p = __hip_atomic_load(&best_of[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        argmax_take(__uint_as_float(unsigned(p)), int(unsigned(p >> 32)), &best, &idx);
+    }
+    argmax_wave(&best, &idx);
+    if (lane == 0) {
+        result[0] = idx;
+        __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+hipError_t launch_argmax(const float* v, int n, ArgmaxWs* ws, int32_t* result, float* host, hipStream_t st) {
     if (n <= 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(argmax_kernel, dim3(1), dim3(1024), 0, st, v, n, result);
+    hipLaunchKernelGGL(argmax_kernel, dim3(std::min(ARGMAX_BLOCKS, (n + 1023) / 1024)), dim3(256), 0, st, v, n, ws->best, &ws->counter, result, host);
     return hipGetLastError();
 }
 
