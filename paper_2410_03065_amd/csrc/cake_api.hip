@@ -173,6 +173,13 @@ static KvView make_view(const cake_ctx* c, const cake_kv* kv, int layer) {
 }
 
 // ------------------------------------------------------------------ kernel dispatch
+// How a bf16 product may leave its K ranges in the split workspace (ksplit 0: it does not).  Not where a test forces a
+// kernel.
+static GemmPartsPlan parts_plan(const cake_ctx* c, int epi, int M, int N, int K, bool fused) {
+    if (c->m.dtype != CAKE_BF16 || c->tun.kernel_path != 0 || c->tun.gemm_config != 0 || c->tun.gemm_ksplit != 0) return GemmPartsPlan{0, false};
+    return gemm_parts_plan(epi, M, N, K, c->split.part ? &c->split : nullptr, fused);
+}
+
 static hipError_t gemm(cake_ctx* c, int epi, const void* a, const void* w, const void* w2, void* out, int M, int N, int K) {
     if (c->m.dtype == CAKE_BF16 && c->tun.kernel_path == 0 && gemm_mfma_supported(epi, M, N, K))
         return launch_gemm_mfma(epi, a, w, w2, out, M, N, K, c->cs, c->tun.gemm_config - 1, c->split.part ? &c->split : nullptr,
@@ -228,23 +235,40 @@ static int enqueue_prefill(cake_ctx* c, int tok_begin, int rows, const cake_kv* 
     const uint64_t attn_bytes = (2 * R * hq + 2 * hkv * (t0 + R)) * e;
     KLAUNCH(c, CAKE_K_EMBED, 0, R * d * (e + 4), launch_embed(m.dtype, c->embed, c->d_ids + tok_begin, c->x, rows, d, m.vocab, c->cs));
     HIP_TRY(c, launch_rope_table(c->rope_cs, tok_begin, rows, m.head_dim, m.rope_theta, c->cs));
+    // A product may leave its K ranges in the split workspace for the kernel after it, which reads them before anything
+    // else is put there: QKV for the rotary step, O and down for the norm (the last layer's down for a sum of its own).
+    const bool rope_adds = m.head_dim == 128 && (uintptr_t(kv->pool) & 15) == 0;
+    const GemmPartsPlan none{0, false};
+    const GemmPartsPlan p_qkv = rope_adds ? parts_plan(c, EPI_STORE_F32, rows, int(nqkv), int(d), true) : none;
+    const GemmPartsPlan p_o = parts_plan(c, EPI_RESIDUAL_F32, rows, int(d), int(hq), true);
+    const GemmPartsPlan p_down = parts_plan(c, EPI_RESIDUAL_F32, rows, int(d), m.ffn_dim, true);
+    float* parts = c->split.part;
+    auto norm = [&](const GemmPartsPlan& left, const float* gain) {
+        return left.ksplit ? launch_rmsnorm_parts(m.dtype, c->x, parts, left.ksplit, gain, c->h, rows, d, m.rms_eps, c->cs)
+                           : launch_rmsnorm(m.dtype, c->x, gain, c->h, rows, d, m.rms_eps, c->cs);
+    };
+    auto product = [&](const GemmPartsPlan& plan, int epi, const void* a, const void* w, float* out, int N, int K) {
+        return plan.ksplit ? launch_gemm_parts(plan, a, w, parts, rows, N, K, c->cs) : gemm(c, epi, a, w, nullptr, out, rows, N, K);
+    };
     for (int l = 0; l < m.n_layers; ++l) {
         const cake_layer_weights& w = c->layers[l];
         KvView view = make_view(c, kv, l);
-        KLAUNCH(c, CAKE_K_RMSNORM, 0, R * d * (4 + e), launch_rmsnorm(m.dtype, c->x, w.attn_norm, c->h, rows, d, m.rms_eps, c->cs));
+        KLAUNCH(c, CAKE_K_RMSNORM, 0, R * d * (4 + e), norm(l > 0 ? p_down : none, w.attn_norm));
         KLAUNCH(c, CAKE_K_GEMM_QKV, 2 * R * nqkv * d, (R * d + nqkv * d) * e + R * nqkv * 4,
-                gemm(c, EPI_STORE_F32, c->h, w.wqkv, nullptr, c->qkv, rows, nqkv, d));
+                product(p_qkv, EPI_STORE_F32, c->h, w.wqkv, c->qkv, nqkv, d));
         KLAUNCH(c, CAKE_K_ROPE_KV, 0, R * nqkv * (4 + e),
-                launch_rope_kv_write(m.dtype, c->qkv, c->rope_cs, c->q, m.n_q_heads, tok_begin, rows, view, c->cs));
+                launch_rope_kv_write(m.dtype, p_qkv.ksplit ? parts : c->qkv, c->rope_cs, c->q, m.n_q_heads, tok_begin, rows, view, c->cs,
+                                     p_qkv.ksplit ? p_qkv.ksplit : 1));
         KLAUNCH(c, CAKE_K_ATTENTION, attn_flops, attn_bytes, attention(c, c->q, c->ao, tok_begin, rows, view));
         KLAUNCH(c, CAKE_K_GEMM_O, 2 * R * d * hq, (R * hq + d * hq) * e + 2 * R * d * 4,
-                gemm(c, EPI_RESIDUAL_F32, c->ao, w.wo, nullptr, c->x, rows, d, hq));
-        KLAUNCH(c, CAKE_K_RMSNORM, 0, R * d * (4 + e), launch_rmsnorm(m.dtype, c->x, w.ffn_norm, c->h, rows, d, m.rms_eps, c->cs));
+                product(p_o, EPI_RESIDUAL_F32, c->ao, w.wo, c->x, d, hq));
+        KLAUNCH(c, CAKE_K_RMSNORM, 0, R * d * (4 + e), norm(p_o, w.ffn_norm));
         KLAUNCH(c, CAKE_K_GEMM_GATEUP, 4 * R * ff * d, (R * d + 2 * ff * d + R * ff) * e,
                 gemm(c, EPI_SWIGLU, c->h, w.w_gate, w.w_up, c->act, rows, m.ffn_dim, d));
         KLAUNCH(c, CAKE_K_GEMM_DOWN, 2 * R * d * ff, (R * ff + d * ff) * e + 2 * R * d * 4,
-                gemm(c, EPI_RESIDUAL_F32, c->act, w.w_down, nullptr, c->x, rows, d, m.ffn_dim));
+                product(p_down, EPI_RESIDUAL_F32, c->act, w.w_down, c->x, d, m.ffn_dim));
     }
+    if (p_down.ksplit) HIP_TRY(c, launch_add_parts(c->x, parts, p_down.ksplit, size_t(rows) * d, c->cs));
     return CAKE_OK;
 }
 

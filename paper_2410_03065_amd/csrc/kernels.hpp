@@ -30,8 +30,13 @@ hipError_t launch_rmsnorm(int dtype, const float* x, const float* gain, void* ou
                           float eps, hipStream_t st);
 hipError_t launch_rope_table(float* cs, int tok_begin, int rows, int head_dim, float theta,
                              hipStream_t st);
+// n_parts > 1: qkv[n_parts][rows][...] is added up as it is read (bf16, head_dim 128, 16-byte aligned pointers only).
 hipError_t launch_rope_kv_write(int dtype, const float* qkv, const float* cs, void* q, int n_q,
-                                int tok_begin, int rows, const KvView& kv, hipStream_t st);
+                                int tok_begin, int rows, const KvView& kv, hipStream_t st, int n_parts = 1);
+// x += parts[0] + ... + parts[n_parts - 1] (each [rows][d], float32, 16-byte aligned), then the norm of the sum.
+hipError_t launch_rmsnorm_parts(int dtype, float* x, const float* parts, int n_parts, const float* gain, void* out, int rows,
+                                int d, float eps, hipStream_t st);
+hipError_t launch_add_parts(float* x, const float* parts, int n_parts, size_t n, hipStream_t st);
 hipError_t launch_gemm_generic(int dtype, int epi, const void* a, const void* w, const void* w2,
                                void* out, int M, int N, int K, hipStream_t st);
 hipError_t launch_attention_generic(int dtype, const void* q, void* out, int n_q, int tok_begin,
@@ -72,6 +77,19 @@ hipError_t launch_gemm_mfma(int epi, const void* a, const void* w, const void* w
 // What launch_gemm_mfma would launch: tile rows / columns and K ranges per tile.
 void gemm_mfma_plan(int epi, int M, int N, int K, int cfg_override, const GemmSplitWs* ws, int ksplit_override,
                     int* bm, int* bn, int* ksplit);
+// out[ks][M][N] float32: one output per K range (K a multiple of 64 ks), for a consumer that adds them up.
+// rows: M <= 192, N a multiple of 128; p256: N a multiple of 256.
+hipError_t launch_gemm_rows_parts(const void* a, const void* w, float* part, int M, int N, int K, int ks, hipStream_t st);
+hipError_t launch_gemm_p256_parts(const void* a, const void* w, float* part, int M, int N, int K, int ks, hipStream_t st);
+// How to leave a product (epi: store or residual) to its consumer: ksplit 0: not, launch_gemm_mfma is faster; else K in
+// that many ranges on the kernel for few rows or on the persistent one.  fused: the consumer reads the result anyway
+// (an RMSNorm, the rotary step); otherwise a pass of its own adds the ranges up.
+struct GemmPartsPlan { int ksplit; bool few_rows; };
+GemmPartsPlan gemm_parts_plan(int epi, int M, int N, int K, const GemmSplitWs* ws, bool fused);
+inline hipError_t launch_gemm_parts(const GemmPartsPlan& plan, const void* a, const void* w, float* part, int M, int N, int K, hipStream_t st) {
+    return plan.few_rows ? launch_gemm_rows_parts(a, w, part, M, N, K, plan.ksplit, st)
+                         : launch_gemm_p256_parts(a, w, part, M, N, K, plan.ksplit, st);
+}
 // MFMA-only yardstick kernel: out holds workgroups * 8 floats; see kernels_gemm.hip.
 hipError_t launch_mfma_rate(float* out, int workgroups, int iters, hipStream_t st);
 bool attention_mfma_supported(int head_dim, int page_tokens);

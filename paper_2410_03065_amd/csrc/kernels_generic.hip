@@ -67,16 +67,31 @@ __global__ void __launch_bounds__(256) rmsnorm_kernel(const float* __restrict__ 
 }
 
 // Rows whose length is a multiple of 1024: every thread keeps its NV float4 pieces of the row in
-// registers (one 16-byte load each, all in flight together), so the row is read once.
-template <typename T, int NV>
-__global__ void __launch_bounds__(256) rmsnorm_vec_kernel(const float* __restrict__ x, const float* __restrict__ gain,
-                                                          T* __restrict__ out, float eps) {
+// registers (one 16-byte load each, all in flight together), so the row is read once.  PARTS: the K ranges of the
+// product in front of the norm, parts[n_parts][rows][d], are added to the residual stream on the way (in that order)
+// and the sum is written back; bound by the ranges' way through memory (1024 x 4096 with four ranges 64 + 32 MB).
+template <typename T, int NV, bool PARTS>
+__global__ void __launch_bounds__(256) rmsnorm_vec_kernel(float* __restrict__ x, const float* __restrict__ parts, int n_parts,
+                                                          const float* __restrict__ gain, T* __restrict__ out, float eps) {
     __shared__ float part[4];
     constexpr int d = NV * 1024;
-    const float4* xr = (const float4*)(x + size_t(blockIdx.x) * d);
+    float4* xr = (float4*)(x + size_t(blockIdx.x) * d);
     float4 v[NV];
 #pragma unroll
     for (int i = 0; i < NV; ++i) v[i] = xr[threadIdx.x + 256 * i];
+    if constexpr (PARTS) {
+        const float4* pr = (const float4*)(parts + size_t(blockIdx.x) * d) + threadIdx.x;
+        const size_t step = size_t(gridDim.x) * (d / 4);
+#pragma unroll 4
+        for (int p = 0; p < n_parts; ++p)
+#pragma unroll
+            for (int i = 0; i < NV; ++i) {
+                const float4 a = pr[p * step + 256 * i];
+                v[i].x += a.x; v[i].y += a.y; v[i].z += a.z; v[i].w += a.w;
+            }
+#pragma unroll
+        for (int i = 0; i < NV; ++i) xr[threadIdx.x + 256 * i] = v[i];
+    }
     float s = 0.f;
 #pragma unroll
     for (int i = 0; i < NV; ++i) s += v[i].x * v[i].x + v[i].y * v[i].y + v[i].z * v[i].z + v[i].w * v[i].w;
@@ -102,11 +117,15 @@ __global__ void __launch_bounds__(256) rmsnorm_vec_kernel(const float* __restric
 }
 
 template <typename T>
-static bool launch_rmsnorm_vec(const float* x, const float* gain, T* out, int rows, int d, float eps, hipStream_t st) {
-    if (d % 1024 != 0 || d > 8192 || ((uintptr_t(x) | uintptr_t(gain) | uintptr_t(out)) & 15)) return false;
+static bool launch_rmsnorm_vec(float* x, const float* parts, int n_parts, const float* gain, T* out, int rows, int d, float eps,
+                               hipStream_t st) {
+    if (d % 1024 != 0 || d > 8192 || ((uintptr_t(x) | uintptr_t(parts) | uintptr_t(gain) | uintptr_t(out)) & 15)) return false;
     switch (d / 1024) {
-#define CAKE_RMS_CASE(NV) \
-    case NV: hipLaunchKernelGGL((rmsnorm_vec_kernel<T, NV>), dim3(rows), dim3(256), 0, st, x, gain, out, eps); return true;
+#define CAKE_RMS_CASE(NV)                                                                                                          \
+    case NV:                                                                                                                       \
+        if (n_parts) hipLaunchKernelGGL((rmsnorm_vec_kernel<T, NV, true>), dim3(rows), dim3(256), 0, st, x, parts, n_parts, gain, out, eps); \
+        else hipLaunchKernelGGL((rmsnorm_vec_kernel<T, NV, false>), dim3(rows), dim3(256), 0, st, x, parts, 0, gain, out, eps);    \
+        return true;
         CAKE_RMS_CASE(1) CAKE_RMS_CASE(2) CAKE_RMS_CASE(3) CAKE_RMS_CASE(4) CAKE_RMS_CASE(5) CAKE_RMS_CASE(6) CAKE_RMS_CASE(7)
         CAKE_RMS_CASE(8)
 #undef CAKE_RMS_CASE
@@ -117,12 +136,43 @@ static bool launch_rmsnorm_vec(const float* x, const float* gain, T* out, int ro
 hipError_t launch_rmsnorm(int dtype, const float* x, const float* gain, void* out, int rows, int d, float eps,
                           hipStream_t st) {
     if (rows <= 0) return hipSuccess;
-    if (dtype == 0 ? launch_rmsnorm_vec(x, gain, (float*)out, rows, d, eps, st)
-                   : launch_rmsnorm_vec(x, gain, (bf16_t*)out, rows, d, eps, st))
+    if (dtype == 0 ? launch_rmsnorm_vec((float*)x, nullptr, 0, gain, (float*)out, rows, d, eps, st)   // without parts x is only read
+                   : launch_rmsnorm_vec((float*)x, nullptr, 0, gain, (bf16_t*)out, rows, d, eps, st))
         return hipGetLastError();
     if (dtype == 0) hipLaunchKernelGGL(rmsnorm_kernel<float>, dim3(rows), dim3(256), 0, st, x, gain, (float*)out, d, eps);
     else hipLaunchKernelGGL(rmsnorm_kernel<bf16_t>, dim3(rows), dim3(256), 0, st, x, gain, (bf16_t*)out, d, eps);
     return hipGetLastError();
+}
+
+// x[n] += parts[0][n] + parts[1][n] + ... in that order; n a multiple of 4.
+__global__ void __launch_bounds__(256) add_parts_kernel(float4* __restrict__ x, const float4* __restrict__ parts, int n_parts, size_t n4) {
+    for (size_t i = blockIdx.x * size_t(256) + threadIdx.x; i < n4; i += gridDim.x * size_t(256)) {
+        float4 v = x[i];
+#pragma unroll 4
+        for (int p = 0; p < n_parts; ++p) {
+            const float4 a = parts[p * n4 + i];
+            v.x += a.x; v.y += a.y; v.z += a.z; v.w += a.w;
+        }
+        x[i] = v;
+    }
+}
+
+hipError_t launch_add_parts(float* x, const float* parts, int n_parts, size_t n, hipStream_t st) {
+    if (n == 0 || n_parts <= 0) return hipSuccess;
+    if (n % 4 || ((uintptr_t(x) | uintptr_t(parts)) & 15)) return hipErrorInvalidValue;
+    const size_t blocks = (n / 4 + 255) / 256;
+    hipLaunchKernelGGL(add_parts_kernel, dim3(unsigned(blocks < 4096 ? blocks : 4096)), dim3(256), 0, st, (float4*)x, (const float4*)parts, n_parts, n / 4);
+    return hipGetLastError();
+}
+
+hipError_t launch_rmsnorm_parts(int dtype, float* x, const float* parts, int n_parts, const float* gain, void* out, int rows, int d,
+                                float eps, hipStream_t st) {
+    if (rows <= 0) return hipSuccess;
+    if (dtype == 0 ? launch_rmsnorm_vec(x, parts, n_parts, gain, (float*)out, rows, d, eps, st)
+                   : launch_rmsnorm_vec(x, parts, n_parts, gain, (bf16_t*)out, rows, d, eps, st))
+        return hipGetLastError();
+    hipError_t e = launch_add_parts(x, parts, n_parts, size_t(rows) * d, st);
+    return e != hipSuccess ? e : launch_rmsnorm(dtype, x, gain, out, rows, d, eps, st);
 }
 
 // ------------------------------------------------------------------ rotary table
@@ -209,9 +259,10 @@ rope_kv_write_kernel(const float* __restrict__ qkv, const float2* __restrict__ c
 
 // bf16, head_dim 128: same grid and semantics as above with 16-byte loads (4 consecutive elements =
 // 2 rotary pairs per thread, 32 threads per token row) and 8-byte stores; V^T leaves the LDS
-// transpose as 16-byte pieces of 8 consecutive tokens.
+// transpose as 16-byte pieces of 8 consecutive tokens.  qkv may come as n_parts outputs, one per K range of the product,
+// qkv[n_parts][rows][...], which are added up (in that order) as they are read.
 __global__ void __launch_bounds__(256)
-rope_kv_write_bf16_hd128_kernel(const float* __restrict__ qkv, const float2* __restrict__ cs, bf16_t* __restrict__ q,
+rope_kv_write_bf16_hd128_kernel(const float* __restrict__ qkv, int n_parts, const float2* __restrict__ cs, bf16_t* __restrict__ q,
                                 int n_q, int tok_begin, int rows, KvView kv) {
     constexpr int HD = 128, HALF = 64;
     typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4_t;
@@ -228,6 +279,17 @@ rope_kv_write_bf16_hd128_kernel(const float* __restrict__ qkv, const float2* __r
     const int in_page0 = tile_tok0 - lpage * kv.page_tokens;
     bf16_t* page = (bf16_t*)kv.pool + (size_t(kv.layer) * kv.n_physical_pages + ppage) * kv.page_elems();
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;   // 4 elements of a row; 8 rows per pass
+    const size_t part_step = size_t(rows) * ldq;
+    auto load = [&](int row) {
+        const float* p = qkv + size_t(row) * ldq + head * HD + 4 * tx;
+        float4 v = *(const float4*)p;
+#pragma unroll 4
+        for (int i = 1; i < n_parts; ++i) {
+            const float4 a = *(const float4*)(p + i * part_step);
+            v.x += a.x; v.y += a.y; v.z += a.z; v.w += a.w;
+        }
+        return v;
+    };
 
     if (head < n_q + n_kv) {
         const bool is_q = head < n_q;
@@ -241,7 +303,7 @@ rope_kv_write_bf16_hd128_kernel(const float* __restrict__ qkv, const float2* __r
                 continue;
             }
             const int row = tok - tok_begin;
-            const float4 v = *(const float4*)(qkv + size_t(row) * ldq + head * HD + 4 * tx);
+            const float4 v = load(row);
             const float4 c = *(const float4*)(cs + row * HALF + 2 * tx);   // (cos, sin) of pairs 2tx, 2tx+1
             bf16x4_t w = {bf16_t(v.x * c.x - v.y * c.y), bf16_t(v.x * c.y + v.y * c.x),
                           bf16_t(v.z * c.z - v.w * c.w), bf16_t(v.z * c.w + v.w * c.z)};
@@ -254,7 +316,7 @@ rope_kv_write_bf16_hd128_kernel(const float* __restrict__ qkv, const float2* __r
         for (int pass = 0; pass < 8; ++pass) {
             const int t = ty + 8 * pass, tok = tile_tok0 + t;
             float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (tok >= lo && tok < hi) v = *(const float4*)(qkv + size_t(tok - tok_begin) * ldq + head * HD + 4 * tx);
+            if (tok >= lo && tok < hi) v = load(tok - tok_begin);
             vt[t][4 * tx + 0] = bf16_t(v.x); vt[t][4 * tx + 1] = bf16_t(v.y);
             vt[t][4 * tx + 2] = bf16_t(v.z); vt[t][4 * tx + 3] = bf16_t(v.w);
         }
@@ -280,16 +342,17 @@ rope_kv_write_bf16_hd128_kernel(const float* __restrict__ qkv, const float2* __r
 }
 
 hipError_t launch_rope_kv_write(int dtype, const float* qkv, const float* cs, void* q, int n_q, int tok_begin,
-                                int rows, const KvView& kv, hipStream_t st) {
+                                int rows, const KvView& kv, hipStream_t st, int n_parts) {
     if (rows <= 0) return hipSuccess;
     int tiles = (tok_begin + rows - 1) / 64 - tok_begin / 64 + 1;
     dim3 grid(tiles, n_q + 2 * kv.n_kv), block(256);
     const float2* c2 = (const float2*)cs;
     const bool aligned = ((uintptr_t(qkv) | uintptr_t(cs) | uintptr_t(q) | uintptr_t(kv.pool)) & 15) == 0;
     if (dtype == 1 && kv.head_dim == 128 && aligned) {
-        hipLaunchKernelGGL(rope_kv_write_bf16_hd128_kernel, grid, block, 0, st, qkv, c2, (bf16_t*)q, n_q, tok_begin, rows, kv);
+        hipLaunchKernelGGL(rope_kv_write_bf16_hd128_kernel, grid, block, 0, st, qkv, n_parts, c2, (bf16_t*)q, n_q, tok_begin, rows, kv);
         return hipGetLastError();
     }
+    if (n_parts > 1) return hipErrorInvalidValue;
     if (dtype == 0 && kv.head_dim == 64)
         hipLaunchKernelGGL((rope_kv_write_kernel<float, 64>), grid, block, 0, st, qkv, c2, (float*)q, n_q, tok_begin, rows, kv);
     else if (dtype == 0 && kv.head_dim == 128)

@@ -43,3 +43,34 @@ def test_gemm_f32(M, N, K):
     plain, residual, swiglu, again = _products("f32", M, N, K)
     tol = 2e-6 * max(1, K / 256)
     assert plain < tol and residual < tol and swiglu < 1.0 and again, (plain, residual, swiglu, again)
+
+
+# A block whose products leave K ranges to the kernel after them (few rows: one tile of all rows; many: the persistent
+# kernel), against the generic kernels on the same weights.  Both round the same activations to bf16, so what differs is
+# float32 summation order, which flips single roundings: the flat 2e-2 of a bf16 block covers both against the exact value.
+@pytest.mark.parametrize("base,rows", [("llama3-8b-shape", r) for r in (1, 31, 33, 100, 137, 192, 193, 700, 1024)] +
+                         [("llama2-7b-shape", 64), ("llama2-7b-shape", 1000), ("longalpaca-13b-shape", 512)])
+def test_block_with_products_left_in_k_ranges(base, rows):
+    import torch
+    import paper_2410_03065_amd as cake
+    shape = si.SHAPES[base].with_(n_layers=2, vocab=2048)
+    begin = 37
+    T = begin + rows
+    pages = (T + 63) // 64
+    eng = cake.Engine(shape, None, max_tokens=pages * 64, max_chunk=min(1024, pages * 64), page_tokens=64, seed=5)
+    toks = si.make_tokens(T, shape.vocab, seed=rows)
+    got = []
+    for path in (1, 0):
+        eng.clear_pool()
+        eng.set_tuning(kernel_path=1)
+        eng.prefill_chunk(toks, 0, begin)
+        eng.set_tuning(kernel_path=path)
+        eng.prefill_chunk(toks, begin, rows)
+        got.append(eng.pool[1].float().clone())
+        torch.cuda.synchronize()
+    err = float((got[0] - got[1]).abs().max() / got[0].abs().max())
+    print("%s rows %d: largest difference %.2e of the largest value" % (base, rows, err))
+    assert err < 2e-2, err
+    eng.set_tuning(kernel_path=0)
+    eng.prefill_chunk(toks, begin, rows)                       # the same bits again
+    assert torch.equal(eng.pool[1].float(), got[1])
