@@ -437,9 +437,11 @@ hipError_t launch_mfma_rate(float* out, int workgroups, int iters, hipStream_t s
 struct GemmCfg { int bm, bn; };
 // GCFG_128x128K: the 128x128 tile as two 128x64 halves, each shared by two waves that divide K (KW = 2)
 // GCFG_P256: the persistent four-wave kernel (256x256 tiles, several per workgroup)
+// GCFG_192x128: gate/up of 129 to 192 rows in one tile of all rows (137 rows of the Llama3-8B shape 76 -> 58 us, 192 rows
+// 78 -> 61, against the persistent kernel's 256 rows; two bands of 128 take 78)
 enum { GCFG_256x256 = 0, GCFG_256x128 = 1, GCFG_128x128 = 2, GCFG_128x192 = 3, GCFG_128x64 = 4, GCFG_128x128K = 5, GCFG_P256 = 6,
-       GCFG_COUNT = 7 };
-static const GemmCfg kGemmCfg[GCFG_COUNT] = {{256, 256}, {256, 128}, {128, 128}, {128, 192}, {128, 64}, {128, 128}, {256, 256}};
+       GCFG_192x128 = 7, GCFG_COUNT = 8 };
+static const GemmCfg kGemmCfg[GCFG_COUNT] = {{256, 256}, {256, 128}, {128, 128}, {128, 192}, {128, 64}, {128, 128}, {256, 256}, {192, 128}};
 
 struct P256Plan;
 static P256Plan p256_plan(int epi, int tiles_m, int N);
@@ -450,6 +452,7 @@ static int out_cols_per_tile(int cfg, int epi) { return epi == EPI_SWIGLU ? kGem
 static bool gemm_cfg_ok(int cfg, int epi, int M, int N, int K) {
     if ((cfg == GCFG_128x192 || cfg == GCFG_128x64) && epi == EPI_SWIGLU) return false;   // odd n-tiles per wave: no gate/up pairs
     if (cfg == GCFG_128x128K && (epi == EPI_SWIGLU || (K % 64) != 0)) return false;
+    if (cfg == GCFG_192x128 && (epi != EPI_SWIGLU || (K % 64) != 0)) return false;
     // the persistent kernel addresses everything through 32-bit buffer offsets
     // (its column panels are 256, 192 or 128 rows of W wide: N in units of 64, of 32 for SwiGLU)
     if (cfg == GCFG_P256)
@@ -478,7 +481,7 @@ static bool ksplit_ok(int cfg, int ks, int epi, int M, int N, int K, const GemmS
     return tiles <= ws->n_counters && size_t(tiles) * ks * c.bm * c.bn * sizeof(float) <= ws->part_bytes;
 }
 static GemmChoice gemm_pick(int epi, int M, int N, int K, const GemmSplitWs* ws, double* cost_out = nullptr) {
-    static const double eff[GCFG_COUNT] = {1.0, 0.60, 0.62, 0.80, 0.40, 0.65, 1.11};   // measured TFLOP/s per busy CU, relative to 256x256
+    static const double eff[GCFG_COUNT] = {1.0, 0.60, 0.62, 0.80, 0.40, 0.65, 1.11, 0.72};   // measured TFLOP/s per busy CU, relative to 256x256
     GemmChoice best{GCFG_128x128, 1};
     double best_cost = 1e30;
     for (int cfg = GCFG_COUNT - 1; cfg >= 0; --cfg) {
@@ -598,6 +601,9 @@ static hipError_t gemm_launch_cfg(int cfg, int ks, const GemmSplitWs* ws, const 
             } else {
                 return hipErrorInvalidValue;
             }
+        case GCFG_192x128:
+            if constexpr (EPI == EPI_SWIGLU) return gemm_launch_t<3, 2, 2, 2, 64, 4, EPI>(A, W, W2, out, M, N, K, st, ks, ws);
+            else return hipErrorInvalidValue;
         case GCFG_128x128K:
             if constexpr (EPI != EPI_SWIGLU) return gemm_launch_t<2, 2, 2, 2, 64, 5, EPI, 2>(A, W, W2, out, M, N, K, st, ks, ws);
             else return hipErrorInvalidValue;

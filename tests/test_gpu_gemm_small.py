@@ -74,3 +74,11 @@ def test_block_with_products_left_in_k_ranges(base, rows):
     eng.set_tuning(kernel_path=0)
     eng.prefill_chunk(toks, begin, rows)                       # the same bits again
     assert torch.equal(eng.pool[1].float(), got[1])
+
+
+# bf16 tiles for few rows: float32 sums over K as above; SwiGLU rounds once to bf16 (2^-8 of a value)
+@pytest.mark.parametrize("M,N,K", [(129, 128, 64), (137, 384, 512), (192, 640, 4096), (33, 256, 192), (160, 64, 128)])
+def test_gemm_bf16_few_rows(M, N, K):
+    plain, residual, swiglu, again = _products("bf16", M, N, K)
+    tol = 2e-6 * max(1, K / 256)
+    assert plain < tol and residual < tol and swiglu < 1.0 and again, (plain, residual, swiglu, again)
