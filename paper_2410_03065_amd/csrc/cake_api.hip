@@ -845,19 +845,28 @@ int32_t cake_write_store(cake_ctx* c, const cake_kv* kv, int32_t n_tokens, const
         rc = ensure_stage(c, image);
         if (rc != CAKE_OK) return rc;
     }
-    for (int p = 0; p < n_pages; ++p) {
-        char* out = (char*)dst->base + uint64_t(p) * dst->page_stride_bytes;
-        const int pp = kv->block_table_host[p];
-        if (bits) {
-            char* stage = (char*)c->q_stage;   // quantise, copy out, next page: one stream keeps them in order
-            HIP_TRY(c, launch_quant_page(c->m.dtype, stage, make_view(c, kv, 0), pp, c->m.n_layers, bits, c->cs));
-            HIP_TRY(c, hipMemcpyAsync(out, stage, image, hipMemcpyDeviceToHost, c->cs));
-        } else {
+    if (bits) {
+        // as many images at a time as the staging buffer holds: quantise, copy out, next; one stream keeps them in order
+        const int per = int(std::min<uint64_t>(uint64_t(n_pages), c->q_stage_bytes / image));
+        for (int p = 0; p < n_pages; p += per) {
+            const int n = std::min(per, n_pages - p);
+            char* out = (char*)dst->base + uint64_t(p) * dst->page_stride_bytes;
+            HIP_TRY(c, launch_quant_pages(c->m.dtype, c->q_stage, image, make_view(c, kv, 0), kv->block_table_host, p, n, c->m.n_layers, bits, c->cs));
+            if (dst->page_stride_bytes == image) {
+                HIP_TRY(c, hipMemcpyAsync(out, c->q_stage, uint64_t(n) * image, hipMemcpyDeviceToHost, c->cs));
+                continue;
+            }
+            for (int k = 0; k < n; ++k)
+                HIP_TRY(c, hipMemcpyAsync(out + uint64_t(k) * dst->page_stride_bytes, (char*)c->q_stage + uint64_t(k) * image, image,
+                                          hipMemcpyDeviceToHost, c->cs));
+        }
+    } else {
+        for (int p = 0; p < n_pages; ++p)
             for (int l = 0; l < c->m.n_layers; ++l) {
-                const char* src = (const char*)kv->pool + (uint64_t(l) * kv->n_physical_pages + pp) * layer_bytes;
+                char* out = (char*)dst->base + uint64_t(p) * dst->page_stride_bytes;
+                const char* src = (const char*)kv->pool + (uint64_t(l) * kv->n_physical_pages + kv->block_table_host[p]) * layer_bytes;
                 HIP_TRY(c, hipMemcpyAsync(out + uint64_t(l) * layer_bytes, src, layer_bytes, hipMemcpyDeviceToHost, c->cs));
             }
-        }
     }
     HIP_TRY(c, hipStreamSynchronize(c->cs));
     return CAKE_OK;

@@ -107,11 +107,12 @@ bool decode_attention_mfma_supported(int dtype, int head_dim, int page_tokens, i
 hipError_t launch_decode_attention_mfma(const float* q, float* part, int n_q, int n_keys, int tiles_per_split,
                                         int n_splits, const KvView& kv, hipStream_t st);
 
-// ---- quantised stored KV (bits = 8 or 4): one page image (all layers) <-> the layer pages of physical page phys_page ----
+// ---- quantised stored KV (bits = 8 or 4): a page image (all layers) <-> the layer pages of a physical page ----
 hipError_t launch_dequant_page(int dtype, const void* image, const KvView& kv, int phys_page, int n_layers, int bits,
                                hipStream_t st);
-hipError_t launch_quant_page(int dtype, void* image, const KvView& kv, int phys_page, int n_layers, int bits,
-                             hipStream_t st);
+// logical pages [first_page, first_page + n_pages) -> images, image_bytes apart
+hipError_t launch_quant_pages(int dtype, void* images, size_t image_bytes, const KvView& kv, const int32_t* block_table_host,
+                              int first_page, int n_pages, int n_layers, int bits, hipStream_t st);
 
 // ---- first-token step (one row of activations: matrix-vector products, one-token attention) ----
 // h = x (gain null: mode 1 only) or its RMSNorm (gain, eps; modes 0, 2, 3): out[n] (mode 0: =, 1: +=) sum_k h[k] w[n][k];
