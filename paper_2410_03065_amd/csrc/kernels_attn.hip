@@ -968,21 +968,25 @@ attention_hd64_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, fl
 // one 32-wide MFMA step consumes 1 KB of them.  There is no reuse between waves, so nothing is
 // staged in LDS: every lane loads its MFMA operand slices straight from the pages (K row
 // sigma16-permuted as above, V^T row = head-dim index), a wave has the V^T tile of this step
-// and the K tile of the next in flight while it works, and the four waves of a workgroup take
-// the key tiles of the workgroup's range in turn.  Partial (max, sum, O) per wave are merged
-// through LDS and written per key range for the combine kernel.
+// and the K tile of the next in flight while it works, and the W waves of a workgroup take
+// the 32-key tiles of the workgroup's range in turn.  Partial (max, sum, O) per wave are merged
+// through LDS and written per key range for the combine kernel.  Eight waves, two per SIMD, where their parts fit the
+// LDS (up to 12 heads to a KV head), so that one's loads are out while the other works; else four.
 // =====================================================================================
-__global__ void __launch_bounds__(256)
+constexpr int DK = 32;   // keys per tile
+
+template <int W>
+__global__ void __launch_bounds__(64 * W)
 decode_attention_mfma_kernel(const float* __restrict__ q, float* __restrict__ part, int n_q, int n_keys,
                              int tiles_per_split, KvView kv) {
-    extern __shared__ float dlds[];   // [4][r][AHD + 2]: O, then max (natural-log units), then sum
+    extern __shared__ float dlds[];   // [W][r][AHD + 2]: O, then max (natural-log units), then sum
     const int g = blockIdx.x, split = blockIdx.y, n_splits = gridDim.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int lrow = lane & 31, lhalf = lane >> 5;
     const int r = n_q / kv.n_kv;
     const int pt = kv.page_tokens;
-    const int n_tiles = (n_keys + AK - 1) / AK;
-    const int tile_lo = split * tiles_per_split, tile_hi = min(tile_lo + tiles_per_split, n_tiles);
+    const int n_tiles = (n_keys + DK - 1) / DK;
+    const int tile_lo = split * tiles_per_split * (AK / DK), tile_hi = min(tile_lo + tiles_per_split * (AK / DK), n_tiles);
     const float sl2 = 0.08838834764831845f * 1.4426950408889634f;
 
     bf16x8 qB[AHD / 16];
@@ -994,9 +998,9 @@ decode_attention_mfma_kernel(const float* __restrict__ q, float* __restrict__ pa
 
     const int krow = 16 * (lrow >> 4) + sigma16(lrow & 15);
     const size_t layer_base = size_t(kv.layer) * kv.n_physical_pages;
-    bf16x8 kA[2][AHD / 16], vA[4][4];
+    bf16x8 kA[AHD / 16], vA[4][2];
     auto tile_page = [&](int tile, int* in_page0) {
-        const int key0 = tile * AK, lpage = key0 / pt;
+        const int key0 = tile * DK, lpage = key0 / pt;
         *in_page0 = key0 - lpage * pt;
         return (const bf16_t*)kv.pool + (layer_base + kv.block_table[lpage]) * kv.page_elems();
     };
@@ -1004,9 +1008,7 @@ decode_attention_mfma_kernel(const float* __restrict__ q, float* __restrict__ pa
         int in_page0;
         const bf16_t* kp = tile_page(tile, &in_page0) + (size_t(g) * pt + in_page0) * AHD + 8 * lhalf;
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int ks = 0; ks < AHD / 16; ++ks) kA[t][ks] = *(const bf16x8*)(kp + size_t(32 * t + krow) * AHD + 16 * ks);
+        for (int ks = 0; ks < AHD / 16; ++ks) kA[ks] = *(const bf16x8*)(kp + size_t(krow) * AHD + 16 * ks);
     };
     auto load_v = [&](int tile) {
         int in_page0;
@@ -1014,7 +1016,7 @@ decode_attention_mfma_kernel(const float* __restrict__ q, float* __restrict__ pa
 #pragma unroll
         for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) vA[dt][c] = *(const bf16x8*)(vp + size_t(32 * dt + lrow) * pt + 16 * c);
+            for (int c = 0; c < 2; ++c) vA[dt][c] = *(const bf16x8*)(vp + size_t(32 * dt + lrow) * pt + 16 * c);
     };
 
     f32x16 o[4];
@@ -1027,26 +1029,20 @@ decode_attention_mfma_kernel(const float* __restrict__ q, float* __restrict__ pa
 
     int tile = tile_lo + wave;
     if (tile < tile_hi) load_k(tile);
-    for (; tile < tile_hi; tile += 4) {
+    for (; tile < tile_hi; tile += W) {
         load_v(tile);
-        f32x16 s[2];
+        f32x16 s;
 #pragma unroll
-        for (int ks = 0; ks < AHD / 16; ++ks)
+        for (int ks = 0; ks < AHD / 16; ++ks) s = mfma32(kA[ks], qB[ks], ks == 0 ? zero16 : s);
+        if (tile + W < tile_hi) load_k(tile + W);
+        if ((tile + 1) * DK > n_keys) {   // ragged last tile: keys past the prompt
 #pragma unroll
-            for (int t = 0; t < 2; ++t) s[t] = mfma32(kA[t][ks], qB[ks], ks == 0 ? zero16 : s[t]);
-        if (tile + 4 < tile_hi) load_k(tile + 4);
-        if ((tile + 1) * AK > n_keys) {   // ragged last tile: keys past the prompt
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int v = 0; v < 16; ++v)
-                    if (tile * AK + 32 * t + 16 * (v >> 3) + 8 * lhalf + (v & 7) >= n_keys) s[t][v] = -INFINITY;
+            for (int v = 0; v < 16; ++v)
+                if (tile * DK + 16 * (v >> 3) + 8 * lhalf + (v & 7) >= n_keys) s[v] = -INFINITY;
         }
-        float mx = s[0][0];
+        float mx = s[0];
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) mx = fmaxf(mx, s[t][v]);
+        for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[v]);
         mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
         const float m_new = fmaxf(m_run, mx);
         const float corr = __builtin_amdgcn_exp2f(m_run - m_new);
@@ -1058,22 +1054,20 @@ decode_attention_mfma_kernel(const float* __restrict__ q, float* __restrict__ pa
 #pragma unroll
                 for (int v = 0; v < 16; ++v) o[t][v] *= corr;
         }
-        bf16x8 pB[4];
+        bf16x8 pB[2];
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
+        for (int v = 0; v < 16; ++v) {
+            const float x = __builtin_amdgcn_exp2f(s[v] - m_new);
+            l_part += x;
+            pB[v >> 3][v & 7] = bf16_t(x);
+        }
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const float x = __builtin_amdgcn_exp2f(s[t][v] - m_new);
-                l_part += x;
-                pB[2 * t + (v >> 3)][v & 7] = bf16_t(x);
-            }
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
+        for (int c = 0; c < 2; ++c)
 #pragma unroll
             for (int dt = 0; dt < 4; ++dt) o[dt] = mfma32(vA[dt][c], pB[c], o[dt]);
     }
 
-    // merge the four waves; column n of a wave belongs to query head g*r + n
+    // merge the waves; column n of a wave belongs to query head g*r + n
     const float l_tot = l_part + __shfl_xor(l_part, 32, 64);
     if (lrow < r) {
         float* w = dlds + size_t(wave * r + lrow) * (AHD + 2);
@@ -1084,14 +1078,14 @@ decode_attention_mfma_kernel(const float* __restrict__ q, float* __restrict__ pa
         if (lhalf == 0) { w[AHD] = m_run * 0.6931471805599453f; w[AHD + 1] = l_tot; }
     }
     __syncthreads();
-    for (int idx = tid; idx < r * AHD; idx += 256) {
+    for (int idx = tid; idx < r * AHD; idx += 64 * W) {
         const int j = idx / AHD, d = idx % AHD;
         float m = -INFINITY;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) m = fmaxf(m, dlds[size_t(w * r + j) * (AHD + 2) + AHD]);
+        for (int w = 0; w < W; ++w) m = fmaxf(m, dlds[size_t(w * r + j) * (AHD + 2) + AHD]);
         float num = 0.f, den = 0.f;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
+        for (int w = 0; w < W; ++w) {
             const float* src = dlds + size_t(w * r + j) * (AHD + 2);
             const float c = __expf(src[AHD] - m);
             num += src[d] * c;
@@ -1111,9 +1105,10 @@ bool decode_attention_mfma_supported(int dtype, int head_dim, int page_tokens, i
 hipError_t launch_decode_attention_mfma(const float* q, float* part, int n_q, int n_keys, int tiles_per_split,
                                         int n_splits, const KvView& kv, hipStream_t st) {
     const int r = n_q / kv.n_kv;
-    const size_t lds = size_t(4) * r * (AHD + 2) * sizeof(float);
-    hipLaunchKernelGGL(decode_attention_mfma_kernel, dim3(kv.n_kv, n_splits), dim3(256), lds, st, q, part, n_q, n_keys,
-                       tiles_per_split, kv);
+    const size_t wave_lds = size_t(r) * (AHD + 2) * sizeof(float);
+    const dim3 grid(kv.n_kv, n_splits);
+    if (r <= 12) hipLaunchKernelGGL(decode_attention_mfma_kernel<8>, grid, dim3(512), 8 * wave_lds, st, q, part, n_q, n_keys, tiles_per_split, kv);
+    else hipLaunchKernelGGL(decode_attention_mfma_kernel<4>, grid, dim3(256), 4 * wave_lds, st, q, part, n_q, n_keys, tiles_per_split, kv);
     return hipGetLastError();
 }
 
