@@ -181,6 +181,11 @@ static GemmPartsPlan parts_plan(const cake_ctx* c, int epi, int M, int N, int K,
 }
 
 static hipError_t gemm(cake_ctx* c, int epi, const void* a, const void* w, const void* w2, void* out, int M, int N, int K) {
+    const GemmPartsPlan plan = M <= 192 ? parts_plan(c, epi, M, N, K, false) : GemmPartsPlan{0, false};
+    if (plan.ksplit && plan.few_rows && (uintptr_t(out) & 15) == 0) {   // K ranges, and a pass that adds them up
+        hipError_t e = launch_gemm_parts(plan, a, w, c->split.part, M, N, K, c->cs);
+        return e != hipSuccess ? e : launch_add_parts((float*)out, c->split.part, plan.ksplit, size_t(M) * N, c->cs, epi == EPI_STORE_F32);
+    }
     if (c->m.dtype == CAKE_BF16 && c->tun.kernel_path == 0 && gemm_mfma_supported(epi, M, N, K))
         return launch_gemm_mfma(epi, a, w, w2, out, M, N, K, c->cs, c->tun.gemm_config - 1, c->split.part ? &c->split : nullptr,
                                 c->tun.gemm_ksplit);
@@ -1251,7 +1256,10 @@ int32_t cake_op_gemm_plan(cake_ctx* c, int32_t residual, int32_t M, int32_t N, i
     if (!c || !tile || !ksplit || M < 0 || N <= 0 || K <= 0) return CAKE_E_INVAL;
     const int epi = residual ? EPI_RESIDUAL_F32 : EPI_STORE_F32;
     tile[0] = tile[1] = 0; *ksplit = 1;
-    if (c->m.dtype == CAKE_BF16 && c->tun.kernel_path == 0 && gemm_mfma_supported(epi, M, N, K)) {
+    const GemmPartsPlan plan = parts_plan(c, epi, M, N, K, false);
+    if (plan.ksplit && plan.few_rows) {
+        tile[0] = (M + 31) / 32 * 32; tile[1] = 128; *ksplit = plan.ksplit;
+    } else if (c->m.dtype == CAKE_BF16 && c->tun.kernel_path == 0 && gemm_mfma_supported(epi, M, N, K)) {
         int bm, bn, ks;
         gemm_mfma_plan(epi, M, N, K, c->tun.gemm_config - 1, c->split.part ? &c->split : nullptr, c->tun.gemm_ksplit, &bm, &bn, &ks);
         tile[0] = bm; tile[1] = bn; *ksplit = ks;

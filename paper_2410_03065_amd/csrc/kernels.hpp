@@ -36,7 +36,8 @@ hipError_t launch_rope_kv_write(int dtype, const float* qkv, const float* cs, vo
 // x += parts[0] + ... + parts[n_parts - 1] (each [rows][d], float32, 16-byte aligned), then the norm of the sum.
 hipError_t launch_rmsnorm_parts(int dtype, float* x, const float* parts, int n_parts, const float* gain, void* out, int rows,
                                 int d, float eps, hipStream_t st);
-hipError_t launch_add_parts(float* x, const float* parts, int n_parts, size_t n, hipStream_t st);
+// x += (store: =) parts[0] + ... + parts[n_parts - 1], n floats each.
+hipError_t launch_add_parts(float* x, const float* parts, int n_parts, size_t n, hipStream_t st, bool store = false);
 hipError_t launch_gemm_generic(int dtype, int epi, const void* a, const void* w, const void* w2,
                                void* out, int M, int N, int K, hipStream_t st);
 hipError_t launch_attention_generic(int dtype, const void* q, void* out, int n_q, int tok_begin,

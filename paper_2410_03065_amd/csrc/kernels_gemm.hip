@@ -640,9 +640,12 @@ hipError_t launch_gemm_p256_parts(const void* a, const void* w, float* part, int
 
 // The same unit (about a microsecond) for the two kernels that leave K ranges to a consumer, plus what the ranges cost
 // there.  Persistent kernel: 1.40 us per slice and item, the ranges written at about 10 TB/s; few rows: a slice takes
-// 0.24 us + 0.075 us per 32 rows, HBM delivers the weights at 5.3 TB/s, L2 the tiles at 10.  Both sides measured, us:
+// 0.24 us + 0.075 us per 32 rows, HBM delivers the weights at 5.3 TB/s, L2 the tiles at 10, or 0.05
+// per workgroup.  Both sides measured, us:
 // down 8B (K = 14336 -> 4096) 1024 rows 140 and 91 in four ranges, 64 rows 40 and 24 in eight; down 70B 1024 rows 459 and
 // 355 in two; O 8B 1024 rows 45 and 36 (no gain with 64 MB of ranges to add), 137 rows 32 and 16; QKV 8B 137 rows 29 and 18.
+// Narrow products (under 2048 columns, under 4096 on the persistent kernel) have too few tiles for either, and stay with
+// kernels whose sums do not depend on M: a narrow model's KV must not show in its bits how many rows a step had.
 GemmPartsPlan gemm_parts_plan(int epi, int M, int N, int K, const GemmSplitWs* ws, bool fused) {
     GemmPartsPlan best{0, false};
     if (epi == EPI_SWIGLU || !ws || !ws->part || M <= 0 || K % 64 || N % 128) return best;
@@ -654,14 +657,16 @@ GemmPartsPlan gemm_parts_plan(int epi, int M, int N, int K, const GemmSplitWs* w
         if (K % (64 * ks) || size_t(ks) * M * N * 4 > ws->part_bytes) continue;
         const double after = (ks * out_mb + (fused ? 0.0 : 2.0 * out_mb)) / 4.5 + (fused ? 0.0 : 4.0) + ks * out_mb / 10.0;
         const double slices = double(K) / ks / 64;
-        if (M <= 192) {
+        if (M <= 192 && N >= 2048) {
             const int bm = (M + 31) / 32 * 32;
             const double tiles = N / 128, rounds = double((long(tiles) * ks + 255) / 256);
+            if (bm >= 160 && tiles * ks < 160) continue;   // 137 and 192 rows of 11008 -> 4096 in four: 41 and 47 us, 38 and 42 without
+            const double l2_rate = std::min(10.0, 0.05 * tiles * ks);   // TB/s
             const double us = after + std::max(rounds * (slices * (0.24 + 0.075 * (bm / 32)) + 4.0),
-                                               std::max(double(N) * K * 2e-6 / 5.3 + 2.0, (bm + 128.0) * K * 2e-6 * tiles / 10.0 + 3.0));
+                                               std::max(double(N) * K * 2e-6 / 5.3 + 2.0, (bm + 128.0) * K * 2e-6 * tiles / l2_rate + 3.0));
             if (us < best_us) { best_us = us; best = GemmPartsPlan{ks, true}; }
         }
-        if (N % 256 == 0 && gemm_cfg_ok(GCFG_P256, EPI_STORE_F32, M, N, K)) {
+        if (N % 256 == 0 && N >= 4096 && gemm_cfg_ok(GCFG_P256, EPI_STORE_F32, M, N, K)) {
             const double rounds = double((long(M + 255) / 256 * (N / 256) * ks + 255) / 256);
             const double us = after + rounds * (slices * 1.40 + 4.0);
             if (us < best_us) { best_us = us; best = GemmPartsPlan{ks, false}; }

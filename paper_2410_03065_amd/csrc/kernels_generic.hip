@@ -162,12 +162,12 @@ hipError_t launch_rmsnorm(int dtype, const float* x, const float* gain, void* ou
     return hipGetLastError();
 }
 
-// x[n] += parts[0][n] + parts[1][n] + ... in that order; n a multiple of 4.
-__global__ void __launch_bounds__(256) add_parts_kernel(float4* __restrict__ x, const float4* __restrict__ parts, int n_parts, size_t n4) {
+// x[n] += parts[0][n] + parts[1][n] + ... in that order (store: x[n] = that sum); n a multiple of 4.
+__global__ void __launch_bounds__(256) add_parts_kernel(float4* __restrict__ x, const float4* __restrict__ parts, int n_parts, size_t n4, bool store) {
     for (size_t i = blockIdx.x * size_t(256) + threadIdx.x; i < n4; i += gridDim.x * size_t(256)) {
-        float4 v = x[i];
+        float4 v = store ? parts[i] : x[i];
 #pragma unroll 4
-        for (int p = 0; p < n_parts; ++p) {
+        for (int p = store ? 1 : 0; p < n_parts; ++p) {
             const float4 a = parts[p * n4 + i];
             v.x += a.x; v.y += a.y; v.z += a.z; v.w += a.w;
         }
@@ -175,11 +175,11 @@ __global__ void __launch_bounds__(256) add_parts_kernel(float4* __restrict__ x, 
     }
 }
 
-hipError_t launch_add_parts(float* x, const float* parts, int n_parts, size_t n, hipStream_t st) {
+hipError_t launch_add_parts(float* x, const float* parts, int n_parts, size_t n, hipStream_t st, bool store) {
     if (n == 0 || n_parts <= 0) return hipSuccess;
     if (n % 4 || ((uintptr_t(x) | uintptr_t(parts)) & 15)) return hipErrorInvalidValue;
     const size_t blocks = (n / 4 + 255) / 256;
-    hipLaunchKernelGGL(add_parts_kernel, dim3(unsigned(blocks < 4096 ? blocks : 4096)), dim3(256), 0, st, (float4*)x, (const float4*)parts, n_parts, n / 4);
+    hipLaunchKernelGGL(add_parts_kernel, dim3(unsigned(blocks < 4096 ? blocks : 4096)), dim3(256), 0, st, (float4*)x, (const float4*)parts, n_parts, n / 4, store);
     return hipGetLastError();
 }
 
