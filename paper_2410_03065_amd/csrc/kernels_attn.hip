@@ -362,9 +362,10 @@ constexpr int A8_RING = 2 * A_KBYTES;        // one ring slot: group A's tile th
 constexpr int A8_VBASE = 2 * A8_RING;        // V^T ring after the K ring
 constexpr int A8_TABLE = 4 * A8_RING;        // page offsets after both rings
 
-// The r query heads that share a KV head are laid side by side: query number x of KV head g is row x / r of head
-// g r + x % r, so a workgroup's queries fill up across heads (137 rows of four heads: five tiles of 128 instead of
-// eight).  QW = query waves per half: 128, 64 or 32 queries per workgroup.
+// side_by_side: the r query heads that share a KV head are laid side by side, query number x of KV head g is row x / r
+// of head g r + x % r, so a workgroup's queries fill up across heads (137 rows of four heads: five tiles of 128 instead
+// of eight).  Where that saves no tile a workgroup keeps to one head (1024 rows at 31744: 1 % less time).
+// QW = query waves per half: 128, 64 or 32 queries per workgroup.
 //
 // Launches with too few query tiles for the chip divide the keys as well: blockIdx.y takes `pairs_per_split` pairs of
 // key tiles and leaves its unnormalised result in `part` for attention_merge_kernel (SPLIT, an instantiation of its
@@ -372,7 +373,7 @@ constexpr int A8_TABLE = 4 * A8_RING;        // page offsets after both rings
 template <int QW, bool SPLIT>
 __global__ void __launch_bounds__(128 * QW)
 attention_mfma8_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, float* __restrict__ part, int n_q, int tok_begin,
-                       int rows, KvView kv, int pairs_per_split) {
+                       int rows, KvView kv, int pairs_per_split, bool side_by_side) {
     constexpr int AQW = 32 * QW;        // queries per workgroup
     constexpr int PER = 16 / QW;        // wave-loads per wave per K (or V^T) tile
     constexpr int KP = QW >= 4 ? 1 : 4 / QW;   // period after which the K swizzle term of a wave's loads repeats,
@@ -394,11 +395,15 @@ attention_mfma8_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, f
     }
     const int pt = kv.page_tokens;
 
-    const int n_queries = rows * r, my_query = min(q0 + wave * 32 + lrow, n_queries - 1);
-    const int my_row = my_query / r, h = g * r + (my_query - my_row * r);
+    // number of queries laid out, heads each stands across, first head; one head: q0 / AQW = q tile * r + head
+    const int rr = side_by_side ? r : 1, n_queries = rows * rr;
+    const int head0 = side_by_side ? g * r : g * r + (q0 / AQW) % r;
+    if (!side_by_side) q0 = (q0 / AQW) / r * AQW;
+    const int my_query = min(q0 + wave * 32 + lrow, n_queries - 1);
+    const int my_row = my_query / rr, h = head0 + (my_query - my_row * rr);
     const int my_pos = tok_begin + my_row;
-    const int wave_first_pos = tok_begin + min(q0 + wave * 32, n_queries - 1) / r;
-    const int wg_last_pos = tok_begin + (min(q0 + AQW, n_queries) - 1) / r;
+    const int wave_first_pos = tok_begin + min(q0 + wave * 32, n_queries - 1) / rr;
+    const int wg_last_pos = tok_begin + (min(q0 + AQW, n_queries) - 1) / rr;
     const int n_tiles = wg_last_pos / AK + 1;
     const int pair_lo = SPLIT ? blockIdx.y * pairs_per_split : 0;
     const int n_pairs = SPLIT ? min(pair_lo + pairs_per_split, (n_tiles + 1) >> 1) : (n_tiles + 1) >> 1;
@@ -1118,8 +1123,8 @@ bool attention_mfma_supported(int head_dim, int page_tokens) {
 
 // How a launch is divided: queries per workgroup (32 qw) and key ranges, by the time of the busiest CU.  A pair of key
 // tiles takes a workgroup (one per CU) about 1.98 us with 128 queries and 1.40 with 64 or fewer (512 rows x 32 heads
-// over 8000 keys and 1024 over 15360, measured), a workgroup about 9 us beyond its pairs (one pair: 10.4); key ranges
-// cost the merge kernel and their parts' way through memory (about 4 bytes per ps each way).  32 heads on 8 KV heads,
+// over 8000 keys and 1024 over 15360, measured), a workgroup 5.5 us beyond its pairs, 9.5 where it leaves a part; key
+// ranges cost the merge kernel and their parts' way through memory (about 4 bytes per ps each way).  32 heads on 8 KV heads,
 // us undivided and divided, merge included: 8 rows at 4000 keys 55 and 15, 39 rows at 14000 174 and 28, 137 rows at
 // 4000 46 and 28; 509 rows of 32 KV heads at 7003 90 and 79.
 constexpr int A_LDS_MAX = 160 * 1024;
@@ -1139,7 +1144,7 @@ static AttnPlan attn_plan(int n_q, int n_kv, int tok_begin, int rows, const Attn
             if (s > 1 && (!ws.part || s * one > double(ws.bytes))) break;
             const int per = use_fixed ? fixed : (n_pairs + s - 1) / s;
             if ((n_pairs + per - 1) / per != s) continue;
-            double us = double((wgs * s + 255) / 256) * (per * k.pair_us + 9.0);
+            double us = double((wgs * s + 255) / 256) * (per * k.pair_us + (s > 1 ? 9.5 : 5.5));
             if (s > 1) us = (us + 4.5 + 2.0 * s * one / 4.0e6) * 1.05;
             if (us < best_us) { best_us = us; best = AttnPlan{k.qw, s, per}; }
         }
@@ -1149,8 +1154,11 @@ static AttnPlan attn_plan(int n_q, int n_kv, int tok_begin, int rows, const Attn
 
 template <int QW>
 static hipError_t launch_mfma8(const bf16_t* q, bf16_t* out, float* part, int n_q, int tok_begin, int rows, const KvView& kv, int splits,
-                               int per, int lds, hipStream_t st) {
-    const int r = n_q / kv.n_kv, q_tiles = (rows * r + 32 * QW - 1) / (32 * QW);
+                               int per, int lds, hipStream_t st, bool fixed_layout) {
+    // (a model whose key ranges are fixed keeps one layout: which queries share a wave shows in their bits)
+    const int r = n_q / kv.n_kv, packed = (rows * r + 32 * QW - 1) / (32 * QW), apart = r * ((rows + 32 * QW - 1) / (32 * QW));
+    const bool side_by_side = fixed_layout || packed < apart;
+    const int q_tiles = side_by_side ? packed : apart;
     auto kern = splits > 1 ? attention_mfma8_kernel<QW, true> : attention_mfma8_kernel<QW, false>;
     static bool attr_set[2] = {false, false};
     if (!attr_set[splits > 1]) {
@@ -1158,7 +1166,7 @@ static hipError_t launch_mfma8(const bf16_t* q, bf16_t* out, float* part, int n_
         if (e != hipSuccess) return e;
         attr_set[splits > 1] = true;
     }
-    hipLaunchKernelGGL(kern, dim3(q_tiles * kv.n_kv, splits), dim3(128 * QW), lds, st, q, out, part, n_q, tok_begin, rows, kv, per);
+    hipLaunchKernelGGL(kern, dim3(q_tiles * kv.n_kv, splits), dim3(128 * QW), lds, st, q, out, part, n_q, tok_begin, rows, kv, per, side_by_side);
     hipError_t e = hipGetLastError();
     return e != hipSuccess || splits == 1 ? e : launch_attention_merge(1, AHD, part, out, n_q, rows, splits, st);
 }
@@ -1184,9 +1192,9 @@ hipError_t launch_attention_mfma(const void* q, void* out, int n_q, int tok_begi
     if (LDS > A_LDS_MAX) return hipErrorInvalidValue;
     const AttnPlan plan = attn_plan(n_q, kv.n_kv, tok_begin, rows, ws, variant == 2 ? 4 : variant == 3 ? 2 : 0);
     const bf16_t* Q = (const bf16_t*)q;
-    if (plan.qw == 4) return launch_mfma8<4>(Q, (bf16_t*)out, ws.part, n_q, tok_begin, rows, kv, plan.splits, plan.per, LDS, st);
-    if (plan.qw == 2) return launch_mfma8<2>(Q, (bf16_t*)out, ws.part, n_q, tok_begin, rows, kv, plan.splits, plan.per, LDS, st);
-    return launch_mfma8<1>(Q, (bf16_t*)out, ws.part, n_q, tok_begin, rows, kv, plan.splits, plan.per, LDS, st);
+    if (plan.qw == 4) return launch_mfma8<4>(Q, (bf16_t*)out, ws.part, n_q, tok_begin, rows, kv, plan.splits, plan.per, LDS, st, ws.range_keys > 0);
+    if (plan.qw == 2) return launch_mfma8<2>(Q, (bf16_t*)out, ws.part, n_q, tok_begin, rows, kv, plan.splits, plan.per, LDS, st, ws.range_keys > 0);
+    return launch_mfma8<1>(Q, (bf16_t*)out, ws.part, n_q, tok_begin, rows, kv, plan.splits, plan.per, LDS, st, ws.range_keys > 0);
 }
 
 // Head dimension 64, 16-byte reads of q, the pages and the result; with fewer keys than 24 the one-wave-per-row kernel
