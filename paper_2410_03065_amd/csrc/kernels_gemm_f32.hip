@@ -6,8 +6,13 @@
 // permutation of K, so a lane reads 16 bytes of its row (elements 16b + 4*(l/16) .. + 3) for four MFMAs.
 //
 // A wave owns T x T MFMA tiles; the four waves of a workgroup stand SP x SP over the output (SP = 1 or 2) or, where
-// SP = 1, divide K among them, 16 * KB elements at a time, and add up through LDS.  Operands go straight to
-// registers, the next 16 * KB elements of K on their way while the present ones are multiplied.
+// SP = 1, divide K among them and add up through LDS.  Operands go straight to registers, the next 16 * KB elements of K
+// on their way while the present ones are multiplied.
+//
+// Every tile adds up in the same order, so that a row's result does not depend on the rows beside it (a float32 model's
+// tokens have the same KV whatever step they are computed in, although M picks the tile): K in four quarters of whole
+// blocks of 32, a sum for each, and the four added in turn.  Waves that divide K hold one sum each; the waves of the
+// 128 x 128 tile form them one after another.
 //
 // What bounds it: for the products of a small model's chunk the number of waves and the latency of a walk along K,
 // so the tile shrinks until the grid fills the chip and K is divided (256 rows of the tiny model, us a launch:
@@ -20,6 +25,10 @@ namespace cake {
 
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
+// Does the tile keep its finished sums in LDS?  128 x 128 with SwiGLU: two times 64 x 64 sums and the operands fill a
+// wave's registers (1024 x 4096 x 4096: spilled 1742 us, in LDS 600).
+constexpr bool f32_lds_total(int t, int sp, int epi) { return sp == 2 && epi == EPI_SWIGLU && t == 4; }
+
 template <int T, int SP, int EPI>
 __global__ void __launch_bounds__(256)
 gemm_f32_kernel(const float* __restrict__ a, const float* __restrict__ w, const float* __restrict__ w2, float* __restrict__ out,
@@ -28,7 +37,9 @@ gemm_f32_kernel(const float* __restrict__ a, const float* __restrict__ w, const 
     constexpr int NM = EPI == EPI_SWIGLU ? 2 : 1;    // weight matrices
     constexpr int KB = NM * T > 4 ? 1 : 2;           // 16-deep blocks per trip (one where 64 x 64 twice fill the registers)
     constexpr int BT = 16 * T * SP;                  // rows and columns of the workgroup's tile
+    constexpr bool LDS_TOTAL = f32_lds_total(T, SP, EPI);
     __shared__ float4 parts[KW > 1 ? (KW - 1) * NM * T * T * 64 : 1];
+    extern __shared__ __attribute__((aligned(16))) float4 total_lds[];   // LDS_TOTAL: [NM][T][T][256]
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int l16 = lane & 15, lq = lane >> 4;
     const int kw = SP == 1 ? wave : 0, wm = SP == 1 ? 0 : wave >> 1, wn = SP == 1 ? 0 : wave & 1;
@@ -75,15 +86,45 @@ gemm_f32_kernel(const float* __restrict__ a, const float* __restrict__ w, const 
                                                                                 acc[n][i][j], 0, 0, 0);
     };
     float4 av[2][T][KB], wv[2][NM][T][KB];
-    int k = 16 * KB * kw;
-    constexpr int STEP = 16 * KB * KW;
-    if (k < K) load(av[0], wv[0], k);
-    for (; k < K; k += 2 * STEP) {   // two trips unrolled, so that the two register sets alternate without copies
-        if (k + STEP < K) load(av[1], wv[1], k + STEP);
-        mul(av[0], wv[0]);
-        if (k + STEP >= K) break;
-        if (k + 2 * STEP < K) load(av[0], wv[0], k + 2 * STEP);
-        mul(av[1], wv[1]);
+    f32x4 total[NM][T][T];   // KW = 1: the finished sums (in LDS where the registers do not hold them as well)
+    const int quarter = (K + 127) / 128 * 32;
+    auto sum_of = [&](int p) {   // quarter p of K into acc
+        constexpr int STEP = 16 * KB;
+        const int k_end = min((p + 1) * quarter, K);
+        int k = p * quarter;
+        if (k < k_end) load(av[0], wv[0], k);
+        for (; k < k_end; k += 2 * STEP) {   // two trips unrolled, so that the two register sets alternate without copies
+            if (k + STEP < k_end) load(av[1], wv[1], k + STEP);
+            mul(av[0], wv[0]);
+            if (k + STEP >= k_end) break;
+            if (k + 2 * STEP < k_end) load(av[0], wv[0], k + 2 * STEP);
+            mul(av[1], wv[1]);
+        }
+    };
+    if constexpr (KW > 1) {
+        sum_of(kw);
+    } else {
+#pragma unroll 1
+        for (int p = 0; p < 4; ++p) {
+            sum_of(p);
+#pragma unroll
+            for (int m = 0; m < NM; ++m)
+#pragma unroll
+                for (int i = 0; i < T; ++i)
+#pragma unroll
+                    for (int j = 0; j < T; ++j) {
+                        f32x4& a = acc[m][i][j];
+                        if constexpr (LDS_TOTAL) {
+                            float4& t = total_lds[((m * T + i) * T + j) * 256 + threadIdx.x];
+                            if (p > 0) a += f32x4{t.x, t.y, t.z, t.w};
+                            if (p < 3) t = make_float4(a[0], a[1], a[2], a[3]);
+                        } else {
+                            if (p > 0) a += total[m][i][j];
+                            if (p < 3) total[m][i][j] = a;
+                        }
+                        if (p < 3) a = f32x4{0.f, 0.f, 0.f, 0.f};
+                    }
+        }
     }
     if constexpr (KW > 1) {   // waves 1 .. 3 hand their sums to wave 0, which adds them in that order
         if (wave > 0) {
@@ -134,7 +175,16 @@ template <int T, int SP, int EPI>
 static hipError_t launch_t(const float* a, const float* w, const float* w2, float* out, int M, int N, int K, hipStream_t st) {
     constexpr int BT = 16 * T * SP;
     const int tiles_m = (M + BT - 1) / BT, tiles_n = (N + BT - 1) / BT;
-    hipLaunchKernelGGL((gemm_f32_kernel<T, SP, EPI>), dim3(tiles_m * tiles_n), dim3(256), 0, st, a, w, w2, out, M, N, K, tiles_m);
+    constexpr int LDS = f32_lds_total(T, SP, EPI) ? 2 * T * T * 256 * int(sizeof(float4)) : 0;
+    if (LDS > 0) {
+        static bool attr_set = false;   // one flag per instantiation
+        if (!attr_set) {
+            hipError_t e = hipFuncSetAttribute((const void*)gemm_f32_kernel<T, SP, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+            if (e != hipSuccess) return e;
+            attr_set = true;
+        }
+    }
+    hipLaunchKernelGGL((gemm_f32_kernel<T, SP, EPI>), dim3(tiles_m * tiles_n), dim3(256), LDS, st, a, w, w2, out, M, N, K, tiles_m);
     return hipGetLastError();
 }
 

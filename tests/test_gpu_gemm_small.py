@@ -45,6 +45,27 @@ def test_gemm_f32(M, N, K):
     assert plain < tol and residual < tol and swiglu < 1.0 and again, (plain, residual, swiglu, again)
 
 
+# The tile is chosen from the rows (16 x 16 to 128 x 128), the order of a sum is not: a row has the same bits beside any
+# others.
+@pytest.mark.parametrize("M,N,K", [(1024, 3072, 328), (1024, 1376, 1000), (300, 688, 40), (897, 6400, 128)])
+def test_gemm_f32_rows_do_not_depend_on_the_rows_beside_them(M, N, K):
+    import torch
+    import paper_2410_03065_amd as cake
+    eng = cake.Engine(si.ModelShape("gemm-small", 1, 256, 4, 4, 64, 512, 64, "f32"), None, max_tokens=64, max_chunk=64, page_tokens=64)
+    g = torch.Generator(device="cuda").manual_seed(N)
+    mk = lambda r, c, std: torch.randn(r, c, device="cuda", generator=g) * std
+    a, w, w2, x0 = mk(M, K, 1.0), mk(N, K, 0.05), mk(N, K, 0.05), mk(M, N, 1.0)
+
+    def products(lo, n):
+        rows, x = a[lo:lo + n].contiguous(), x0[lo:lo + n].clone()
+        torch.cuda.synchronize()
+        return eng.op_gemm(rows, w), eng.op_gemm_residual(rows, w, x), eng.op_gemm_swiglu(rows, w, w2)
+    whole = products(0, M)
+    for lo, n in [(0, 1), (M - 1, 1), (5, 37), (64, 101), (100, 200), (0, min(M, 512))]:
+        for name, got, want in zip(("store", "residual", "swiglu"), products(lo, n), whole):
+            assert torch.equal(got, want[lo:lo + n]), (name, lo, n)
+
+
 # A block whose products leave K ranges to the kernel after them (few rows: one tile of all rows; many: the persistent
 # kernel), against the generic kernels on the same weights.  Both round the same activations to bf16, so what differs is
 # float32 summation order, which flips single roundings: the flat 2e-2 of a bf16 block covers both against the exact value.
