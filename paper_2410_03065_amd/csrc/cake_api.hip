@@ -49,7 +49,7 @@ struct cake_ctx {
     int32_t* t_tok = nullptr;
     void* static_scratch = nullptr;   // this device's copy of the file-scope scratch array (set by cake_create)
     GemmSplitWs split{};       // float32 parts and ticket counters of launches that split K or keys (compute stream only)
-    int attn_range_keys = 0;   // fixed key ranges of the attention launches of a model of few heads, else 0 (see AttnWs)
+    int attn_range_keys = 0;   // length of the attention launches' key ranges, 0: chosen per launch (see AttnWs)
     void* q_stage = nullptr;   // device staging for quantised page images: a ring of image slots (cake_create)
     size_t q_stage_bytes = 0;
     // second hop of a file-backed store: two pinned buffers of one DMA piece each
@@ -200,7 +200,7 @@ static hipError_t attention(cake_ctx* c, const void* q, void* out, int tok_begin
         return launch_attention_mfma(q, out, c->m.n_q_heads, tok_begin, rows, kv, c->cs, c->tun.attn_variant, ws);
     if (c->m.dtype == CAKE_BF16 && c->tun.kernel_path == 0 && attention_hd64_supported(q, out, tok_begin + rows, kv))
         return launch_attention_hd64(q, out, c->m.n_q_heads, tok_begin, rows, kv, c->cs, ws);
-    if (c->m.dtype == CAKE_F32 && c->tun.kernel_path == 0 && attention_f32_supported(q, tok_begin + rows, kv))
+    if (c->m.dtype == CAKE_F32 && c->tun.kernel_path == 0 && attention_f32_supported(q, kv))
         return launch_attention_f32((const float*)q, (float*)out, c->m.n_q_heads, tok_begin, rows, kv, c->cs, ws);
     return launch_attention_generic(c->m.dtype, q, out, c->m.n_q_heads, tok_begin, rows, kv, c->cs);
 }
@@ -565,13 +565,16 @@ int32_t cake_create(cake_ctx** out, const cake_model_desc* model, const cake_wei
         ok = ok && hipMemset(c->split.counters, 0, size_t(c->split.n_counters) * 4) == hipSuccess;
     }
     {
-        // A model of few heads divides its keys in every launch.  It does so into the same ranges however many rows a
-        // step has, so that the chunk a token is computed in does not show in its bits: the shortest power of two
-        // whose parts for max_chunk rows at the end of max_tokens fit the workspace.
+        // Attention divides its keys into the same ranges however many rows a step has where the chunk a token is
+        // computed in must not show in its bits: for float32 models, whose other kernels keep to that too, and for
+        // models of few heads, whose keys every launch divides anyway.  The shortest power of two from a least length
+        // whose parts for max_chunk rows at the end of max_tokens fit the workspace.  Shorter ranges help few rows
+        // and cost many (float32, 32 heads of 64, us with ranges of 512, 1024, 2048 and of a length chosen per launch:
+        // 8 rows at 4000 keys 23, 33, 55, 31; 137 at 1900 52, 59, 54, 48; 1024 at 3072 482, 419, 387, 368).
         const bool f32 = m.dtype == CAKE_F32;
         const size_t row = size_t(m.n_q_heads) * max_chunk * (m.head_dim + 2) * 4;
-        if (m.n_q_heads <= (f32 ? 4 : 16))
-            for (c->attn_range_keys = f32 ? 256 : 1024; (max_tokens + c->attn_range_keys - 1) / c->attn_range_keys * row > c->split.part_bytes;)
+        if (f32 || m.n_q_heads <= 16)
+            for (c->attn_range_keys = f32 && m.n_q_heads <= 4 ? 256 : 1024; (max_tokens + c->attn_range_keys - 1) / c->attn_range_keys * row > c->split.part_bytes;)
                 if ((c->attn_range_keys *= 2) >= max_tokens) break;
     }
     {

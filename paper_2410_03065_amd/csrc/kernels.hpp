@@ -23,7 +23,7 @@ struct KvView {
 
 enum GemmEpilogue { EPI_STORE_F32 = 0, EPI_RESIDUAL_F32 = 1, EPI_SWIGLU = 2 };
 
-// ---- generic kernels (any supported shape; the only path for float32 models) ----
+// ---- generic kernels (any supported shape) ----
 hipError_t launch_embed(int dtype, const void* table, const int32_t* ids, float* x, int rows,
                         int d, int vocab, hipStream_t st);
 hipError_t launch_rmsnorm(int dtype, const float* x, const float* gain, void* out, int rows, int d,
@@ -45,11 +45,11 @@ hipError_t launch_attention_generic(int dtype, const void* q, void* out, int n_q
 
 // Where an attention launch may leave the parts of its key ranges: float32 workspace (part null: never divide the keys);
 // launches sharing it must not overlap.  range_keys > 0: the keys are divided into ranges of that many whatever the
-// number of rows, so that a token's result does not depend on the step it is computed in; 0: by a cost model.
+// number of rows (in float32 a token's result then does not depend on the step it is computed in); 0: by a cost model.
 struct AttnWs { float* part; size_t bytes; int range_keys; };
 
 // ---- float32 on the matrix cores ----
-bool attention_f32_supported(const void* q, int n_keys, const KvView& kv);
+bool attention_f32_supported(const void* q, const KvView& kv);
 hipError_t launch_attention_f32(const float* q, float* out, int n_q, int tok_begin, int rows, const KvView& kv,
                                 hipStream_t st, const AttnWs& ws);
 hipError_t launch_gemm_f32(int epi, const float* a, const float* w, const float* w2, float* out, int M, int N, int K,

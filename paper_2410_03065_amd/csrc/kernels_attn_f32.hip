@@ -229,25 +229,25 @@ hipError_t launch_attention_merge(int dtype, int head_dim, const float* part, vo
     return hipGetLastError();
 }
 
-// 16-byte reads of q and of the pages.  Below one key tile the kernel with a wave per row and head is as fast or
-// faster (16 heads x 64, us: 8 rows of 8 keys 3.9 against 6.3, 24 of 24 5.3 against 6.1, 32 of 32 6.0 against 5.8).
-bool attention_f32_supported(const void* q, int n_keys, const KvView& kv) {
-    return n_keys >= FK && (kv.head_dim == 64 || kv.head_dim == 128) && kv.page_tokens % 64 == 0 && ((uintptr_t(q) | uintptr_t(kv.pool)) & 15) == 0;
+// 16-byte reads of q and of the pages.
+bool attention_f32_supported(const void* q, const KvView& kv) {
+    return (kv.head_dim == 64 || kv.head_dim == 128) && kv.page_tokens % 64 == 0 && ((uintptr_t(q) | uintptr_t(kv.pool)) & 15) == 0;
 }
 
-// Key ranges: enough workgroups for two per CU, as long as every wave of a range still has two tiles to overlap
-// (the next tile's keys are read while this one is worked on) and the parts fit the workspace.
+// Key ranges of ws.range_keys whatever the rows.  A row's sums are then over the same keys in the same order in every
+// launch, however many rows and keys the launch has: a wave takes the same tiles of a range, a tile that a row does not
+// see adds zeros to it, and so does a range.  (Prompts under one tile come here for the same reason, though a wave per
+// row and head would be faster: 16 heads x 64, us: 8 rows of 8 keys 6.3 against 3.9, 24 of 24 6.1 against 5.3.)
+// More rows than the ranges' parts fit (an op call beyond the context's chunk) take fewer, longer ranges.
 hipError_t launch_attention_f32(const float* q, float* out, int n_q, int tok_begin, int rows, const KvView& kv, hipStream_t st,
                                 const AttnWs& ws) {
     if (rows <= 0) return hipSuccess;
     float* part = ws.part;
     const int q_tiles = (rows + FQ - 1) / FQ, n_tiles = (tok_begin + rows - 1) / FK + 1;
-    const int want = ws.range_keys ? (n_tiles * FK + ws.range_keys - 1) / ws.range_keys
-                                   : std::max(1, std::min(512 / std::max(1, q_tiles * n_q), n_tiles / 8));
     const size_t one = size_t(n_q) * rows * (kv.head_dim + 2) * sizeof(float);
-    const int room = part ? int(std::min<size_t>(size_t(want), ws.bytes / one)) : 1;
-    const bool fixed = ws.range_keys && room >= want;
-    const int per = fixed ? ws.range_keys / FK : (n_tiles + std::max(1, room) - 1) / std::max(1, room);
+    const size_t room = part ? std::max<size_t>(1, ws.bytes / one) : 1;
+    int per = ws.range_keys > 0 ? std::max(1, ws.range_keys / FK) : n_tiles;
+    if (size_t((n_tiles + per - 1) / per) > room) per = int((n_tiles + room - 1) / room);
     const int splits = (n_tiles + per - 1) / per;
     const dim3 grid(q_tiles, n_q, splits), block(256);
     float* p = splits > 1 ? part : nullptr;

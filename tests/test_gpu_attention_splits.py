@@ -114,3 +114,30 @@ def test_attention_of_a_model_of_few_heads_does_not_depend_on_the_step(kind, hd,
             torch.cuda.synchronize()
             part = eng.op_attention(q, 0, begin + r)
             assert torch.equal(part, whole[r:r + piece]), (piece, r)
+
+
+def _prefill_in_steps(eng, toks, steps):
+    """The pool after a prefill in steps of the given numbers of tokens, taken in turn until the prompt is through."""
+    import torch
+    eng.clear_pool()
+    at, i = 0, 0
+    while at < len(toks):
+        n = min(steps[i % len(steps)], len(toks) - at)
+        eng.prefill_chunk(toks, at, n)
+        at, i = at + n, i + 1
+    torch.cuda.synchronize()
+    return eng.pool.clone()
+
+
+@pytest.mark.parametrize("n_q,n_kv,hd,d,ffn", [(4, 4, 64, 256, 688), (8, 2, 64, 512, 1376), (20, 4, 64, 640, 1024), (6, 2, 128, 768, 2056)])
+def test_f32_prefill_does_not_depend_on_its_steps(n_q, n_kv, hd, d, ffn):
+    """A float32 model's KV has the same bits whatever steps the prompt is computed in: whole chunks, pieces that end
+    inside a key tile and a 32-row block, a first step shorter than a key tile."""
+    import torch
+    import paper_2410_03065_amd as cake
+    shape = si.ModelShape("f32-steps", 2, d, n_q, n_kv, hd, ffn, 128, "f32", rope_theta=500000.0)
+    eng = cake.Engine(shape, None, max_tokens=2048, max_chunk=1024, page_tokens=128, seed=3)
+    toks = si.make_tokens(1500, shape.vocab, seed=7)
+    whole = _prefill_in_steps(eng, toks, [1024])
+    for steps in ([512], [256], [7, 101, 300], [37], [33, 1, 950]):
+        assert torch.equal(_prefill_in_steps(eng, toks, steps), whole), steps
