@@ -76,6 +76,35 @@ def test_attention_f32_hidden_values_do_not_leak():
     _poisoned("f32", 64, 4, 2, 200, 77, 128, 50, 2e-5)
 
 
+# Probabilities down to e^-80, one to an element of the result: scores, their differences and V are exact, so a value
+# carries the error of the exponentials that formed it (against the tile's reference and, merged, against the row's: 2^-23
+# each) and of six roundings in products, sums and the division: 10 * 2^-24.
+@pytest.mark.parametrize("first", [1, 40, 300])      # the reference's key in the same tile, another one, another key range
+def test_attention_f32_small_probabilities(first):
+    import torch
+    import paper_2410_03065_amd as cake
+    T, hd = 600, 64
+    eng = cake.Engine(si.ModelShape("attn-exp", 1, 256, 4, 4, hd, 512, 64, "f32"), None, max_tokens=640, max_chunk=64, page_tokens=64)
+    x = (np.round(np.linspace(2.0, 80.0, hd - 1) * 1024) / 1024).astype(np.float32)   # differences of scores are exact too
+    cache = otf.KVCache(1, T, 4, hd)
+    cache.k[0], cache.v[0] = 0.0, 0.0
+    cache.k[0][:, :, 0] = -1000.0
+    cache.k[0][0, :, 0] = 0.0                                             # probability 1 before the division, V = 0
+    cache.k[0][first:first + hd - 1, :, 0] = -x[:, None]
+    for j in range(hd - 1):
+        cache.v[0][first + j, :, j] = 1.0
+    eng.set_store(ostore.pack_store(cache, 64, "f32"))
+    eng.load_chunk(0, T)
+    q = torch.zeros(4, 1, hd, device="cuda")
+    q[..., 0] = 8.0                                                       # 8 / sqrt(64) = 1
+    torch.cuda.synchronize()
+    got = eng.op_attention(q, 0, T - 1).cpu().numpy().astype(np.float64).reshape(4, hd)[:, :hd - 1]
+    want = np.exp(-x.astype(np.float64)) / (1.0 + np.exp(-x.astype(np.float64)).sum())
+    err = float(np.abs(got / want - 1.0).max())
+    print("largest relative error %.2e" % err)
+    assert err < 10 * 2.0 ** -24, err
+
+
 # bf16, heads of 64: the scores and the probabilities keep float32's precision (16 bits in the second product), so what
 # is left is the rounding of the result to 8 significant bits (in [1, 2) the values lie 2^-7 apart: at most half of
 # that, 2^-8 of a value), and 2^-15 for the probabilities and the sums
