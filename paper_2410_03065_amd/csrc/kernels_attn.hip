@@ -891,11 +891,26 @@ attention_hd64_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, fl
         }
     }
 
-    // Diagonal tiles with an infinity or a NaN in V: key by key, over the keys a query sees, straight from the page
+    // An infinity in V that a query does see: p_hi and p_lo may differ in sign and p_lo may be 0, so their sum gives a NaN
+    // where p times the infinity is the infinity.  Such a range is taken again.
+    bool nan = false;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int v = 0; v < 16; v += 2) nan |= __builtin_isunordered(o[t][v], o[t][v + 1]);
+    const bool again = __builtin_amdgcn_ballot_w64(nan) != 0;
+    if (again) {
+        o[0] = o[1] = zero16;
+        m_run = -FLT_MAX;
+        l_part = 0.f;
+    }
+    // Tiles taken again or left out: key by key, over the keys a query sees, straight from the page
     // (wave-uniform bases and one lane offset, so that this loop costs the one above no registers).
+    const int tile_end = again || left_out != 0 ? min(2 * pair_hi, n_tiles) : 0;
 #pragma unroll 1
-    for (; left_out != 0; left_out &= left_out - 1) {
-        const int key0 = (first_masked + __builtin_ctz(left_out)) * AK;
+    for (int tile = 2 * pair_lo + grp; tile < tile_end; tile += 2) {
+        if (!again && (tile < first_masked || (left_out >> (tile - first_masked) & 1) == 0)) continue;
+        const int key0 = tile * AK;
         const char* page = page_of(key0);
         const unsigned in_page0 = unsigned(key0 % pt);
 #pragma unroll 1

@@ -119,6 +119,33 @@ def test_attention_bf16_hd64_hidden_values_do_not_leak():
     _poisoned("bf16", 64, 4, 2, 200, 77, 128, 50, 2.0 ** -8 + 2.0 ** -15)
 
 
+def test_attention_bf16_hd64_visible_infinities():
+    """Infinities in V at keys that the queries see: a query's result is that infinity in that element, a NaN where two of
+    opposite sign meet, and every other element is what it would be."""
+    import torch
+    begin, rows, pt, n_q, n_kv = 900, 70, 128, 8, 2
+    eng, Q, q, k, v = _case("bf16", 64, n_q, n_kv, begin, rows, pt)
+    vt = eng.pool[0].view(eng.kv.n_physical_pages, 2, -1)[:, 1].view(-1, n_kv, 64, pt)
+    where = [(3, 0, 5, np.inf), (130, 0, 6, -np.inf), (517, 1, 7, np.inf), (518, 1, 8, np.inf), (700, 1, 8, -np.inf),
+             (910, 0, 9, -np.inf)]                                        # key, KV head, element; the last among the chunk's own
+    for key, g, e, x in where:
+        vt[int(eng.block_table_host[key // pt]), g, e, key % pt] = x
+    torch.cuda.synchronize()
+    got = eng.op_attention(Q, 0, begin).float().cpu().numpy().reshape(rows, n_q, 64)
+    finite = otf.attention(q, k, v, np.arange(begin, begin + rows), np.arange(begin + rows))
+    want = finite.copy()
+    for row in range(rows):
+        for h in range(n_q):
+            for e in range(64):
+                hit = [x for key, g, el, x in where if g == h // (n_q // n_kv) and el == e and key <= begin + row]
+                if hit:
+                    want[row, h, e] = np.nan if len(set(hit)) == 2 else hit[0]
+    hit = ~np.isfinite(want)
+    assert np.array_equal(got[hit], want[hit], equal_nan=True)
+    assert np.isfinite(got[~hit]).all()
+    assert float(np.abs(got[~hit] - want[~hit]).max() / np.abs(finite).max()) < 2.0 ** -8 + 2.0 ** -15
+
+
 # bf16, heads of 128: the result, each probability and the scaled query are rounded to bf16; 2^-7 of the largest value
 # covers the three (tests/test_gpu_ops.py::test_attention).  Query heads of a KV head are laid side by side, so a tile of
 # queries ends inside a row's heads (r = 3) and a workgroup's rows inside a key tile.
