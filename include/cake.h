@@ -229,6 +229,9 @@ typedef struct {
  * head weights, a pinned buffer for the first-token step's logits),
  * and starts the load worker.  Loads allocate nothing; a page of more than max_chunk tokens
  * cannot be loaded from a quantised store.  compute_stream / copy_stream: hipStream_t, default priority.
+ * The steps that a prompt is computed in do not show in its KV (the bits are the same) in a float32 context, and in
+ * a bf16 context whose products add up in one order for every step of up to max_chunk tokens: at any width up to 128
+ * tokens, for narrow models up to several hundred.  Other bf16 contexts choose kernels by the tokens of a step.
  * Errors: CAKE_E_INVAL (shape not supported), CAKE_E_NOMEM, CAKE_E_HIP. */
 int32_t cake_create(cake_ctx** out, const cake_model_desc* model, const cake_weights* weights,
                     int32_t max_tokens, int32_t max_chunk, void* compute_stream, void* copy_stream);

@@ -49,6 +49,9 @@ struct cake_ctx {
     int32_t* t_tok = nullptr;
     void* static_scratch = nullptr;   // this device's copy of the file-scope scratch array (set by cake_create)
     GemmSplitWs split{};       // float32 parts and ticket counters of launches that split K or keys (compute stream only)
+    // A token's K and V have the same bits whatever step it is computed in: float32 models, and bf16 models whose products
+    // add up in one order for every step of up to max_chunk tokens (gemm_order_fixed).
+    bool step_free = false;
     int attn_range_keys = 0;   // length of the attention launches' key ranges, 0: chosen per launch (see AttnWs)
     void* q_stage = nullptr;   // device staging for quantised page images: a ring of image slots (cake_create)
     size_t q_stage_bytes = 0;
@@ -180,9 +183,10 @@ static GemmPartsPlan parts_plan(const cake_ctx* c, int epi, int M, int N, int K,
     return gemm_parts_plan(epi, M, N, K, c->split.part ? &c->split : nullptr, fused);
 }
 
-static hipError_t gemm(cake_ctx* c, int epi, const void* a, const void* w, const void* w2, void* out, int M, int N, int K) {
-    const GemmPartsPlan plan = M <= 192 ? parts_plan(c, epi, M, N, K, false) : GemmPartsPlan{0, false};
-    if (plan.ksplit && plan.few_rows && (uintptr_t(out) & 15) == 0) {   // K ranges, and a pass that adds them up
+// plan_rows: the rows that choose whether K ranges are left (M, or one number for all steps of a context).
+static hipError_t gemm(cake_ctx* c, int epi, const void* a, const void* w, const void* w2, void* out, int M, int N, int K, int plan_rows) {
+    const GemmPartsPlan plan = plan_rows <= 192 ? parts_plan(c, epi, plan_rows, N, K, false) : GemmPartsPlan{0, false};
+    if (plan.ksplit && plan.few_rows && M > 0 && (uintptr_t(out) & 15) == 0) {   // K ranges, and a pass that adds them up
         hipError_t e = launch_gemm_parts(plan, a, w, c->split.part, M, N, K, c->cs);
         return e != hipSuccess ? e : launch_add_parts((float*)out, c->split.part, plan.ksplit, size_t(M) * N, c->cs, epi == EPI_STORE_F32);
     }
@@ -198,7 +202,7 @@ static hipError_t attention(cake_ctx* c, const void* q, void* out, int tok_begin
     const AttnWs ws{c->split.part, c->split.part_bytes, c->attn_range_keys};
     if (c->m.dtype == CAKE_BF16 && c->tun.kernel_path == 0 && attention_mfma_supported(kv.head_dim, kv.page_tokens))
         return launch_attention_mfma(q, out, c->m.n_q_heads, tok_begin, rows, kv, c->cs, c->tun.attn_variant, ws);
-    if (c->m.dtype == CAKE_BF16 && c->tun.kernel_path == 0 && attention_hd64_supported(q, out, tok_begin + rows, kv))
+    if (c->m.dtype == CAKE_BF16 && c->tun.kernel_path == 0 && attention_hd64_supported(q, out, tok_begin + rows, kv, ws))
         return launch_attention_hd64(q, out, c->m.n_q_heads, tok_begin, rows, kv, c->cs, ws);
     if (c->m.dtype == CAKE_F32 && c->tun.kernel_path == 0 && attention_f32_supported(q, kv))
         return launch_attention_f32((const float*)q, (float*)out, c->m.n_q_heads, tok_begin, rows, kv, c->cs, ws);
@@ -243,17 +247,23 @@ static int enqueue_prefill(cake_ctx* c, int tok_begin, int rows, const cake_kv* 
     // A product may leave its K ranges in the split workspace for the kernel after it, which reads them before anything
     // else is put there: QKV for the rotary step, O and down for the norm (the last layer's down for a sum of its own).
     const bool rope_adds = m.head_dim == 128 && (uintptr_t(kv->pool) & 15) == 0;
+    // In a step-free context the longest step decides, for the kernel for few rows if it takes that one too.
     const GemmPartsPlan none{0, false};
-    const GemmPartsPlan p_qkv = rope_adds ? parts_plan(c, EPI_STORE_F32, rows, int(nqkv), int(d), true) : none;
-    const GemmPartsPlan p_o = parts_plan(c, EPI_RESIDUAL_F32, rows, int(d), int(hq), true);
-    const GemmPartsPlan p_down = parts_plan(c, EPI_RESIDUAL_F32, rows, int(d), m.ffn_dim, true);
+    const int plan_rows = c->step_free ? c->max_chunk : rows;
+    auto ranges = [&](int epi, int N, int K) {
+        const GemmPartsPlan p = parts_plan(c, epi, plan_rows, N, K, true);
+        return c->step_free && !p.few_rows ? none : p;
+    };
+    const GemmPartsPlan p_qkv = rope_adds ? ranges(EPI_STORE_F32, int(nqkv), int(d)) : none;
+    const GemmPartsPlan p_o = ranges(EPI_RESIDUAL_F32, int(d), int(hq));
+    const GemmPartsPlan p_down = ranges(EPI_RESIDUAL_F32, int(d), m.ffn_dim);
     float* parts = c->split.part;
     auto norm = [&](const GemmPartsPlan& left, const float* gain) {
         return left.ksplit ? launch_rmsnorm_parts(m.dtype, c->x, parts, left.ksplit, gain, c->h, rows, d, m.rms_eps, c->cs)
                            : launch_rmsnorm(m.dtype, c->x, gain, c->h, rows, d, m.rms_eps, c->cs);
     };
     auto product = [&](const GemmPartsPlan& plan, int epi, const void* a, const void* w, float* out, int N, int K) {
-        return plan.ksplit ? launch_gemm_parts(plan, a, w, parts, rows, N, K, c->cs) : gemm(c, epi, a, w, nullptr, out, rows, N, K);
+        return plan.ksplit ? launch_gemm_parts(plan, a, w, parts, rows, N, K, c->cs) : gemm(c, epi, a, w, nullptr, out, rows, N, K, plan_rows);
     };
     for (int l = 0; l < m.n_layers; ++l) {
         const cake_layer_weights& w = c->layers[l];
@@ -269,7 +279,7 @@ static int enqueue_prefill(cake_ctx* c, int tok_begin, int rows, const cake_kv* 
                 product(p_o, EPI_RESIDUAL_F32, c->ao, w.wo, c->x, d, hq));
         KLAUNCH(c, CAKE_K_RMSNORM, 0, R * d * (4 + e), norm(p_o, w.ffn_norm));
         KLAUNCH(c, CAKE_K_GEMM_GATEUP, 4 * R * ff * d, (R * d + 2 * ff * d + R * ff) * e,
-                gemm(c, EPI_SWIGLU, c->h, w.w_gate, w.w_up, c->act, rows, m.ffn_dim, d));
+                gemm(c, EPI_SWIGLU, c->h, w.w_gate, w.w_up, c->act, rows, m.ffn_dim, d, plan_rows));
         KLAUNCH(c, CAKE_K_GEMM_DOWN, 2 * R * d * ff, (R * ff + d * ff) * e + 2 * R * d * 4,
                 product(p_down, EPI_RESIDUAL_F32, c->act, w.w_down, c->x, d, m.ffn_dim));
     }
@@ -565,16 +575,20 @@ int32_t cake_create(cake_ctx** out, const cake_model_desc* model, const cake_wei
         ok = ok && hipMemset(c->split.counters, 0, size_t(c->split.n_counters) * 4) == hipSuccess;
     }
     {
-        // Attention divides its keys into the same ranges however many rows a step has where the chunk a token is
-        // computed in must not show in its bits: for float32 models, whose other kernels keep to that too, and for
-        // models of few heads, whose keys every launch divides anyway.  The shortest power of two from a least length
-        // whose parts for max_chunk rows at the end of max_tokens fit the workspace.  Shorter ranges help few rows
-        // and cost many (float32, 32 heads of 64, us with ranges of 512, 1024, 2048 and of a length chosen per launch:
-        // 8 rows at 4000 keys 23, 33, 55, 31; 137 at 1900 52, 59, 54, 48; 1024 at 3072 482, 419, 387, 368).
+        // Attention divides its keys into the same ranges however many rows a step has where the step must not show in a
+        // token's bits, and for models of few heads, whose keys every launch divides anyway.  The shortest power of two
+        // from a least length whose parts for max_chunk rows at the end of max_tokens fit the workspace.  Shorter ranges
+        // help few rows and cost many; us with ranges of 512, 1024, 2048 and of a length chosen per launch: float32, 32
+        // heads of 64, 8 rows at 4000 keys 23, 33, 55, 31; 1024 at 3072 482, 419, 387, 368.  bf16, 20 heads of 64, 8 rows
+        // at 2000 13.5, 17, 24, 13.5; 256 at 8000 40, 44, 45, 41.  24 heads of 128, the same 14, 18, 24, 13; 42, 56, 47, 42,
+        // and 256 at 4000 43, 33, 42, 33.
         const bool f32 = m.dtype == CAKE_F32;
+        const int d = m.d_model, ff = m.ffn_dim;
+        c->step_free = f32 || (gemm_order_fixed(EPI_STORE_F32, max_chunk, int(nqkv), d, &c->split) && gemm_order_fixed(EPI_RESIDUAL_F32, max_chunk, d, int(hq), &c->split) &&
+                               gemm_order_fixed(EPI_RESIDUAL_F32, max_chunk, d, ff, &c->split) && gemm_order_fixed(EPI_SWIGLU, max_chunk, ff, d, &c->split));
         const size_t row = size_t(m.n_q_heads) * max_chunk * (m.head_dim + 2) * 4;
-        if (f32 || m.n_q_heads <= 16)
-            for (c->attn_range_keys = f32 && m.n_q_heads <= 4 ? 256 : 1024; (max_tokens + c->attn_range_keys - 1) / c->attn_range_keys * row > c->split.part_bytes;)
+        if (c->step_free || m.n_q_heads <= 16)
+            for (c->attn_range_keys = f32 && m.n_q_heads <= 4 ? 256 : !f32 && m.head_dim == 64 && m.n_q_heads > 16 ? 512 : 1024; (max_tokens + c->attn_range_keys - 1) / c->attn_range_keys * row > c->split.part_bytes;)
                 if ((c->attn_range_keys *= 2) >= max_tokens) break;
     }
     {
@@ -1245,13 +1259,13 @@ int32_t cake_op_rmsnorm(cake_ctx* c, const float* x, const float* gain, void* ou
 
 int32_t cake_op_gemm(cake_ctx* c, const void* a, const void* w, float* out, int32_t M, int32_t N, int32_t K) {
     if (!c || !a || !w || !out || M < 0 || N <= 0 || K <= 0 || (K & 7)) return CAKE_E_INVAL;
-    HIP_TRY(c, gemm(c, EPI_STORE_F32, a, w, nullptr, out, M, N, K));
+    HIP_TRY(c, gemm(c, EPI_STORE_F32, a, w, nullptr, out, M, N, K, M));
     return CAKE_OK;
 }
 
 int32_t cake_op_gemm_residual(cake_ctx* c, const void* a, const void* w, float* x, int32_t M, int32_t N, int32_t K) {
     if (!c || !a || !w || !x || M < 0 || N <= 0 || K <= 0 || (K & 7)) return CAKE_E_INVAL;
-    HIP_TRY(c, gemm(c, EPI_RESIDUAL_F32, a, w, nullptr, x, M, N, K));
+    HIP_TRY(c, gemm(c, EPI_RESIDUAL_F32, a, w, nullptr, x, M, N, K, M));
     return CAKE_OK;
 }
 
@@ -1308,7 +1322,7 @@ int32_t cake_device_info(cake_ctx* c, int32_t* compute_units, int32_t* clock_khz
 int32_t cake_op_gemm_swiglu(cake_ctx* c, const void* a, const void* wg, const void* wu, void* out, int32_t M,
                             int32_t N, int32_t K) {
     if (!c || !a || !wg || !wu || !out || M < 0 || N <= 0 || K <= 0 || (K & 7)) return CAKE_E_INVAL;
-    HIP_TRY(c, gemm(c, EPI_SWIGLU, a, wg, wu, out, M, N, K));
+    HIP_TRY(c, gemm(c, EPI_SWIGLU, a, wg, wu, out, M, N, K, M));
     return CAKE_OK;
 }
 

@@ -45,7 +45,7 @@ hipError_t launch_attention_generic(int dtype, const void* q, void* out, int n_q
 
 // Where an attention launch may leave the parts of its key ranges: float32 workspace (part null: never divide the keys);
 // launches sharing it must not overlap.  range_keys > 0: the keys are divided into ranges of that many whatever the
-// number of rows (in float32 a token's result then does not depend on the step it is computed in); 0: by a cost model.
+// number of rows, and a token's result does not depend on the step that it is computed in; 0: by a cost model.
 struct AttnWs { float* part; size_t bytes; int range_keys; };
 
 // ---- float32 on the matrix cores ----
@@ -78,6 +78,8 @@ hipError_t launch_gemm_mfma(int epi, const void* a, const void* w, const void* w
 // What launch_gemm_mfma would launch: tile rows / columns and K ranges per tile.
 void gemm_mfma_plan(int epi, int M, int N, int K, int cfg_override, const GemmSplitWs* ws, int ksplit_override,
                     int* bm, int* bn, int* ksplit);
+// Does launch_gemm_mfma add up in the same order for every M from 1 to max_rows?
+bool gemm_order_fixed(int epi, int max_rows, int N, int K, const GemmSplitWs* ws);
 // out[ks][M][N] float32: one output per K range (K a multiple of 64 ks), for a consumer that adds them up.
 // rows: M <= 192, N a multiple of 128; p256: N a multiple of 256.
 hipError_t launch_gemm_rows_parts(const void* a, const void* w, float* part, int M, int N, int K, int ks, hipStream_t st);
@@ -100,7 +102,7 @@ hipError_t launch_attention_mfma(const void* q, void* out, int n_q, int tok_begi
                                  const KvView& kv, hipStream_t st, int variant, const AttnWs& ws);
 
 // bf16, head_dim 64
-bool attention_hd64_supported(const void* q, const void* out, int n_keys, const KvView& kv);
+bool attention_hd64_supported(const void* q, const void* out, int n_keys, const KvView& kv, const AttnWs& ws);
 hipError_t launch_attention_hd64(const void* q, void* out, int n_q, int tok_begin, int rows, const KvView& kv,
                                  hipStream_t st, const AttnWs& ws);
 

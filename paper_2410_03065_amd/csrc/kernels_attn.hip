@@ -528,7 +528,7 @@ attention_mfma8_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, f
         raw = fmaxf(raw, __shfl_xor(raw, 32, 64));
         moved_cur = raw > RESCALE_LOG2;
         if (__builtin_amdgcn_ballot_w64(moved_cur) != 0) {
-            delta_cur = fmaxf(raw, 0.f);            // the reference only ever rises; -inf (all masked) leaves it
+            delta_cur = moved_cur ? raw : 0.f;      // of this query alone: a row's bits do not depend on the rows beside it
             corr_cur = __builtin_amdgcn_exp2f(-delta_cur);
             m_run += delta_cur;
             moved_cur = true;
@@ -685,7 +685,9 @@ attention_mfma8_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, f
         const float m_b = l_b_row > 0.f ? park[65 * 64] : -1.0e30f;         // a half that saw no key has no reference
         const float m = fmaxf(m_run, m_b);
         const float ca = __builtin_amdgcn_exp2f(m_run - m), cb = __builtin_amdgcn_exp2f(m_b - m);
-        float l_mine = l_part * ca + l_b * cb;
+        // (sums written as fmaf, so that both instantiations round them alike)
+        float l_mine = __builtin_fmaf(l_part, ca, l_b * cb);
+        auto merged = [&](int t, int v) { return __builtin_fmaf(o[t][v], ca, park[(16 * t + v) * 64] * cb); };
         const float l_tot = l_mine + __shfl_xor(l_mine, 32, 64);
         if constexpr (SPLIT) {
             if (is_query) {
@@ -694,7 +696,7 @@ attention_mfma8_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, f
 #pragma unroll
                     for (int v = 0; v < 16; v += 2)
                         *(float2*)(my_part + t * 32 + 8 * (v >> 2) + 4 * lhalf + (v & 3)) =
-                            make_float2(o[t][v] * ca + park[(16 * t + v) * 64] * cb, o[t][v + 1] * ca + park[(16 * t + v + 1) * 64] * cb);
+                            make_float2(merged(t, v), merged(t, v + 1));
                 if (lhalf == 0) *(float2*)(my_part + AHD) = make_float2(l_tot > 0.f ? m * 0.6931471805599453f : -FLT_MAX, l_tot);
             }
             return;
@@ -708,10 +710,7 @@ attention_mfma8_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, f
                 for (int v4 = 0; v4 < 4; ++v4) {
                     bf16x4 w;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int v = 4 * v4 + e;
-                        w[e] = bf16_t((o[t][v] * ca + park[(16 * t + v) * 64] * cb) * inv);
-                    }
+                    for (int e = 0; e < 4; ++e) w[e] = bf16_t(merged(t, 4 * v4 + e) * inv);
                     *(bf16x4*)(op + t * 32 + 8 * v4 + 4 * lhalf) = w;
                 }
         }
@@ -846,8 +845,9 @@ attention_hd64_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, fl
 #pragma unroll
             for (int v = 0; v < 16; ++v) mx = fmaxf(mx, s[t][v]);
         mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * sl2;
-        if (__builtin_amdgcn_ballot_w64(mx > m_run + RESCALE_LOG2) != 0) {
-            const float m_new = fmaxf(m_run, mx), corr = __builtin_amdgcn_exp2f(m_run - m_new);
+        const bool moved = mx > m_run + RESCALE_LOG2;   // each query's reference by itself, as above
+        if (__builtin_amdgcn_ballot_w64(moved) != 0) {
+            const float m_new = moved ? mx : m_run, corr = __builtin_amdgcn_exp2f(m_run - m_new);
             m_run = m_new;
             l_part *= corr;
 #pragma unroll
@@ -1169,10 +1169,9 @@ static AttnPlan attn_plan(int n_q, int n_kv, int tok_begin, int rows, const Attn
 
 template <int QW>
 static hipError_t launch_mfma8(const bf16_t* q, bf16_t* out, float* part, int n_q, int tok_begin, int rows, const KvView& kv, int splits,
-                               int per, int lds, hipStream_t st, bool fixed_layout) {
-    // (a model whose key ranges are fixed keeps one layout: which queries share a wave shows in their bits)
+                               int per, int lds, hipStream_t st) {
     const int r = n_q / kv.n_kv, packed = (rows * r + 32 * QW - 1) / (32 * QW), apart = r * ((rows + 32 * QW - 1) / (32 * QW));
-    const bool side_by_side = fixed_layout || packed < apart;
+    const bool side_by_side = packed < apart;
     const int q_tiles = side_by_side ? packed : apart;
     auto kern = splits > 1 ? attention_mfma8_kernel<QW, true> : attention_mfma8_kernel<QW, false>;
     static bool attr_set[2] = {false, false};
@@ -1207,18 +1206,19 @@ hipError_t launch_attention_mfma(const void* q, void* out, int n_q, int tok_begi
     if (LDS > A_LDS_MAX) return hipErrorInvalidValue;
     const AttnPlan plan = attn_plan(n_q, kv.n_kv, tok_begin, rows, ws, variant == 2 ? 4 : variant == 3 ? 2 : 0);
     const bf16_t* Q = (const bf16_t*)q;
-    if (plan.qw == 4) return launch_mfma8<4>(Q, (bf16_t*)out, ws.part, n_q, tok_begin, rows, kv, plan.splits, plan.per, LDS, st, ws.range_keys > 0);
-    if (plan.qw == 2) return launch_mfma8<2>(Q, (bf16_t*)out, ws.part, n_q, tok_begin, rows, kv, plan.splits, plan.per, LDS, st, ws.range_keys > 0);
-    return launch_mfma8<1>(Q, (bf16_t*)out, ws.part, n_q, tok_begin, rows, kv, plan.splits, plan.per, LDS, st, ws.range_keys > 0);
+    if (plan.qw == 4) return launch_mfma8<4>(Q, (bf16_t*)out, ws.part, n_q, tok_begin, rows, kv, plan.splits, plan.per, LDS, st);
+    if (plan.qw == 2) return launch_mfma8<2>(Q, (bf16_t*)out, ws.part, n_q, tok_begin, rows, kv, plan.splits, plan.per, LDS, st);
+    return launch_mfma8<1>(Q, (bf16_t*)out, ws.part, n_q, tok_begin, rows, kv, plan.splits, plan.per, LDS, st);
 }
 
-// Head dimension 64, 16-byte reads of q, the pages and the result; with fewer keys than 24 the one-wave-per-row kernel
-// is as fast or faster (32 heads, us: 8 rows of 8 keys 5.6 here, 4.3 there; 16: 5.6, 5.2; 24: 5.6, 5.9).  Queries per workgroup by the rows there are; key
-// ranges until two workgroups per CU, as long as a range keeps four tile pairs and the parts fit the workspace.
-bool attention_hd64_supported(const void* q, const void* out, int n_keys, const KvView& kv) {
+// Head dimension 64, 16-byte reads of q, the pages and the result.  With fewer keys than 24 the one-wave-per-row kernel
+// is as fast or faster (32 heads, us: 8 rows of 8 keys 5.6 here, 4.3 there; 16: 5.6, 5.2; 24: 5.6, 5.9), but not where a
+// token's result must not depend on its step.  Queries per workgroup by the rows there are; key ranges until two
+// workgroups per CU, as long as a range keeps four tile pairs and the parts fit the workspace, or fixed ones.
+bool attention_hd64_supported(const void* q, const void* out, int n_keys, const KvView& kv, const AttnWs& ws) {
     const size_t table = 8 * (size_t(n_keys - 1) / kv.page_tokens + 1);
-    return n_keys >= 24 && kv.head_dim == 64 && kv.page_tokens % AK == 0 && ((uintptr_t(q) | uintptr_t(out) | uintptr_t(kv.pool)) & 15) == 0 &&
-           H64_TABLE + table <= 160 * 1024;
+    return (n_keys >= 24 || ws.range_keys > 0) && kv.head_dim == 64 && kv.page_tokens % AK == 0 &&
+           ((uintptr_t(q) | uintptr_t(out) | uintptr_t(kv.pool)) & 15) == 0 && H64_TABLE + table <= 160 * 1024;
 }
 
 template <int QW>

@@ -556,6 +556,26 @@ static P256Plan p256_plan(int epi, int tiles_m, int N) {
     return best;
 }
 
+// 128 x 192, at most one workgroup per CU: the whole 160 KB of LDS as a ring of 64-deep slices, whose halves two waves
+// take (120 KB in flight hide the latency of weights that come from HBM: 64 against 75 us for N = 6144).
+static bool deep_192(int M, int N, int K, int ks) { return long((M + 127) / 128) * (N / 192) * ks <= 256 && (K / ks % 64) == 0; }
+
+// The choice goes by M, and with it the order of a sum: K from end to end (every template tile in one K range), its
+// slices' halves apart, 32 instead of 16 elements to an MFMA (the persistent kernel), K ranges apart.  Choices change at
+// multiples of 64 rows only.
+bool gemm_order_fixed(int epi, int max_rows, int N, int K, const GemmSplitWs* ws) {
+    if (!gemm_mfma_supported(epi, 1, N, K)) return true;   // the generic kernel walks K in one order
+    int first = -1;
+    for (int M = 1; M <= max_rows; M += 64) {
+        const GemmChoice ch = gemm_pick(epi, M, N, K, ws);
+        const bool halves = ch.cfg == GCFG_128x128K || (ch.cfg == GCFG_128x192 && deep_192(M, N, K, ch.ksplit));
+        const int order = 4 * ch.ksplit + (ch.cfg == GCFG_P256 ? 2 : halves ? 1 : 0);
+        if (first >= 0 && order != first) return false;
+        first = order;
+    }
+    return true;
+}
+
 template <int EPI>
 static hipError_t gemm_launch_cfg(int cfg, int ks, const GemmSplitWs* ws, const bf16_t* A, const bf16_t* W, const bf16_t* W2,
                                   void* out, int M, int N, int K, hipStream_t st) {
@@ -593,9 +613,7 @@ static hipError_t gemm_launch_cfg(int cfg, int ks, const GemmSplitWs* ws, const 
             return gemm_launch_t<4, 2, 2, 2, 32, 4, EPI>(A, W, W2, out, M, N, K, st, ks, ws);
         case GCFG_128x192:
             if constexpr (EPI != EPI_SWIGLU) {
-                // at most one workgroup per CU: the whole 160 KB of LDS as a ring of 64-deep slices (120 KB in
-                // flight hide the latency of weights that come from HBM: 64 against 75 us for N = 6144)
-                if (long((M + 127) / 128) * (N / 192) * ks <= 256 && (K / ks % 64) == 0)
+                if (deep_192(M, N, K, ks))
                     return gemm_launch_t<2, 3, 2, 2, 64, 4, EPI, 2>(A, W, W2, out, M, N, K, st, ks, ws);
                 return gemm_launch_t<2, 3, 2, 2, 32, 4, EPI>(A, W, W2, out, M, N, K, st, ks, ws);
             } else {
@@ -644,8 +662,7 @@ hipError_t launch_gemm_p256_parts(const void* a, const void* w, float* part, int
 // per workgroup.  Both sides measured, us:
 // down 8B (K = 14336 -> 4096) 1024 rows 140 and 91 in four ranges, 64 rows 40 and 24 in eight; down 70B 1024 rows 459 and
 // 355 in two; O 8B 1024 rows 45 and 36 (no gain with 64 MB of ranges to add), 137 rows 32 and 16; QKV 8B 137 rows 29 and 18.
-// Narrow products (under 2048 columns, under 4096 on the persistent kernel) have too few tiles for either, and stay with
-// kernels whose sums do not depend on M: a narrow model's KV must not show in its bits how many rows a step had.
+// Narrow products (under 2048 columns, under 4096 on the persistent kernel) have too few tiles for either.
 GemmPartsPlan gemm_parts_plan(int epi, int M, int N, int K, const GemmSplitWs* ws, bool fused) {
     GemmPartsPlan best{0, false};
     if (epi == EPI_SWIGLU || !ws || !ws->part || M <= 0 || K % 64 || N % 128) return best;

@@ -197,3 +197,34 @@ def test_f32_prefill_does_not_depend_on_its_steps(n_q, n_kv, hd, d, ffn):
     whole = _prefill_in_steps(eng, toks, [1024])
     for steps in ([512], [256], [7, 101, 300], [37], [33, 1, 950]):
         assert torch.equal(_prefill_in_steps(eng, toks, steps), whole), steps
+
+
+@pytest.mark.parametrize("hd,n_q,n_kv", [(128, 8, 2), (128, 6, 2), (64, 8, 2), (64, 16, 16)])
+def test_attention_of_a_model_of_few_heads_in_ragged_pieces(hd, n_q, n_kv):
+    """Pieces that end inside a wave's queries, on both sides of the first key range's end."""
+    import torch
+    begin, rows = 700, 700
+    eng, Q, *_ = _case("bf16", hd, n_q, n_kv, begin, rows, 128)
+    whole = eng.op_attention(Q, 0, begin)
+    for piece in (101, 37, 450):
+        for r in range(0, rows, piece):
+            q = Q[:, r:r + piece].contiguous()
+            torch.cuda.synchronize()
+            assert torch.equal(eng.op_attention(q, 0, begin + r), whole[r:r + piece]), (piece, r)
+
+
+# Contexts whose bf16 products add up in one order for every step they can have: narrow models, and steps of one tile of
+# rows.  few_rows: K ranges are left by the kernel for few rows, as many for a short step as for the longest.
+@pytest.mark.parametrize("hd,n_q,n_kv,d,ffn,max_chunk,few_rows", [
+    (64, 20, 4, 1280, 3456, 512, False), (64, 32, 8, 2048, 3072, 256, False), (64, 32, 8, 2048, 8192, 128, True),
+    (128, 24, 8, 3072, 8192, 128, True), (128, 8, 2, 1024, 2816, 256, False), (64, 8, 8, 512, 1408, 512, False)])
+def test_bf16_prefill_of_a_step_free_context_does_not_depend_on_its_steps(hd, n_q, n_kv, d, ffn, max_chunk, few_rows):
+    import torch
+    import paper_2410_03065_amd as cake
+    shape = si.ModelShape("bf16-steps", 2, d, n_q, n_kv, hd, ffn, 128, "bf16", rope_theta=500000.0)
+    eng = cake.Engine(shape, None, max_tokens=2048, max_chunk=max_chunk, page_tokens=128, seed=3)
+    assert (eng.op_gemm_plan(max_chunk, d, ffn)[0] == max_chunk and eng.op_gemm_plan(max_chunk, d, ffn)[2] > 1) == few_rows
+    toks = si.make_tokens(1500, shape.vocab, seed=7)
+    whole = _prefill_in_steps(eng, toks, [max_chunk])
+    for steps in ([64], [7, 101, 120], [37], [33, 1, 90]):
+        assert torch.equal(_prefill_in_steps(eng, toks, steps), whole), steps
