@@ -40,6 +40,10 @@ __device__ __forceinline__ float group_sum(float v) {
     return v;
 }
 
+// Four floats from a caller's array that is aligned to its elements only, as norm gains may be (one 16-byte load all the
+// same: the hardware asks for 4-byte alignment).
+typedef float float4_any __attribute__((ext_vector_type(4), aligned(4)));
+
 // 16 bytes of T -> floats
 template <typename T> struct Ld16;
 template <> struct Ld16<float> {
@@ -125,7 +129,7 @@ __global__ void __launch_bounds__(256) gemv_kernel(const float* __restrict__ x, 
             const float4 xv = STAGED ? *(const float4*)(xs + k + e) : *(const float4*)(x + k + e);
             xf[e] = xv.x; xf[e + 1] = xv.y; xf[e + 2] = xv.z; xf[e + 3] = xv.w;
             if constexpr (NORM && !STAGED) {
-                const float4 gv = *(const float4*)(gain + k + e);
+                const float4_any gv = *(const float4_any*)(gain + k + e);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) ss = __builtin_fmaf(xf[e + i], xf[e + i], ss);
                 xf[e] *= gv.x; xf[e + 1] *= gv.y; xf[e + 2] *= gv.z; xf[e + 3] *= gv.w;
@@ -160,7 +164,7 @@ __global__ void __launch_bounds__(256) gemv_kernel(const float* __restrict__ x, 
         for (int k = threadIdx.x * 4; k < K; k += 1024) {
             float4 v = *(const float4*)(x + k);
             if constexpr (NORM) {
-                const float4 g = *(const float4*)(gain + k);
+                const float4_any g = *(const float4_any*)(gain + k);
                 ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
                 v.x *= g.x; v.y *= g.y; v.z *= g.z; v.w *= g.w;
             }

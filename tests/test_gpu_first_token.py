@@ -54,3 +54,33 @@ def test_first_of_equal_logits():
     eng.lm_head[:] = eng.lm_head * torch.sign(torch.tensor(float(eng.first_token(toks, want_logits=True)[2][39999])))
     torch.cuda.synchronize()
     assert eng.first_token(toks)[0] == 31000
+
+
+@pytest.mark.parametrize("kind,d,hd", [("f32", 1000, 64), ("f32", 2048, 64), ("bf16", 1000, 128), ("bf16", 4096, 128)])
+def test_norm_gains_aligned_to_their_elements_only(kind, d, hd):
+    """Gains at addresses 4, 8 and 12 past a multiple of 16 give the same logits as aligned ones."""
+    import torch
+    import paper_2410_03065_amd as cake
+    shape = si.ModelShape("first-token-gains", 2, d, 4, 2, hd, 512, 301, kind)
+
+    class Shifted(cake.Engine):
+        def _build_weights(self, weights, seed):
+            super()._build_weights(weights, seed)
+            g = torch.Generator(device=self.dev).manual_seed(9)
+
+            def moved(by):
+                t = torch.zeros(d + 4, device=self.dev)[by:by + d]
+                t.copy_(torch.rand(d, device=self.dev, generator=g) + 0.5)
+                self._tensors.append(t)
+                return t.data_ptr()
+            for l in range(shape.n_layers):
+                self._layer_arr[l].attn_norm, self._layer_arr[l].ffn_norm = moved(self.shift), moved(self.shift)
+            self._weights.final_norm = moved(self.shift)
+    logits = []
+    for by in range(4):
+        eng = type("E", (Shifted,), {"shift": by})(shape, None, max_tokens=64, max_chunk=64, page_tokens=64, seed=2, with_head=True)
+        eng.pool.normal_(generator=torch.Generator(device="cuda").manual_seed(1))
+        torch.cuda.synchronize()
+        logits.append(eng.first_token(si.make_tokens(50, shape.vocab, seed=1), want_logits=True)[2].copy())
+    for other in logits[1:]:
+        assert np.array_equal(other, logits[0])
