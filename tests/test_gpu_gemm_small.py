@@ -97,9 +97,34 @@ def test_block_with_products_left_in_k_ranges(base, rows):
     assert torch.equal(eng.pool[1].float(), got[1])
 
 
-# bf16 tiles for few rows: float32 sums over K as above; SwiGLU rounds once to bf16 (2^-8 of a value)
+# Narrow bf16 products of few rows, on the ordinary tiles: float32 sums over K as above; SwiGLU rounds once to bf16 (2^-8
+# of a value)
 @pytest.mark.parametrize("M,N,K", [(129, 128, 64), (137, 384, 512), (192, 640, 4096), (33, 256, 192), (160, 64, 128)])
 def test_gemm_bf16_few_rows(M, N, K):
     plain, residual, swiglu, again = _products("bf16", M, N, K)
     tol = 2e-6 * max(1, K / 256)
     assert plain < tol and residual < tol and swiglu < 1.0 and again, (plain, residual, swiglu, again)
+
+
+# Plain and residual products of up to 192 rows that are taken in K ranges by one tile of all rows and added up by a pass
+# of its own: every tile height, ranges of one slice (64) and of many.
+@pytest.mark.parametrize("M,N,K,ranges", [
+    (1, 2048, 512, 8), (1, 4096, 4096, 8), (33, 4096, 4096, 8), (64, 2048, 8192, 8), (96, 2176, 1024, 4), (128, 4096, 4096, 8),
+    (129, 4096, 4096, 8), (137, 6144, 4096, 4), (192, 4096, 4096, 8)])
+def test_gemm_bf16_few_rows_in_k_ranges(M, N, K, ranges):
+    import paper_2410_03065_amd as cake
+    eng = cake.Engine(si.ModelShape("gemm-small", 1, 256, 4, 4, 64, 512, 64, "bf16"), None, max_tokens=1024, max_chunk=1024, page_tokens=64)
+    for residual in (False, True):
+        assert eng.op_gemm_plan(M, N, K, residual) == ((M + 31) // 32 * 32, 128, ranges)
+    plain, residual, swiglu, again = _products("bf16", M, N, K)
+    tol = 2e-6 * max(1, K / 256)
+    assert plain < tol and residual < tol and swiglu < 1.0 and again, (plain, residual, swiglu, again)
+
+
+# Gate/up of 129 to 192 rows in one tile of 192 (wide feed-forward layers only: 9216 columns and more here), and the rows
+# on both sides of that; K from one slice of 64 to more than its ring holds.
+@pytest.mark.parametrize("M,N,K", [(128, 9216, 64), (129, 9216, 64), (137, 11008, 320), (160, 10240, 128), (192, 9216, 192), (193, 9216, 192),
+                                   (150, 14336, 1024)])
+def test_gemm_swiglu_in_one_tile_of_192_rows(M, N, K):
+    _, _, swiglu, again = _products("bf16", M, N, K)
+    assert swiglu < 1.0 and again, (swiglu, again)
