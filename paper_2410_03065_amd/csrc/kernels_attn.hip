@@ -722,18 +722,18 @@ attention_mfma8_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, f
 // V^T tiles of 8 KB in two LDS slots per half, filled one pair ahead by direct loads.
 //
 // Nothing is rounded that the one-wave-per-row kernel keeps in float32: the softmax scale stays out of Q (it is
-// applied in the exponent's multiply-add) and a probability enters the second product as the sum of two bf16 values
-// (the nearest, and the nearest to what that leaves: 16 bits), so P V takes two MFMAs per tile instead of one.
+// applied in the exponent's multiply-add) and a probability enters the second product as the sum of three bf16 values
+// that hold its 24 bits, so P V takes three MFMAs per tile instead of one.  (Two values, 16 bits: 5 to 8 % less time, and
+// two parts in a million more error of the bf16 result, 1.658401e-3 against 1.658399e-3.)
 //
-// What bounds it: the vector work per score (exponential, running sum, two conversions and a subtraction) against
-// 24 MFMAs per 64 x 32 scores.  Two workgroups share a CU, so that four waves per SIMD cover each other's waits.
-// 512 rows x 32 heads (8 KV heads) against 2048 keys: 35 us, against 5203 us for the one-wave-per-row kernel; 1024 rows
-// against 31K keys 493 us (519 TFLOP/s, 780 with the doubled P V), 556 while the registers held one workgroup per CU.
+// What bounds it: the vector work per score (exponential, running sum, three cuts) beside 32 MFMAs per 64 x 32 scores.  Two
+// workgroups share a CU, so that four waves per SIMD cover each other's waits.  512 rows x 32 heads (8 KV heads) against
+// 2048 keys: 5203 -> 37 us from the one-wave-per-row kernel; 1024 rows against 8192 keys 155 us.
 // =====================================================================================
 constexpr int H64_TILE = AK * 64 * 2, H64_GROUP = 4 * H64_TILE, H64_TABLE = 2 * H64_GROUP;
 
 template <int QW>
-__global__ void __launch_bounds__(128 * QW)
+__global__ void __launch_bounds__(128 * QW, QW == 4 ? 4 : 1)
 attention_hd64_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, float* __restrict__ part, int n_q, int tok_begin,
                       int rows, KvView kv, int pairs_per_split) {
     constexpr int HD = 64, AQW = 32 * QW, PER = 8 / QW;
@@ -874,25 +874,36 @@ attention_hd64_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, fl
         }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            bf16x8 p_hi, p_lo;
+            // x = hi + mid + lo exactly: its upper, middle and lower 8 significant bits, cut off one after the other
+            unsigned w[3][4];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const float x = __builtin_amdgcn_exp2f(__builtin_fmaf(s[j >> 1][8 * (j & 1) + i], sl2, -m_run));
-                l_part += x;
-                p_hi[i] = bf16_t(x);
-                p_lo[i] = bf16_t(x - float(p_hi[i]));
+            for (int i = 0; i < 8; i += 2) {
+                float x[2];
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    x[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[j >> 1][8 * (j & 1) + i + e], sl2, -m_run));
+                    l_part += x[e];
+                }
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    w[k][i / 2] = __builtin_amdgcn_perm(__float_as_uint(x[1]), __float_as_uint(x[0]), 0x07060302);
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) x[e] -= __uint_as_float(__float_as_uint(x[e]) & 0xFFFF0000u);
+                }
             }
+            bf16x8 p[3];
+            __builtin_memcpy(p, w, sizeof p);
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
                 const bf16x8 v = *(const bf16x8*)(st + t * 32 * 128 + vaddr[j]);
-                o[t] = mfma32(v, p_hi, o[t]);
-                o[t] = mfma32(v, p_lo, o[t]);
+#pragma unroll
+                for (int k = 0; k < 3; ++k) o[t] = mfma32(v, p[k], o[t]);
             }
         }
     }
 
-    // An infinity in V that a query does see: p_hi and p_lo may differ in sign and p_lo may be 0, so their sum gives a NaN
-    // where p times the infinity is the infinity.  Such a range is taken again.
+    // An infinity in V that a query does see: the lower parts of a probability may be 0, and 0 times the infinity is a NaN
+    // where the probability times it is the infinity.  Such a range is taken again.
     bool nan = false;
 #pragma unroll
     for (int t = 0; t < 2; ++t)

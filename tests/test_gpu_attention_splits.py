@@ -105,7 +105,7 @@ def test_attention_f32_small_probabilities(first):
     assert err < 10 * 2.0 ** -24, err
 
 
-# bf16, heads of 64: the scores and the probabilities keep float32's precision (16 bits in the second product), so what
+# bf16, heads of 64: the scores and the probabilities keep float32's precision (24 bits in the second product), so what
 # is left is the rounding of the result to 8 significant bits (in [1, 2) the values lie 2^-7 apart: at most half of
 # that, 2^-8 of a value), and 2^-15 for the probabilities and the sums
 @pytest.mark.parametrize("n_q,n_kv", [(4, 4), (8, 2), (16, 8)])
@@ -117,6 +117,36 @@ def test_attention_bf16_hd64(n_q, n_kv, tok_begin, rows, pt):
 
 def test_attention_bf16_hd64_hidden_values_do_not_leak():
     _poisoned("bf16", 64, 4, 2, 200, 77, 128, 50, 2.0 ** -8 + 2.0 ** -15)
+
+
+def test_attention_bf16_hd64_probabilities_keep_float32s_bits():
+    """Keys of scores 0, -a and -a - c, c from 2^-10, with V = 0, 1 and -1: the result is the difference of two
+    probabilities, 2^-11 of them, so an error of theirs comes out 2^11 times as large.  Float32 exponentials leave 2^-23 of
+    each, in all 2^-11 of the result, which is then rounded to bf16 (8 significant bits: 2^-8 of a value at most);
+    probabilities of 16 bits are up to 2^-7 off before that."""
+    import torch
+    import paper_2410_03065_amd as cake
+    T, rows, hd = 400, 128, 64
+    eng = cake.Engine(si.ModelShape("attn-bits", 1, 256, 4, 4, hd, 512, 64, "bf16"), None, max_tokens=448, max_chunk=128, page_tokens=64)
+    cache = otf.KVCache(1, T, 4, hd)
+    cache.k[0], cache.v[0] = 0.0, 0.0
+    a = 0.30078125
+    cache.k[0][:, :, 0] = -1024.0
+    cache.k[0][3, :, 0], cache.k[0][170, :, 0], cache.k[0][60, :, 0] = -a, -a, 0.0
+    cache.k[0][170, :, 1] = -1.0
+    cache.v[0][3], cache.v[0][170] = 1.0, -1.0
+    eng.set_store(ostore.pack_store(cache, 64, "bf16"))
+    eng.load_chunk(0, T)
+    c = 2.0 ** -10 * (1.0 + np.arange(rows) / 128.0)                      # bf16 values
+    q = torch.zeros(4, rows, hd)
+    q[..., 0], q[..., 1] = 8.0, torch.from_numpy(8.0 * c).float()         # scores -a, -a - c and 0, by 1 / sqrt(64)
+    q = q.cuda().to(torch.bfloat16)
+    torch.cuda.synchronize()
+    got = eng.op_attention(q, 0, T - rows).float().cpu().numpy().reshape(rows, 4 * hd)
+    want = ((np.exp(-a) - np.exp(-a - c)) / (1.0 + np.exp(-a) + np.exp(-a - c)))[:, None]
+    err = float(np.abs(got / want - 1.0).max())
+    print("largest relative error %.2e" % err)
+    assert err < 2.0 ** -8 + 2.0 ** -11, err
 
 
 def test_attention_bf16_hd64_visible_infinities():
