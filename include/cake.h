@@ -223,7 +223,8 @@ typedef struct {
 /* ---- life cycle ------------------------------------------------------- */
 
 /* Creates a context on the current device: copies the layer table, allocates the
- * activation workspace for chunks of up to max_chunk tokens, a device buffer for
+ * activation workspace for chunks of up to max_chunk tokens, up to 64 MiB for the parts of
+ * divided sums (products and attention, float32 and bf16), a device buffer for
  * max_tokens token ids and the staging of the load path (device room for the 8-bit page
  * images of max_chunk tokens; two pinned buffers of one DMA piece for file-backed stores; with
  * head weights, a pinned buffer for the first-token step's logits),

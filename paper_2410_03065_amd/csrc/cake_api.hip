@@ -283,6 +283,7 @@ static int enqueue_prefill(cake_ctx* c, int tok_begin, int rows, const cake_kv* 
         KLAUNCH(c, CAKE_K_GEMM_DOWN, 2 * R * d * ff, (R * ff + d * ff) * e + 2 * R * d * 4,
                 product(p_down, EPI_RESIDUAL_F32, c->act, w.w_down, c->x, d, m.ffn_dim));
     }
+    // the residual stream complete, as the other routes leave it (the first-token step starts from the embedding again)
     if (p_down.ksplit) HIP_TRY(c, launch_add_parts(c->x, parts, p_down.ksplit, size_t(rows) * d, c->cs));
     return CAKE_OK;
 }

@@ -26,7 +26,7 @@ typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 //
 // What bounds it: the float32 matrix rate where there are enough queries; for the few queries of a small model's
 // chunk the number of waves, hence the key ranges (launch_attention_f32).  256 rows x 4 heads x 64 against 2048
-// keys: 17 us with the merge, against 352 us for one wave per row and query head with a lane per key, whose 64
+// keys: 18 us with the merge, against 352 us for one wave per row and query head with a lane per key, whose 64
 // lanes each walked a key row of their own (one cache line per lane and load).
 //
 // The exponentials are expf, not the hardware's exp2 of a product with log2 e: that product's rounding is worth

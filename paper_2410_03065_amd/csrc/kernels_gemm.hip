@@ -662,7 +662,9 @@ hipError_t launch_gemm_p256_parts(const void* a, const void* w, float* part, int
 // per workgroup.  Both sides measured, us:
 // down 8B (K = 14336 -> 4096) 1024 rows 140 and 91 in four ranges, 64 rows 40 and 24 in eight; down 70B 1024 rows 459 and
 // 355 in two; O 8B 1024 rows 45 and 36 (no gain with 64 MB of ranges to add), 137 rows 32 and 16; QKV 8B 137 rows 29 and 18.
-// Narrow products (under 2048 columns, under 4096 on the persistent kernel) have too few tiles for either.
+// Narrow products (under 2048 columns, under 4096 on the persistent kernel) stay with launch_gemm_mfma, where the order of
+// their sums changes with M at fewer sizes, so that a narrow model's KV shows less of its steps.  They would gain: 64 rows
+// of 4096 -> 1024 18.7 and 9.5 us, 1024 rows through four layers of d 2048 and ffn 8192 840 and 785.
 GemmPartsPlan gemm_parts_plan(int epi, int M, int N, int K, const GemmSplitWs* ws, bool fused) {
     GemmPartsPlan best{0, false};
     if (epi == EPI_SWIGLU || !ws || !ws->part || M <= 0 || K % 64 || N % 128) return best;
