@@ -258,3 +258,24 @@ def test_bf16_prefill_of_a_step_free_context_does_not_depend_on_its_steps(hd, n_
     whole = _prefill_in_steps(eng, toks, [max_chunk])
     for steps in ([64], [7, 101, 120], [37], [33, 1, 90]):
         assert torch.equal(_prefill_in_steps(eng, toks, steps), whole), steps
+
+
+def test_bf16_prefill_of_a_wide_model_in_steps():
+    """The 8B shape: with steps of up to 128 tokens the same bits whatever the steps; with steps of up to 1024 the kernels
+    go by the tokens of a step, and a short last step rounds differently (one bf16 block's flat 2e-2 of the largest value,
+    tests/test_gpu_gemm_small.py)."""
+    import torch
+    import paper_2410_03065_amd as cake
+    shape = si.SHAPES["llama3-8b-shape"].with_(n_layers=2, vocab=2048)
+    toks = si.make_tokens(1200, shape.vocab, seed=11)
+    eng = cake.Engine(shape, None, max_tokens=1280, max_chunk=128, page_tokens=256, seed=5)
+    whole = _prefill_in_steps(eng, toks, [128])
+    for steps in ([37], [101, 7, 64]):
+        assert torch.equal(_prefill_in_steps(eng, toks, steps), whole), steps
+    del eng
+    eng = cake.Engine(shape, None, max_tokens=1280, max_chunk=1024, page_tokens=256, seed=5)
+    for steps in ([1024], [512], [137, 700], [1000, 8]):
+        other = _prefill_in_steps(eng, toks, steps)
+        err = float((other.float() - whole.float()).abs().max() / whole.float().abs().max())
+        print("steps %s: largest difference %.2e of the largest value" % (steps, err))
+        assert err < 2e-2, (steps, err)
