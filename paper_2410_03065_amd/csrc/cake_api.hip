@@ -55,6 +55,8 @@ struct cake_ctx {
     int attn_range_keys = 0;   // length of the attention launches' key ranges, 0: chosen per launch (see AttnWs)
     void* q_stage = nullptr;   // device staging for quantised page images: a ring of image slots (cake_create)
     size_t q_stage_bytes = 0;
+    void* w_stage = nullptr;   // one image of a store being written while loads use q_stage (null until that happens)
+    size_t w_stage_bytes = 0;
     // second hop of a file-backed store: two pinned buffers of one DMA piece each
     void* f_stage[2] = {nullptr, nullptr};
     size_t f_stage_bytes = 0;
@@ -636,7 +638,7 @@ int32_t cake_destroy(cake_ctx* c) {
     (void)hipFree(c->ao); (void)hipFree(c->act); (void)hipFree(c->rope_cs); (void)hipFree(c->d_ids);
     (void)hipFree(c->t_cs); (void)hipFree(c->t_argmax); (void)hipFree(c->t_qr); (void)hipFree(c->t_ao);
     (void)hipFree(c->t_act); (void)hipFree(c->t_logits); (void)hipFree(c->t_part); (void)hipFree(c->t_tok);
-    (void)hipFree(c->q_stage); (void)hipFree(c->split.part); (void)hipFree(c->split.counters);
+    (void)hipFree(c->q_stage); (void)hipFree(c->w_stage); (void)hipFree(c->split.part); (void)hipFree(c->split.counters);
     if (c->t_host) (void)hipHostFree(c->t_host);
     for (int i = 0; i < 2; ++i)
         if (c->f_stage[i]) (void)hipHostFree(c->f_stage[i]);
@@ -865,22 +867,34 @@ int32_t cake_write_store(cake_ctx* c, const cake_kv* kv, int32_t n_tokens, const
     const uint64_t layer_bytes = uint64_t(2) * c->m.n_kv_heads * pt * c->m.head_dim * esize(c);
     const int bits = store_code_bits(dst->format);
     if (bits) {
+        if (c->q_stage_bytes < image) c->load_thread.wait();   // queued loads use the buffer that growing frees
         rc = ensure_stage(c, image);
         if (rc != CAKE_OK) return rc;
-    }
-    if (bits) {
+        char* stage = (char*)c->q_stage;
+        int per = int(std::min<uint64_t>(uint64_t(n_pages), c->q_stage_bytes / image));
+        if (!c->load_thread.idle() || hipStreamQuery(c->ls) != hipSuccess) {
+            // a load that was queued before may still go through the ring of slots: one image at a time beside it
+            (void)hipGetLastError();   // "not ready" is no error
+            if (c->w_stage_bytes < image) {
+                (void)hipFree(c->w_stage);
+                c->w_stage = nullptr; c->w_stage_bytes = 0;
+                if (hipMalloc(&c->w_stage, image) != hipSuccess) { (void)hipGetLastError(); return fail(c, CAKE_E_NOMEM, "staging buffer of %llu bytes", (unsigned long long)image); }
+                c->w_stage_bytes = image;
+            }
+            stage = (char*)c->w_stage;
+            per = 1;
+        }
         // as many images at a time as the staging buffer holds: quantise, copy out, next; one stream keeps them in order
-        const int per = int(std::min<uint64_t>(uint64_t(n_pages), c->q_stage_bytes / image));
         for (int p = 0; p < n_pages; p += per) {
             const int n = std::min(per, n_pages - p);
             char* out = (char*)dst->base + uint64_t(p) * dst->page_stride_bytes;
-            HIP_TRY(c, launch_quant_pages(c->m.dtype, c->q_stage, image, make_view(c, kv, 0), kv->block_table_host, p, n, c->m.n_layers, bits, c->cs));
+            HIP_TRY(c, launch_quant_pages(c->m.dtype, stage, image, make_view(c, kv, 0), kv->block_table_host, p, n, c->m.n_layers, bits, c->cs));
             if (dst->page_stride_bytes == image) {
-                HIP_TRY(c, hipMemcpyAsync(out, c->q_stage, uint64_t(n) * image, hipMemcpyDeviceToHost, c->cs));
+                HIP_TRY(c, hipMemcpyAsync(out, stage, uint64_t(n) * image, hipMemcpyDeviceToHost, c->cs));
                 continue;
             }
             for (int k = 0; k < n; ++k)
-                HIP_TRY(c, hipMemcpyAsync(out + uint64_t(k) * dst->page_stride_bytes, (char*)c->q_stage + uint64_t(k) * image, image,
+                HIP_TRY(c, hipMemcpyAsync(out + uint64_t(k) * dst->page_stride_bytes, stage + uint64_t(k) * image, image,
                                           hipMemcpyDeviceToHost, c->cs));
         }
     } else {

@@ -73,6 +73,11 @@ public:
         std::unique_lock<std::mutex> lk(mu_);
         cv_.wait(lk, [&] { return !busy_ && jobs_.empty(); });
     }
+    // has every job handed over so far finished?
+    bool idle() {
+        std::lock_guard<std::mutex> lk(mu_);
+        return !busy_ && jobs_.empty();
+    }
     void stop() {
         if (!th_.joinable()) return;
         {

@@ -50,3 +50,48 @@ def test_quantised_store_with_a_larger_stride():
     assert eng.lib.cake_write_store(eng.ctx, ctypes.byref(eng.kv), 512, ctypes.byref(st)) == 0
     np.testing.assert_array_equal(wide.numpy()[:, :dense.shape[1]], dense)
     assert not wide.numpy()[:, dense.shape[1]:].any()
+
+
+@pytest.mark.parametrize("bits", [8, 4])
+def test_write_store_beside_a_queued_load(bits):
+    """Quantised pages are loaded through the context's staging slots while another sequence's pages are written to a
+    store from the same context: both come out as each does alone."""
+    import ctypes
+    import time
+    import torch
+    import paper_2410_03065_amd as cake
+    fmt = cake.STORE_INT8 if bits == 8 else cake.STORE_INT4
+    shape = si.ModelShape("store-beside", 2, 256, 4, 2, 128, 256, 64, "bf16")
+    pt, n = 64, 24
+    eng = cake.Engine(shape, None, max_tokens=n * pt, max_chunk=4 * pt, page_tokens=pt)      # four 8-bit slots
+    g = torch.Generator(device="cuda").manual_seed(5)
+    eng.pool.normal_(generator=g)
+    other = torch.empty_like(eng.pool).normal_(generator=g)
+    torch.cuda.synchronize()
+    eng.write_store(n * pt, fmt)                                   # the store that is loaded
+    eng.clear_pool()
+    eng.load_chunk(0, n * pt)
+    loaded = eng.pool.clone()
+    kv = cake.Kv(other.data_ptr(), eng.block_table_host.ctypes.data, eng.block_table_dev.data_ptr(), pt, n, n)
+    image = eng.store_tensor.shape[1]
+
+    def write(into):
+        st = cake.KvStore(into.data_ptr(), image, pt, n, fmt, cake.STORE_PINNED, -1, 0, 0)
+        assert eng.lib.cake_write_store(eng.ctx, ctypes.byref(kv), n * pt, ctypes.byref(st)) == 0
+    alone = torch.zeros((n, image), dtype=torch.uint8, pin_memory=True)
+    write(alone)
+    eng.clear_pool()
+    beside = torch.zeros((n, image), dtype=torch.uint8, pin_memory=True)
+    gbps = n * image / 0.1 / 1e9                                   # the load takes 0.1 s
+    t0 = time.monotonic()
+    eng.load_chunk(0, n * pt, gbps=gbps, sync=False)
+    writes = 0
+    while time.monotonic() - t0 < 0.08:
+        beside.zero_()
+        write(beside)
+        assert torch.equal(beside, alone)
+        writes += 1
+    assert writes > 1                                              # they did not wait for the load
+    eng._check(eng.lib.cake_sync_load(eng.ctx), "cake_sync_load")
+    torch.cuda.synchronize()
+    assert torch.equal(eng.pool, loaded)
