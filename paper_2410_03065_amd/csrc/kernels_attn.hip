@@ -23,6 +23,13 @@ __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
+// v_mfma_f32_16x16x32_bf16, D[16x16] += A[16x32] * B[32x16]: lane l supplies A[l%16][8*(l/16) .. +7] and
+// B[8*(l/16) .. +7][l%16], and holds D[4*(l/16) + v][l%16] in accumulator register v (0..3).
+__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
 #define CAKE_GLOBAL_AS __attribute__((address_space(1)))
 #define CAKE_LDS_AS __attribute__((address_space(3)))
 
@@ -350,6 +357,16 @@ attention_mfma_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, in
 // the two partial results are merged through LDS at the end (softmax over a union of key sets:
 // rescale both to the common reference and add).
 //
+// The products are 16x16x32 MFMAs (two columns of 16 queries per wave): per FLOP they move a quarter of the accumulators
+// of 32x32x16 ones, and this kernel runs at the power limit (1024 rows at 31744 keys, 32 heads on 8: 4.5 % less time).
+// The two halves run half a step apart, a barrier between the phases of a step keeping them there: a SIMD then holds one
+// wave whose scores are being formed beside the exponentials (vector work above the MFMAs') and one that only adds P V up,
+// at lower priority.  Together they overlap, where two waves in the same phase first compete for the vector unit and then
+// leave it idle (6 % more; with 32x32x16 MFMAs it gained nothing).  The maximum that is only compared with the reference
+// is taken on integers (2 %).  494 -> 439 us for that launch, 1.23 PFLOP/s; 1024 rows at 15360 250 -> 222; 509 rows of
+// 32 KV heads at 7003 78 -> 72.  What bounds it now: one LDS read per two MFMAs, 3.5 vector instructions per two, one of
+// them an exponential; a loop of just these on two waves per SIMD sustains 1.34 PFLOP/s.
+//
 // LDS: K ring of 2 x (two 16 KB tiles) and V^T ring of 2 x (two 16 KB tiles).  K of a tile pair
 // is consumed one iteration before its V^T, so per iteration the V^T of pair i+1 and the K of
 // pair i+2 are fetched, each into the buffer its group finished with in the previous iteration.
@@ -376,13 +393,13 @@ attention_mfma8_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, f
                        int rows, KvView kv, int pairs_per_split, bool side_by_side) {
     constexpr int AQW = 32 * QW;        // queries per workgroup
     constexpr int PER = 16 / QW;        // wave-loads per wave per K (or V^T) tile
-    constexpr int KP = QW >= 4 ? 1 : 4 / QW;   // period after which the K swizzle term of a wave's loads repeats,
-    constexpr int VP = QW >= 2 ? 1 : 2;        // and the V^T term
+    constexpr int KN = QW == 4 ? 2 : 4, KE = QW == 1 ? 2 : 1;   // the K swizzle term of a wave's loads has KN values in turn, KE loads each
+    constexpr int VP = QW >= 2 ? 1 : 2;                         // period after which the V^T term repeats
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave8 = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wave = wave8 % QW, grp = wave8 / QW;
-    const int lrow = lane & 31, lhalf = lane >> 5;
+    const int l16 = lane & 15, lq = lane >> 4;
     const int G = kv.n_kv, r = n_q / G;
     int g, q0;
     if ((G & 7) == 0) {
@@ -399,46 +416,62 @@ attention_mfma8_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, f
     const int rr = side_by_side ? r : 1, n_queries = rows * rr;
     const int head0 = side_by_side ? g * r : g * r + (q0 / AQW) % r;
     if (!side_by_side) q0 = (q0 / AQW) / r * AQW;
-    const int my_query = min(q0 + wave * 32 + lrow, n_queries - 1);
-    const int my_row = my_query / rr, h = head0 + (my_query - my_row * rr);
-    const int my_pos = tok_begin + my_row;
+    // this lane's two queries, one in each tile of 16 columns
+    int my_row[2], h[2], my_pos[2];
+    bool is_query[2];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        const int x = q0 + wave * 32 + 16 * c + l16, my_query = min(x, n_queries - 1);
+        is_query[c] = x < n_queries;
+        my_row[c] = my_query / rr;
+        h[c] = head0 + (my_query - my_row[c] * rr);
+        my_pos[c] = tok_begin + my_row[c];
+    }
     const int wave_first_pos = tok_begin + min(q0 + wave * 32, n_queries - 1) / rr;
     const int wg_last_pos = tok_begin + (min(q0 + AQW, n_queries) - 1) / rr;
     const int n_tiles = wg_last_pos / AK + 1;
     const int pair_lo = SPLIT ? blockIdx.y * pairs_per_split : 0;
     const int n_pairs = SPLIT ? min(pair_lo + pairs_per_split, (n_tiles + 1) >> 1) : (n_tiles + 1) >> 1;
-    const bool is_query = q0 + wave * 32 + lrow < n_queries;
-    float* my_part = SPLIT ? part + ((size_t(blockIdx.y) * n_q + h) * rows + my_row) * (AHD + 2) : nullptr;
+    auto my_part = [&](int c) { return part + ((size_t(blockIdx.y) * n_q + h[c]) * rows + my_row[c]) * (AHD + 2); };
     if (SPLIT && pair_lo >= n_pairs) {   // a range wholly above this workgroup's diagonal
-        if (grp == 0 && is_query) {
-            for (int d = lhalf * (AHD / 2); d < (lhalf + 1) * (AHD / 2); d += 2) *(float2*)(my_part + d) = make_float2(0.f, 0.f);
-            if (lhalf == 0) *(float2*)(my_part + AHD) = make_float2(-FLT_MAX, 0.f);
-        }
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+            if (grp == 0 && is_query[c]) {
+                float* p = my_part(c);
+                for (int d = lq * (AHD / 4); d < (lq + 1) * (AHD / 4); d += 2) *(float2*)(p + d) = make_float2(0.f, 0.f);
+                if (lq == 0) *(float2*)(p + AHD) = make_float2(-FLT_MAX, 0.f);
+            }
         return;
     }
     const int first_masked = (wave_first_pos + 1) / AK;   // first tile with a key some query of this wave must not see
 
-    bf16x8 qreg[AHD / 16];
-    {
-        const bf16_t* qp = q + (size_t(h) * rows + my_row) * AHD + 8 * lhalf;
+    bf16x8 qreg[2][AHD / 32];
 #pragma unroll
-        for (int ks = 0; ks < AHD / 16; ++ks) qreg[ks] = *(const bf16x8*)(qp + 16 * ks);
-        // softmax scale and log2(e) go into Q once, so a score leaves the MFMA in the exponent's units
+    for (int c = 0; c < 2; ++c) {
+        const bf16_t* qp = q + (size_t(h[c]) * rows + my_row[c]) * AHD + 8 * lq;
+#pragma unroll
+        for (int ks = 0; ks < AHD / 32; ++ks) qreg[c][ks] = *(const bf16x8*)(qp + 32 * ks);
+    }
+    {   // softmax scale and log2(e) go into Q once, so a score leaves the MFMA in the exponent's units
         const float sl2q = 0.08838834764831845f * 1.4426950408889634f;
 #pragma unroll
-        for (int ks = 0; ks < AHD / 16; ++ks)
+        for (int c = 0; c < 2; ++c)
 #pragma unroll
-            for (int e = 0; e < 8; ++e) qreg[ks][e] = bf16_t(float(qreg[ks][e]) * sl2q);
+            for (int ks = 0; ks < AHD / 32; ++ks)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) qreg[c][ks][e] = bf16_t(float(qreg[c][ks][e]) * sl2q);
     }
     // lane offsets of this wave's K / V^T wave-loads of a tile: load i covers 1 KB = key rows
-    // 4j .. 4j+3 (V^T: head-dim rows 8j .. 8j+7) with j = wave + QW*i.  The swizzle term of the K
-    // rows repeats every KP loads, that of the V^T rows every VP loads, so the other loads are a
-    // wave-uniform distance from these.
-    unsigned koffp[KP], voffp[VP];
+    // 4j .. 4j+3 (V^T: head-dim rows 8j .. 8j+7) with j = wave + QW*i.  Chunk c of key row x is stored at
+    // c ^ kswz(x), so that the sixteen rows a quarter-wave reads (x = 8 q + v, plus a constant) lie in sixteen
+    // different chunks; of V^T row x at c ^ ((x >> 1) & 7).  Loads with the
+    // same swizzle term are a wave-uniform distance apart.
+    auto kswz = [](int x) { return (x & 3) | (x >> 1 & 12); };
+    unsigned koffp[KN], voffp[VP];
 #pragma unroll
-    for (int i = 0; i < KP; ++i) {
-        int krow = 4 * (wave + QW * i) + (lane >> 4), kpos = lane & 15;
-        koffp[i] = unsigned(krow * AHD + ((kpos ^ (krow & 15)) << 3)) * 2u;
+    for (int i = 0; i < KN; ++i) {
+        int krow = 4 * (wave + QW * KE * i) + (lane >> 4), kpos = lane & 15;
+        koffp[i] = unsigned(krow * AHD + ((kpos ^ kswz(krow)) << 3)) * 2u;
     }
 #pragma unroll
     for (int i = 0; i < VP; ++i) {
@@ -470,7 +503,7 @@ attention_mfma8_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, f
         unsigned char* sa = lds + (pair & 1) * A8_RING + grp * A_KBYTES;
 #pragma unroll
         for (int i = 0; i < PER; ++i)
-            __builtin_amdgcn_global_load_lds((const CAKE_GLOBAL_AS void*)(kp + size_t(i / KP) * (4 * QW * KP * AHD * 2) + koffp[i % KP]),
+            __builtin_amdgcn_global_load_lds((const CAKE_GLOBAL_AS void*)(kp + size_t(i - i / KE % KN * KE) * (4 * QW * AHD * 2) + koffp[i / KE % KN]),
                                              (CAKE_LDS_AS void*)(sa + (wave + QW * i) * 1024), 16, 0, 0);
     };
     auto issue_v = [&](int pair) {
@@ -483,92 +516,110 @@ attention_mfma8_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, f
                                              (CAKE_LDS_AS void*)(sa + (wave + QW * i) * 1024), 16, 0, 0);
     };
 
-    const int sk = sigma16(lrow & 15);
-    const int krow_base = (16 * (lrow >> 4) + sk) * (AHD * 2);
-    int kaddr[AHD / 16];
+    // Score tiles t = 2 j and 2 j + 1 (16 keys each) hold the keys 32 j + 8 q + v and 32 j + 8 q + 4 + v at their rows
+    // 4 q + v, so that a lane's eight scores of the two are the eight consecutive keys 32 j + 8 lq .. + 7, which is what it
+    // has to supply to the second product's k-step j.
+    const int krow0 = 8 * (l16 >> 2) + (l16 & 3), sk = kswz(krow0);   // + 32 j + 4 (t & 1) changes no term of kswz
+    int kaddr[AHD / 32], vaddr[2];
 #pragma unroll
-    for (int ks = 0; ks < AHD / 16; ++ks) kaddr[ks] = grp * A_KBYTES + krow_base + (((2 * ks + lhalf) ^ sk) << 4);
-    const int sv = (lrow >> 1) & 7;
-    int vaddr[4];
+    for (int ks = 0; ks < AHD / 32; ++ks) kaddr[ks] = grp * A_KBYTES + krow0 * (AHD * 2) + (((4 * ks + lq) ^ sk) << 4);
+    const int sv = (l16 >> 1) & 7;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) vaddr[j] = A8_VBASE + grp * A_KBYTES + lrow * (AK * 2) + (((2 * j + lhalf) ^ sv) << 4);
+    for (int j = 0; j < 2; ++j) vaddr[j] = A8_VBASE + grp * A_KBYTES + l16 * (AK * 2) + (((4 * j + lq) ^ sv) << 4);
 
-    f32x16 o[4];
+    const f32x4 zero4 = {0, 0, 0, 0};
+    f32x4 o[8][2];
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
+    for (int t = 0; t < 8; ++t)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) o[t][v] = 0.f;
+        for (int c = 0; c < 2; ++c) o[t][c] = zero4;
     // The running reference m_run of a query (log2 units) is SUBTRACTED INSIDE THE MFMA: the score
     // accumulators start from negm = -m_run instead of zero, so a finished score is already
     // s - m_run and the exponential needs no multiply-add of its own.  When the reference moves
     // (rarely, see RESCALE_LOG2) the scores formed against the old one are shifted by hand.
-    float m_run = 0.f, l_part = 0.f;
-    const f32x16 zero16 = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-    f32x16 negm = zero16;
-    float corr_cur = 1.f, delta_cur = 0.f;
-    bool moved_cur = false;
+    float m_run[2] = {0.f, 0.f}, l_part[2] = {0.f, 0.f};
+    f32x4 negm[2] = {zero4, zero4};
+    float raw_cur = 0.f;
     constexpr float RESCALE_LOG2 = 6.0f;
-    auto mask_tile = [&](f32x16* s, int tile, int last_visible) {
-        const int key0 = tile * AK;
+    auto mask_tile = [&](f32x4 (*s)[2], int tile, const int* last_visible) {
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
+        for (int c = 0; c < 2; ++c) {
+            const int limit = last_visible[c] - (tile * AK + 8 * lq);
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                int key = key0 + 32 * t + (v & 7) + 8 * lhalf + 16 * (v >> 3);
-                if (key > last_visible) s[t][v] = -INFINITY;
-            }
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (32 * (t >> 1) + 4 * (t & 1) + v > limit) s[t][c][v] = -INFINITY;
+        }
     };
-    auto part_max = [&](const f32x16* s, int part, float acc) {
+    auto part_max = [&](f32x4 (*s)[2], int c, int t, float acc) {   // tiles t and t + 1
 #pragma unroll
-        for (int i = 0; i < 8; ++i) acc = fmaxf(acc, s[part >> 1][8 * (part & 1) + i]);
+        for (int e = 0; e < 8; ++e) acc = fmaxf(acc, s[t + (e >> 2)][c][e & 3]);
         return acc;
     };
-    // raw: this lane's largest score of the next tile, already relative to m_run
-    auto finish_max = [&](float raw) {
-        raw = fmaxf(raw, __shfl_xor(raw, 32, 64));
-        moved_cur = raw > RESCALE_LOG2;
-        if (__builtin_amdgcn_ballot_w64(moved_cur) != 0) {
-            delta_cur = moved_cur ? raw : 0.f;      // of this query alone: a row's bits do not depend on the rows beside it
-            corr_cur = __builtin_amdgcn_exp2f(-delta_cur);
-            m_run += delta_cur;
-            moved_cur = true;
-        } else {
-            delta_cur = 0.f;
-            corr_cur = 1.0f;
-        }
+    // raw[c]: this lane's largest score of query c -> the query's, of column tile 0 in lanes 0 .. 31 and of 1 in the others
+    auto row_max = [&](const float* raw) {
+        const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(raw[0]), __float_as_uint(raw[1]), false, false);
+        const float y = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+        const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(y), __float_as_uint(y), false, false);
+        return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+    };
+    // The same for the test against RESCALE_LOG2, on the bit patterns as integers: of values of which one is positive the
+    // largest is found (where none is, some negative one), without the canonicalising that fmaxf costs.
+    auto part_top = [&](f32x4 (*s)[2], int c, int t, int acc) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc = max(acc, __float_as_int(s[t + (e >> 2)][c][e & 3]));
+        return acc;
+    };
+    auto row_top = [&](const int* raw) {
+        const auto a = __builtin_amdgcn_permlane32_swap(raw[0], raw[1], false, false);
+        const int y = max(int(a[0]), int(a[1]));
+        const auto b = __builtin_amdgcn_permlane16_swap(y, y, false, false);
+        return __int_as_float(max(int(b[0]), int(b[1])));
+    };
+    auto spread = [&](float y, float* of) {   // that value back to all lanes of its column
+        const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false, false);
+        of[0] = __uint_as_float(a[0]);
+        of[1] = __uint_as_float(a[1]);
     };
 
     // iteration i: this group's tile 2i+grp is in K slot i&1 (scores already formed) and V slot i&1
-    auto step = [&](int i, f32x16* s_cur, f32x16* s_nxt) {
+    auto step = [&](int i, f32x4 (*s_cur)[2], f32x4 (*s_nxt)[2]) {
         asm volatile("s_waitcnt vmcnt(0)");
         __builtin_amdgcn_s_barrier();
         if (i + 1 < n_pairs) issue_v(i + 1);
         if (i + 2 < n_pairs) issue_k(i + 2);
         const unsigned char* stk = lds + ((i + 1) & 1) * A8_RING;   // past the last pair: stale, result unused
         const unsigned char* stv = lds + (i & 1) * A8_RING;
-        bf16x8 opa[4], opb[4], p[4];
-        auto read_k = [&](bf16x8* dst, int grpk) {
+        bf16x8 opa[4], opb[4], p[4];   // p[2 j + c]
+        auto read_k = [&](bf16x8* dst, int ks) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                dst[t] = *(const bf16x8*)(stk + (32 * (t >> 1) + 4 * (t & 1)) * (AHD * 2) + kaddr[ks]);
+        };
+        auto read_v = [&](bf16x8* dst, int u) {   // k-step u >> 1, head-dim tiles 4 (u & 1) .. + 3
+#pragma unroll
+            for (int e = 0; e < 4; ++e) dst[e] = *(const bf16x8*)(stv + (4 * (u & 1) + e) * 16 * (AK * 2) + vaddr[u >> 1]);
+        };
+        auto mma_k = [&](const bf16x8* src, int ks) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int c = 0; c < 2; ++c) s_nxt[t][c] = mfma16(src[t], qreg[c][ks], ks == 0 ? negm[c] : s_nxt[t][c]);
+        };
+        auto mma_v = [&](const bf16x8* src, int u) {
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                dst[e] = *(const bf16x8*)(stk + (e & 1) * 32 * (AHD * 2) + kaddr[2 * grpk + (e >> 1)]);
-        };
-        auto read_v = [&](bf16x8* dst, int j) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) dst[e] = *(const bf16x8*)(stv + e * 32 * (AK * 2) + vaddr[j]);
+                for (int c = 0; c < 2; ++c) o[4 * (u & 1) + e][c] = mfma16(src[e], p[2 * (u >> 1) + c], o[4 * (u & 1) + e][c]);
         };
-        auto mma_k = [&](const bf16x8* src, int grpk) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int ks = 2 * grpk + (e >> 1), t = e & 1;
-                s_nxt[t] = mfma32(src[e], qreg[ks], ks == 0 ? negm : s_nxt[t]);
-            }
-        };
-        auto expo = [&](int grpe) {
+        auto expo = [&](int u) {
+            const int j = u >> 1, c = u & 1;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                float x = __builtin_amdgcn_exp2f(s_cur[grpe >> 1][8 * (grpe & 1) + e]);
-                l_part += x;
-                p[grpe][e] = bf16_t(x);
+                float x = __builtin_amdgcn_exp2f(s_cur[2 * j + (e >> 2)][c][e & 3]);
+                l_part[c] += x;
+                p[u][e] = bf16_t(x);
             }
         };
         read_k(opa, 0);
@@ -579,49 +630,58 @@ attention_mfma8_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, f
         __builtin_amdgcn_sched_barrier(0);
         read_k(opb, 3); mma_k(opa, 2); expo(2);
         __builtin_amdgcn_sched_barrier(0);
-        read_v(opa, 0); mma_k(opb, 3); expo(3);
+        read_v(opa, 0); mma_k(opb, 3);
         // the probabilities are only consumed after the branch below; pin them here, or the compiler
         // sinks the exponentials out of the block whose MFMAs they are meant to overlap with
 #pragma unroll
-        for (int e = 0; e < 4; ++e) asm volatile("" ::"v"(p[e]));
-        asm volatile("" ::"v"(l_part));
+        for (int e = 0; e < 3; ++e) asm volatile("" ::"v"(p[e]));
+        asm volatile("" ::"v"(l_part[0]), "v"(l_part[1]));
         __builtin_amdgcn_sched_barrier(0);
+        if constexpr (QW == 4) {   // the other half's step begins
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_s_setprio(0);
+        }
         const int next_tile = 2 * (i + 1) + grp;
         // blanks tiles past the end, and what was formed from a stale slot after the range's last pair
-        if (next_tile >= first_masked || (SPLIT && i + 1 >= n_pairs)) mask_tile(s_nxt, next_tile, !SPLIT || i + 1 < n_pairs ? my_pos : -1);
-        float raw;
+        if (next_tile >= first_masked || (SPLIT && i + 1 >= n_pairs)) {
+            const bool real = !SPLIT || i + 1 < n_pairs;
+            const int last_visible[2] = {real ? my_pos[0] : -1, real ? my_pos[1] : -1};
+            mask_tile(s_nxt, next_tile, last_visible);
+        }
+        int raw[2];
         read_v(opb, 1);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) o[t] = mfma32(opa[t], p[0], o[t]);
-        raw = part_max(s_nxt, 0, s_nxt[0][0]);
-        raw = part_max(s_nxt, 1, raw);
+        mma_v(opa, 0);
+        expo(3);
+        raw[0] = part_top(s_nxt, 0, 0, __float_as_int(s_nxt[0][0][0]));
+        raw[0] = part_top(s_nxt, 0, 2, raw[0]);
         __builtin_amdgcn_sched_barrier(0);
         read_v(opa, 2);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) o[t] = mfma32(opb[t], p[1], o[t]);
-        raw = part_max(s_nxt, 2, raw);
-        raw = part_max(s_nxt, 3, raw);
+        mma_v(opb, 1);
+        raw[1] = part_top(s_nxt, 1, 0, __float_as_int(s_nxt[0][1][0]));
+        raw[1] = part_top(s_nxt, 1, 2, raw[1]);
         __builtin_amdgcn_sched_barrier(0);
         read_v(opb, 3);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) o[t] = mfma32(opa[t], p[2], o[t]);
-        finish_max(raw);
+        mma_v(opa, 2);
+        raw_cur = row_top(raw);
         __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) o[t] = mfma32(opb[t], p[3], o[t]);
+        mma_v(opb, 3);
         __builtin_amdgcn_sched_barrier(0);
-        if (__builtin_amdgcn_ballot_w64(moved_cur) != 0) {
-            l_part *= corr_cur;
+        if constexpr (QW == 4) __builtin_amdgcn_s_setprio(1);
+        if (__builtin_amdgcn_ballot_w64(raw_cur > RESCALE_LOG2) != 0) {
+            float delta[2];
+            spread(raw_cur, delta);
 #pragma unroll
-            for (int t = 0; t < 4; ++t)
+            for (int c = 0; c < 2; ++c) {
+                delta[c] = delta[c] > RESCALE_LOG2 ? delta[c] : 0.f;   // of this query alone: a row's bits do not depend on the rows beside it
+                const float corr = __builtin_amdgcn_exp2f(-delta[c]);
+                m_run[c] += delta[c];
+                l_part[c] *= corr;
 #pragma unroll
-                for (int v = 0; v < 16; ++v) o[t][v] *= corr_cur;
+                for (int t = 0; t < 8; ++t) o[t][c] *= f32x4{corr, corr, corr, corr};
 #pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) s_nxt[t][v] -= delta_cur;   // formed against the old reference
-#pragma unroll
-            for (int v = 0; v < 16; ++v) negm[v] = -m_run;
+                for (int t = 0; t < 4; ++t) s_nxt[t][c] -= f32x4{delta[c], delta[c], delta[c], delta[c]};   // formed against the old reference
+                negm[c] = f32x4{-m_run[c], -m_run[c], -m_run[c], -m_run[c]};
+            }
         }
     };
 
@@ -635,84 +695,97 @@ attention_mfma8_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, f
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER));
     }
     __builtin_amdgcn_s_barrier();
-    f32x16 s_a[2], s_b[2];
+    f32x4 s_a[4][2], s_b[4][2];
     {
         const unsigned char* stk = lds + (pair_lo & 1) * A8_RING;
 #pragma unroll
-        for (int ks = 0; ks < AHD / 16; ++ks)
+        for (int ks = 0; ks < AHD / 32; ++ks)
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                bf16x8 a = *(const bf16x8*)(stk + t * 32 * (AHD * 2) + kaddr[ks]);
-                s_a[t] = mfma32(a, qreg[ks], ks == 0 ? zero16 : s_a[t]);
+            for (int t = 0; t < 4; ++t) {
+                const bf16x8 a = *(const bf16x8*)(stk + (32 * (t >> 1) + 4 * (t & 1)) * (AHD * 2) + kaddr[ks]);
+#pragma unroll
+                for (int c = 0; c < 2; ++c) s_a[t][c] = mfma16(a, qreg[c][ks], ks == 0 ? zero4 : s_a[t][c]);
             }
     }
     if (2 * pair_lo + grp >= first_masked) mask_tile(s_a, 2 * pair_lo + grp, my_pos);
     {
         // the first tile fixes the reference exactly; a row that sees none of its keys (possible for
         // the second wave half only) keeps reference 0 and contributes nothing
-        float raw = s_a[0][0];
+        float raw[2], top[2];
 #pragma unroll
-        for (int part = 0; part < 4; ++part) raw = part_max(s_a, part, raw);
-        raw = fmaxf(raw, __shfl_xor(raw, 32, 64));
-        m_run = raw > -INFINITY ? raw : 0.f;
+        for (int c = 0; c < 2; ++c) raw[c] = part_max(s_a, c, 2, part_max(s_a, c, 0, s_a[0][c][0]));
+        spread(row_max(raw), top);
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) s_a[t][v] -= m_run;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) negm[v] = -m_run;
-    }
-    for (int i = pair_lo; i < n_pairs; i += 2) {
-        step(i, s_a, s_b);
-        if (i + 1 < n_pairs) step(i + 1, s_b, s_a);
-    }
-
-    // merge the two key halves: group B parks (O, l, reference) in LDS, group A combines and stores
-    __syncthreads();
-    float* park = (float*)lds + size_t(wave) * 66 * 64 + lane;
-    if (grp == 1) {
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) park[(16 * t + v) * 64] = o[t][v];
-        park[64 * 64] = l_part;
-        park[65 * 64] = m_run;
-    }
-    __syncthreads();
-    if (grp == 0) {
-        const float l_b = park[64 * 64];
-        const float l_b_row = l_b + park[64 * 64 + ((lane ^ 32) - lane)];   // both half-waves of the row
-        const float m_b = l_b_row > 0.f ? park[65 * 64] : -1.0e30f;         // a half that saw no key has no reference
-        const float m = fmaxf(m_run, m_b);
-        const float ca = __builtin_amdgcn_exp2f(m_run - m), cb = __builtin_amdgcn_exp2f(m_b - m);
-        // (sums written as fmaf, so that both instantiations round them alike)
-        float l_mine = __builtin_fmaf(l_part, ca, l_b * cb);
-        auto merged = [&](int t, int v) { return __builtin_fmaf(o[t][v], ca, park[(16 * t + v) * 64] * cb); };
-        const float l_tot = l_mine + __shfl_xor(l_mine, 32, 64);
-        if constexpr (SPLIT) {
-            if (is_query) {
-#pragma unroll
-                for (int t = 0; t < 4; ++t)
-#pragma unroll
-                    for (int v = 0; v < 16; v += 2)
-                        *(float2*)(my_part + t * 32 + 8 * (v >> 2) + 4 * lhalf + (v & 3)) =
-                            make_float2(merged(t, v), merged(t, v + 1));
-                if (lhalf == 0) *(float2*)(my_part + AHD) = make_float2(l_tot > 0.f ? m * 0.6931471805599453f : -FLT_MAX, l_tot);
-            }
-            return;
-        }
-        const float inv = 1.0f / l_tot;
-        if (is_query) {
-            bf16_t* op = out + size_t(my_row) * n_q * AHD + h * AHD;
+        for (int c = 0; c < 2; ++c) {
+            m_run[c] = top[c] > -INFINITY ? top[c] : 0.f;
 #pragma unroll
             for (int t = 0; t < 4; ++t)
 #pragma unroll
-                for (int v4 = 0; v4 < 4; ++v4) {
+                for (int v = 0; v < 4; ++v) s_a[t][c][v] -= m_run[c];
+            negm[c] = f32x4{-m_run[c], -m_run[c], -m_run[c], -m_run[c]};
+        }
+    }
+    if (QW == 4 && grp == 1) __builtin_amdgcn_s_barrier();   // half a step behind; the first half makes up for it at the end
+    int pair = pair_lo;
+    for (; pair + 1 < n_pairs; pair += 2) {   // two to a trip, so that the score buffers alternate without copies
+        step(pair, s_a, s_b);
+        step(pair + 1, s_b, s_a);
+    }
+    if (pair < n_pairs) step(pair, s_a, s_b);
+    if (QW == 4 && grp == 0) __builtin_amdgcn_s_barrier();
+
+    // merge the two key halves: group B parks (O, l, reference) in LDS, group A combines and stores
+    __syncthreads();
+    float* park = (float*)lds + size_t(wave) * 68 * 64 + lane;
+    float l_row[2];   // of the whole row, all of its lanes
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        l_row[c] = l_part[c] + __shfl_xor(l_part[c], 32, 64);
+        l_row[c] += __shfl_xor(l_row[c], 16, 64);
+    }
+    if (grp == 1) {
+#pragma unroll
+        for (int t = 0; t < 8; ++t)
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) park[(8 * t + 4 * c + v) * 64] = o[t][c][v];
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            park[(64 + c) * 64] = l_row[c];
+            park[(66 + c) * 64] = m_run[c];
+        }
+    }
+    __syncthreads();
+    if (grp == 0) {
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const float l_b = park[(64 + c) * 64];
+            const float m_b = l_b > 0.f ? park[(66 + c) * 64] : -1.0e30f;         // a half that saw no key has no reference
+            const float m = fmaxf(m_run[c], m_b);
+            const float ca = __builtin_amdgcn_exp2f(m_run[c] - m), cb = __builtin_amdgcn_exp2f(m_b - m);
+            // (sums written as fmaf, so that both instantiations round them alike)
+            const float l_tot = __builtin_fmaf(l_row[c], ca, l_b * cb);
+            auto merged = [&](int t, int v) { return __builtin_fmaf(o[t][c][v], ca, park[(8 * t + 4 * c + v) * 64] * cb); };
+            if (!is_query[c]) continue;
+            if constexpr (SPLIT) {
+                float* p = my_part(c);
+#pragma unroll
+                for (int t = 0; t < 8; ++t)
+#pragma unroll
+                    for (int v = 0; v < 4; v += 2) *(float2*)(p + t * 16 + 4 * lq + v) = make_float2(merged(t, v), merged(t, v + 1));
+                if (lq == 0) *(float2*)(p + AHD) = make_float2(l_tot > 0.f ? m * 0.6931471805599453f : -FLT_MAX, l_tot);
+            } else {
+                const float inv = 1.0f / l_tot;
+                bf16_t* op = out + size_t(my_row[c]) * n_q * AHD + h[c] * AHD;
+#pragma unroll
+                for (int t = 0; t < 8; ++t) {
                     bf16x4 w;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) w[e] = bf16_t(merged(t, 4 * v4 + e) * inv);
-                    *(bf16x4*)(op + t * 32 + 8 * v4 + 4 * lhalf) = w;
+                    for (int v = 0; v < 4; ++v) w[v] = bf16_t(merged(t, v) * inv);
+                    *(bf16x4*)(op + t * 16 + 4 * lq) = w;
                 }
+            }
         }
     }
 }
