@@ -275,19 +275,21 @@ rope_kv_write_kernel(const float* __restrict__ qkv, const float2* __restrict__ c
     }
 }
 
-// bf16, head_dim 128: same grid and semantics as above with 16-byte loads (4 consecutive elements =
-// 2 rotary pairs per thread, 32 threads per token row) and 8-byte stores; V^T leaves the LDS
-// transpose as 16-byte pieces of 8 consecutive tokens.  qkv may come as n_parts outputs, one per K range of the product,
-// qkv[n_parts][rows][...], which are added up (in that order) as they are read.  A workgroup takes TOK tokens of a
-// 64-token tile: all of them, or 16 where that leaves too few workgroups to hide the latency of the reads.
-template <int TOK>
+// The same grid and semantics with 16-byte loads (4 consecutive elements = 2 rotary pairs per thread, HD / 4 threads per
+// token row) and 8- or 16-byte stores; V^T leaves the LDS transpose in 16-byte pieces of consecutive tokens.  qkv may come
+// as n_parts outputs, one per K range of the product, qkv[n_parts][rows][...], which are added up (in that order) as they
+// are read.  A workgroup takes TOK tokens of a 64-token tile: all of them, or 16 where that leaves too few workgroups to
+// hide the latency of the reads, which is what bounds it for small models (us, one pair or element per thread
+// above and here: 512 rows of 48 bf16 heads of 64 9.2 and 4.9, 256 rows of 12 float32 heads of 64 8.5 and 3.0).
+template <typename T, int HD, int TOK>
 __global__ void __launch_bounds__(256)
-rope_kv_write_bf16_hd128_kernel(const float* __restrict__ qkv, int n_parts, const float2* __restrict__ cs, bf16_t* __restrict__ q,
-                                int n_q, int tok_begin, int rows, KvView kv) {
-    constexpr int HD = 128, HALF = 64;
-    typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4_t;
-    typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
-    __shared__ bf16_t vt[TOK][HD + 2];
+rope_kv_write_vec_kernel(const float* __restrict__ qkv, int n_parts, const float2* __restrict__ cs, T* __restrict__ q,
+                         int n_q, int tok_begin, int rows, KvView kv) {
+    constexpr int HALF = HD / 2, TPR = HD / 4, RPP = 256 / TPR, PASSES = TOK / RPP;   // threads per row, rows per pass
+    constexpr int E = 16 / sizeof(T), PP = TOK / E;                                   // tokens per V^T piece, pieces per head-dim row
+    typedef __attribute__((__vector_size__(4 * sizeof(T)))) T vec4_t;
+    typedef __attribute__((__vector_size__(16))) T piece_t;
+    __shared__ T vt[TOK][HD + 4 / sizeof(T)];
     const int n_kv = kv.n_kv;
     const int ldq = (n_q + 2 * n_kv) * HD;
     const int head = blockIdx.y;
@@ -297,8 +299,8 @@ rope_kv_write_bf16_hd128_kernel(const float* __restrict__ qkv, int n_parts, cons
     const int lpage = tile_tok0 / kv.page_tokens;
     const int ppage = kv.block_table[lpage];
     const int in_page0 = tile_tok0 - lpage * kv.page_tokens;
-    bf16_t* page = (bf16_t*)kv.pool + (size_t(kv.layer) * kv.n_physical_pages + ppage) * kv.page_elems();
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;   // 4 elements of a row; 8 rows per pass
+    T* page = (T*)kv.pool + (size_t(kv.layer) * kv.n_physical_pages + ppage) * kv.page_elems();
+    const int tx = threadIdx.x % TPR, ty = threadIdx.x / TPR;
     const size_t part_step = size_t(rows) * ldq;
     auto load = [&](int row) {
         const float* p = qkv + size_t(row) * ldq + head * HD + 4 * tx;
@@ -314,52 +316,61 @@ rope_kv_write_bf16_hd128_kernel(const float* __restrict__ qkv, int n_parts, cons
     if (head < n_q + n_kv) {
         const bool is_q = head < n_q;
 #pragma unroll
-        for (int pass = 0; pass < TOK / 8; ++pass) {
-            const int t = ty + 8 * pass, tok = tile_tok0 + t;
+        for (int pass = 0; pass < PASSES; ++pass) {
+            const int t = ty + RPP * pass, tok = tile_tok0 + t;
             if (tok < lo) continue;
-            bf16_t* kdst = page + (size_t(head - n_q) * kv.page_tokens + in_page0 + t) * HD + 4 * tx;
+            T* kdst = page + (size_t(head - n_q) * kv.page_tokens + in_page0 + t) * HD + 4 * tx;
             if (tok >= hi) {  // slots of this tile past the range: keep them finite for masked reads
-                if (!is_q) *(bf16x4_t*)kdst = bf16x4_t{0, 0, 0, 0};
+                if (!is_q) *(vec4_t*)kdst = vec4_t{0, 0, 0, 0};
                 continue;
             }
             const int row = tok - tok_begin;
             const float4 v = load(row);
             const float4 c = *(const float4*)(cs + row * HALF + 2 * tx);   // (cos, sin) of pairs 2tx, 2tx+1
-            bf16x4_t w = {bf16_t(v.x * c.x - v.y * c.y), bf16_t(v.x * c.y + v.y * c.x),
-                          bf16_t(v.z * c.z - v.w * c.w), bf16_t(v.z * c.w + v.w * c.z)};
-            bf16_t* dst = is_q ? q + (size_t(head) * rows + row) * HD + 4 * tx : kdst;
-            *(bf16x4_t*)dst = w;
+            vec4_t w = {from_f<T>(v.x * c.x - v.y * c.y), from_f<T>(v.x * c.y + v.y * c.x),
+                        from_f<T>(v.z * c.z - v.w * c.w), from_f<T>(v.z * c.w + v.w * c.z)};
+            T* dst = is_q ? q + (size_t(head) * rows + row) * HD + 4 * tx : kdst;
+            *(vec4_t*)dst = w;
         }
     } else {
         const int g = head - n_q - n_kv;
 #pragma unroll
-        for (int pass = 0; pass < TOK / 8; ++pass) {
-            const int t = ty + 8 * pass, tok = tile_tok0 + t;
+        for (int pass = 0; pass < PASSES; ++pass) {
+            const int t = ty + RPP * pass, tok = tile_tok0 + t;
             float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
             if (tok >= lo && tok < hi) v = load(tok - tok_begin);
-            vt[t][4 * tx + 0] = bf16_t(v.x); vt[t][4 * tx + 1] = bf16_t(v.y);
-            vt[t][4 * tx + 2] = bf16_t(v.z); vt[t][4 * tx + 3] = bf16_t(v.w);
+            vt[t][4 * tx + 0] = from_f<T>(v.x); vt[t][4 * tx + 1] = from_f<T>(v.y);
+            vt[t][4 * tx + 2] = from_f<T>(v.z); vt[t][4 * tx + 3] = from_f<T>(v.w);
         }
         __syncthreads();
-        bf16_t* vpage = page + size_t(n_kv) * kv.page_tokens * HD + size_t(g) * HD * kv.page_tokens;
-        // 128 rows (head-dim index) x TOK / 8 pieces of 8 tokens
-        constexpr int PP = TOK / 8;
+        T* vpage = page + size_t(n_kv) * kv.page_tokens * HD + size_t(g) * HD * kv.page_tokens;
+        // HD rows (head-dim index) x PP pieces of E tokens
 #pragma unroll
-        for (int i = 0; i < (128 * PP + 255) / 256; ++i) {
-            const int piece = threadIdx.x + 256 * i, e = piece / PP, t0 = (piece % PP) * 8;
-            bf16x8_t w;
+        for (int i = 0; i < (HD * PP + 255) / 256; ++i) {
+            const int piece = threadIdx.x + 256 * i, e = piece / PP, t0 = (piece % PP) * E;
+            if (HD * PP % 256 != 0 && piece >= HD * PP) break;
+            piece_t w;
 #pragma unroll
-            for (int k = 0; k < 8; ++k) w[k] = vt[t0 + k][e];
-            bf16_t* dst = vpage + size_t(e) * kv.page_tokens + in_page0 + t0;
+            for (int k = 0; k < E; ++k) w[k] = vt[t0 + k][e];
+            T* dst = vpage + size_t(e) * kv.page_tokens + in_page0 + t0;
             if (tile_tok0 + t0 >= lo) {
-                *(bf16x8_t*)dst = w;   // zeros past the range
+                *(piece_t*)dst = w;    // zeros past the range
             } else {                   // tokens before the range belong to an earlier call: leave them
 #pragma unroll
-                for (int k = 0; k < 8; ++k)
+                for (int k = 0; k < E; ++k)
                     if (tile_tok0 + t0 + k >= lo) dst[k] = w[k];
             }
         }
     }
+}
+
+template <typename T, int HD>
+static void launch_rope_vec(dim3 grid, const float* qkv, int n_parts, const float2* cs, void* q, int n_q, int tok_begin, int rows,
+                            const KvView& kv, hipStream_t st) {
+    if (long(grid.x) * grid.y < 512)
+        hipLaunchKernelGGL((rope_kv_write_vec_kernel<T, HD, 16>), dim3(4 * grid.x, grid.y), dim3(256), 0, st, qkv, n_parts, cs, (T*)q, n_q, tok_begin, rows, kv);
+    else
+        hipLaunchKernelGGL((rope_kv_write_vec_kernel<T, HD, 64>), grid, dim3(256), 0, st, qkv, n_parts, cs, (T*)q, n_q, tok_begin, rows, kv);
 }
 
 hipError_t launch_rope_kv_write(int dtype, const float* qkv, const float* cs, void* q, int n_q, int tok_begin,
@@ -369,11 +380,11 @@ hipError_t launch_rope_kv_write(int dtype, const float* qkv, const float* cs, vo
     dim3 grid(tiles, n_q + 2 * kv.n_kv), block(256);
     const float2* c2 = (const float2*)cs;
     const bool aligned = ((uintptr_t(qkv) | uintptr_t(cs) | uintptr_t(q) | uintptr_t(kv.pool)) & 15) == 0;
-    if (dtype == 1 && kv.head_dim == 128 && aligned) {
-        if (long(grid.x) * grid.y < 512)
-            hipLaunchKernelGGL(rope_kv_write_bf16_hd128_kernel<16>, dim3(4 * grid.x, grid.y), block, 0, st, qkv, n_parts, c2, (bf16_t*)q, n_q, tok_begin, rows, kv);
-        else
-            hipLaunchKernelGGL(rope_kv_write_bf16_hd128_kernel<64>, grid, block, 0, st, qkv, n_parts, c2, (bf16_t*)q, n_q, tok_begin, rows, kv);
+    if (aligned && (dtype == 0 || dtype == 1) && (kv.head_dim == 64 || kv.head_dim == 128)) {
+        if (dtype == 0 && kv.head_dim == 64) launch_rope_vec<float, 64>(grid, qkv, n_parts, c2, q, n_q, tok_begin, rows, kv, st);
+        else if (dtype == 0) launch_rope_vec<float, 128>(grid, qkv, n_parts, c2, q, n_q, tok_begin, rows, kv, st);
+        else if (kv.head_dim == 64) launch_rope_vec<bf16_t, 64>(grid, qkv, n_parts, c2, q, n_q, tok_begin, rows, kv, st);
+        else launch_rope_vec<bf16_t, 128>(grid, qkv, n_parts, c2, q, n_q, tok_begin, rows, kv, st);
         return hipGetLastError();
     }
     if (n_parts > 1) return hipErrorInvalidValue;
