@@ -180,15 +180,17 @@ static KvView make_view(const cake_ctx* c, const cake_kv* kv, int layer) {
 // ------------------------------------------------------------------ kernel dispatch
 // How a bf16 product may leave its K ranges in the split workspace (ksplit 0: it does not).  Not where a test forces a
 // kernel.
-static GemmPartsPlan parts_plan(const cake_ctx* c, int epi, int M, int N, int K, bool fused) {
-    if (c->m.dtype != CAKE_BF16 || c->tun.kernel_path != 0 || c->tun.gemm_config != 0 || c->tun.gemm_ksplit != 0) return GemmPartsPlan{0, false};
-    return gemm_parts_plan(epi, M, N, K, c->split.part ? &c->split : nullptr, fused);
+static GemmPartsPlan parts_plan(const cake_ctx* c, int epi, int M, int N, int K, bool fused, bool rows_only) {
+    if (c->m.dtype != CAKE_BF16 || c->tun.kernel_path != 0 || c->tun.gemm_config != 0 || c->tun.gemm_ksplit != 0) return GemmPartsPlan{0, GEMM_PARTS_ROWS};
+    return gemm_parts_plan(epi, M, N, K, c->split.part ? &c->split : nullptr, fused, rows_only);
 }
 
-// plan_rows: the rows that choose whether K ranges are left (M, or one number for all steps of a context).
-static hipError_t gemm(cake_ctx* c, int epi, const void* a, const void* w, const void* w2, void* out, int M, int N, int K, int plan_rows) {
-    const GemmPartsPlan plan = plan_rows <= 192 ? parts_plan(c, epi, plan_rows, N, K, false) : GemmPartsPlan{0, false};
-    if (plan.ksplit && plan.few_rows && M > 0 && (uintptr_t(out) & 15) == 0) {   // K ranges, and a pass that adds them up
+// plan_rows: the rows that choose whether K ranges are left (M, or one number for all steps of a context, which then
+// leaves them on the kernel for few rows only).
+static hipError_t gemm(cake_ctx* c, int epi, const void* a, const void* w, const void* w2, void* out, int M, int N, int K, int plan_rows,
+                       bool rows_only = false) {
+    const GemmPartsPlan plan = parts_plan(c, epi, plan_rows, N, K, false, rows_only);
+    if (plan.ksplit && M > 0 && (uintptr_t(out) & 15) == 0) {   // K ranges, and a pass that adds them up
         hipError_t e = launch_gemm_parts(plan, a, w, c->split.part, M, N, K, c->cs);
         return e != hipSuccess ? e : launch_add_parts((float*)out, c->split.part, plan.ksplit, size_t(M) * N, c->cs, epi == EPI_STORE_F32);
     }
@@ -248,14 +250,11 @@ static int enqueue_prefill(cake_ctx* c, int tok_begin, int rows, const cake_kv* 
     HIP_TRY(c, launch_rope_table(c->rope_cs, tok_begin, rows, m.head_dim, m.rope_theta, c->cs));
     // A product may leave its K ranges in the split workspace for the kernel after it, which reads them before anything
     // else is put there: QKV for the rotary step, O and down for the norm (the last layer's down for a sum of its own).
-    const bool rope_adds = m.head_dim == 128 && (uintptr_t(kv->pool) & 15) == 0;
+    const bool rope_adds = (uintptr_t(kv->pool) & 15) == 0;
     // In a step-free context the longest step decides, for the kernel for few rows if it takes that one too.
-    const GemmPartsPlan none{0, false};
+    const GemmPartsPlan none{0, GEMM_PARTS_ROWS};
     const int plan_rows = c->step_free ? c->max_chunk : rows;
-    auto ranges = [&](int epi, int N, int K) {
-        const GemmPartsPlan p = parts_plan(c, epi, plan_rows, N, K, true);
-        return c->step_free && !p.few_rows ? none : p;
-    };
+    auto ranges = [&](int epi, int N, int K) { return parts_plan(c, epi, plan_rows, N, K, true, c->step_free); };
     const GemmPartsPlan p_qkv = rope_adds ? ranges(EPI_STORE_F32, int(nqkv), int(d)) : none;
     const GemmPartsPlan p_o = ranges(EPI_RESIDUAL_F32, int(d), int(hq));
     const GemmPartsPlan p_down = ranges(EPI_RESIDUAL_F32, int(d), m.ffn_dim);
@@ -265,7 +264,7 @@ static int enqueue_prefill(cake_ctx* c, int tok_begin, int rows, const cake_kv* 
                            : launch_rmsnorm(m.dtype, c->x, gain, c->h, rows, d, m.rms_eps, c->cs);
     };
     auto product = [&](const GemmPartsPlan& plan, int epi, const void* a, const void* w, float* out, int N, int K) {
-        return plan.ksplit ? launch_gemm_parts(plan, a, w, parts, rows, N, K, c->cs) : gemm(c, epi, a, w, nullptr, out, rows, N, K, plan_rows);
+        return plan.ksplit ? launch_gemm_parts(plan, a, w, parts, rows, N, K, c->cs) : gemm(c, epi, a, w, nullptr, out, rows, N, K, plan_rows, c->step_free);
     };
     for (int l = 0; l < m.n_layers; ++l) {
         const cake_layer_weights& w = c->layers[l];
@@ -281,7 +280,7 @@ static int enqueue_prefill(cake_ctx* c, int tok_begin, int rows, const cake_kv* 
                 product(p_o, EPI_RESIDUAL_F32, c->ao, w.wo, c->x, d, hq));
         KLAUNCH(c, CAKE_K_RMSNORM, 0, R * d * (4 + e), norm(p_o, w.ffn_norm));
         KLAUNCH(c, CAKE_K_GEMM_GATEUP, 4 * R * ff * d, (R * d + 2 * ff * d + R * ff) * e,
-                gemm(c, EPI_SWIGLU, c->h, w.w_gate, w.w_up, c->act, rows, m.ffn_dim, d, plan_rows));
+                gemm(c, EPI_SWIGLU, c->h, w.w_gate, w.w_up, c->act, rows, m.ffn_dim, d, plan_rows, c->step_free));
         KLAUNCH(c, CAKE_K_GEMM_DOWN, 2 * R * d * ff, (R * ff + d * ff) * e + 2 * R * d * 4,
                 product(p_down, EPI_RESIDUAL_F32, c->act, w.w_down, c->x, d, m.ffn_dim));
     }
@@ -1288,9 +1287,11 @@ int32_t cake_op_gemm_plan(cake_ctx* c, int32_t residual, int32_t M, int32_t N, i
     if (!c || !tile || !ksplit || M < 0 || N <= 0 || K <= 0) return CAKE_E_INVAL;
     const int epi = residual ? EPI_RESIDUAL_F32 : EPI_STORE_F32;
     tile[0] = tile[1] = 0; *ksplit = 1;
-    const GemmPartsPlan plan = parts_plan(c, epi, M, N, K, false);
-    if (plan.ksplit && plan.few_rows) {
-        tile[0] = (M + 31) / 32 * 32; tile[1] = 128; *ksplit = plan.ksplit;
+    const GemmPartsPlan plan = parts_plan(c, epi, M, N, K, false, false);
+    if (plan.ksplit) {
+        tile[0] = plan.kind == GEMM_PARTS_ROWS ? (M + 31) / 32 * 32 : plan.kind == GEMM_PARTS_P256 ? 256 : 128;
+        tile[1] = plan.kind == GEMM_PARTS_P256 ? 256 : plan.kind == GEMM_PARTS_192 ? 192 : 128;
+        *ksplit = plan.ksplit;
     } else if (c->m.dtype == CAKE_BF16 && c->tun.kernel_path == 0 && gemm_mfma_supported(epi, M, N, K)) {
         int bm, bn, ks;
         gemm_mfma_plan(epi, M, N, K, c->tun.gemm_config - 1, c->split.part ? &c->split : nullptr, c->tun.gemm_ksplit, &bm, &bn, &ks);

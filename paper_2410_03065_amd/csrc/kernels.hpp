@@ -80,19 +80,16 @@ void gemm_mfma_plan(int epi, int M, int N, int K, int cfg_override, const GemmSp
                     int* bm, int* bn, int* ksplit);
 // Does launch_gemm_mfma add up in the same order for every M from 1 to max_rows?
 bool gemm_order_fixed(int epi, int max_rows, int N, int K, const GemmSplitWs* ws);
-// out[ks][M][N] float32: one output per K range (K a multiple of 64 ks), for a consumer that adds them up.
-// rows: M <= 192, N a multiple of 128; p256: N a multiple of 256.
+// out[ks][M][N] float32: one output per K range (K a multiple of 64 ks), for a consumer that adds them up; M <= 192, N a
+// multiple of 128.
 hipError_t launch_gemm_rows_parts(const void* a, const void* w, float* part, int M, int N, int K, int ks, hipStream_t st);
-hipError_t launch_gemm_p256_parts(const void* a, const void* w, float* part, int M, int N, int K, int ks, hipStream_t st);
 // How to leave a product (epi: store or residual) to its consumer: ksplit 0: not, launch_gemm_mfma is faster; else K in
-// that many ranges on the kernel for few rows or on the persistent one.  fused: the consumer reads the result anyway
-// (an RMSNorm, the rotary step); otherwise a pass of its own adds the ranges up.
-struct GemmPartsPlan { int ksplit; bool few_rows; };
-GemmPartsPlan gemm_parts_plan(int epi, int M, int N, int K, const GemmSplitWs* ws, bool fused);
-inline hipError_t launch_gemm_parts(const GemmPartsPlan& plan, const void* a, const void* w, float* part, int M, int N, int K, hipStream_t st) {
-    return plan.few_rows ? launch_gemm_rows_parts(a, w, part, M, N, K, plan.ksplit, st)
-                         : launch_gemm_p256_parts(a, w, part, M, N, K, plan.ksplit, st);
-}
+// that many ranges on the kernel for few rows, on the persistent one or on the 128 x 128 or 128 x 192 tiles.  fused: the
+// consumer reads the result anyway (an RMSNorm, the rotary step); otherwise a pass of its own adds the ranges up.
+enum GemmPartsKind { GEMM_PARTS_ROWS = 0, GEMM_PARTS_P256 = 1, GEMM_PARTS_128 = 2, GEMM_PARTS_192 = 3 };
+struct GemmPartsPlan { int ksplit; GemmPartsKind kind; };
+GemmPartsPlan gemm_parts_plan(int epi, int M, int N, int K, const GemmSplitWs* ws, bool fused, bool rows_only = false);
+hipError_t launch_gemm_parts(const GemmPartsPlan& plan, const void* a, const void* w, float* part, int M, int N, int K, hipStream_t st);
 // MFMA-only yardstick kernel: out holds workgroups * 8 floats; see kernels_gemm.hip.
 hipError_t launch_mfma_rate(float* out, int workgroups, int iters, hipStream_t st);
 bool attention_mfma_supported(int head_dim, int page_tokens);

@@ -5,6 +5,7 @@
 // lane l supplies A[l%32][8*(l/32) .. +7] and B[8*(l/32) .. +7][l%32], and holds
 // D[8*(v/4) + 4*(l/32) + v%4][l%32] in accumulator register v (0..15).
 #include <algorithm>
+#include <cmath>
 #include <mutex>
 #include <vector>
 
@@ -90,7 +91,10 @@ gemm_p256_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, con
     for (int u = 0; u < tiles_per_wg; ++u)
         if (item_of(u) < nb) ++n_mine;
     if (n_mine == 0) return;
-    const int nk = K / ksplit / 64;   // slices per item
+    // K ranges of whole 64-deep slices, the first n_long of them one slice longer
+    const int nk_short = K / 64 / ksplit, n_long = K / 64 - nk_short * ksplit;
+    auto slices_of = [&](int range) { return nk_short + (range < n_long); };
+    auto first_k = [&](int range) { return (range * nk_short + min(range, n_long)) * 64; };
     // geometry of tile t: MFMA tiles per wave along N, first row of A, first column (in units of UNIT)
     auto tile_geom = [&](int t, int* nj, int* m0, int* col_units) {
         int c, p;
@@ -111,16 +115,18 @@ gemm_p256_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, con
     const unsigned voff_w = EPI == EPI_SWIGLU ? unsigned((8 * (wave & 1) + lr) * K * 2) + chunk : voff_a;
     const unsigned step_w = EPI == EPI_SWIGLU ? unsigned(16 * K * 2) : step_a;
     __amdgpu_buffer_rsrc_t ra, rw;
-    int ka = 0, ua = 0, kw = 0, uw = 0, slot_a = 1, slot_w = 0;
+    int ka = 0, ua = 0, kw = 0, uw = 0, slot_a = 1, slot_w = 0, nk_a = 0, nk_w = 0;
     // descriptors start at the item's first row and first K element
     auto set_a = [&]() {
-        const int q = item_of(ua), kbeg = (q / n_tiles) * nk * 64;
+        const int q = item_of(ua), kbeg = first_k(q / n_tiles);
+        nk_a = slices_of(q / n_tiles);
         int nj, m0, cu;
         tile_geom(q % n_tiles, &nj, &m0, &cu);
         ra = __builtin_amdgcn_make_buffer_rsrc((void*)(A + size_t(m0) * K + kbeg), 0, min(256, M - m0) * K * 2 - kbeg * 2, 0x00020000);
     };
     auto set_w = [&]() {
-        const int q = item_of(uw), kbeg = (q / n_tiles) * nk * 64;
+        const int q = item_of(uw), kbeg = first_k(q / n_tiles);
+        nk_w = slices_of(q / n_tiles);
         int nj, m0, cu;
         tile_geom(q % n_tiles, &nj, &m0, &cu);
         const bf16_t* base = (EPI == EPI_SWIGLU && (wave >> 1) ? W2 : W) + size_t(cu) * UNIT * K;
@@ -128,7 +134,7 @@ gemm_p256_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, con
     };
     auto next_a = [&]() {
         slot_a = slot_a >= P_SLOTS - 2 ? slot_a + 2 - P_SLOTS : slot_a + 2;
-        if (++ka == nk) {
+        if (++ka == nk_a) {
             ka = 0; ++ua;
             if (ua < n_mine) set_a();
             else ra = __builtin_amdgcn_make_buffer_rsrc((void*)A, 0, 0, 0x00020000);
@@ -136,7 +142,7 @@ gemm_p256_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, con
     };
     auto next_w = [&]() {
         slot_w = slot_w >= P_SLOTS - 2 ? slot_w + 2 - P_SLOTS : slot_w + 2;
-        if (++kw == nk) {
+        if (++kw == nk_w) {
             kw = 0; ++uw;
             if (uw < n_mine) set_w();
             else rw = __builtin_amdgcn_make_buffer_rsrc((void*)W, 0, 0, 0x00020000);
@@ -234,7 +240,7 @@ gemm_p256_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, con
     constexpr int OUT_ELT = EPI == EPI_SWIGLU ? 2 : 4;
     __amdgpu_buffer_rsrc_t obuf = __builtin_amdgcn_make_buffer_rsrc(outv, 0, int(size_t(M) * N * OUT_ELT), 0x00020000);
     // The K loop of an item of class nj (a constant at each of the three call sites)
-    auto k_loop = [&](const int nj, int b_wave, int b_wave_next) __attribute__((always_inline)) {
+    auto k_loop = [&](const int nj, const int nk, int b_wave, int b_wave_next) __attribute__((always_inline)) {
         for (int kt = 0; kt < nk; ++kt) {
             // phase A: k-step 0; operands of k-step 1; the W item of the slice after next (the weights come from HBM
             // and get the longer run-up: a slice and a half; the activations are L2 hits)
@@ -326,10 +332,11 @@ gemm_p256_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, con
         const int q = item_of(u);
         int nj_next = nj_cur, m0_next = 0, cu_next = 0;
         if (u + 1 < n_mine) tile_geom(item_of(u + 1) % n_tiles, &nj_next, &m0_next, &cu_next);
+        const int nk = slices_of(q / n_tiles);
         const int b_wave = wn * nj_cur * 512, b_wave_next = wn * nj_next * 512;   // 16 nj rows = nj / 2 KB steps
-        if (nj_cur == 8) k_loop(8, b_wave, b_wave_next);
-        else if (nj_cur == 6) k_loop(6, b_wave, b_wave_next);
-        else k_loop(4, b_wave, b_wave_next);
+        if (nj_cur == 8) k_loop(8, nk, b_wave, b_wave_next);
+        else if (nj_cur == 6) k_loop(6, nk, b_wave, b_wave_next);
+        else k_loop(4, nk, b_wave, b_wave_next);
         // The asm MFMAs are opaque to the compiler's hazard handling: let the last of them (four passes) retire
         // before the accumulators are read.
         __builtin_amdgcn_sched_barrier(0);
@@ -640,9 +647,10 @@ static hipError_t gemm_launch_cfg(int cfg, int ks, const GemmSplitWs* ws, const 
     }
 }
 
-// K in `ks` ranges on the persistent kernel, each range stored as an output of its own (256-wide panels).
-hipError_t launch_gemm_p256_parts(const void* a, const void* w, float* part, int M, int N, int K, int ks, hipStream_t st) {
-    if (N % 256 || K % (64 * ks) || !gemm_cfg_ok(GCFG_P256, EPI_STORE_F32, M, N, K)) return hipErrorInvalidValue;
+// K in `ks` ranges (whole slices of 64, as even as they go) on the persistent kernel, each range stored as an output of its
+// own (256-wide panels).
+static hipError_t launch_gemm_p256_parts(const void* a, const void* w, float* part, int M, int N, int K, int ks, hipStream_t st) {
+    if (N % 256 || ks <= 0 || K / 64 < ks || !gemm_cfg_ok(GCFG_P256, EPI_STORE_F32, M, N, K)) return hipErrorInvalidValue;
     const int tiles_m = (M + 255) / 256, nb = tiles_m * (N / 256) * ks, rounds = (nb + 255) / 256, wgs = (nb + rounds - 1) / rounds;
     auto kern = gemm_p256_kernel<EPI_STORE_F32, false>;
     static bool attr_set = false;
@@ -656,42 +664,86 @@ hipError_t launch_gemm_p256_parts(const void* a, const void* w, float* part, int
     return hipGetLastError();
 }
 
-// The same unit (about a microsecond) for the two kernels that leave K ranges to a consumer, plus what the ranges cost
-// there.  Persistent kernel: 1.40 us per slice and item, the ranges written at about 10 TB/s; few rows: a slice takes
-// 0.24 us + 0.075 us per 32 rows, HBM delivers the weights at 5.3 TB/s, L2 the tiles at 10, or 0.05
-// per workgroup.  Both sides measured, us:
-// down 8B (K = 14336 -> 4096) 1024 rows 140 and 91 in four ranges, 64 rows 40 and 24 in eight; down 70B 1024 rows 459 and
-// 355 in two; O 8B 1024 rows 45 and 36 (no gain with 64 MB of ranges to add), 137 rows 32 and 16; QKV 8B 137 rows 29 and 18.
-// Narrow products (under 2048 columns, under 4096 on the persistent kernel) stay with launch_gemm_mfma, where the order of
-// their sums changes with M at fewer sizes, so that a narrow model's KV shows less of its steps.  They would gain: 64 rows
-// of 4096 -> 1024 18.7 and 9.5 us, 1024 rows through four layers of d 2048 and ffn 8192 840 and 785.
-GemmPartsPlan gemm_parts_plan(int epi, int M, int N, int K, const GemmSplitWs* ws, bool fused) {
-    GemmPartsPlan best{0, false};
-    if (epi == EPI_SWIGLU || !ws || !ws->part || M <= 0 || K % 64 || N % 128) return best;
-    double best_us;
-    gemm_pick(epi, M, N, K, ws, &best_us);
-    best_us *= 0.95;
+// K in `ks` ranges on the 128-row tiles whose slices two waves divide, each range stored as an output of its own.
+static hipError_t launch_gemm_tile_parts(int bn, const void* a, const void* w, float* part, int M, int N, int K, int ks, hipStream_t st) {
+    const bf16_t *A = (const bf16_t*)a, *W = (const bf16_t*)w;
+    if (M <= 0 || N <= 0 || K <= 0 || ks <= 0 || N % bn || K % (64 * ks)) return hipErrorInvalidValue;
+    if (bn == 128) return gemm_launch_t<2, 2, 2, 2, 64, 5, EPI_STORE_F32, 2>(A, W, nullptr, part, M, N, K, st, ks, nullptr, true);
+    if (bn == 192) return gemm_launch_t<2, 3, 2, 2, 64, 4, EPI_STORE_F32, 2>(A, W, nullptr, part, M, N, K, st, ks, nullptr, true);
+    return hipErrorInvalidValue;
+}
+
+// The same unit (about a microsecond) for the kernels that leave K ranges to a consumer, plus what the ranges cost
+// there.  Persistent kernel: 1.40 us per slice and item; 128 x 128 tiles 0.585, 128 x 192 0.71; the ranges written at about
+// 10 TB/s; few rows: a slice takes 0.24 us + 0.075 us per 32 rows, HBM delivers the weights at 5.3 TB/s, L2 the tiles at
+// 10, or 0.05 per workgroup.  A pass of its own that adds the ranges up reads and writes the result too; whole tiles are
+// left to one only where that promises a tenth (128 x 128, 128 x 192) or a sixth.  Both sides measured, us (the second without the consumer's part):
+// down 8B (K = 14336 -> 4096) 1024 rows 133 and 87 in four ranges, 512 rows 81 and 51 in eight, 64 rows 40 and 24 in eight;
+// down 70B 1024 rows 434 and 334 in two, 512 rows 284 and 183 in four; O 8B 512 rows 40 and 24 (128 x 128, two), 137 rows
+// 32 and 16; QKV 8B 320 rows 37 and 27 (128 x 192, two), 137 rows 29 and 18; 512 rows of 8192 -> 2048 42 and 24 (128 x 128,
+// four), of 2048 -> 2048 16 and 10, of 2048 -> 3072 21 and 12 (128 x 192, four).  No gain: 1024 rows of O 8B 43 and 39.
+// rows_only: only the kernel for few rows.  Products of under 2048 columns stay with launch_gemm_mfma, where the order of
+// their sums changes with M at fewer sizes, so that a narrow model's KV shows less of its steps; 64 rows of 4096 -> 1024
+// would take 9.5 instead of 18.7.
+GemmPartsPlan gemm_parts_plan(int epi, int M, int N, int K, const GemmSplitWs* ws, bool fused, bool rows_only) {
+    GemmPartsPlan best{0, GEMM_PARTS_ROWS};
+    if (epi == EPI_SWIGLU || !ws || !ws->part || M <= 0 || K % 64 || N % 128 || N < 2048) return best;
+    double plain_us;
+    const GemmChoice plain = gemm_pick(epi, M, N, K, ws, &plain_us);
+    double best_us = plain_us * 0.95;
     const double out_mb = double(M) * N * 4e-6;
-    for (int ks = 1; ks <= 8; ks *= 2) {
-        if (K % (64 * ks) || size_t(ks) * M * N * 4 > ws->part_bytes) continue;
-        const double after = (ks * out_mb + (fused ? 0.0 : 2.0 * out_mb)) / 4.5 + (fused ? 0.0 : 4.0) + ks * out_mb / 10.0;
-        const double slices = double(K) / ks / 64;
-        if (M <= 192 && N >= 2048) {
+    auto after = [&](int ks, double rate, double pass) { return (ks * out_mb + (fused ? 0.0 : 2.0 * out_mb)) / rate + (fused ? 0.0 : pass) + ks * out_mb / 10.0; };
+    auto fits = [&](int ks) { return size_t(ks) * M * N * 4 <= ws->part_bytes; };
+    auto take = [&](int ks, GemmPartsKind kind, double us) {
+        if (us < best_us) { best_us = us; best = GemmPartsPlan{ks, kind}; }
+    };
+    if (M <= 192)
+        for (int ks = 1; ks <= 8; ks *= 2) {
+            if (K % (64 * ks) || !fits(ks)) continue;
+            const double slices = double(K) / ks / 64;
             const int bm = (M + 31) / 32 * 32;
             const double tiles = N / 128, rounds = double((long(tiles) * ks + 255) / 256);
             if (bm >= 160 && tiles * ks < 160) continue;   // 137 and 192 rows of 11008 -> 4096 in four: 41 and 47 us, 38 and 42 without
             const double l2_rate = std::min(10.0, 0.05 * tiles * ks);   // TB/s
-            const double us = after + std::max(rounds * (slices * (0.24 + 0.075 * (bm / 32)) + 4.0),
-                                               std::max(double(N) * K * 2e-6 / 5.3 + 2.0, (bm + 128.0) * K * 2e-6 * tiles / l2_rate + 3.0));
-            if (us < best_us) { best_us = us; best = GemmPartsPlan{ks, true}; }
+            take(ks, GEMM_PARTS_ROWS, after(ks, 4.5, 4.0) + std::max(rounds * (slices * (0.24 + 0.075 * (bm / 32)) + 4.0),
+                                                           std::max(double(N) * K * 2e-6 / 5.3 + 2.0, (bm + 128.0) * K * 2e-6 * tiles / l2_rate + 3.0)));
         }
-        if (N % 256 == 0 && N >= 4096 && gemm_cfg_ok(GCFG_P256, EPI_STORE_F32, M, N, K)) {
-            const double rounds = double((long(M + 255) / 256 * (N / 256) * ks + 255) / 256);
-            const double us = after + rounds * (slices * 1.40 + 4.0);
-            if (us < best_us) { best_us = us; best = GemmPartsPlan{ks, false}; }
-        }
+    if (rows_only || (best.ksplit && M <= 192)) return best;
+    // Whole tiles.  A launch of fewer workgroups than CUs runs its slices up to a fifth faster (L2); gemm_pick's price of a
+    // small tile split by ticket is one to be beaten by a tenth, here is what it takes.
+    auto fill = [](long wgs) { return 0.8 + 0.2 * double(wgs) / double((wgs + 255) / 256 * 256); };
+    if (!fused) {
+        const GemmCfg& c = kGemmCfg[plain.cfg];
+        const long tiles = long((M + c.bm - 1) / c.bm) * (N / c.bn);
+        const double area = c.bm * c.bn / 65536.0;
+        if (plain.ksplit > 1 && area <= 0.25) plain_us = plain_us / 1.08 - 10.0 - 20.0 * plain.ksplit * area + 8.0;
+        plain_us *= fill(tiles * plain.ksplit);
+        // unsplit tiles that fill the chip: 1024 rows of down 8B 133 us, 87 + 18 in four ranges with a pass of their own
+        if (plain.ksplit == 1 && fill(tiles) > 0.98) plain_us *= 0.85;
+    }
+    auto whole = [&](int ks, GemmPartsKind kind, int bm, int bn, double slice_us, double promise) {
+        const long wgs = long(M + bm - 1) / bm * (N / bn) * ks;
+        const double us = after(ks, fused ? 4.5 : 6.0, 2.5) + double((wgs + 255) / 256) * (std::ceil(double(K) / 64 / ks) * slice_us * fill(wgs) + 4.0);
+        if (us < plain_us * promise) take(ks, kind, us);
+    };
+    for (int ks = 1; ks <= 8; ++ks) {
+        if (K / 64 < ks || !fits(ks)) continue;
+        if (N % 256 == 0 && gemm_cfg_ok(GCFG_P256, EPI_STORE_F32, M, N, K)) whole(ks, GEMM_PARTS_P256, 256, 256, 1.40, fused ? 0.95 : 0.83);
+        if (K % (64 * ks)) continue;
+        whole(ks, GEMM_PARTS_128, 128, 128, 0.60, fused ? 0.95 : 0.90);
+        if (N % 192 == 0) whole(ks, GEMM_PARTS_192, 128, 192, 0.72, fused ? 0.95 : 0.90);
     }
     return best;
+}
+
+hipError_t launch_gemm_parts(const GemmPartsPlan& plan, const void* a, const void* w, float* part, int M, int N, int K, hipStream_t st) {
+    switch (plan.kind) {
+        case GEMM_PARTS_ROWS: return launch_gemm_rows_parts(a, w, part, M, N, K, plan.ksplit, st);
+        case GEMM_PARTS_P256: return launch_gemm_p256_parts(a, w, part, M, N, K, plan.ksplit, st);
+        case GEMM_PARTS_128: return launch_gemm_tile_parts(128, a, w, part, M, N, K, plan.ksplit, st);
+        case GEMM_PARTS_192: return launch_gemm_tile_parts(192, a, w, part, M, N, K, plan.ksplit, st);
+    }
+    return hipErrorInvalidValue;
 }
 
 static GemmChoice gemm_choose(int epi, int M, int N, int K, int cfg_override, const GemmSplitWs* ws, int ksplit_override) {
