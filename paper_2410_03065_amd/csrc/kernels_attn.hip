@@ -1066,43 +1066,40 @@ attention_hd64_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, fl
 // One-token attention on the matrix cores (first-token step; bf16 pages, head_dim 128).
 //
 // The "queries" of a workgroup are the r query heads that share KV head g, all at the same
-// position; they fill r of the 32 columns of the same transposed products as above
-// (S^T = K Q^T, O^T = V^T P^T), the other columns stay zero.  That wastes most of the MFMA
-// columns, which is free here: the kernel is bound by streaming the layer's K and V once, and
-// one 32-wide MFMA step consumes 1 KB of them.  There is no reuse between waves, so nothing is
-// staged in LDS: every lane loads its MFMA operand slices straight from the pages (K row
-// sigma16-permuted as above, V^T row = head-dim index), a wave has the V^T tile of this step
+// position; they fill r of the 16 C columns of transposed products as in the kernel of eight waves
+// (S^T = K Q^T, O^T = V^T P^T in 16x16x32 MFMAs), the other columns stay zero.  That wastes most of the MFMA
+// columns, which is free here: the kernel is bound by streaming the layer's K and V once.
+// There is no reuse between waves, so nothing is
+// staged in LDS: every lane loads its MFMA operand slices straight from the pages (K rows in the order of
+// the eight-wave kernel, V^T row = head-dim index), a wave has the V^T tile of this step
 // and the K tile of the next in flight while it works, and the W waves of a workgroup take
-// the 32-key tiles of the workgroup's range in turn.  Partial (max, sum, O) per wave are merged
+// the 32-key tiles of the workgroup's range in turn.  An operand of the 16-row MFMA is 64 bytes of each row; that of the
+// 32-row one was 32, half of what a request fetches.  Partial (max, sum, O) per wave are merged
 // through LDS and written per key range for the combine kernel.  Eight waves, two per SIMD, where their parts fit the
-// LDS (up to 12 heads to a KV head), so that one's loads are out while the other works; else four.
+// LDS (up to 12 heads to a KV head), so that one's loads are out while the other works; else four.  us with the
+// combine kernel (of one thread per output), 32-row and 16-row MFMAs: 32 heads on 8 at 32768 keys (134 MB) 37.7 and 34.4,
+// at 8000 16.6 and 14.6, 32 on 32 at 16000 (262 MB) 55.9 and 51.
 // =====================================================================================
 constexpr int DK = 32;   // keys per tile
 
-template <int W>
+template <int W, int C>
 __global__ void __launch_bounds__(64 * W)
 decode_attention_mfma_kernel(const float* __restrict__ q, float* __restrict__ part, int n_q, int n_keys,
                              int tiles_per_split, KvView kv) {
     extern __shared__ float dlds[];   // [W][r][AHD + 2]: O, then max (natural-log units), then sum
     const int g = blockIdx.x, split = blockIdx.y, n_splits = gridDim.y;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int lrow = lane & 31, lhalf = lane >> 5;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: a page number comes by a scalar load and waits for no tile
+    const int l16 = lane & 15, lq = lane >> 4;
     const int r = n_q / kv.n_kv;
     const int pt = kv.page_tokens;
     const int n_tiles = (n_keys + DK - 1) / DK;
     const int tile_lo = split * tiles_per_split * (AK / DK), tile_hi = min(tile_lo + tiles_per_split * (AK / DK), n_tiles);
     const float sl2 = 0.08838834764831845f * 1.4426950408889634f;
 
-    bf16x8 qB[AHD / 16];
-#pragma unroll
-    for (int ks = 0; ks < AHD / 16; ++ks)
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-            qB[ks][e] = lrow < r ? bf16_t(q[size_t(g * r + lrow) * AHD + 16 * ks + 8 * lhalf + e] * sl2) : bf16_t(0.f);
-
-    const int krow = 16 * (lrow >> 4) + sigma16(lrow & 15);
+    const int krow = 8 * (l16 >> 2) + (l16 & 3);   // of score tile 0; four keys on in tile 1
     const size_t layer_base = size_t(kv.layer) * kv.n_physical_pages;
-    bf16x8 kA[AHD / 16], vA[4][2];
+    bf16x8 kA[2][AHD / 32], vA[AHD / 16];
     auto tile_page = [&](int tile, int* in_page0) {
         const int key0 = tile * DK, lpage = key0 / pt;
         *in_page0 = key0 - lpage * pt;
@@ -1110,76 +1107,100 @@ decode_attention_mfma_kernel(const float* __restrict__ q, float* __restrict__ pa
     };
     auto load_k = [&](int tile) {
         int in_page0;
-        const bf16_t* kp = tile_page(tile, &in_page0) + (size_t(g) * pt + in_page0) * AHD + 8 * lhalf;
+        const bf16_t* kp = tile_page(tile, &in_page0) + (size_t(g) * pt + in_page0 + krow) * AHD + 8 * lq;
 #pragma unroll
-        for (int ks = 0; ks < AHD / 16; ++ks) kA[ks] = *(const bf16x8*)(kp + size_t(krow) * AHD + 16 * ks);
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int ks = 0; ks < AHD / 32; ++ks) kA[t][ks] = *(const bf16x8*)(kp + 4 * t * AHD + 32 * ks);
     };
     auto load_v = [&](int tile) {
         int in_page0;
-        const bf16_t* vp = tile_page(tile, &in_page0) + size_t(kv.n_kv) * pt * AHD + size_t(g) * AHD * pt + in_page0 + 8 * lhalf;
+        const bf16_t* vp = tile_page(tile, &in_page0) + size_t(kv.n_kv) * pt * AHD + (size_t(g) * AHD + l16) * pt + in_page0 + 8 * lq;
 #pragma unroll
-        for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-            for (int c = 0; c < 2; ++c) vA[dt][c] = *(const bf16x8*)(vp + size_t(32 * dt + lrow) * pt + 16 * c);
+        for (int dt = 0; dt < AHD / 16; ++dt) vA[dt] = *(const bf16x8*)(vp + size_t(16 * dt) * pt);
     };
 
-    f32x16 o[4];
+    const f32x4 zero4 = {0, 0, 0, 0};
+    f32x4 o[AHD / 16][C];
+    float m_run[C], l_part[C];
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
+    for (int c = 0; c < C; ++c) {
+        m_run[c] = -1.0e30f;   // finite start: exp2(-inf - m) of a masked key is 0, never NaN
+        l_part[c] = 0.f;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) o[t][v] = 0.f;
-    float m_run = -1.0e30f, l_part = 0.f;   // finite start: exp2(-inf - m) of a masked key is 0, never NaN
-    const f32x16 zero16 = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+        for (int dt = 0; dt < AHD / 16; ++dt) o[dt][c] = zero4;
+    }
 
     int tile = tile_lo + wave;
     if (tile < tile_hi) load_k(tile);
+    bf16x8 qB[C][AHD / 32];
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+#pragma unroll
+        for (int ks = 0; ks < AHD / 32; ++ks)
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                qB[c][ks][e] = 16 * c + l16 < r ? bf16_t(q[size_t(g * r + 16 * c + l16) * AHD + 32 * ks + 8 * lq + e] * sl2) : bf16_t(0.f);
     for (; tile < tile_hi; tile += W) {
         load_v(tile);
-        f32x16 s;
+        f32x4 s[2][C];
 #pragma unroll
-        for (int ks = 0; ks < AHD / 16; ++ks) s = mfma32(kA[ks], qB[ks], ks == 0 ? zero16 : s);
+        for (int ks = 0; ks < AHD / 32; ++ks)
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int c = 0; c < C; ++c) s[t][c] = mfma16(kA[t][ks], qB[c][ks], ks == 0 ? zero4 : s[t][c]);
         if (tile + W < tile_hi) load_k(tile + W);
         if ((tile + 1) * DK > n_keys) {   // ragged last tile: keys past the prompt
 #pragma unroll
-            for (int v = 0; v < 16; ++v)
-                if (tile * DK + 16 * (v >> 3) + 8 * lhalf + (v & 7) >= n_keys) s[v] = -INFINITY;
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int c = 0; c < C; ++c)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        if (tile * DK + 8 * lq + 4 * t + v >= n_keys) s[t][c][v] = -INFINITY;
         }
-        float mx = s[0];
+        bf16x8 pB[C];
 #pragma unroll
-        for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[v]);
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-        const float m_new = fmaxf(m_run, mx);
-        const float corr = __builtin_amdgcn_exp2f(m_run - m_new);
-        m_run = m_new;
-        if (__builtin_amdgcn_ballot_w64(corr != 1.0f) != 0) {   // what was summed so far moves to the new reference
-            l_part *= corr;
+        for (int c = 0; c < C; ++c) {
+            float mx = s[0][c][0];
 #pragma unroll
-            for (int t = 0; t < 4; ++t)
+            for (int v = 1; v < 8; ++v) mx = fmaxf(mx, s[v >> 2][c][v & 3]);
+            mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+            mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+            const float m_new = fmaxf(m_run[c], mx);
+            const float corr = __builtin_amdgcn_exp2f(m_run[c] - m_new);
+            m_run[c] = m_new;
+            if (__builtin_amdgcn_ballot_w64(corr != 1.0f) != 0) {   // what was summed so far moves to the new reference
+                l_part[c] *= corr;
 #pragma unroll
-                for (int v = 0; v < 16; ++v) o[t][v] *= corr;
+                for (int dt = 0; dt < AHD / 16; ++dt) o[dt][c] *= f32x4{corr, corr, corr, corr};
+            }
+#pragma unroll
+            for (int v = 0; v < 8; ++v) {
+                const float x = __builtin_amdgcn_exp2f(s[v >> 2][c][v & 3] - m_new);
+                l_part[c] += x;
+                pB[c][v] = bf16_t(x);
+            }
         }
-        bf16x8 pB[2];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const float x = __builtin_amdgcn_exp2f(s[v] - m_new);
-            l_part += x;
-            pB[v >> 3][v & 7] = bf16_t(x);
-        }
+        for (int dt = 0; dt < AHD / 16; ++dt)
 #pragma unroll
-        for (int c = 0; c < 2; ++c)
-#pragma unroll
-            for (int dt = 0; dt < 4; ++dt) o[dt] = mfma32(vA[dt][c], pB[c], o[dt]);
+            for (int c = 0; c < C; ++c) o[dt][c] = mfma16(vA[dt], pB[c], o[dt][c]);
     }
 
     // merge the waves; column n of a wave belongs to query head g*r + n
-    const float l_tot = l_part + __shfl_xor(l_part, 32, 64);
-    if (lrow < r) {
-        float* w = dlds + size_t(wave * r + lrow) * (AHD + 2);
 #pragma unroll
-        for (int dt = 0; dt < 4; ++dt)
+    for (int c = 0; c < C; ++c) {
+        float l_tot = l_part[c] + __shfl_xor(l_part[c], 16, 64);
+        l_tot += __shfl_xor(l_tot, 32, 64);
+        if (16 * c + l16 >= r) continue;
+        float* w = dlds + size_t(wave * r + 16 * c + l16) * (AHD + 2);
 #pragma unroll
-            for (int v = 0; v < 16; ++v) w[32 * dt + 8 * (v >> 2) + 4 * lhalf + (v & 3)] = o[dt][v];
-        if (lhalf == 0) { w[AHD] = m_run * 0.6931471805599453f; w[AHD + 1] = l_tot; }
+        for (int dt = 0; dt < AHD / 16; ++dt)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) w[16 * dt + 4 * lq + v] = o[dt][c][v];
+        if (lq == 0) { w[AHD] = m_run[c] * 0.6931471805599453f; w[AHD + 1] = l_tot; }
     }
     __syncthreads();
     for (int idx = tid; idx < r * AHD; idx += 64 * W) {
@@ -1211,8 +1232,9 @@ hipError_t launch_decode_attention_mfma(const float* q, float* part, int n_q, in
     const int r = n_q / kv.n_kv;
     const size_t wave_lds = size_t(r) * (AHD + 2) * sizeof(float);
     const dim3 grid(kv.n_kv, n_splits);
-    if (r <= 12) hipLaunchKernelGGL(decode_attention_mfma_kernel<8>, grid, dim3(512), 8 * wave_lds, st, q, part, n_q, n_keys, tiles_per_split, kv);
-    else hipLaunchKernelGGL(decode_attention_mfma_kernel<4>, grid, dim3(256), 4 * wave_lds, st, q, part, n_q, n_keys, tiles_per_split, kv);
+    if (r <= 12) hipLaunchKernelGGL((decode_attention_mfma_kernel<8, 1>), grid, dim3(512), 8 * wave_lds, st, q, part, n_q, n_keys, tiles_per_split, kv);
+    else if (r <= 16) hipLaunchKernelGGL((decode_attention_mfma_kernel<4, 1>), grid, dim3(256), 4 * wave_lds, st, q, part, n_q, n_keys, tiles_per_split, kv);
+    else hipLaunchKernelGGL((decode_attention_mfma_kernel<4, 2>), grid, dim3(256), 4 * wave_lds, st, q, part, n_q, n_keys, tiles_per_split, kv);
     return hipGetLastError();
 }
 
