@@ -311,8 +311,8 @@ static int enqueue_first_token(cake_ctx* c, int n_tokens, int last_id, const cak
         KLAUNCH(c, CAKE_K_GEMV, 2 * d * ff, d * ff * e, launch_gemv(m.dtype, 1, {nullptr, 0.f}, c->t_act, w.w_down, nullptr, c->x, d, ff, c->cs));
     }
     KLAUNCH(c, CAKE_K_GEMV, 2 * uint64_t(m.vocab) * d, uint64_t(m.vocab) * d * e,
-            launch_gemv(m.dtype, 0, {c->final_norm, m.rms_eps}, c->x, c->lm_head, nullptr, c->t_logits, m.vocab, d, c->cs));
-    HIP_TRY(c, launch_argmax(c->t_logits, m.vocab, c->t_argmax, token, logits_host, c->cs));
+            launch_gemv(m.dtype, 0, {c->final_norm, m.rms_eps}, c->x, c->lm_head, nullptr, c->t_logits, m.vocab, d, c->cs, nullptr, 0, logits_host));
+    HIP_TRY(c, launch_argmax(c->t_logits, m.vocab, c->t_argmax, token, c->cs));
     return CAKE_OK;
 }
 

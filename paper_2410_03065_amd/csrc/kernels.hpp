@@ -117,10 +117,10 @@ hipError_t launch_quant_pages(int dtype, void* images, size_t image_bytes, const
 // ---- first-token step (one row of activations: matrix-vector products, one-token attention) ----
 // h = x (gain null: mode 1 only) or its RMSNorm (gain, eps; modes 0, 2, 3): out[n] (mode 0: =, 1: +=) sum_k h[k] w[n][k];
 // mode 2: out[n] = silu(h.w[n]) * (h.w2[n]); mode 3: mode 0 with adjacent rows of a head rotated by cs[head_dim / 2]
-// (cos, sin).  x, out float32.
+// (cos, sin).  x, out float32.  host (mode 0): null, or pinned memory, 16-byte aligned, for a copy of the result.
 struct GemvNorm { const float* gain; float eps; };
 hipError_t launch_gemv(int dtype, int mode, const GemvNorm& nm, const float* x, const void* w, const void* w2, float* out,
-                       int N, int K, hipStream_t st, const double* cs = nullptr, int head_dim = 0);
+                       int N, int K, hipStream_t st, const double* cs = nullptr, int head_dim = 0, float* host = nullptr);
 // x = row `id` of the embedding table; cs[head_dim / 2] = (cos, sin) of the rotary pairs at position pos.
 hipError_t launch_token_begin(int dtype, const void* table, int id, float* x, int d, double* cs, int head_dim, int pos,
                               float theta, hipStream_t st);
@@ -131,7 +131,6 @@ hipError_t launch_decode_attention(int dtype, const float* q, float* out, float*
 // Device memory of launch_argmax; counter is zero between launches.
 constexpr int ARGMAX_BLOCKS = 128;
 struct ArgmaxWs { unsigned long long best[ARGMAX_BLOCKS]; unsigned counter; };
-// host: null, or pinned memory for a copy of the n values.
-hipError_t launch_argmax(const float* v, int n, ArgmaxWs* ws, int32_t* result, float* host, hipStream_t st);
+hipError_t launch_argmax(const float* v, int n, ArgmaxWs* ws, int32_t* result, hipStream_t st);
 
 }  // namespace cake

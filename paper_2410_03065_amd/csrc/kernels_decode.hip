@@ -80,6 +80,8 @@ template <> struct Ld16<bf16_t> {
 // its own: the squares are summed beside the products, the sums scaled at the end; and a wave holds both rows of a
 // rotary pair.  Where x is normed and long enough to be worth a barrier, the workgroup stages x times the gain in LDS
 // behind the first weight loads (STAGED: 2048 to 16K elements), otherwise every wave reads both from the caches.
+// The logits may go to pinned memory as well, from the waves that form them, while the others still stream: a copy by the
+// arg max afterwards took 9 us more for 128 256 values and 3 for 32 000.
 // One row per wave (two for a rotary pair; four where there are 16K rows and more).  us for the Llama3-8B shape: W_q
 // with norm and rotation 9.8 (norm 4.3, product 7.7 and rotation 4.5 as three launches), gate/up with norm 42 (4.3 and
 // 41), LM head 171 (4.3 and 182); two rows per wave took 23.1 instead of 22.7 for the down product, and a second set of
@@ -87,7 +89,7 @@ template <> struct Ld16<bf16_t> {
 template <typename T, int MODE, int RB, bool NORM, bool STAGED>
 __global__ void __launch_bounds__(256) gemv_kernel(const float* __restrict__ x, const float* __restrict__ gain, float eps,
                                                    const T* __restrict__ w, const T* __restrict__ w2, float* __restrict__ out, int N,
-                                                   int K, const double2* __restrict__ cs, int head_dim) {
+                                                   int K, const double2* __restrict__ cs, int head_dim, float* __restrict__ host) {
     constexpr int E = Ld16<T>::N, NM = MODE == 2 ? 2 : 1;
     constexpr int U = RB * NM >= 4 ? 2 : 4, PIECE = 64 * E;   // pieces in flight per row
     extern __shared__ __attribute__((aligned(16))) float xs[];
@@ -189,12 +191,16 @@ __global__ void __launch_bounds__(256) gemv_kernel(const float* __restrict__ x, 
 #pragma unroll
         for (int r = 0; r < RB; ++r) acc[m][r] = wsum(acc[m][r]) * norm;
     if (lane != 0) return;
+    if constexpr (MODE == 0 && RB == 4)
+        if (host && row0 + RB <= N) *(float4*)(host + row0) = make_float4(acc[0][0], acc[0][1], acc[0][2], acc[0][3]);
 #pragma unroll
     for (int r = 0; r < RB; ++r) {
         const int row = row0 + r;
         if (row >= N) break;
-        if constexpr (MODE == 0) out[row] = acc[0][r];
-        else if constexpr (MODE == 1) out[row] += acc[0][r];
+        if constexpr (MODE == 0) {
+            out[row] = acc[0][r];
+            if (host && (RB != 4 || row0 + RB > N)) host[row] = acc[0][r];
+        } else if constexpr (MODE == 1) out[row] += acc[0][r];
         else if constexpr (MODE == 2) out[row] = acc[0][r] / (1.0f + __expf(-acc[0][r])) * acc[1][r];
         else if ((r & 1) == 0) {   // N and the head dimension are even
             const double2 c = cs[(row % head_dim) / 2];
@@ -206,11 +212,11 @@ __global__ void __launch_bounds__(256) gemv_kernel(const float* __restrict__ x, 
 
 template <typename T, int MODE, bool NORM>
 static hipError_t gemv_launch(const GemvNorm& nm, const float* x, const void* w, const void* w2, float* out, int N, int K,
-                              const double* cs, int head_dim, hipStream_t st) {
+                              const double* cs, int head_dim, float* host, hipStream_t st) {
     constexpr int RB_MIN = MODE == 3 ? 2 : 1;
 #define CAKE_GEMV(RB, STAGED, LDS)                                                                                        \
     hipLaunchKernelGGL((gemv_kernel<T, MODE, RB, NORM, STAGED>), dim3((N + 4 * RB - 1) / (4 * RB)), dim3(256), LDS, st, x, \
-                       nm.gain, nm.eps, (const T*)w, (const T*)w2, out, N, K, (const double2*)cs, head_dim)
+                       nm.gain, nm.eps, (const T*)w, (const T*)w2, out, N, K, (const double2*)cs, head_dim, host)
     const size_t lds = size_t(K) * sizeof(float);
     if constexpr (NORM) {
         if (K >= 2048 && lds <= 65000) {
@@ -226,12 +232,12 @@ static hipError_t gemv_launch(const GemvNorm& nm, const float* x, const void* w,
 }
 
 hipError_t launch_gemv(int dtype, int mode, const GemvNorm& nm, const float* x, const void* w, const void* w2, float* out, int N,
-                       int K, hipStream_t st, const double* cs, int head_dim) {
+                       int K, hipStream_t st, const double* cs, int head_dim, float* host) {
     if (N <= 0) return hipSuccess;
-    if (K % (dtype == 0 ? 4 : 8) || mode < 0 || mode > 3 || (mode == 3 && (!cs || !nm.gain)) || (mode == 1 && nm.gain)) return hipErrorInvalidValue;
+    if (K % (dtype == 0 ? 4 : 8) || mode < 0 || mode > 3 || (mode == 3 && (!cs || !nm.gain)) || (mode == 1 && nm.gain) || (host && (mode != 0 || (uintptr_t(host) & 15)))) return hipErrorInvalidValue;
 #define CAKE_GEMV(MODE, NORM)                                                                              \
-    return dtype == 0 ? gemv_launch<float, MODE, NORM>(nm, x, w, w2, out, N, K, cs, head_dim, st)          \
-                      : gemv_launch<bf16_t, MODE, NORM>(nm, x, w, w2, out, N, K, cs, head_dim, st)
+    return dtype == 0 ? gemv_launch<float, MODE, NORM>(nm, x, w, w2, out, N, K, cs, head_dim, host, st)          \
+                      : gemv_launch<bf16_t, MODE, NORM>(nm, x, w, w2, out, N, K, cs, head_dim, host, st)
     if (mode == 1) CAKE_GEMV(1, false);
     if (mode == 3) CAKE_GEMV(3, true);
     if (!nm.gain) return hipErrorInvalidValue;   // the step's other products all follow a norm
@@ -419,32 +425,42 @@ decode_attention_kernel(const float* __restrict__ q, float* __restrict__ part, i
     }
 }
 
-// One workgroup per query head; thread d owns output element d.  The per-split (max, sum) pairs are
-// read by one lane each and reduced across the wave, so no thread walks the splits one dependent
-// load after another.
+// One workgroup per query head; thread (part, d), part < 4, adds up output element d over the splits part, part + 4, ...
+// The per-split (max, sum) pairs are read by one lane each and reduced across the first wave, so no thread walks the
+// splits one dependent load after another; a thread's first eight values are on their way meanwhile.  All latency: with one
+// thread per output element 4.8 us at 32 splits of 32 heads, 4.0 so.
 template <int HD>
-__global__ void __launch_bounds__(HD) decode_combine_kernel(const float* __restrict__ part, float* __restrict__ out,
-                                                            int n_splits) {
+__global__ void __launch_bounds__(4 * HD) decode_combine_kernel(const float* __restrict__ part, float* __restrict__ out,
+                                                                int n_splits) {
     __shared__ float coef[DEC_MAX_SPLITS];
-    __shared__ float den_s;
-    const int h = blockIdx.x, d = threadIdx.x;
+    __shared__ float den_s, sums[4][HD];
+    const int h = blockIdx.x, d = threadIdx.x % HD, quarter = threadIdx.x / HD;
     const float* p = part + size_t(h) * n_splits * (HD + 2);
-    if (d < 64) {   // first wave: splits d and d + 64
-        const float m0 = d < n_splits ? p[d * (HD + 2) + HD] : -INFINITY;
-        const float m1 = d + 64 < n_splits ? p[(d + 64) * (HD + 2) + HD] : -INFINITY;
+    float first[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) first[i] = quarter + 4 * i < n_splits ? p[(quarter + 4 * i) * (HD + 2) + d] : 0.f;
+    if (threadIdx.x < 64) {   // first wave: splits x and x + 64
+        const int x = threadIdx.x;
+        const float m0 = x < n_splits ? p[x * (HD + 2) + HD] : -INFINITY;
+        const float m1 = x + 64 < n_splits ? p[(x + 64) * (HD + 2) + HD] : -INFINITY;
+        const float l0 = x < n_splits ? p[x * (HD + 2) + HD + 1] : 0.f, l1 = x + 64 < n_splits ? p[(x + 64) * (HD + 2) + HD + 1] : 0.f;
         const float m = wmax(fmaxf(m0, m1));
-        const float c0 = d < n_splits ? __expf(m0 - m) : 0.f, c1 = d + 64 < n_splits ? __expf(m1 - m) : 0.f;
-        float den = (d < n_splits ? p[d * (HD + 2) + HD + 1] * c0 : 0.f) + (d + 64 < n_splits ? p[(d + 64) * (HD + 2) + HD + 1] * c1 : 0.f);
-        den = wsum(den);
-        coef[d] = c0;
-        coef[d + 64] = c1;
-        if (d == 0) den_s = den;
+        const float c0 = x < n_splits ? __expf(m0 - m) : 0.f, c1 = x + 64 < n_splits ? __expf(m1 - m) : 0.f;
+        const float den = wsum(l0 * c0 + l1 * c1);
+        coef[x] = c0;
+        coef[x + 64] = c1;
+        if (x == 0) den_s = den;
     }
     __syncthreads();
     float num = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+        if (quarter + 4 * i < n_splits) num += first[i] * coef[quarter + 4 * i];
 #pragma unroll 8
-    for (int s = 0; s < n_splits; ++s) num += p[s * (HD + 2) + d] * coef[s];
-    out[size_t(h) * HD + d] = num / den_s;
+    for (int s = quarter + 32; s < n_splits; s += 4) num += p[s * (HD + 2) + d] * coef[s];
+    sums[quarter][d] = num;
+    __syncthreads();
+    if (quarter == 0) out[size_t(h) * HD + d] = (sums[0][d] + sums[1][d] + sums[2][d] + sums[3][d]) / den_s;
 }
 
 int decode_attention_splits(int n_keys, int n_kv) {
@@ -494,15 +510,13 @@ hipError_t launch_decode_attention(int dtype, const float* q, float* out, float*
     else if (dtype == 1 && kv.head_dim == 128) e = decode_launch_r<bf16_t, 128>(r, grid, st, q, part, n_keys, tps, kv);
     else return hipErrorInvalidValue;
     if (e != hipSuccess) return e;
-    if (kv.head_dim == 64) hipLaunchKernelGGL(decode_combine_kernel<64>, dim3(n_q), dim3(64), 0, st, part, out, used);
-    else hipLaunchKernelGGL(decode_combine_kernel<128>, dim3(n_q), dim3(128), 0, st, part, out, used);
+    if (kv.head_dim == 64) hipLaunchKernelGGL(decode_combine_kernel<64>, dim3(n_q), dim3(256), 0, st, part, out, used);
+    else hipLaunchKernelGGL(decode_combine_kernel<128>, dim3(n_q), dim3(512), 0, st, part, out, used);
     return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ argmax over the logits
-// result[0] = index of the largest value (the lowest index among equal values); `host`, if given, gets a copy of the
-// values (pinned memory: a copy by the copy engine into the caller's pageable buffer takes 88 us for 32 000 and 241 us
-// for 128 256 values, writing them here and copying on the CPU 28 and 41 with the wait).  Workgroups take 1024-element pieces in
+// result[0] = index of the largest value (the lowest index among equal values).  Workgroups take 1024-element pieces in
 // turn and leave their best in `best`; the one that draws the last ticket looks those through and puts the counter back.
 // (One workgroup over 128 256 logits took 56 us, most of it waiting for one load after another.)
 __device__ __forceinline__ void argmax_take(float x, int i, float* best, int* idx) {
@@ -518,8 +532,7 @@ __device__ __forceinline__ void argmax_wave(float* best, int* idx) {
 }
 
 __global__ void __launch_bounds__(256) argmax_kernel(const float* __restrict__ v, int n, unsigned long long* __restrict__ best_of,
-                                                     unsigned* __restrict__ counter, int32_t* __restrict__ result,
-                                                     float* __restrict__ host) {
+                                                     unsigned* __restrict__ counter, int32_t* __restrict__ result) {
     __shared__ float bv[4];
     __shared__ int bi[4];
     __shared__ unsigned ticket;
@@ -532,7 +545,6 @@ __global__ void __launch_bounds__(256) argmax_kernel(const float* __restrict__ v
             const int at = base + threadIdx.x + 256 * i;
             if (at < n) {
                 const float x = v[at];
-                if (host) host[at] = x;
                 argmax_take(x, at, &best, &idx);
             }
         }
@@ -560,9 +572,9 @@ __global__ void __launch_bounds__(256) argmax_kernel(const float* __restrict__ v
     }
 }
 
-hipError_t launch_argmax(const float* v, int n, ArgmaxWs* ws, int32_t* result, float* host, hipStream_t st) {
+hipError_t launch_argmax(const float* v, int n, ArgmaxWs* ws, int32_t* result, hipStream_t st) {
     if (n <= 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(argmax_kernel, dim3(std::min(ARGMAX_BLOCKS, (n + 1023) / 1024)), dim3(256), 0, st, v, n, ws->best, &ws->counter, result, host);
+    hipLaunchKernelGGL(argmax_kernel, dim3(std::min(ARGMAX_BLOCKS, (n + 1023) / 1024)), dim3(256), 0, st, v, n, ws->best, &ws->counter, result);
     return hipGetLastError();
 }
 
