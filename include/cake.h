@@ -210,7 +210,8 @@ typedef struct {
 /* Priors used before the first measurement, and pacing granularity. 0 = default. */
 typedef struct {
     uint64_t prior_compute_ns, prior_compute_flops; /* default 1e9 ns per 5e14 FLOP */
-    uint64_t piece_bytes;                           /* largest single DMA; default 4 MiB */
+    uint64_t piece_bytes;                           /* largest single DMA; default 4 MiB, and
+                                                       whole images where a load is not throttled */
     int32_t kernel_path; /* 0: MFMA kernels where the shape allows (bf16); 1: generic kernels only */
     int32_t gemm_config; /* 0: tile shape chosen per GEMM; 1..7: force 256x256 / 256x128 / 128x128 / 128x192 / 128x64 /
                             128x128 with the waves dividing K / the persistent four-wave 256x256 kernel (testing) */

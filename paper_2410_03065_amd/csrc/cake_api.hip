@@ -55,6 +55,7 @@ struct cake_ctx {
     int attn_range_keys = 0;   // length of the attention launches' key ranges, 0: chosen per launch (see AttnWs)
     void* q_stage = nullptr;   // device staging for quantised page images: a ring of image slots (cake_create)
     size_t q_stage_bytes = 0;
+    bool piece_limited = false;   // the caller has set the largest copy (cake_set_tuning)
     void* w_stage = nullptr;   // one image of a store being written while loads use q_stage (null until that happens)
     size_t w_stage_bytes = 0;
     // second hop of a file-backed store: two pinned buffers of one DMA piece each
@@ -464,23 +465,42 @@ static int enqueue_load(cake_ctx* c, const cake_kv_store* st, int tok_begin, int
         }
         return CAKE_OK;
     };
-    for (int p = p0; p < p1; ++p) {
-        const uint64_t img = (from_file ? st->file_offset : uint64_t((uintptr_t)st->base)) + uint64_t(p) * st->page_stride_bytes;
-        const int pp = kv->block_table_host[p];
-        if (bits) {
-            // the whole image lands in the staging buffer, then one kernel on the copy stream
-            // dequantises it into the page of every layer; stream order keeps the two apart
-            char* stage = (char*)c->q_stage + (uint64_t(p - p0) % n_slots) * image_bytes;
-            int rc = paced_copy(stage, img, image_bytes);
-            if (rc != CAKE_OK) return rc;
-            HIP_TRY(c, launch_dequant_page(m.dtype, stage, make_view(c, kv, 0), pp, m.n_layers, bits, c->ls));
+    const KvView view = make_view(c, kv, 0);
+    const uint64_t base = from_file ? st->file_offset : uint64_t((uintptr_t)st->base);
+    // Unthrottled, from memory: whole images, as many as the ring holds, in one copy and one kernel.  Each copy costs 9 us
+    // beyond its bytes, and each change from copy to kernel and back as much; the pieces only serve the pacing.  4096
+    // tokens of four Llama3-8B layers, us, page by page and so: pages of 256 raw 1781 and 1351, 8 bits 958 and 711, 4 bits
+    // 669 and 405; pages of 64 raw 3579 and 1359, 8 bits 1939 and 716.
+    const uint64_t n_fit = bits ? n_slots : import_pages_supported(c->q_stage, layer_bytes, view) ? c->q_stage_bytes / image_bytes : 0;
+    const bool runs = fixed_gbps == 0 && !from_file && !c->piece_limited && n_fit > 0;
+    const int per = runs ? int(std::min<uint64_t>(n_fit, PageRun::MAX)) : 1;
+    for (int p = p0; p < p1; p += per) {
+        const uint64_t img = base + uint64_t(p) * st->page_stride_bytes;
+        if (!runs && !bits) {
+            for (int l = 0; l < m.n_layers; ++l) {
+                char* dst = (char*)kv->pool + (uint64_t(l) * kv->n_physical_pages + kv->block_table_host[p]) * layer_bytes;
+                int rc = paced_copy(dst, img + uint64_t(l) * layer_bytes, layer_bytes);
+                if (rc != CAKE_OK) return rc;
+            }
             continue;
         }
-        for (int l = 0; l < m.n_layers; ++l) {
-            char* dst = (char*)kv->pool + (uint64_t(l) * kv->n_physical_pages + pp) * layer_bytes;
-            int rc = paced_copy(dst, img + uint64_t(l) * layer_bytes, layer_bytes);
+        // images land in the staging buffer, then one kernel on the copy stream brings them into the pages of every
+        // layer; stream order keeps the two apart
+        PageRun run{std::min(per, p1 - p), {}};
+        for (int k = 0; k < run.n; ++k) run.phys[k] = kv->block_table_host[p + k];
+        char* stage = (char*)c->q_stage + (runs ? 0 : (uint64_t(p - p0) % n_slots) * image_bytes);
+        if (!runs) {
+            int rc = paced_copy(stage, img, image_bytes);
             if (rc != CAKE_OK) return rc;
+        } else {
+            const bool whole = st->page_stride_bytes == image_bytes;
+            for (int k = 0; k < (whole ? 1 : run.n); ++k)
+                HIP_TRY(c, hipMemcpyAsync(stage + k * image_bytes, (const void*)(uintptr_t)(img + k * st->page_stride_bytes),
+                                          whole ? run.n * image_bytes : image_bytes, hipMemcpyHostToDevice, c->ls));
+            c->load_bytes_done.fetch_add(run.n * image_bytes, std::memory_order_relaxed);
         }
+        if (bits) HIP_TRY(c, launch_dequant_pages(m.dtype, stage, image_bytes, view, run, m.n_layers, bits, c->ls));
+        else HIP_TRY(c, launch_import_pages(stage, image_bytes, view, run, layer_bytes, m.n_layers, c->ls));
     }
     return CAKE_OK;
 }
@@ -661,6 +681,7 @@ int32_t cake_set_tuning(cake_ctx* c, const cake_tuning* t) {
         if (t->piece_bytes < 4096) return fail(c, CAKE_E_INVAL, "piece_bytes below 4096");
         c->tun.piece_bytes = t->piece_bytes;
         c->load_thread.wait();   // a queued load may be using the staging buffers this resizes
+        c->piece_limited = true;
         int rc = ensure_file_stage(c, t->piece_bytes);
         if (rc != CAKE_OK) return rc;
     }

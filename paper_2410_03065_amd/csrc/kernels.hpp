@@ -108,8 +108,14 @@ hipError_t launch_decode_attention_mfma(const float* q, float* part, int n_q, in
                                         int n_splits, const KvView& kv, hipStream_t st);
 
 // ---- quantised stored KV (bits = 8 or 4): a page image (all layers) <-> the layer pages of a physical page ----
-hipError_t launch_dequant_page(int dtype, const void* image, const KvView& kv, int phys_page, int n_layers, int bits,
-                               hipStream_t st);
+// Images side by side in device memory and the physical page of each.
+struct PageRun { static constexpr int MAX = 32; int n; int32_t phys[MAX]; };
+hipError_t launch_dequant_pages(int dtype, const void* images, size_t image_bytes, const KvView& kv, const PageRun& run, int n_layers,
+                                int bits, hipStream_t st);
+// the same for raw images (images and pool 16-byte aligned, layer pages of whole 16 KB)
+bool import_pages_supported(const void* images, size_t layer_bytes, const KvView& kv);
+hipError_t launch_import_pages(const void* images, size_t image_bytes, const KvView& kv, const PageRun& run, size_t layer_bytes,
+                               int n_layers, hipStream_t st);
 // logical pages [first_page, first_page + n_pages) -> images, image_bytes apart.  to_host: the images are pinned memory,
 // which few workgroups fill at the link's rate (only where supported).
 bool quant_pages_to_host_supported(int dtype, const void* images, size_t image_bytes, const KvView& kv);

@@ -29,20 +29,21 @@ template <> __device__ __forceinline__ float qto_f<bf16_t>(bf16_t v) { return fl
 __device__ __forceinline__ int nibble(unsigned b, int n) { return (int(b << (28 - 4 * n))) >> 28; }
 }  // namespace
 
-// One page image -> layer pages.  grid.x: (layer, K|V, kv_head); grid.y: 64-token tiles of the page.
+// Page images, image_bytes apart -> layer pages.  grid.x: (layer, K|V, kv_head); grid.y: 64-token tiles of the page;
+// grid.z: images.
 template <typename T, int HD, int BITS>
 __global__ void __launch_bounds__(256)
-dequant_page_kernel(const unsigned char* __restrict__ image, KvView kv, int phys_page, int n_layers) {
+dequant_page_kernel(const unsigned char* __restrict__ images, size_t image_bytes, KvView kv, PageRun run) {
     __shared__ float tile[64][HD + 1];
     constexpr int ROWB = HD * BITS / 8;          // code bytes per token row
     const int pt = kv.page_tokens, n_kv = kv.n_kv;
     const int g = blockIdx.x % n_kv, which = (blockIdx.x / n_kv) & 1, layer = blockIdx.x / (2 * n_kv);
     const int t0 = blockIdx.y * 64;
     const size_t slab = size_t(n_kv) * pt * (ROWB + 4);
-    const unsigned char* base = image + (size_t(layer) * 2 + which) * slab;
+    const unsigned char* base = images + blockIdx.z * image_bytes + (size_t(layer) * 2 + which) * slab;
     const unsigned char* codes = base + (size_t(g) * pt + t0) * ROWB;
     const float* scales = (const float*)(base + size_t(n_kv) * pt * ROWB) + size_t(g) * pt + t0;
-    T* page = (T*)kv.pool + (size_t(layer) * kv.n_physical_pages + phys_page) * kv.page_elems();
+    T* page = (T*)kv.pool + (size_t(layer) * kv.n_physical_pages + run.phys[blockIdx.z]) * kv.page_elems();
     // 64 tokens x HD elements, 4 per thread per pass (coalesced 4- or 2-byte reads)
     for (int idx = threadIdx.x * 4; idx < 64 * HD; idx += 256 * 4) {
         const int t = idx / HD, e = idx % HD;
@@ -83,17 +84,17 @@ typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 q_bf16x8;
 
 template <int HD, int BITS>
 __global__ void __launch_bounds__(256)
-dequant_page_bf16_kernel(const unsigned char* __restrict__ image, KvView kv, int phys_page) {
+dequant_page_bf16_kernel(const unsigned char* __restrict__ images, size_t image_bytes, KvView kv, PageRun run) {
     __shared__ unsigned tile[64][HD / 2 + 1];     // bf16 pairs
     constexpr int ROWB = HD * BITS / 8, LPR = HD / 8, RPP = 256 / LPR;
     const int pt = kv.page_tokens, n_kv = kv.n_kv;
     const int g = blockIdx.x % n_kv, which = (blockIdx.x / n_kv) & 1, layer = blockIdx.x / (2 * n_kv);
     const int t0 = blockIdx.y * 64;
     const size_t slab = size_t(n_kv) * pt * (ROWB + 4);
-    const unsigned char* base = image + (size_t(layer) * 2 + which) * slab;
+    const unsigned char* base = images + blockIdx.z * image_bytes + (size_t(layer) * 2 + which) * slab;
     const unsigned char* codes = base + (size_t(g) * pt + t0) * ROWB;
     const float* scales = (const float*)(base + size_t(n_kv) * pt * ROWB) + size_t(g) * pt + t0;
-    bf16_t* page = (bf16_t*)kv.pool + (size_t(layer) * kv.n_physical_pages + phys_page) * kv.page_elems();
+    bf16_t* page = (bf16_t*)kv.pool + (size_t(layer) * kv.n_physical_pages + run.phys[blockIdx.z]) * kv.page_elems();
     const int e0 = (threadIdx.x % LPR) * 8, r0 = threadIdx.x / LPR;
     uint2 c[64 / RPP];
     float sc[64 / RPP];
@@ -215,26 +216,26 @@ quant_pages_bf16_kernel(unsigned char* __restrict__ images, size_t image_bytes, 
 }
 
 template <int BITS>
-static hipError_t launch_dequant_bits(int dtype, const unsigned char* img, const KvView& kv, int phys_page, int n_layers,
-                                      hipStream_t st) {
-    dim3 grid(n_layers * 2 * kv.n_kv, kv.page_tokens / 64), block(256);
-    const bool wide = ((uintptr_t(img) | uintptr_t(kv.pool)) & 15) == 0;   // 8- and 16-byte accesses
-    if (dtype == 0 && kv.head_dim == 64) hipLaunchKernelGGL((dequant_page_kernel<float, 64, BITS>), grid, block, 0, st, img, kv, phys_page, n_layers);
-    else if (dtype == 0 && kv.head_dim == 128) hipLaunchKernelGGL((dequant_page_kernel<float, 128, BITS>), grid, block, 0, st, img, kv, phys_page, n_layers);
-    else if (dtype == 1 && kv.head_dim == 64 && wide) hipLaunchKernelGGL((dequant_page_bf16_kernel<64, BITS>), grid, block, 0, st, img, kv, phys_page);
-    else if (dtype == 1 && kv.head_dim == 128 && wide) hipLaunchKernelGGL((dequant_page_bf16_kernel<128, BITS>), grid, block, 0, st, img, kv, phys_page);
-    else if (dtype == 1 && kv.head_dim == 64) hipLaunchKernelGGL((dequant_page_kernel<bf16_t, 64, BITS>), grid, block, 0, st, img, kv, phys_page, n_layers);
-    else if (dtype == 1 && kv.head_dim == 128) hipLaunchKernelGGL((dequant_page_kernel<bf16_t, 128, BITS>), grid, block, 0, st, img, kv, phys_page, n_layers);
+static hipError_t launch_dequant_bits(int dtype, const unsigned char* img, size_t image_bytes, const KvView& kv, const PageRun& run,
+                                      int n_layers, hipStream_t st) {
+    dim3 grid(n_layers * 2 * kv.n_kv, kv.page_tokens / 64, run.n), block(256);
+    const bool wide = ((uintptr_t(img) | uintptr_t(kv.pool) | image_bytes) & 15) == 0;   // 8- and 16-byte accesses
+    if (dtype == 0 && kv.head_dim == 64) hipLaunchKernelGGL((dequant_page_kernel<float, 64, BITS>), grid, block, 0, st, img, image_bytes, kv, run);
+    else if (dtype == 0 && kv.head_dim == 128) hipLaunchKernelGGL((dequant_page_kernel<float, 128, BITS>), grid, block, 0, st, img, image_bytes, kv, run);
+    else if (dtype == 1 && kv.head_dim == 64 && wide) hipLaunchKernelGGL((dequant_page_bf16_kernel<64, BITS>), grid, block, 0, st, img, image_bytes, kv, run);
+    else if (dtype == 1 && kv.head_dim == 128 && wide) hipLaunchKernelGGL((dequant_page_bf16_kernel<128, BITS>), grid, block, 0, st, img, image_bytes, kv, run);
+    else if (dtype == 1 && kv.head_dim == 64) hipLaunchKernelGGL((dequant_page_kernel<bf16_t, 64, BITS>), grid, block, 0, st, img, image_bytes, kv, run);
+    else if (dtype == 1 && kv.head_dim == 128) hipLaunchKernelGGL((dequant_page_kernel<bf16_t, 128, BITS>), grid, block, 0, st, img, image_bytes, kv, run);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
-hipError_t launch_dequant_page(int dtype, const void* image, const KvView& kv, int phys_page, int n_layers, int bits,
-                               hipStream_t st) {
-    if (kv.page_tokens % 64) return hipErrorInvalidValue;
-    const unsigned char* img = (const unsigned char*)image;
-    if (bits == 8) return launch_dequant_bits<8>(dtype, img, kv, phys_page, n_layers, st);
-    if (bits == 4) return launch_dequant_bits<4>(dtype, img, kv, phys_page, n_layers, st);
+hipError_t launch_dequant_pages(int dtype, const void* images, size_t image_bytes, const KvView& kv, const PageRun& run, int n_layers,
+                                int bits, hipStream_t st) {
+    if (kv.page_tokens % 64 || run.n <= 0 || run.n > PageRun::MAX) return hipErrorInvalidValue;
+    const unsigned char* img = (const unsigned char*)images;
+    if (bits == 8) return launch_dequant_bits<8>(dtype, img, image_bytes, kv, run, n_layers, st);
+    if (bits == 4) return launch_dequant_bits<4>(dtype, img, image_bytes, kv, run, n_layers, st);
     return hipErrorInvalidValue;
 }
 
@@ -353,6 +354,37 @@ hipError_t launch_export_pages(void* images, size_t image_stride, const KvView& 
     if (layer_bytes == 0 || (layer_bytes & 16383) || ((uintptr_t(images) | uintptr_t(kv.pool) | image_stride) & 15)) return hipErrorInvalidValue;
     const long items = long(layer_bytes >> 14) * n_layers * n_pages;
     hipLaunchKernelGGL(export_pages_kernel, dim3(unsigned(std::min(items, 64L))), dim3(256), 0, st, (char*)images, image_stride, kv, layer_bytes, n_layers, items);
+    return hipGetLastError();
+}
+
+// Raw images in device memory, image_bytes apart -> layer pages: 16 KB (a divisor of every layer page) per workgroup and
+// turn.  Streaming; a 256-token page of eight layers is 512 of these.
+__global__ void __launch_bounds__(256) import_pages_kernel(const char* __restrict__ images, size_t image_bytes, KvView kv, PageRun run,
+                                                           size_t layer_bytes, int n_layers) {
+    const int per_layer = int(layer_bytes >> 14), n_items = per_layer * n_layers;
+    for (int item = blockIdx.x; item < n_items; item += gridDim.x) {
+        const int layer = item / per_layer;
+        const size_t off = size_t(item % per_layer) << 14;
+        const uint4* src = (const uint4*)(images + blockIdx.y * image_bytes + layer * layer_bytes + off);
+        uint4* dst = (uint4*)((char*)kv.pool + (size_t(layer) * kv.n_physical_pages + run.phys[blockIdx.y]) * layer_bytes + off);
+        uint4 v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = src[threadIdx.x + 256 * i];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) dst[threadIdx.x + 256 * i] = v[i];
+    }
+}
+
+bool import_pages_supported(const void* images, size_t layer_bytes, const KvView& kv) {
+    return layer_bytes && (layer_bytes & 16383) == 0 && ((uintptr_t(images) | uintptr_t(kv.pool)) & 15) == 0;
+}
+
+hipError_t launch_import_pages(const void* images, size_t image_bytes, const KvView& kv, const PageRun& run, size_t layer_bytes,
+                               int n_layers, hipStream_t st) {
+    if (!import_pages_supported(images, layer_bytes, kv) || (image_bytes & 15) || run.n <= 0 || run.n > PageRun::MAX) return hipErrorInvalidValue;
+    const long items = long(layer_bytes >> 14) * n_layers;
+    hipLaunchKernelGGL(import_pages_kernel, dim3(unsigned(std::min(items, 2048L)), run.n), dim3(256), 0, st, (const char*)images, image_bytes, kv,
+                       run, layer_bytes, n_layers);
     return hipGetLastError();
 }
 
