@@ -25,7 +25,7 @@ MODES = {"bidir": 0, "compute_only": 1, "load_only": 2, "forced": 3, "greedy": 4
 SRC_COMPUTE, SRC_LOAD = 0, 1
 
 EXPORTS = [
-    "cake_create", "cake_destroy", "cake_last_error", "cake_set_tuning", "cake_prefill_chunk",
+    "cake_create", "cake_streams_overlap", "cake_destroy", "cake_last_error", "cake_set_tuning", "cake_prefill_chunk",
     "cake_load_chunk", "cake_plan_meet_point", "cake_bidirectional_prefill", "cake_set_bandwidth",
     "cake_schedule_bandwidth_step", "cake_chunk_state", "cake_sync_compute", "cake_sync_load",
     "cake_range_flops", "cake_page_image_bytes", "cake_simulate_race", "cake_op_rmsnorm",
@@ -132,6 +132,7 @@ def load_library():
     P = C.POINTER
     sig = {
         "cake_create": (i32, [P(vp), P(ModelDesc), P(Weights), i32, i32, vp, vp]),
+        "cake_streams_overlap": (i32, [vp, vp, P(i32)]),
         "cake_destroy": (i32, [vp]),
         "cake_last_error": (C.c_char_p, [vp]),
         "cake_set_tuning": (i32, [vp, P(Tuning)]),
@@ -298,7 +299,7 @@ class Engine:
         self.page_tokens = page_tokens
         self.max_tokens, self.max_chunk = max_tokens, max_chunk
         self.compute_stream = torch.cuda.Stream(device=self.dev)
-        self.copy_stream = torch.cuda.Stream(device=self.dev)
+        self.copy_stream = self._stream_beside(self.compute_stream)
         self._tensors = []
         self.with_head = with_head or (weights is not None and "lm_head" in weights)
         self._build_weights(weights, seed)
@@ -321,6 +322,19 @@ class Engine:
         if rc != OK:
             raise CakeError(rc, "cake_create")
         torch.cuda.synchronize()
+
+    def _stream_beside(self, other):
+        """A stream whose work runs beside that of `other`: torch's streams in a row are not all on hardware queues of
+        their own.  The last of eight candidates if none does."""
+        for _ in range(8):
+            s = self.torch.cuda.Stream(device=self.dev)
+            overlap = C.c_int32()
+            rc = self.lib.cake_streams_overlap(other.cuda_stream, s.cuda_stream, C.byref(overlap))
+            if rc != OK:
+                raise CakeError(rc, "cake_streams_overlap")
+            if overlap.value:
+                break
+        return s
 
     # -- weights ---------------------------------------------------------------------
     def _dev(self, a, dtype=None):

@@ -505,6 +505,50 @@ static int enqueue_load(cake_ctx* c, const cake_kv_store* st, int tok_begin, int
     return CAKE_OK;
 }
 
+// ------------------------------------------------------------------ streams side by side
+// flags: {running, let go, timed out}, pinned.  One lane that says that it runs and ends when the host lets it go or, at
+// the latest, after `ticks` of the constant-rate clock.
+static __global__ void hold_kernel(unsigned* flags, unsigned long long ticks) {
+    const unsigned long long t0 = wall_clock64();
+    __hip_atomic_store(flags, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    while (__hip_atomic_load(flags + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == 0) {
+        if (wall_clock64() - t0 > ticks) {
+            __hip_atomic_store(flags + 2, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            return;
+        }
+        __builtin_amdgcn_s_sleep(8);
+    }
+}
+static __global__ void nothing_kernel() {}
+
+// Does a kernel on b end while one on a runs?  (yes only if a's certainly still ran)
+static hipError_t streams_overlap(hipStream_t a, hipStream_t b, volatile unsigned* flags, unsigned* flags_dev, hipEvent_t ev, bool* yes) {
+    int device = 0, khz = 0;
+    hipError_t e = hipGetDevice(&device);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, device);
+    if (e != hipSuccess) return e;
+    flags[0] = flags[1] = flags[2] = 0;
+    std::atomic_thread_fence(std::memory_order_seq_cst);
+    hipLaunchKernelGGL(hold_kernel, dim3(1), dim3(1), 0, a, flags_dev, 20ull * khz);   // 20 ms
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    for (const uint64_t t0 = mono_ns(); !flags[0] && mono_ns() - t0 < 1000000000ull;) std::this_thread::yield();
+    if (flags[0]) {
+        hipLaunchKernelGGL(nothing_kernel, dim3(1), dim3(64), 0, b);
+        e = hipGetLastError();
+        if (e == hipSuccess) e = hipEventRecord(ev, b);
+        for (const uint64_t t0 = mono_ns(); e == hipSuccess && !*yes && !flags[2] && mono_ns() - t0 < 2000000ull;) {
+            const hipError_t q = hipEventQuery(ev);
+            if (q == hipSuccess) *yes = !flags[2];
+            else if (q == hipErrorNotReady) (void)hipGetLastError();
+            else e = q;
+        }
+    }
+    flags[1] = 1;
+    const hipError_t ea = hipStreamSynchronize(a), eb = hipStreamSynchronize(b);
+    return e != hipSuccess ? e : ea != hipSuccess ? ea : eb;
+}
+
 // ------------------------------------------------------------------ executor backend
 namespace {
 struct HipBackend : Backend {
@@ -646,6 +690,27 @@ int32_t cake_create(cake_ctx** out, const cake_model_desc* model, const cake_wei
         (void)prctl(PR_SET_TIMERSLACK, 1000UL, 0UL, 0UL, 0UL);   // this thread's sleeps end within ~1 us of their deadline
     });
     *out = c;
+    return CAKE_OK;
+}
+
+int32_t cake_streams_overlap(void* stream_a, void* stream_b, int32_t* overlap) {
+    if (!overlap) return CAKE_E_INVAL;
+    *overlap = 0;
+    if (stream_a == stream_b) return CAKE_OK;
+    unsigned *flags = nullptr, *flags_dev = nullptr;
+    hipEvent_t ev = nullptr;
+    bool yes = false;
+    hipError_t e = hipHostMalloc((void**)&flags, 64, hipHostMallocCoherent);
+    if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&flags_dev, flags, 0);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+    if (e == hipSuccess) e = streams_overlap((hipStream_t)stream_a, (hipStream_t)stream_b, flags, flags_dev, ev, &yes);
+    if (ev) (void)hipEventDestroy(ev);
+    if (flags) (void)hipHostFree(flags);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return CAKE_E_HIP;
+    }
+    *overlap = yes;
     return CAKE_OK;
 }
 
