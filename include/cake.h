@@ -407,9 +407,9 @@ uint64_t cake_store_image_bytes(const cake_model_desc* model, int32_t page_token
 /* Writes the pages that hold tokens [0, n_tokens) of `kv` into `dst` (pinned host, writable
  * despite the const base) in dst->format: CAKE_STORE_RAW copies, CAKE_STORE_INT8 / CAKE_STORE_INT4
  * quantise on the GPU (scale = absmax / 127 resp. / 7 per token and KV head, codes rounded half to
- * even).  Blocking, but not on loads: ranges queued by cake_load_chunk go on beside it.  Kernels write pinned memory
- * directly; other host memory, a base or stride that is no multiple of 16 bytes and quantised float32 pages go through a
- * staging buffer (of one page image, allocated by the first such call, while loads are queued).
+ * even).  Blocking, but not on loads: ranges queued by cake_load_chunk go on beside it (the first such call
+ * allocates a buffer of one page image).  Images pass through the context's staging buffer, raw ones larger than that
+ * leave the pool layer page by layer page; dst may be any host memory with any stride, pinned memory is the fast one.
  * Errors: CAKE_E_INVAL, CAKE_E_NOMEM (staging), CAKE_E_HIP. */
 int32_t cake_write_store(cake_ctx* ctx, const cake_kv* kv, int32_t n_tokens, const cake_kv_store* dst);
 

@@ -471,7 +471,7 @@ static int enqueue_load(cake_ctx* c, const cake_kv_store* st, int tok_begin, int
     // beyond its bytes, and each change from copy to kernel and back as much; the pieces only serve the pacing.  4096
     // tokens of four Llama3-8B layers, us, page by page and so: pages of 256 raw 1781 and 1351, 8 bits 958 and 711, 4 bits
     // 669 and 405; pages of 64 raw 3579 and 1359, 8 bits 1939 and 716.
-    const uint64_t n_fit = bits ? n_slots : import_pages_supported(c->q_stage, layer_bytes, view) ? c->q_stage_bytes / image_bytes : 0;
+    const uint64_t n_fit = bits ? n_slots : move_pages_supported(c->q_stage, layer_bytes, view) ? c->q_stage_bytes / image_bytes : 0;
     const bool runs = fixed_gbps == 0 && !from_file && !c->piece_limited && n_fit > 0;
     const int per = runs ? int(std::min<uint64_t>(n_fit, PageRun::MAX)) : 1;
     for (int p = p0; p < p1; p += per) {
@@ -939,18 +939,6 @@ int32_t cake_first_token(cake_ctx* c, const int32_t* token_ids, int32_t n_tokens
     return CAKE_OK;
 }
 
-// Where kernels reach `bytes` of pinned host memory, or null if it is something else (pageable, device memory).
-static char* device_view(const void* host, uint64_t bytes) {
-    hipPointerAttribute_t first{}, last{};
-    if (hipPointerGetAttributes(&first, host) != hipSuccess || hipPointerGetAttributes(&last, (const char*)host + bytes - 1) != hipSuccess) {
-        (void)hipGetLastError();   // memory that the runtime does not know
-        return nullptr;
-    }
-    const bool pinned = first.type == hipMemoryTypeHost && last.type == hipMemoryTypeHost && first.devicePointer && last.devicePointer &&
-                        uint64_t((char*)last.devicePointer - (char*)first.devicePointer) == bytes - 1;
-    return pinned ? (char*)first.devicePointer : nullptr;
-}
-
 int32_t cake_write_store(cake_ctx* c, const cake_kv* kv, int32_t n_tokens, const cake_kv_store* dst) {
     if (!c || !dst || !dst->base) return CAKE_E_INVAL;
     if (n_tokens <= 0 || n_tokens > c->max_tokens) return fail(c, CAKE_E_INVAL, "n_tokens %d outside (0, %d]", n_tokens, c->max_tokens);
@@ -964,19 +952,19 @@ int32_t cake_write_store(cake_ctx* c, const cake_kv* kv, int32_t n_tokens, const
     const uint64_t layer_bytes = uint64_t(2) * c->m.n_kv_heads * pt * c->m.head_dim * esize(c);
     const int bits = store_code_bits(dst->format);
     const KvView view = make_view(c, kv, 0);
-    // Pinned memory is written by the kernels themselves: at the link's rate, without staging and without a copy per layer
-    // page, each of which costs 9 us beyond its bytes (16 pages of 4 Llama3-8B layers in 8 bits 728 -> 656 us, raw 1775 -> 1235).
-    char* const pinned = (dst->page_stride_bytes & 15) == 0 && ((uintptr_t(dst->base) | uintptr_t(kv->pool)) & 15) == 0
-                             ? device_view(dst->base, uint64_t(n_pages - 1) * dst->page_stride_bytes + image) : nullptr;
-    if (pinned && (!bits || quant_pages_to_host_supported(c->m.dtype, pinned, dst->page_stride_bytes, view))) {
-        if (bits) HIP_TRY(c, launch_quant_pages(c->m.dtype, pinned, dst->page_stride_bytes, view, kv->block_table_host, 0, n_pages, c->m.n_layers, bits, c->cs, true));
-        else HIP_TRY(c, launch_export_pages(pinned, dst->page_stride_bytes, view, layer_bytes, c->m.n_layers, n_pages, c->cs));
-    } else if (bits) {
-        if (c->q_stage_bytes < image) c->load_thread.wait();   // queued loads use the buffer that growing frees
+    // A kernel puts images together in device memory and the copy engine takes them out, as many at a time as the staging
+    // buffer holds.  A kernel that writes the pinned memory itself is faster alone (16 pages of 4 Llama3-8B layers in 8 bits
+    // 656 us against 728), but while its stores queue for the link nothing else on the GPU gets on: a prefill of another
+    // context, 0.95 ms, took 5.5 beside a write of 5.1, and with 16 workgroups 1.9 beside one of 8.3; 1.05 so.
+    // Raw, 128 pages of 4 layers: a copy per layer page 14.4 ms, each 9 us beyond its bytes; 10.8 so, the kernel alone 9.7.
+    if (bits && c->q_stage_bytes < image) {
+        c->load_thread.wait();   // queued loads use the buffer that growing frees
         rc = ensure_stage(c, image);
         if (rc != CAKE_OK) return rc;
+    }
+    if (bits || (c->q_stage_bytes >= image && move_pages_supported(c->q_stage, layer_bytes, view))) {
         char* stage = (char*)c->q_stage;
-        int per = int(std::min<uint64_t>(uint64_t(n_pages), c->q_stage_bytes / image));
+        int per = int(std::min<uint64_t>(uint64_t(bits ? n_pages : std::min(n_pages, PageRun::MAX)), c->q_stage_bytes / image));
         if (!c->load_thread.idle() || hipStreamQuery(c->ls) != hipSuccess) {
             // a load that was queued before may still go through the ring of slots: one image at a time beside it
             (void)hipGetLastError();   // "not ready" is no error
@@ -989,11 +977,17 @@ int32_t cake_write_store(cake_ctx* c, const cake_kv* kv, int32_t n_tokens, const
             stage = (char*)c->w_stage;
             per = 1;
         }
-        // as many images at a time as the staging buffer holds: quantise, copy out, next; one stream keeps them in order
+        // images into the staging buffer, copy out, next; one stream keeps them in order
         for (int p = 0; p < n_pages; p += per) {
             const int n = std::min(per, n_pages - p);
             char* out = (char*)dst->base + uint64_t(p) * dst->page_stride_bytes;
-            HIP_TRY(c, launch_quant_pages(c->m.dtype, stage, image, view, kv->block_table_host, p, n, c->m.n_layers, bits, c->cs));
+            if (bits) {
+                HIP_TRY(c, launch_quant_pages(c->m.dtype, stage, image, view, kv->block_table_host, p, n, c->m.n_layers, bits, c->cs));
+            } else {
+                PageRun run{n, {}};
+                for (int k = 0; k < n; ++k) run.phys[k] = kv->block_table_host[p + k];
+                HIP_TRY(c, launch_export_pages(stage, image, view, run, layer_bytes, c->m.n_layers, c->cs));
+            }
             if (dst->page_stride_bytes == image) {
                 HIP_TRY(c, hipMemcpyAsync(out, stage, uint64_t(n) * image, hipMemcpyDeviceToHost, c->cs));
                 continue;
@@ -1002,7 +996,7 @@ int32_t cake_write_store(cake_ctx* c, const cake_kv* kv, int32_t n_tokens, const
                 HIP_TRY(c, hipMemcpyAsync(out + uint64_t(k) * dst->page_stride_bytes, stage + uint64_t(k) * image, image,
                                           hipMemcpyDeviceToHost, c->cs));
         }
-    } else {
+    } else {   // raw images larger than the staging buffer: a copy per layer page
         for (int p = 0; p < n_pages; ++p)
             for (int l = 0; l < c->m.n_layers; ++l) {
                 char* out = (char*)dst->base + uint64_t(p) * dst->page_stride_bytes;

@@ -112,17 +112,15 @@ hipError_t launch_decode_attention_mfma(const float* q, float* part, int n_q, in
 struct PageRun { static constexpr int MAX = 32; int n; int32_t phys[MAX]; };
 hipError_t launch_dequant_pages(int dtype, const void* images, size_t image_bytes, const KvView& kv, const PageRun& run, int n_layers,
                                 int bits, hipStream_t st);
-// the same for raw images (images and pool 16-byte aligned, layer pages of whole 16 KB)
-bool import_pages_supported(const void* images, size_t layer_bytes, const KvView& kv);
+// raw images -> pages and pages -> raw images (images and pool 16-byte aligned, layer pages of whole 16 KB)
+bool move_pages_supported(const void* images, size_t layer_bytes, const KvView& kv);
 hipError_t launch_import_pages(const void* images, size_t image_bytes, const KvView& kv, const PageRun& run, size_t layer_bytes,
                                int n_layers, hipStream_t st);
-// logical pages [first_page, first_page + n_pages) -> images, image_bytes apart.  to_host: the images are pinned memory,
-// which few workgroups fill at the link's rate (only where supported).
-bool quant_pages_to_host_supported(int dtype, const void* images, size_t image_bytes, const KvView& kv);
+hipError_t launch_export_pages(void* images, size_t image_bytes, const KvView& kv, const PageRun& run, size_t layer_bytes, int n_layers,
+                               hipStream_t st);
+// logical pages [first_page, first_page + n_pages) -> images, image_bytes apart
 hipError_t launch_quant_pages(int dtype, void* images, size_t image_bytes, const KvView& kv, const int32_t* block_table_host,
-                              int first_page, int n_pages, int n_layers, int bits, hipStream_t st, bool to_host = false);
-// the same for raw images in pinned memory, image_stride apart (pointers and stride multiples of 16 bytes)
-hipError_t launch_export_pages(void* images, size_t image_stride, const KvView& kv, size_t layer_bytes, int n_layers, int n_pages, hipStream_t st);
+                              int first_page, int n_pages, int n_layers, int bits, hipStream_t st);
 
 // ---- first-token step (one row of activations: matrix-vector products, one-token attention) ----
 // h = x (gain null: mode 1 only) or its RMSNorm (gain, eps; modes 0, 2, 3): out[n] (mode 0: =, 1: +=) sum_k h[k] w[n][k];

@@ -139,79 +139,68 @@ dequant_page_bf16_kernel(const unsigned char* __restrict__ images, size_t image_
     }
 }
 
-// Logical pages first_page + z of `kv`, z < n_pages, into images + z * image_bytes, one 64-token tile of a (layer, K|V,
-// head) after another.  The images may be pinned memory: a tile's codes and scales then leave as whole lines, and 256
-// workgroups keep the link busy (16 pages of 4 Llama3-8B layers, 34.6 MB: 64 workgroups 688 us, 128 664, 256 656, 512 655;
-// through a staging buffer and the copy engine 728).
+// Logical pages first_page + z of `kv`, z < gridDim.z, into images[z].
 template <int HD, int BITS>
 __global__ void __launch_bounds__(256)
-quant_pages_bf16_kernel(unsigned char* __restrict__ images, size_t image_bytes, KvView kv, int first_page, int n_layers, long n_items) {
+quant_pages_bf16_kernel(unsigned char* __restrict__ images, size_t image_bytes, KvView kv, int first_page) {
     __shared__ unsigned tile[64][HD / 2 + 1];
-    __shared__ float scale_of[64];
     constexpr int ROWB = HD * BITS / 8, LPR = HD / 8, RPP = 256 / LPR;
     constexpr float QMAX = BITS == 8 ? 127.0f : 7.0f;
     const int pt = kv.page_tokens, n_kv = kv.n_kv;
-    for (long item = blockIdx.x; item < n_items; item += gridDim.x) {
-        const int x = int(item % (2 * n_kv * n_layers));
-        const long yz = item / (2 * n_kv * n_layers);
-        const int g = x % n_kv, which = (x / n_kv) & 1, layer = x / (2 * n_kv);
-        const int t0 = int(yz % (pt / 64)) * 64, z = int(yz / (pt / 64));
-        const size_t slab = size_t(n_kv) * pt * (ROWB + 4);
-        unsigned char* base = images + z * image_bytes + (size_t(layer) * 2 + which) * slab;
-        unsigned char* codes = base + (size_t(g) * pt + t0) * ROWB;
-        float* scales = (float*)(base + size_t(n_kv) * pt * ROWB) + size_t(g) * pt + t0;
-        const bf16_t* page = (const bf16_t*)kv.pool + (size_t(layer) * kv.n_physical_pages + kv.block_table[first_page + z]) * kv.page_elems();
-        const int e0 = (threadIdx.x % LPR) * 8, r0 = threadIdx.x / LPR;
-        q_bf16x8 v[64 / RPP];
-        if (which == 0) {
+    const int g = blockIdx.x % n_kv, which = (blockIdx.x / n_kv) & 1, layer = blockIdx.x / (2 * n_kv);
+    const int t0 = blockIdx.y * 64;
+    const size_t slab = size_t(n_kv) * pt * (ROWB + 4);
+    unsigned char* base = images + blockIdx.z * image_bytes + (size_t(layer) * 2 + which) * slab;
+    unsigned char* codes = base + (size_t(g) * pt + t0) * ROWB;
+    float* scales = (float*)(base + size_t(n_kv) * pt * ROWB) + size_t(g) * pt + t0;
+    const bf16_t* page = (const bf16_t*)kv.pool + (size_t(layer) * kv.n_physical_pages + kv.block_table[first_page + blockIdx.z]) * kv.page_elems();
+    const int e0 = (threadIdx.x % LPR) * 8, r0 = threadIdx.x / LPR;
+    q_bf16x8 v[64 / RPP];
+    if (which == 0) {
 #pragma unroll
-            for (int i = 0; i < 64 / RPP; ++i) v[i] = *(const q_bf16x8*)(page + (size_t(g) * pt + t0 + r0 + i * RPP) * HD + e0);
-        } else {
-            const bf16_t* vpage = page + size_t(n_kv) * pt * HD + size_t(g) * HD * pt + t0;
-            bf16_t* tb = (bf16_t*)&tile[0][0];
+        for (int i = 0; i < 64 / RPP; ++i) v[i] = *(const q_bf16x8*)(page + (size_t(g) * pt + t0 + r0 + i * RPP) * HD + e0);
+    } else {
+        const bf16_t* vpage = page + size_t(n_kv) * pt * HD + size_t(g) * HD * pt + t0;
+        bf16_t* tb = (bf16_t*)&tile[0][0];
 #pragma unroll
-            for (int i = 0; i < HD * 8 / 256; ++i) {
-                const int piece = threadIdx.x + 256 * i, e = piece >> 3, t = (piece & 7) * 8;
-                const q_bf16x8 x = *(const q_bf16x8*)(vpage + size_t(e) * pt + t);
+        for (int i = 0; i < HD * 8 / 256; ++i) {
+            const int piece = threadIdx.x + 256 * i, e = piece >> 3, t = (piece & 7) * 8;
+            const q_bf16x8 x = *(const q_bf16x8*)(vpage + size_t(e) * pt + t);
 #pragma unroll
-                for (int k = 0; k < 8; ++k) tb[(t + k) * (HD + 2) + e] = x[k];
-            }
-            __syncthreads();
-#pragma unroll
-            for (int i = 0; i < 64 / RPP; ++i) {
-                unsigned w[4];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) w[k] = tile[r0 + i * RPP][e0 / 2 + k];
-                __builtin_memcpy(&v[i], w, 16);
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < 64 / RPP; ++i) {
-            const int t = r0 + i * RPP;
-            float amax = 0.f;
-#pragma unroll
-            for (int k = 0; k < 8; ++k) amax = fmaxf(amax, fabsf(float(v[i][k])));
-#pragma unroll
-            for (int o = 1; o < LPR; o <<= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 64));
-            const float scale = amax / QMAX;
-            const float safe = scale > 0.f ? scale : 1.0f;
-            unsigned out[2] = {0, 0};
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                float q = rintf(float(v[i][k]) / safe);
-                q = fminf(fmaxf(q, -QMAX), QMAX);
-                const int code = scale > 0.f ? int(q) : 0;
-                if constexpr (BITS == 8) out[k >> 2] |= (unsigned(code) & 0xFFu) << (8 * (k & 3));
-                else out[0] |= (unsigned(code) & 0xFu) << (4 * k);
-            }
-            unsigned char* dst = codes + size_t(t) * ROWB + e0 * BITS / 8;
-            if constexpr (BITS == 8) *(uint2*)dst = make_uint2(out[0], out[1]);
-            else *(unsigned*)dst = out[0];
-            if (e0 == 0) scale_of[t] = scale;
+            for (int k = 0; k < 8; ++k) tb[(t + k) * (HD + 2) + e] = x[k];
         }
         __syncthreads();
-        if (threadIdx.x < 64) scales[threadIdx.x] = scale_of[threadIdx.x];
-        __syncthreads();   // the tile and the scales are the next item's
+#pragma unroll
+        for (int i = 0; i < 64 / RPP; ++i) {
+            unsigned w[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) w[k] = tile[r0 + i * RPP][e0 / 2 + k];
+            __builtin_memcpy(&v[i], w, 16);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 64 / RPP; ++i) {
+        const int t = r0 + i * RPP;
+        float amax = 0.f;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) amax = fmaxf(amax, fabsf(float(v[i][k])));
+#pragma unroll
+        for (int o = 1; o < LPR; o <<= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 64));
+        const float scale = amax / QMAX;
+        const float safe = scale > 0.f ? scale : 1.0f;
+        unsigned out[2] = {0, 0};
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            float q = rintf(float(v[i][k]) / safe);
+            q = fminf(fmaxf(q, -QMAX), QMAX);
+            const int code = scale > 0.f ? int(q) : 0;
+            if constexpr (BITS == 8) out[k >> 2] |= (unsigned(code) & 0xFFu) << (8 * (k & 3));
+            else out[0] |= (unsigned(code) & 0xFu) << (4 * k);
+        }
+        unsigned char* dst = codes + size_t(t) * ROWB + e0 * BITS / 8;
+        if constexpr (BITS == 8) *(uint2*)dst = make_uint2(out[0], out[1]);
+        else *(unsigned*)dst = out[0];
+        if (e0 == 0) scales[t] = scale;
     }
 }
 
@@ -289,24 +278,18 @@ quant_page_kernel(unsigned char* __restrict__ image, KvView kv, int phys_page, i
     if (part == 0) scales[t] = scale;
 }
 
-bool quant_pages_to_host_supported(int dtype, const void* images, size_t image_bytes, const KvView& kv) {
-    return dtype == 1 && ((uintptr_t(images) | uintptr_t(kv.pool) | image_bytes) & 15) == 0 && (kv.head_dim == 64 || kv.head_dim == 128);
-}
-
 // images + z * image_bytes = the image of logical page first_page + z, z < n_pages (block_table_host: the physical pages,
 // for the kernel that takes one at a time).
 template <int BITS>
 static hipError_t launch_quant_bits(int dtype, unsigned char* img, size_t image_bytes, const KvView& kv, const int32_t* block_table_host,
-                                    int first_page, int n_pages, int n_layers, bool to_host, hipStream_t st) {
+                                    int first_page, int n_pages, int n_layers, hipStream_t st) {
     dim3 grid(n_layers * 2 * kv.n_kv, kv.page_tokens / 64), block(256);
-    if (quant_pages_to_host_supported(dtype, img, image_bytes, kv)) {
-        const long items = long(grid.x) * grid.y * n_pages;
-        const dim3 wgs(unsigned(to_host ? std::min(items, 256L) : std::min(items, 65536L)));
-        if (kv.head_dim == 64) hipLaunchKernelGGL((quant_pages_bf16_kernel<64, BITS>), wgs, block, 0, st, img, image_bytes, kv, first_page, n_layers, items);
-        else hipLaunchKernelGGL((quant_pages_bf16_kernel<128, BITS>), wgs, block, 0, st, img, image_bytes, kv, first_page, n_layers, items);
+    if (dtype == 1 && ((uintptr_t(img) | uintptr_t(kv.pool) | image_bytes) & 15) == 0 && (kv.head_dim == 64 || kv.head_dim == 128)) {
+        grid.z = n_pages;
+        if (kv.head_dim == 64) hipLaunchKernelGGL((quant_pages_bf16_kernel<64, BITS>), grid, block, 0, st, img, image_bytes, kv, first_page);
+        else hipLaunchKernelGGL((quant_pages_bf16_kernel<128, BITS>), grid, block, 0, st, img, image_bytes, kv, first_page);
         return hipGetLastError();
     }
-    if (to_host) return hipErrorInvalidValue;
     for (int p = 0; p < n_pages; ++p, img += image_bytes) {
         const int phys_page = block_table_host[first_page + p];
         if (dtype == 0 && kv.head_dim == 64) hipLaunchKernelGGL((quant_page_kernel<float, 64, BITS>), grid, block, 0, st, img, kv, phys_page, n_layers);
@@ -321,52 +304,28 @@ static hipError_t launch_quant_bits(int dtype, unsigned char* img, size_t image_
 }
 
 hipError_t launch_quant_pages(int dtype, void* images, size_t image_bytes, const KvView& kv, const int32_t* block_table_host, int first_page,
-                              int n_pages, int n_layers, int bits, hipStream_t st, bool to_host) {
+                              int n_pages, int n_layers, int bits, hipStream_t st) {
     if (kv.page_tokens % 64) return hipErrorInvalidValue;
     if (n_pages <= 0) return hipSuccess;
     unsigned char* img = (unsigned char*)images;
-    if (bits == 8) return launch_quant_bits<8>(dtype, img, image_bytes, kv, block_table_host, first_page, n_pages, n_layers, to_host, st);
-    if (bits == 4) return launch_quant_bits<4>(dtype, img, image_bytes, kv, block_table_host, first_page, n_pages, n_layers, to_host, st);
+    if (bits == 8) return launch_quant_bits<8>(dtype, img, image_bytes, kv, block_table_host, first_page, n_pages, n_layers, st);
+    if (bits == 4) return launch_quant_bits<4>(dtype, img, image_bytes, kv, block_table_host, first_page, n_pages, n_layers, st);
     return hipErrorInvalidValue;
 }
 
-// Raw images: the layer pages of logical pages 0 .. n_pages - 1 one after another into pinned memory, 16 KB (a divisor of
-// every layer page) per workgroup and turn.
-__global__ void __launch_bounds__(256) export_pages_kernel(char* __restrict__ images, size_t image_stride, KvView kv, size_t layer_bytes,
-                                                           int n_layers, long n_items) {
-    const int per_layer = int(layer_bytes >> 14);
-    for (long item = blockIdx.x; item < n_items; item += gridDim.x) {
-        const int part = int(item % per_layer), layer = int(item / per_layer % n_layers);
-        const size_t page = size_t(item / per_layer / n_layers);
-        const size_t off = size_t(part) << 14;
-        const uint4* src = (const uint4*)((const char*)kv.pool + (size_t(layer) * kv.n_physical_pages + kv.block_table[page]) * layer_bytes + off);
-        uint4* dst = (uint4*)(images + page * image_stride + layer * layer_bytes + off);
-        uint4 v[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = src[threadIdx.x + 256 * i];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) dst[threadIdx.x + 256 * i] = v[i];
-    }
-}
-
-hipError_t launch_export_pages(void* images, size_t image_stride, const KvView& kv, size_t layer_bytes, int n_layers, int n_pages, hipStream_t st) {
-    if (n_pages <= 0) return hipSuccess;
-    if (layer_bytes == 0 || (layer_bytes & 16383) || ((uintptr_t(images) | uintptr_t(kv.pool) | image_stride) & 15)) return hipErrorInvalidValue;
-    const long items = long(layer_bytes >> 14) * n_layers * n_pages;
-    hipLaunchKernelGGL(export_pages_kernel, dim3(unsigned(std::min(items, 64L))), dim3(256), 0, st, (char*)images, image_stride, kv, layer_bytes, n_layers, items);
-    return hipGetLastError();
-}
-
-// Raw images in device memory, image_bytes apart -> layer pages: 16 KB (a divisor of every layer page) per workgroup and
+// Raw images in device memory, image_bytes apart <-> layer pages: 16 KB (a divisor of every layer page) per workgroup and
 // turn.  Streaming; a 256-token page of eight layers is 512 of these.
-__global__ void __launch_bounds__(256) import_pages_kernel(const char* __restrict__ images, size_t image_bytes, KvView kv, PageRun run,
-                                                           size_t layer_bytes, int n_layers) {
+template <bool EXPORT>
+__global__ void __launch_bounds__(256) move_pages_kernel(char* __restrict__ images, size_t image_bytes, KvView kv, PageRun run,
+                                                         size_t layer_bytes, int n_layers) {
     const int per_layer = int(layer_bytes >> 14), n_items = per_layer * n_layers;
     for (int item = blockIdx.x; item < n_items; item += gridDim.x) {
         const int layer = item / per_layer;
         const size_t off = size_t(item % per_layer) << 14;
-        const uint4* src = (const uint4*)(images + blockIdx.y * image_bytes + layer * layer_bytes + off);
-        uint4* dst = (uint4*)((char*)kv.pool + (size_t(layer) * kv.n_physical_pages + run.phys[blockIdx.y]) * layer_bytes + off);
+        uint4* image = (uint4*)(images + blockIdx.y * image_bytes + layer * layer_bytes + off);
+        uint4* page = (uint4*)((char*)kv.pool + (size_t(layer) * kv.n_physical_pages + run.phys[blockIdx.y]) * layer_bytes + off);
+        const uint4* src = EXPORT ? page : image;
+        uint4* dst = EXPORT ? image : page;
         uint4 v[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) v[i] = src[threadIdx.x + 256 * i];
@@ -375,17 +334,27 @@ __global__ void __launch_bounds__(256) import_pages_kernel(const char* __restric
     }
 }
 
-bool import_pages_supported(const void* images, size_t layer_bytes, const KvView& kv) {
+bool move_pages_supported(const void* images, size_t layer_bytes, const KvView& kv) {
     return layer_bytes && (layer_bytes & 16383) == 0 && ((uintptr_t(images) | uintptr_t(kv.pool)) & 15) == 0;
+}
+
+template <bool EXPORT>
+static hipError_t launch_move_pages(char* images, size_t image_bytes, const KvView& kv, const PageRun& run, size_t layer_bytes, int n_layers,
+                                    hipStream_t st) {
+    if (!move_pages_supported(images, layer_bytes, kv) || (image_bytes & 15) || run.n <= 0 || run.n > PageRun::MAX) return hipErrorInvalidValue;
+    const long items = long(layer_bytes >> 14) * n_layers;
+    hipLaunchKernelGGL(move_pages_kernel<EXPORT>, dim3(unsigned(std::min(items, 2048L)), run.n), dim3(256), 0, st, images, image_bytes, kv, run,
+                       layer_bytes, n_layers);
+    return hipGetLastError();
 }
 
 hipError_t launch_import_pages(const void* images, size_t image_bytes, const KvView& kv, const PageRun& run, size_t layer_bytes,
                                int n_layers, hipStream_t st) {
-    if (!import_pages_supported(images, layer_bytes, kv) || (image_bytes & 15) || run.n <= 0 || run.n > PageRun::MAX) return hipErrorInvalidValue;
-    const long items = long(layer_bytes >> 14) * n_layers;
-    hipLaunchKernelGGL(import_pages_kernel, dim3(unsigned(std::min(items, 2048L)), run.n), dim3(256), 0, st, (const char*)images, image_bytes, kv,
-                       run, layer_bytes, n_layers);
-    return hipGetLastError();
+    return launch_move_pages<false>((char*)images, image_bytes, kv, run, layer_bytes, n_layers, st);
+}
+hipError_t launch_export_pages(void* images, size_t image_bytes, const KvView& kv, const PageRun& run, size_t layer_bytes, int n_layers,
+                               hipStream_t st) {
+    return launch_move_pages<true>((char*)images, image_bytes, kv, run, layer_bytes, n_layers, st);
 }
 
 }  // namespace cake
