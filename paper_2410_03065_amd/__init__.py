@@ -283,7 +283,9 @@ class PrefillResult:
 
 class Engine:
     """Owns the device tensors (weights in ABI layout, KV pool, block tables), the pinned
-    store and the two streams, and forwards to the C ABI."""
+    store and the two streams, and forwards to the C ABI.  The op_* calls wait for what torch's current
+    stream was given before them (their operands come from there); the others do not: synchronise
+    after torch has written to the pool."""
 
     def __init__(self, shape, weights=None, *, max_tokens, max_chunk, page_tokens=256, block_table=None,
                  n_physical_pages=None, device="cuda:0", seed=0, with_head=False):
@@ -524,6 +526,7 @@ class Engine:
         a tensor made beforehand so that nothing is allocated around the call either."""
         if out is None:
             out = self.torch.empty_like(q)
+        self._operands()
         fn = self.lib.cake_op_decode_attention_static if static else self.lib.cake_op_decode_attention
         self._check(fn(self.ctx, q.data_ptr(), out.data_ptr(), layer, n_keys, C.byref(self.kv)),
                     "cake_op_decode_attention_static" if static else "cake_op_decode_attention")
@@ -658,8 +661,14 @@ class Engine:
         self._check(self.lib.cake_sync_load(self.ctx), "cake_sync_load")
 
     # -- single kernels (tensors are torch device tensors) -----------------------------
+    def _operands(self):
+        """The engine's streams are not ordered after torch's, which may still be writing an op's operands, or reading
+        the memory that its result has just been given."""
+        self.torch.cuda.current_stream(self.dev).synchronize()
+
     def op_rmsnorm(self, x, gain):
         out = self.torch.empty(x.shape, dtype=self.tdtype, device=self.dev)
+        self._operands()
         self._check(self.lib.cake_op_rmsnorm(self.ctx, x.data_ptr(), gain.data_ptr(), out.data_ptr(), x.shape[0],
                                              x.shape[1]), "cake_op_rmsnorm")
         self.sync()
@@ -667,12 +676,14 @@ class Engine:
 
     def op_gemm(self, a, w):
         out = self.torch.empty((a.shape[0], w.shape[0]), dtype=self.torch.float32, device=self.dev)
+        self._operands()
         self._check(self.lib.cake_op_gemm(self.ctx, a.data_ptr(), w.data_ptr(), out.data_ptr(), a.shape[0], w.shape[0],
                                           a.shape[1]), "cake_op_gemm")
         self.sync()
         return out
 
     def op_gemm_residual(self, a, w, x):
+        self._operands()
         self._check(self.lib.cake_op_gemm_residual(self.ctx, a.data_ptr(), w.data_ptr(), x.data_ptr(), a.shape[0],
                                                    w.shape[0], a.shape[1]), "cake_op_gemm_residual")
         self.sync()
@@ -687,6 +698,7 @@ class Engine:
 
     def op_gemm_swiglu(self, a, wg, wu):
         out = self.torch.empty((a.shape[0], wg.shape[0]), dtype=self.tdtype, device=self.dev)
+        self._operands()
         self._check(self.lib.cake_op_gemm_swiglu(self.ctx, a.data_ptr(), wg.data_ptr(), wu.data_ptr(), out.data_ptr(),
                                                  a.shape[0], wg.shape[0], a.shape[1]), "cake_op_gemm_swiglu")
         self.sync()
@@ -695,6 +707,7 @@ class Engine:
     def op_rope_kv_write(self, qkv, layer, tok_begin):
         rows = qkv.shape[0]
         q = self.torch.empty((self.shape.n_q, rows, self.shape.head_dim), dtype=self.tdtype, device=self.dev)
+        self._operands()
         self._check(self.lib.cake_op_rope_kv_write(self.ctx, qkv.data_ptr(), q.data_ptr(), layer, tok_begin, rows,
                                                    C.byref(self.kv)), "cake_op_rope_kv_write")
         self.sync()
@@ -703,6 +716,7 @@ class Engine:
     def op_attention(self, q, layer, tok_begin):
         rows = q.shape[1]
         out = self.torch.empty((rows, self.shape.n_q * self.shape.head_dim), dtype=self.tdtype, device=self.dev)
+        self._operands()
         self._check(self.lib.cake_op_attention(self.ctx, q.data_ptr(), out.data_ptr(), layer, tok_begin, rows,
                                                C.byref(self.kv)), "cake_op_attention")
         self.sync()

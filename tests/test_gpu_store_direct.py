@@ -102,6 +102,7 @@ def test_another_context_computes_beside_a_write(fmt):
         assert b.lib.cake_streams_overlap(a.compute_stream.cuda_stream, b.compute_stream.cuda_stream, ctypes.byref(overlap)) == 0
     toks = si.make_tokens(2048, shape.vocab, seed=1)
     a.pool.normal_()
+    torch.cuda.synchronize()
     store = a.write_store(T, f).numpy()
     first, last = store[0, :256].copy(), store[-1, -256:].copy()
     b.prefill_chunk(toks, 1024, 1024)

@@ -1,5 +1,5 @@
 """An engine's loads run beside its compute step also where the streams that torch deals out in a row meet on one of the
-runtime's four hardware queues."""
+runtime's four hardware queues; and its ops wait for operands that torch's stream has yet to write."""
 import ctypes
 
 import pytest
@@ -67,3 +67,36 @@ def test_streams_overlap():
     assert found == [[a is not b and _beside(a, b) for b in streams] for a in streams]
     assert sum(map(sum, found)) < 30                          # six streams on four queues: some meet
     assert lib.cake_streams_overlap(streams[0].cuda_stream, streams[1].cuda_stream, None) == cake.E_INVAL
+
+
+def test_ops_wait_for_their_operands():
+    import torch
+    import paper_2410_03065_amd as cake
+    shape = si.ModelShape("operands", 1, 256, 4, 2, 64, 256, 64, "bf16")
+    while True:                                               # on one hardware queue they would wait by chance
+        eng = cake.Engine(shape, None, max_tokens=128, max_chunk=64, page_tokens=64, with_head=True)
+        if _beside(torch.cuda.default_stream(), eng.compute_stream):
+            break
+    eng.pool.normal_()
+    rnd = lambda dtype, *dims: torch.randn(*dims, device="cuda").to(dtype)
+    bf, f32 = torch.bfloat16, torch.float32
+    a, w, x, q, q1, qkv = rnd(bf, 64, 256), rnd(bf, 256, 256), rnd(f32, 64, 256), rnd(bf, 4, 64, 64), rnd(f32, 4, 64), rnd(f32, 64, 512)
+    gain = torch.ones(256, device="cuda")
+    ops = {"rmsnorm": (x, lambda t: eng.op_rmsnorm(t, gain)), "gemm": (a, lambda t: eng.op_gemm(t, w)),
+           "gemm_residual": (a, lambda t: eng.op_gemm_residual(t, w, x.clone())), "gemm_swiglu": (a, lambda t: eng.op_gemm_swiglu(t, w, w)),
+           "attention": (q, lambda t: eng.op_attention(t, 0, 0)), "decode_attention": (q1, lambda t: eng.op_decode_attention(t, 0, 128)),
+           "rope_kv_write": (qkv, lambda t: eng.op_rope_kv_write(t, 0, 64))}   # last: it writes to the pool
+    wrong = []
+    for name, (operand, op) in ops.items():
+        torch.cuda.synchronize()
+        want = op(operand).clone()
+        late = torch.zeros_like(operand)
+        torch.cuda.synchronize()
+        torch.cuda._sleep(HELD)
+        late.copy_(operand)
+        got = op(late)
+        torch.cuda.synchronize()
+        assert float(want.abs().max()) > 0
+        if not torch.equal(got, want):
+            wrong.append(name)
+    assert not wrong, wrong
