@@ -673,11 +673,28 @@ static hipError_t launch_gemm_tile_parts(int bn, const void* a, const void* w, f
     return hipErrorInvalidValue;
 }
 
-// The same unit (about a microsecond) for the kernels that leave K ranges to a consumer, plus what the ranges cost
-// there.  Persistent kernel: 1.40 us per slice and item; 128 x 128 tiles 0.585, 128 x 192 0.71; the ranges written at about
-// 10 TB/s; few rows: a slice takes 0.24 us + 0.075 us per 32 rows, HBM delivers the weights at 5.3 TB/s, L2 the tiles at
-// 10, or 0.05 per workgroup.  A pass of its own that adds the ranges up reads and writes the result too; whole tiles are
-// left to one only where that promises a tenth (128 x 128, 128 x 192) or a sixth.  Both sides measured, us (the second without the consumer's part):
+// What a launch of launch_gemm_mfma takes, us: a slice of the tile, a round beyond its slices, the ticket of a launch that
+// splits K (which writes its parts and reads them back).  A launch of fewer workgroups than CUs runs its slices up to a fifth
+// faster (L2).  Fitted to 868 measured launches (23 shapes of 512 to 20480 x 2048 to 15360, 64 to 1024 rows), 4 to 13 % off in
+// the mean.  gemm_pick's prices, which only have to rank tiles, are up to 60 % above these.
+static double chip_fill(long wgs) { return 0.8 + 0.2 * double(wgs) / double((wgs + 255) / 256 * 256); }
+static double plain_launch_us(const GemmChoice& ch, int epi, int M, int N, int K) {
+    static const struct { double slice, round, ticket; } price[GCFG_COUNT] = {{1.75, 3.0, 0.0}, {1.0, 3.0, 14.0}, {0.555, 2.7, 14.0}, {0.80, 3.0, 14.0},
+                                                                             {0.42, 2.4, 6.0}, {0.555, 2.7, 14.0}, {1.10, 4.0, 0.0}, {0.80, 3.0, 14.0}};
+    const GemmCfg& c = kGemmCfg[ch.cfg];
+    const auto& p = price[ch.cfg];
+    const long wgs = long((M + c.bm - 1) / c.bm) * (N / c.bn) * ch.ksplit;
+    return double((wgs + 255) / 256) * (double(K) / 64 / ch.ksplit * p.slice * chip_fill(wgs) + p.round) + (ch.ksplit > 1 ? p.ticket : 0.0) +
+           (epi == EPI_RESIDUAL_F32 ? double(M) * N * 2e-6 : 0.0);
+}
+
+// K ranges on the kernel for few rows: a slice takes 0.24 us + 0.075 us per 32 rows, HBM delivers the weights at 5.3 TB/s, L2
+// the tiles at 10, or 0.05 per workgroup; a pass of its own that adds the ranges up reads and writes the result too.
+// Whole tiles beyond that (kWhole): where the consumer adds the ranges up, against gemm_pick's price; where a pass does,
+// fitted to the same 23 shapes in two to eight ranges, against plain_launch_us, of which they must save a tenth.  Over those
+// 868 launches a choice then takes 2.8 % more than the best one (of plain and all ranges), and 17 of them 3 % more than plain
+// (against gemm_pick's prices it was 4.2 % and 60, with 512 rows of 2048 -> 2048 at 20.7 us instead of 12.3).
+// Both sides measured, us (the second without the consumer's part):
 // down 8B (K = 14336 -> 4096) 1024 rows 133 and 87 in four ranges, 512 rows 81 and 51 in eight, 64 rows 40 and 24 in eight;
 // down 70B 1024 rows 434 and 334 in two, 512 rows 284 and 183 in four; O 8B 512 rows 40 and 24 (128 x 128, two), 137 rows
 // 32 and 16; QKV 8B 320 rows 37 and 27 (128 x 192, two), 137 rows 29 and 18; 512 rows of 8192 -> 2048 42 and 24 (128 x 128,
@@ -688,11 +705,10 @@ static hipError_t launch_gemm_tile_parts(int bn, const void* a, const void* w, f
 GemmPartsPlan gemm_parts_plan(int epi, int M, int N, int K, const GemmSplitWs* ws, bool fused, bool rows_only) {
     GemmPartsPlan best{0, GEMM_PARTS_ROWS};
     if (epi == EPI_SWIGLU || !ws || !ws->part || M <= 0 || K % 64 || N % 128 || N < 2048) return best;
-    double plain_us;
-    const GemmChoice plain = gemm_pick(epi, M, N, K, ws, &plain_us);
-    double best_us = plain_us * 0.95;
+    double pick_cost;
+    const GemmChoice plain = gemm_pick(epi, M, N, K, ws, &pick_cost);
+    double best_us = pick_cost * 0.95;
     const double out_mb = double(M) * N * 4e-6;
-    auto after = [&](int ks, double rate, double pass) { return (ks * out_mb + (fused ? 0.0 : 2.0 * out_mb)) / rate + (fused ? 0.0 : pass) + ks * out_mb / 10.0; };
     auto fits = [&](int ks) { return size_t(ks) * M * N * 4 <= ws->part_bytes; };
     auto take = [&](int ks, GemmPartsKind kind, double us) {
         if (us < best_us) { best_us = us; best = GemmPartsPlan{ks, kind}; }
@@ -705,34 +721,32 @@ GemmPartsPlan gemm_parts_plan(int epi, int M, int N, int K, const GemmSplitWs* w
             const double tiles = N / 128, rounds = double((long(tiles) * ks + 255) / 256);
             if (bm >= 160 && tiles * ks < 160) continue;   // 137 and 192 rows of 11008 -> 4096 in four: 41 and 47 us, 38 and 42 without
             const double l2_rate = std::min(10.0, 0.05 * tiles * ks);   // TB/s
-            take(ks, GEMM_PARTS_ROWS, after(ks, 4.5, 4.0) + std::max(rounds * (slices * (0.24 + 0.075 * (bm / 32)) + 4.0),
-                                                           std::max(double(N) * K * 2e-6 / 5.3 + 2.0, (bm + 128.0) * K * 2e-6 * tiles / l2_rate + 3.0)));
+            const double after = (ks * out_mb + (fused ? 0.0 : 2.0 * out_mb)) / 4.5 + (fused ? 0.0 : 4.0) + ks * out_mb / 10.0;
+            take(ks, GEMM_PARTS_ROWS, after + std::max(rounds * (slices * (0.24 + 0.075 * (bm / 32)) + 4.0),
+                                                       std::max(double(N) * K * 2e-6 / 5.3 + 2.0, (bm + 128.0) * K * 2e-6 * tiles / l2_rate + 3.0)));
         }
     if (rows_only || (best.ksplit && M <= 192)) return best;
-    // Whole tiles.  A launch of fewer workgroups than CUs runs its slices up to a fifth faster (L2); gemm_pick's price of a
-    // small tile split by ticket is one to be beaten by a tenth, here is what it takes.
-    auto fill = [](long wgs) { return 0.8 + 0.2 * double(wgs) / double((wgs + 255) / 256 * 256); };
+    // us per slice, per round, per MB of ranges, per MB of result and once; [1]: with a pass of its own
+    struct Price { double slice, round, range_mb, out_mb, once; };
+    static const struct { GemmPartsKind kind; int bm, bn; Price price[2]; } kWhole[3] = {
+        {GEMM_PARTS_P256, 256, 256, {{1.40, 4.0, 1 / 4.5 + 1 / 10.0, 0.0, 0.0}, {1.26, 0.0, 0.340, 0.04, 9.5}}},
+        {GEMM_PARTS_128, 128, 128, {{0.60, 4.0, 1 / 4.5 + 1 / 10.0, 0.0, 0.0}, {0.53, 0.0, 0.577, 0.04, 4.7}}},
+        {GEMM_PARTS_192, 128, 192, {{0.72, 4.0, 1 / 4.5 + 1 / 10.0, 0.0, 0.0}, {0.67, 0.0, 0.484, 0.04, 5.2}}}};
     if (!fused) {
-        const GemmCfg& c = kGemmCfg[plain.cfg];
-        const long tiles = long((M + c.bm - 1) / c.bm) * (N / c.bn);
-        const double area = c.bm * c.bn / 65536.0;
-        if (plain.ksplit > 1 && area <= 0.25) plain_us = plain_us / 1.08 - 10.0 - 20.0 * plain.ksplit * area + 8.0;
-        plain_us *= fill(tiles * plain.ksplit);
-        // unsplit tiles that fill the chip: 1024 rows of down 8B 133 us, 87 + 18 in four ranges with a pass of their own
-        if (plain.ksplit == 1 && fill(tiles) > 0.98) plain_us *= 0.85;
+        // Unsplit 128 x 128 tiles, one to every CU, keep the order of their sums unless ranges save a third (1024 rows of 14336 ->
+        // 4096 137 us, in four ranges it would be 107).
+        const bool one_each = plain.cfg == GCFG_128x128K && plain.ksplit == 1 && chip_fill(long((M + 127) / 128) * (N / 128)) > 0.98;
+        best_us = plain_launch_us(plain, epi, M, N, K) * (one_each ? 0.67 : 0.90);
     }
-    auto whole = [&](int ks, GemmPartsKind kind, int bm, int bn, double slice_us, double promise) {
-        const long wgs = long(M + bm - 1) / bm * (N / bn) * ks;
-        const double us = after(ks, fused ? 4.5 : 6.0, 2.5) + double((wgs + 255) / 256) * (std::ceil(double(K) / 64 / ks) * slice_us * fill(wgs) + 4.0);
-        if (us < plain_us * promise) take(ks, kind, us);
-    };
-    for (int ks = 1; ks <= 8; ++ks) {
-        if (K / 64 < ks || !fits(ks)) continue;
-        if (N % 256 == 0 && gemm_cfg_ok(GCFG_P256, EPI_STORE_F32, M, N, K)) whole(ks, GEMM_PARTS_P256, 256, 256, 1.40, fused ? 0.95 : 0.83);
-        if (K % (64 * ks)) continue;
-        whole(ks, GEMM_PARTS_128, 128, 128, 0.60, fused ? 0.95 : 0.90);
-        if (N % 192 == 0) whole(ks, GEMM_PARTS_192, 128, 192, 0.72, fused ? 0.95 : 0.90);
-    }
+    for (int ks = fused ? 1 : 2; ks <= 8; ++ks)
+        for (const auto& t : kWhole) {
+            if (N % t.bn || K / 64 < ks || !fits(ks)) continue;
+            if (t.kind == GEMM_PARTS_P256 ? !gemm_cfg_ok(GCFG_P256, EPI_STORE_F32, M, N, K) : K % (64 * ks) != 0) continue;
+            const Price& p = t.price[!fused];
+            const long wgs = long(M + t.bm - 1) / t.bm * (N / t.bn) * ks;
+            take(ks, t.kind, double((wgs + 255) / 256) * (std::ceil(double(K) / 64 / ks) * p.slice * chip_fill(wgs) + p.round) +
+                                 ks * out_mb * p.range_mb + (epi == EPI_RESIDUAL_F32 ? 2.0 : 1.0) * out_mb * p.out_mb + p.once);
+        }
     return best;
 }
 
