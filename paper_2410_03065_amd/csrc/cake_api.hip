@@ -405,6 +405,11 @@ static int pread_all(cake_ctx* c, int fd, void* dst, uint64_t n, uint64_t off) {
     return CAKE_OK;
 }
 
+// Raw layer pages from which on a run of images goes through the staging buffer and a kernel, 13 us with the change from one
+// to the other, instead of as a copy per layer page, 9 us each beyond its bytes (us, copies and so: one layer page of 256 KB
+// loaded 22 and 35, written 14 and 27; two of 256 KB 31 and 34, of 1 MB 45 and 49; four of 256 KB 59 and 49, 56 and 41).
+constexpr int MOVE_MIN_PAGES = 3;
+
 // fixed_gbps > 0: that rate; == 0: unthrottled; < 0: the context's live rate.
 static int enqueue_load(cake_ctx* c, const cake_kv_store* st, int tok_begin, int tok_count, const cake_kv* kv,
                         double fixed_gbps) {
@@ -470,23 +475,27 @@ static int enqueue_load(cake_ctx* c, const cake_kv_store* st, int tok_begin, int
     // Unthrottled, from memory: whole images, as many as the ring holds, in one copy and one kernel.  Each copy costs 9 us
     // beyond its bytes, and each change from copy to kernel and back as much; the pieces only serve the pacing.  4096
     // tokens of four Llama3-8B layers, us, page by page and so: pages of 256 raw 1781 and 1351, 8 bits 958 and 711, 4 bits
-    // 669 and 405; pages of 64 raw 3579 and 1359, 8 bits 1939 and 716.
+    // 669 and 405; pages of 64 raw 3579 and 1359, 8 bits 1939 and 716.  Raw images pay with a pass through HBM: four prefills
+    // of 1024 tokens beside four such loads take 7480 us instead of 7320 (7290 alone) in pages of 256, 7500 instead of 8060 in
+    // pages of 64; where loads are the longer half, 16 beside them take 24.1 ms instead of 28.4, in pages of 64 24 instead of 57.
     const uint64_t n_fit = bits ? n_slots : move_pages_supported(c->q_stage, layer_bytes, view) ? c->q_stage_bytes / image_bytes : 0;
     const bool runs = fixed_gbps == 0 && !from_file && !c->piece_limited && n_fit > 0;
     const int per = runs ? int(std::min<uint64_t>(n_fit, PageRun::MAX)) : 1;
     for (int p = p0; p < p1; p += per) {
         const uint64_t img = base + uint64_t(p) * st->page_stride_bytes;
-        if (!runs && !bits) {
-            for (int l = 0; l < m.n_layers; ++l) {
-                char* dst = (char*)kv->pool + (uint64_t(l) * kv->n_physical_pages + kv->block_table_host[p]) * layer_bytes;
-                int rc = paced_copy(dst, img + uint64_t(l) * layer_bytes, layer_bytes);
-                if (rc != CAKE_OK) return rc;
-            }
+        const int n = std::min(per, p1 - p);
+        if (!bits && (!runs || n * m.n_layers < MOVE_MIN_PAGES)) {
+            for (int k = 0; k < n; ++k)
+                for (int l = 0; l < m.n_layers; ++l) {
+                    char* dst = (char*)kv->pool + (uint64_t(l) * kv->n_physical_pages + kv->block_table_host[p + k]) * layer_bytes;
+                    int rc = paced_copy(dst, img + uint64_t(k) * st->page_stride_bytes + uint64_t(l) * layer_bytes, layer_bytes);
+                    if (rc != CAKE_OK) return rc;
+                }
             continue;
         }
         // images land in the staging buffer, then one kernel on the copy stream brings them into the pages of every
         // layer; stream order keeps the two apart
-        PageRun run{std::min(per, p1 - p), {}};
+        PageRun run{n, {}};
         for (int k = 0; k < run.n; ++k) run.phys[k] = kv->block_table_host[p + k];
         char* stage = (char*)c->q_stage + (runs ? 0 : (uint64_t(p - p0) % n_slots) * image_bytes);
         if (!runs) {
@@ -952,6 +961,15 @@ int32_t cake_write_store(cake_ctx* c, const cake_kv* kv, int32_t n_tokens, const
     const uint64_t layer_bytes = uint64_t(2) * c->m.n_kv_heads * pt * c->m.head_dim * esize(c);
     const int bits = store_code_bits(dst->format);
     const KvView view = make_view(c, kv, 0);
+    auto copy_layer_pages = [&](int p0, int n) -> int {
+        for (int p = p0; p < p0 + n; ++p)
+            for (int l = 0; l < c->m.n_layers; ++l) {
+                char* out = (char*)dst->base + uint64_t(p) * dst->page_stride_bytes;
+                const char* src = (const char*)kv->pool + (uint64_t(l) * kv->n_physical_pages + kv->block_table_host[p]) * layer_bytes;
+                HIP_TRY(c, hipMemcpyAsync(out + uint64_t(l) * layer_bytes, src, layer_bytes, hipMemcpyDeviceToHost, c->cs));
+            }
+        return CAKE_OK;
+    };
     // A kernel puts images together in device memory and the copy engine takes them out, as many at a time as the staging
     // buffer holds.  A kernel that writes the pinned memory itself is faster alone (16 pages of 4 Llama3-8B layers in 8 bits
     // 656 us against 728), but while its stores queue for the link nothing else on the GPU gets on: a prefill of another
@@ -983,10 +1001,14 @@ int32_t cake_write_store(cake_ctx* c, const cake_kv* kv, int32_t n_tokens, const
             char* out = (char*)dst->base + uint64_t(p) * dst->page_stride_bytes;
             if (bits) {
                 HIP_TRY(c, launch_quant_pages(c->m.dtype, stage, image, view, kv->block_table_host, p, n, c->m.n_layers, bits, c->cs));
-            } else {
+            } else if (n * c->m.n_layers >= MOVE_MIN_PAGES) {
                 PageRun run{n, {}};
                 for (int k = 0; k < n; ++k) run.phys[k] = kv->block_table_host[p + k];
                 HIP_TRY(c, launch_export_pages(stage, image, view, run, layer_bytes, c->m.n_layers, c->cs));
+            } else {
+                rc = copy_layer_pages(p, n);
+                if (rc != CAKE_OK) return rc;
+                continue;
             }
             if (dst->page_stride_bytes == image) {
                 HIP_TRY(c, hipMemcpyAsync(out, stage, uint64_t(n) * image, hipMemcpyDeviceToHost, c->cs));
@@ -996,13 +1018,9 @@ int32_t cake_write_store(cake_ctx* c, const cake_kv* kv, int32_t n_tokens, const
                 HIP_TRY(c, hipMemcpyAsync(out + uint64_t(k) * dst->page_stride_bytes, stage + uint64_t(k) * image, image,
                                           hipMemcpyDeviceToHost, c->cs));
         }
-    } else {   // raw images larger than the staging buffer: a copy per layer page
-        for (int p = 0; p < n_pages; ++p)
-            for (int l = 0; l < c->m.n_layers; ++l) {
-                char* out = (char*)dst->base + uint64_t(p) * dst->page_stride_bytes;
-                const char* src = (const char*)kv->pool + (uint64_t(l) * kv->n_physical_pages + kv->block_table_host[p]) * layer_bytes;
-                HIP_TRY(c, hipMemcpyAsync(out + uint64_t(l) * layer_bytes, src, layer_bytes, hipMemcpyDeviceToHost, c->cs));
-            }
+    } else {   // raw images larger than the staging buffer
+        rc = copy_layer_pages(0, n_pages);
+        if (rc != CAKE_OK) return rc;
     }
     HIP_TRY(c, hipStreamSynchronize(c->cs));
     return CAKE_OK;

@@ -1,6 +1,7 @@
 """Unthrottled loads bring whole images, several to a copy and a kernel, into the pages; paced ones go piece by piece.  Both
 leave the same bits in the range's pages and none elsewhere: ranges of fewer and more pages than the staging buffer and a
-launch hold, a staging buffer under a raw image, a stride larger than an image, pageable memory."""
+launch hold, runs whose last part is copied layer page by layer page (10 + 10 + 1 pages), a staging buffer under a raw
+image, a stride larger than an image, pageable memory."""
 import numpy as np
 import pytest
 
@@ -11,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("memory", ["pinned", "stride", "pageable"])
 @pytest.mark.parametrize("fmt", ["RAW", "INT8", "INT4"])
-@pytest.mark.parametrize("kind,hd,n_kv,layers,pt,pages,chunk_pages", [("bf16", 64, 1, 1, 64, 71, 70), ("bf16", 128, 3, 2, 128, 9, 3),
+@pytest.mark.parametrize("kind,hd,n_kv,layers,pt,pages,chunk_pages", [("bf16", 64, 1, 1, 64, 71, 70), ("bf16", 64, 1, 1, 64, 21, 19), ("bf16", 128, 3, 2, 128, 9, 3),
                                                                      ("f32", 64, 2, 2, 64, 6, 4), ("bf16", 128, 2, 3, 64, 3, 1)])
 def test_unthrottled_and_paced_loads_are_alike(kind, hd, n_kv, layers, pt, pages, chunk_pages, fmt, memory):
     import ctypes

@@ -14,9 +14,9 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("fmt", ["RAW", "INT8", "INT4"])
-@pytest.mark.parametrize("kind,hd,n_kv,layers,pt,T", [("bf16", 64, 1, 1, 64, 64), ("bf16", 64, 3, 2, 128, 500),
+@pytest.mark.parametrize("kind,hd,n_kv,layers,pt,T", [("bf16", 64, 1, 1, 64, 64), ("bf16", 64, 1, 1, 64, 1344), ("bf16", 64, 3, 2, 128, 500),
                                                       ("bf16", 128, 8, 2, 256, 1300), ("f32", 64, 2, 2, 64, 300)])
-@pytest.mark.parametrize("chunk_pages", [1, 4])              # a raw image is larger than the staging buffer, and fits it
+@pytest.mark.parametrize("chunk_pages", [1, 8])              # a raw image is larger than the staging buffer, and fits it
 def test_pinned_and_staged_stores_are_alike(fmt, kind, hd, n_kv, layers, pt, T, chunk_pages):
     import torch
     import paper_2410_03065_amd as cake
