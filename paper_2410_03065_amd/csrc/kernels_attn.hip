@@ -363,8 +363,11 @@ attention_mfma_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, in
 // wave whose scores are being formed beside the exponentials (vector work above the MFMAs') and one that only adds P V up,
 // at lower priority.  Together they overlap, where two waves in the same phase first compete for the vector unit and then
 // leave it idle (6 % more; with 32x32x16 MFMAs it gained nothing).  The maximum that is only compared with the reference
-// is taken on integers (2 %).  494 -> 439 us for that launch, 1.23 PFLOP/s; 1024 rows at 15360 250 -> 222; 509 rows of
-// 32 KV heads at 7003 78 -> 72.  What bounds it now: one LDS read per two MFMAs, 3.5 vector instructions per two, one of
+// is taken on integers (2 %).  Launches of few pairs are all fixed cost, so the last step forms no scores, row sums cross
+// lanes without LDS and both columns' parts are read before either is stored (the first with 32x32x16 MFMAs, then these
+// without and with that, us: 64 rows of 32 heads on 8 at 0 6.9, 7.3, 6.8, at 500 11.7, 12.4, 11.6; 1024 at 0 21.4, 21.2,
+// 20.4).  494 -> 427 us for the launch above, 1.27 PFLOP/s; 1024 rows at 16000 250 -> 221; 509 rows of
+// 32 KV heads at 7003 78 -> 70.  What bounds it now: one LDS read per two MFMAs, 3.5 vector instructions per two, one of
 // them an exponential; a loop of just these on two waves per SIMD sustains 1.34 PFLOP/s.
 //
 // LDS: K ring of 2 x (two 16 KB tiles) and V^T ring of 2 x (two 16 KB tiles).  K of a tile pair
@@ -423,7 +426,7 @@ attention_mfma8_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, f
     for (int c = 0; c < 2; ++c) {
         const int x = q0 + wave * 32 + 16 * c + l16, my_query = min(x, n_queries - 1);
         is_query[c] = x < n_queries;
-        my_row[c] = my_query / rr;
+        my_row[c] = rr == 1 ? my_query : my_query / rr;
         h[c] = head0 + (my_query - my_row[c] * rr);
         my_pos[c] = tok_begin + my_row[c];
     }
@@ -583,13 +586,17 @@ attention_mfma8_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, f
         of[1] = __uint_as_float(a[1]);
     };
 
-    // iteration i: this group's tile 2i+grp is in K slot i&1 (scores already formed) and V slot i&1
-    auto step = [&](int i, f32x4 (*s_cur)[2], f32x4 (*s_nxt)[2]) {
+    // iteration i: this group's tile 2i+grp is in K slot i&1 (scores already formed) and V slot i&1.  The last one forms no
+    // further scores (a launch of one pair: 0.5 us less)
+    auto step = [&](auto last_step, int i, f32x4 (*s_cur)[2], f32x4 (*s_nxt)[2]) {
+        constexpr bool LAST = decltype(last_step)::value;
         asm volatile("s_waitcnt vmcnt(0)");
         __builtin_amdgcn_s_barrier();
-        if (i + 1 < n_pairs) issue_v(i + 1);
-        if (i + 2 < n_pairs) issue_k(i + 2);
-        const unsigned char* stk = lds + ((i + 1) & 1) * A8_RING;   // past the last pair: stale, result unused
+        if constexpr (!LAST) {
+            issue_v(i + 1);
+            if (i + 2 < n_pairs) issue_k(i + 2);
+        }
+        const unsigned char* stk = lds + ((i + 1) & 1) * A8_RING;
         const unsigned char* stv = lds + (i & 1) * A8_RING;
         bf16x8 opa[4], opb[4], p[4];   // p[2 j + c]
         auto read_k = [&](bf16x8* dst, int ks) {
@@ -622,15 +629,20 @@ attention_mfma8_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, f
                 p[u][e] = bf16_t(x);
             }
         };
-        read_k(opa, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        read_k(opb, 1); mma_k(opa, 0); expo(0);
-        __builtin_amdgcn_sched_barrier(0);
-        read_k(opa, 2); mma_k(opb, 1); expo(1);
-        __builtin_amdgcn_sched_barrier(0);
-        read_k(opb, 3); mma_k(opa, 2); expo(2);
-        __builtin_amdgcn_sched_barrier(0);
-        read_v(opa, 0); mma_k(opb, 3);
+        if constexpr (LAST) {
+            read_v(opa, 0);
+            expo(0); expo(1); expo(2);
+        } else {
+            read_k(opa, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            read_k(opb, 1); mma_k(opa, 0); expo(0);
+            __builtin_amdgcn_sched_barrier(0);
+            read_k(opa, 2); mma_k(opb, 1); expo(1);
+            __builtin_amdgcn_sched_barrier(0);
+            read_k(opb, 3); mma_k(opa, 2); expo(2);
+            __builtin_amdgcn_sched_barrier(0);
+            read_v(opa, 0); mma_k(opb, 3);
+        }
         // the probabilities are only consumed after the branch below; pin them here, or the compiler
         // sinks the exponentials out of the block whose MFMAs they are meant to overlap with
 #pragma unroll
@@ -641,33 +653,34 @@ attention_mfma8_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, f
             __builtin_amdgcn_s_barrier();
             __builtin_amdgcn_s_setprio(0);
         }
-        const int next_tile = 2 * (i + 1) + grp;
-        // blanks tiles past the end, and what was formed from a stale slot after the range's last pair
-        if (next_tile >= first_masked || (SPLIT && i + 1 >= n_pairs)) {
-            const bool real = !SPLIT || i + 1 < n_pairs;
-            const int last_visible[2] = {real ? my_pos[0] : -1, real ? my_pos[1] : -1};
-            mask_tile(s_nxt, next_tile, last_visible);
+        if constexpr (!LAST) {
+            const int next_tile = 2 * (i + 1) + grp;
+            if (next_tile >= first_masked) mask_tile(s_nxt, next_tile, my_pos);   // tiles past the end are blanked too
         }
         int raw[2];
         read_v(opb, 1);
         mma_v(opa, 0);
         expo(3);
-        raw[0] = part_top(s_nxt, 0, 0, __float_as_int(s_nxt[0][0][0]));
-        raw[0] = part_top(s_nxt, 0, 2, raw[0]);
+        if constexpr (!LAST) {
+            raw[0] = part_top(s_nxt, 0, 0, __float_as_int(s_nxt[0][0][0]));
+            raw[0] = part_top(s_nxt, 0, 2, raw[0]);
+        }
         __builtin_amdgcn_sched_barrier(0);
         read_v(opa, 2);
         mma_v(opb, 1);
-        raw[1] = part_top(s_nxt, 1, 0, __float_as_int(s_nxt[0][1][0]));
-        raw[1] = part_top(s_nxt, 1, 2, raw[1]);
+        if constexpr (!LAST) {
+            raw[1] = part_top(s_nxt, 1, 0, __float_as_int(s_nxt[0][1][0]));
+            raw[1] = part_top(s_nxt, 1, 2, raw[1]);
+        }
         __builtin_amdgcn_sched_barrier(0);
         read_v(opb, 3);
         mma_v(opa, 2);
-        raw_cur = row_top(raw);
+        if constexpr (!LAST) raw_cur = row_top(raw);
         __builtin_amdgcn_sched_barrier(0);
         mma_v(opb, 3);
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (QW == 4) __builtin_amdgcn_s_setprio(1);
-        if (__builtin_amdgcn_ballot_w64(raw_cur > RESCALE_LOG2) != 0) {
+        if (!LAST && __builtin_amdgcn_ballot_w64(raw_cur > RESCALE_LOG2) != 0) {
             float delta[2];
             spread(raw_cur, delta);
 #pragma unroll
@@ -726,22 +739,32 @@ attention_mfma8_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, f
         }
     }
     if (QW == 4 && grp == 1) __builtin_amdgcn_s_barrier();   // half a step behind; the first half makes up for it at the end
+    const std::integral_constant<bool, false> more;
+    const std::integral_constant<bool, true> last;
     int pair = pair_lo;
-    for (; pair + 1 < n_pairs; pair += 2) {   // two to a trip, so that the score buffers alternate without copies
-        step(pair, s_a, s_b);
-        step(pair + 1, s_b, s_a);
+    for (; pair + 2 < n_pairs; pair += 2) {   // two to a trip, so that the score buffers alternate without copies
+        step(more, pair, s_a, s_b);
+        step(more, pair + 1, s_b, s_a);
     }
-    if (pair < n_pairs) step(pair, s_a, s_b);
+    if (pair + 1 < n_pairs) {
+        step(more, pair++, s_a, s_b);
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) s_a[t][c] = s_b[t][c];
+    }
+    step(last, pair, s_a, s_b);
     if (QW == 4 && grp == 0) __builtin_amdgcn_s_barrier();
 
     // merge the two key halves: group B parks (O, l, reference) in LDS, group A combines and stores
     __syncthreads();
     float* park = (float*)lds + size_t(wave) * 68 * 64 + lane;
     float l_row[2];   // of the whole row, all of its lanes
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-        l_row[c] = l_part[c] + __shfl_xor(l_part[c], 32, 64);
-        l_row[c] += __shfl_xor(l_row[c], 16, 64);
+    {
+        const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_part[0]), __float_as_uint(l_part[1]), false, false);
+        const float y = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+        const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(y), __float_as_uint(y), false, false);
+        spread(__uint_as_float(b[0]) + __uint_as_float(b[1]), l_row);
     }
     if (grp == 1) {
 #pragma unroll
@@ -758,31 +781,42 @@ attention_mfma8_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ out, f
     }
     __syncthreads();
     if (grp == 0) {
+        float ca[2], cb[2], m[2], l_tot[2], inv[2];
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
             const float l_b = park[(64 + c) * 64];
             const float m_b = l_b > 0.f ? park[(66 + c) * 64] : -1.0e30f;         // a half that saw no key has no reference
-            const float m = fmaxf(m_run[c], m_b);
-            const float ca = __builtin_amdgcn_exp2f(m_run[c] - m), cb = __builtin_amdgcn_exp2f(m_b - m);
+            m[c] = fmaxf(m_run[c], m_b);
+            ca[c] = __builtin_amdgcn_exp2f(m_run[c] - m[c]);
+            cb[c] = __builtin_amdgcn_exp2f(m_b - m[c]);
             // (sums written as fmaf, so that both instantiations round them alike)
-            const float l_tot = __builtin_fmaf(l_row[c], ca, l_b * cb);
-            auto merged = [&](int t, int v) { return __builtin_fmaf(o[t][c][v], ca, park[(8 * t + 4 * c + v) * 64] * cb); };
+            l_tot[c] = __builtin_fmaf(l_row[c], ca[c], l_b * cb[c]);
+            inv[c] = SPLIT ? 1.0f : 1.0f / l_tot[c];
+        }
+        // before the branches, so that the columns do not wait for their reads one after the other
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) o[t][c][v] = __builtin_fmaf(o[t][c][v], ca[c], park[(8 * t + 4 * c + v) * 64] * cb[c]);
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
             if (!is_query[c]) continue;
             if constexpr (SPLIT) {
                 float* p = my_part(c);
 #pragma unroll
                 for (int t = 0; t < 8; ++t)
 #pragma unroll
-                    for (int v = 0; v < 4; v += 2) *(float2*)(p + t * 16 + 4 * lq + v) = make_float2(merged(t, v), merged(t, v + 1));
-                if (lq == 0) *(float2*)(p + AHD) = make_float2(l_tot > 0.f ? m * 0.6931471805599453f : -FLT_MAX, l_tot);
+                    for (int v = 0; v < 4; v += 2) *(float2*)(p + t * 16 + 4 * lq + v) = make_float2(o[t][c][v], o[t][c][v + 1]);
+                if (lq == 0) *(float2*)(p + AHD) = make_float2(l_tot[c] > 0.f ? m[c] * 0.6931471805599453f : -FLT_MAX, l_tot[c]);
             } else {
-                const float inv = 1.0f / l_tot;
                 bf16_t* op = out + size_t(my_row[c]) * n_q * AHD + h[c] * AHD;
 #pragma unroll
                 for (int t = 0; t < 8; ++t) {
                     bf16x4 w;
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) w[v] = bf16_t(merged(t, v) * inv);
+                    for (int v = 0; v < 4; ++v) w[v] = bf16_t(o[t][c][v] * inv[c]);
                     *(bf16x4*)(op + t * 16 + 4 * lq) = w;
                 }
             }
