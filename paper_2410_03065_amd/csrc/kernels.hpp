@@ -30,7 +30,7 @@ hipError_t launch_rmsnorm(int dtype, const float* x, const float* gain, void* ou
                           float eps, hipStream_t st);
 hipError_t launch_rope_table(float* cs, int tok_begin, int rows, int head_dim, float theta,
                              hipStream_t st);
-// n_parts > 1: qkv[n_parts][rows][...] is added up as it is read (bf16, head_dim 128, 16-byte aligned pointers only).
+// n_parts > 1: qkv[n_parts][rows][...] is added up as it is read (16-byte aligned pointers only).
 hipError_t launch_rope_kv_write(int dtype, const float* qkv, const float* cs, void* q, int n_q,
                                 int tok_begin, int rows, const KvView& kv, hipStream_t st, int n_parts = 1);
 // x += parts[0] + ... + parts[n_parts - 1] (each [rows][d], float32, 16-byte aligned), then the norm of the sum.

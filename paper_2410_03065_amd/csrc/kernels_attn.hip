@@ -1276,12 +1276,15 @@ bool attention_mfma_supported(int head_dim, int page_tokens) {
     return head_dim == AHD && page_tokens % AK == 0;
 }
 
-// How a launch is divided: queries per workgroup (32 qw) and key ranges, by the time of the busiest CU.  A pair of key
-// tiles takes a workgroup (one per CU) about 1.98 us with 128 queries and 1.40 with 64 or fewer (512 rows x 32 heads
-// over 8000 keys and 1024 over 15360, measured), a workgroup 5.5 us beyond its pairs, 9.5 where it leaves a part; key
-// ranges cost the merge kernel and their parts' way through memory (about 4 bytes per ps each way).  32 heads on 8 KV heads,
-// us undivided and divided, merge included: 8 rows at 4000 keys 55 and 15, 39 rows at 14000 174 and 28, 137 rows at
-// 4000 46 and 28; 509 rows of 32 KV heads at 7003 90 and 79.
+// How a launch is divided: queries per workgroup (32 qw) and key ranges, by the time of the busiest CU: a workgroup (one per
+// CU) takes 1.98 us a pair of key tiles with 128 queries and 1.40 with 64 or fewer, 5.5 beyond its pairs, 9.5 where it leaves a
+// part; key ranges cost the merge kernel and their parts' way through memory (about 4 bytes per ps each way).  These are
+// prices of the kernel with 32x32x16 MFMAs.  The present one takes 1.42 us a pair (128 queries) and 1.23 (64, 32) and 7.1, 5.2
+// and 4.7 beyond them, 1.54, 1.36 and 1.36 and 10.2, 8.6 and 8.2 where it leaves a part; over 490 launches (32 heads on 8 and 32,
+// 64 on 8, 40 on 40, 24 on 8; 1 to 1024 rows behind 0 to 31744 keys) a choice takes 2.1 % more than the best, the worst 25 %
+// (200 rows of 32 KV heads at 2000: 27.7 us, 22.2 in two ranges).  us undivided and divided, merge included, 32 heads on 8 KV
+// heads: 8 rows at 4000 keys 50 and 17, 33 rows at 16000 175 and 29, 137 rows at 4000 53 and 26; 509 rows of 32 KV heads at
+// 8000 101 and 73.
 constexpr int A_LDS_MAX = 160 * 1024;
 struct AttnPlan { int qw, splits, per; };   // 32 qw queries per workgroup, key ranges of `per` pairs
 static AttnPlan attn_plan(int n_q, int n_kv, int tok_begin, int rows, const AttnWs& ws, int force_qw) {

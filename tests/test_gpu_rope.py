@@ -38,3 +38,34 @@ def test_rope_pieces(kind, hd, n_q, n_kv, tok_begin, rows):
     assert np.all(np.abs(q - want_q) <= tol * np.abs(want_q) + 1e-6)
     assert np.all(np.abs(got - want) <= tol * np.abs(want) + 1e-6)
     np.testing.assert_array_equal(got[:, :, 1], want[:, :, 1])            # V is a copy
+
+
+@pytest.mark.parametrize("kind,hd", [("f32", 64), ("f32", 128), ("bf16", 64), ("bf16", 128)])
+@pytest.mark.parametrize("odd", ["pool", "q", "qkv"])
+def test_rope_of_pointers_off_16_bytes(kind, hd, odd):
+    """One element off 16 bytes the kernel of single elements runs: the same bits."""
+    import ctypes
+    import torch
+    import paper_2410_03065_amd as cake
+    n_q, n_kv, pt, tok_begin, rows = 6, 2, 64, 77, 211
+    shape = si.ModelShape("rope-odd", 1, 256, n_q, n_kv, hd, 512, 64, kind)
+    pages = (tok_begin + rows + pt - 1) // pt
+    bt = np.random.default_rng(2).permutation(pages).astype(np.int32)
+    eng = cake.Engine(shape, None, max_tokens=pages * pt, max_chunk=pages * pt, page_tokens=pt, block_table=bt)
+    qkv = torch.from_numpy(np.random.default_rng(rows).standard_normal((rows, (n_q + 2 * n_kv) * hd)).astype(np.float32)).cuda()
+
+    def run(offset):
+        def place(n, dtype, here):
+            t = torch.full((n + 4,), 3.0, dtype=dtype, device="cuda")
+            return t[1:n + 1] if here else t[:n]
+        pool = place(eng.pool.numel(), eng.tdtype, offset == "pool")
+        q = place(n_q * rows * hd, eng.tdtype, offset == "q")
+        x = place(qkv.numel(), torch.float32, offset == "qkv")
+        x.copy_(qkv.flatten())
+        kv = cake.Kv(pool.data_ptr(), eng.block_table_host.ctypes.data, eng.block_table_dev.data_ptr(), pt, pages, pages)
+        torch.cuda.synchronize()
+        assert eng.lib.cake_op_rope_kv_write(eng.ctx, x.data_ptr(), q.data_ptr(), 0, tok_begin, rows, ctypes.byref(kv)) == 0
+        eng.sync()
+        return q.cpu(), pool.cpu()
+    for got, want in zip(run(odd), run(None)):
+        assert torch.equal(got, want)
