@@ -241,8 +241,8 @@ int32_t cake_create(cake_ctx** out, const cake_model_desc* model, const cake_wei
 /* *overlap = 1 if work on the one stream runs while work on the other does.  The runtime deals a process's streams out
  * over a few hardware queues (four by default), and what shares a queue runs one after another: of eight streams made in
  * a row the third and the fourth were seen on one.  A stream keeps its queue once it has been used.  Measured with a small
- * kernel on each (one that waits for the host, 20 ms at the most): both streams should be idle and not be captured; 0.1 ms
- * if they overlap, 2 ms if not.  Host pointer.  Errors: CAKE_E_INVAL, CAKE_E_HIP. */
+ * kernel on each (one that waits for the host, 20 ms at the most): both streams should be idle and not be captured; 30 us
+ * if they overlap, 0.2 ms if not.  Host pointer.  Errors: CAKE_E_INVAL, CAKE_E_HIP. */
 int32_t cake_streams_overlap(void* stream_a, void* stream_b, int32_t* overlap);
 int32_t cake_destroy(cake_ctx* ctx);
 const char* cake_last_error(const cake_ctx* ctx);

@@ -546,11 +546,14 @@ static hipError_t streams_overlap(hipStream_t a, hipStream_t b, volatile unsigne
         hipLaunchKernelGGL(nothing_kernel, dim3(1), dim3(64), 0, b);
         e = hipGetLastError();
         if (e == hipSuccess) e = hipEventRecord(ev, b);
-        for (const uint64_t t0 = mono_ns(); e == hipSuccess && !*yes && !flags[2] && mono_ns() - t0 < 2000000ull;) {
+        const uint64_t t0 = mono_ns();
+        while (e == hipSuccess && !*yes) {
+            const bool late = mono_ns() - t0 > 200000;   // before the question: a thread that was held up asks once more
             const hipError_t q = hipEventQuery(ev);
             if (q == hipSuccess) *yes = !flags[2];
             else if (q == hipErrorNotReady) (void)hipGetLastError();
             else e = q;
+            if (late || flags[2]) break;
         }
     }
     flags[1] = 1;
@@ -706,15 +709,18 @@ int32_t cake_streams_overlap(void* stream_a, void* stream_b, int32_t* overlap) {
     if (!overlap) return CAKE_E_INVAL;
     *overlap = 0;
     if (stream_a == stream_b) return CAKE_OK;
-    unsigned *flags = nullptr, *flags_dev = nullptr;
+    // one call at a time: 64 bytes of pinned memory serve them all, held until the process ends
+    static std::mutex mu;
+    static unsigned* flags = nullptr;
+    std::lock_guard<std::mutex> lock(mu);
+    unsigned* flags_dev = nullptr;
     hipEvent_t ev = nullptr;
     bool yes = false;
-    hipError_t e = hipHostMalloc((void**)&flags, 64, hipHostMallocCoherent);
+    hipError_t e = flags ? hipSuccess : hipHostMalloc((void**)&flags, 64, hipHostMallocCoherent | hipHostMallocPortable);
     if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&flags_dev, flags, 0);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
     if (e == hipSuccess) e = streams_overlap((hipStream_t)stream_a, (hipStream_t)stream_b, flags, flags_dev, ev, &yes);
     if (ev) (void)hipEventDestroy(ev);
-    if (flags) (void)hipHostFree(flags);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         return CAKE_E_HIP;

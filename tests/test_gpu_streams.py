@@ -1,5 +1,6 @@
 """An engine's loads run beside its compute step also where the streams that torch deals out in a row meet on one of the
-runtime's four hardware queues; and its ops wait for operands that torch's stream has yet to write."""
+runtime's four hardware queues, and so do the compute steps of three engines in turn; and its ops wait for operands that
+torch's stream has yet to write."""
 import ctypes
 
 import pytest
@@ -67,6 +68,17 @@ def test_streams_overlap():
     assert found == [[a is not b and _beside(a, b) for b in streams] for a in streams]
     assert sum(map(sum, found)) < 30                          # six streams on four queues: some meet
     assert lib.cake_streams_overlap(streams[0].cuda_stream, streams[1].cuda_stream, None) == cake.E_INVAL
+
+
+def test_engines_in_turn_compute_side_by_side():
+    import torch
+    import paper_2410_03065_amd as cake
+    shape = si.ModelShape("streams", 1, 256, 4, 2, 64, 256, 64, "bf16")
+    engines = [cake.Engine(shape, None, max_tokens=128, max_chunk=64, page_tokens=64) for _ in range(6)]
+    for k, e in enumerate(engines):
+        assert _beside(e.compute_stream, e.copy_stream)
+        for other in engines[max(0, k - 2):k]:
+            assert _beside(e.compute_stream, other.compute_stream)
 
 
 def test_ops_wait_for_their_operands():
