@@ -673,27 +673,35 @@ static hipError_t launch_gemm_tile_parts(int bn, const void* a, const void* w, f
     return hipErrorInvalidValue;
 }
 
-// What a launch of launch_gemm_mfma takes, us: a slice of the tile, a round beyond its slices, the ticket of a launch that
-// splits K (which writes its parts and reads them back).  A launch of fewer workgroups than CUs runs its slices up to a fifth
-// faster (L2).  Fitted to 868 measured launches (23 shapes of 512 to 20480 x 2048 to 15360, 64 to 1024 rows), 4 to 13 % off in
-// the mean.  gemm_pick's prices, which only have to rank tiles, are up to 60 % above these.
+// What a launch of launch_gemm_mfma takes, us, plain and with K split by ticket: a slice of the tile, a round beyond its slices,
+// once, and a MB of the result that a residual product reads.  A launch of fewer workgroups than CUs runs its slices up to a
+// fifth faster (L2).  Fitted, together with kWhole's, for the choices that they lead to, to 1464 measured products (39 shapes
+// of 512 to 20480 x 2048 to 15360, 64 to 1024 rows, each plain and in two to eight ranges on every tile; fitted to half of the
+// shapes, a choice on the others takes 1.8 to 2.0 % more than the best).  gemm_pick's prices, which only have to rank tiles,
+// are up to 60 % above what launches take.
 static double chip_fill(long wgs) { return 0.8 + 0.2 * double(wgs) / double((wgs + 255) / 256 * 256); }
 static double plain_launch_us(const GemmChoice& ch, int epi, int M, int N, int K) {
-    static const struct { double slice, round, ticket; } price[GCFG_COUNT] = {{1.75, 3.0, 0.0}, {1.0, 3.0, 14.0}, {0.555, 2.7, 14.0}, {0.80, 3.0, 14.0},
-                                                                             {0.42, 2.4, 6.0}, {0.555, 2.7, 14.0}, {1.10, 4.0, 0.0}, {0.80, 3.0, 14.0}};
+    struct Price { double slice, round, once, residual_mb; };
+    static const Price price[GCFG_COUNT][2] = {{{1.30, 3.0, 0.0, 0.50}, {2.12, 0.0, 0.3, 1.11}},      // 256 x 256
+                                               {{1.00, 3.0, 0.0, 0.50}, {1.00, 0.0, 11.0, 0.80}},     // 256 x 128
+                                               {{0.566, 2.0, 0.0, 0.45}, {0.634, 0.0, 10.9, 0.82}},   // 128 x 128
+                                               {{0.693, 4.1, 0.0, 0.18}, {0.946, 0.0, 10.7, 0.49}},   // 128 x 192
+                                               {{0.435, 3.5, 0.0, 1.02}, {0.401, 0.0, 9.4, 4.13}},    // 128 x 64
+                                               {{0.566, 2.0, 0.0, 0.45}, {0.634, 0.0, 10.9, 0.82}},   // 128 x 128, waves along K
+                                               {{0.853, 7.5, 0.0, 0.48}, {0.853, 7.5, 45.0, 0.48}},   // persistent
+                                               {{0.693, 4.1, 0.0, 0.18}, {0.946, 0.0, 10.7, 0.49}}};  // 192 x 128 (gate/up only)
     const GemmCfg& c = kGemmCfg[ch.cfg];
-    const auto& p = price[ch.cfg];
+    const Price& p = price[ch.cfg][ch.ksplit > 1];
     const long wgs = long((M + c.bm - 1) / c.bm) * (N / c.bn) * ch.ksplit;
-    return double((wgs + 255) / 256) * (double(K) / 64 / ch.ksplit * p.slice * chip_fill(wgs) + p.round) + (ch.ksplit > 1 ? p.ticket : 0.0) +
-           (epi == EPI_RESIDUAL_F32 ? double(M) * N * 2e-6 : 0.0);
+    return double((wgs + 255) / 256) * (double(K) / 64 / ch.ksplit * p.slice * chip_fill(wgs) + p.round) + p.once +
+           (epi == EPI_RESIDUAL_F32 ? double(M) * N * 4e-6 * p.residual_mb : 0.0);
 }
 
 // K ranges on the kernel for few rows: a slice takes 0.24 us + 0.075 us per 32 rows, HBM delivers the weights at 5.3 TB/s, L2
 // the tiles at 10, or 0.05 per workgroup; a pass of its own that adds the ranges up reads and writes the result too.
 // Whole tiles beyond that (kWhole): where the consumer adds the ranges up, against gemm_pick's price; where a pass does,
-// fitted to the same 23 shapes in two to eight ranges, against plain_launch_us, of which they must save a tenth.  Over those
-// 868 launches a choice then takes 2.8 % more than the best one (of plain and all ranges), and 17 of them 3 % more than plain
-// (against gemm_pick's prices it was 4.2 % and 60, with 512 rows of 2048 -> 2048 at 20.7 us instead of 12.3).
+// against plain_launch_us.  Over those 1464 products a choice takes 1.5 % more than the best of all (against gemm_pick's prices
+// it was 4.0 %, with 512 rows of 2048 -> 2048 at 20.7 us instead of 12.3).
 // Both sides measured, us (the second without the consumer's part):
 // down 8B (K = 14336 -> 4096) 1024 rows 133 and 87 in four ranges, 512 rows 81 and 51 in eight, 64 rows 40 and 24 in eight;
 // down 70B 1024 rows 434 and 334 in two, 512 rows 284 and 183 in four; O 8B 512 rows 40 and 24 (128 x 128, two), 137 rows
@@ -729,14 +737,14 @@ GemmPartsPlan gemm_parts_plan(int epi, int M, int N, int K, const GemmSplitWs* w
     // us per slice, per round, per MB of ranges, per MB of result and once; [1]: with a pass of its own
     struct Price { double slice, round, range_mb, out_mb, once; };
     static const struct { GemmPartsKind kind; int bm, bn; Price price[2]; } kWhole[3] = {
-        {GEMM_PARTS_P256, 256, 256, {{1.40, 4.0, 1 / 4.5 + 1 / 10.0, 0.0, 0.0}, {1.26, 0.0, 0.340, 0.04, 9.5}}},
-        {GEMM_PARTS_128, 128, 128, {{0.60, 4.0, 1 / 4.5 + 1 / 10.0, 0.0, 0.0}, {0.53, 0.0, 0.577, 0.04, 4.7}}},
-        {GEMM_PARTS_192, 128, 192, {{0.72, 4.0, 1 / 4.5 + 1 / 10.0, 0.0, 0.0}, {0.67, 0.0, 0.484, 0.04, 5.2}}}};
+        {GEMM_PARTS_P256, 256, 256, {{1.40, 4.0, 1 / 4.5 + 1 / 10.0, 0.0, 0.0}, {1.14, 0.0, 0.315, 0.035, 8.1}}},
+        {GEMM_PARTS_128, 128, 128, {{0.60, 4.0, 1 / 4.5 + 1 / 10.0, 0.0, 0.0}, {0.473, 0.0, 0.663, 0.033, 5.8}}},
+        {GEMM_PARTS_192, 128, 192, {{0.72, 4.0, 1 / 4.5 + 1 / 10.0, 0.0, 0.0}, {0.605, 0.0, 0.501, 0.046, 6.4}}}};
     if (!fused) {
-        // Unsplit 128 x 128 tiles, one to every CU, keep the order of their sums unless ranges save a third (1024 rows of 14336 ->
-        // 4096 137 us, in four ranges it would be 107).
+        // Unsplit 128 x 128 tiles, one to every CU, keep the order of their sums unless ranges promise a third (1024 rows of
+        // 14336 -> 4096 137 us, in four ranges it would be 107; 512 of 28672 -> 8192 286 and 207).
         const bool one_each = plain.cfg == GCFG_128x128K && plain.ksplit == 1 && chip_fill(long((M + 127) / 128) * (N / 128)) > 0.98;
-        best_us = plain_launch_us(plain, epi, M, N, K) * (one_each ? 0.67 : 0.90);
+        best_us = plain_launch_us(plain, epi, M, N, K) * (one_each ? 0.66 : 0.945);
     }
     for (int ks = fused ? 1 : 2; ks <= 8; ++ks)
         for (const auto& t : kWhole) {
