@@ -976,7 +976,7 @@ int32_t cake_write_store(cake_ctx* c, const cake_kv* kv, int32_t n_tokens, const
             }
         return CAKE_OK;
     };
-    // A kernel puts images together in device memory and the copy engine takes them out, as many at a time as the staging
+    // A kernel puts images together in device memory and the runtime copies them out, as many at a time as the staging
     // buffer holds.  A kernel that writes the pinned memory itself is faster alone (16 pages of 4 Llama3-8B layers in 8 bits
     // 656 us against 728), but while its stores queue for the link nothing else on the GPU gets on: a prefill of another
     // context, 0.95 ms, took 5.5 beside a write of 5.1, and with 16 workgroups 1.9 beside one of 8.3; 1.05 so.
