@@ -11,12 +11,15 @@ named on the command line,
     before it, or
   * an MFMA reads or overwrites an AGPR that another instruction wrote fewer than OTHER_TO_MFMA wait states before,
 
-following straight-line order and every branch (the instructions before a branch against those after its target).
+following straight-line order and every branch (the instructions before a branch against those after its target); with
+--by-name also if an AGPR is named outside the asm statements: such a kernel places its accumulators itself, and the
+compiler, which does not know that they are in use, must have found no use of its own for them.
 Every instruction counts as one wait state, `s_nop n` as n + 1.  The distances are those of the longest MFMA
 (16 passes) in the CDNA3 instruction set manual's table of required software wait states, so they cover the
 4-pass MFMA used here with room to spare.
 
     python check_mfma_hazards.py listing.s gemm_p256_kernel
+    python check_mfma_hazards.py listing.s gemm_pp_kernel --by-name
 """
 import re
 import sys
@@ -25,7 +28,7 @@ MFMA_TO_OTHER = 19
 OTHER_TO_MFMA = 4
 WINDOW = max(MFMA_TO_OTHER, OTHER_TO_MFMA)
 
-AREG = re.compile(r"\ba(\d+)\b|\ba\[(\d+):(\d+)\]")
+AREG = re.compile(r"\ba(\d+)\b|\ba\[(\w+)(?::(\w+))?\]")   # a5, a[5], a[4:7], the numbers also in hexadecimal
 
 
 def aregs(text):
@@ -34,7 +37,7 @@ def aregs(text):
         if m.group(1) is not None:
             regs.add(int(m.group(1)))
         else:
-            regs.update(range(int(m.group(2)), int(m.group(3)) + 1))
+            regs.update(range(int(m.group(2), 0), int(m.group(3) or m.group(2), 0) + 1))
     return regs
 
 
@@ -113,7 +116,22 @@ def check_kernel(name, lines):
     return n_mfma, problems
 
 
+def compiler_placed(lines):
+    """The instructions that name an AGPR and stand in no asm statement."""
+    inside, found = False, []
+    for raw in lines:
+        if "#ASMSTART" in raw or "#ASMEND" in raw:
+            inside = "#ASMSTART" in raw
+            continue
+        line = raw.split(";")[0].strip()
+        if not inside and line and not line.startswith(".") and not line.endswith(":") and aregs(line):
+            found.append("an accumulator outside the asm statements\n    " + line)
+    return found
+
+
 def main(argv):
+    by_name = "--by-name" in argv
+    argv = [a for a in argv if a != "--by-name"]
     if len(argv) != 3:
         sys.exit(__doc__)
     text = open(argv[1]).read().split("\n")
@@ -128,6 +146,8 @@ def main(argv):
             e += 1
         name = text[s].split(":")[0]
         n_mfma, problems = check_kernel(name, text[s + 1:e])
+        if by_name:
+            problems += compiler_placed(text[s + 1:e])
         print("check_mfma_hazards: %s: %d MFMAs, %d problem(s)" % (name, n_mfma, len(problems)))
         for p in problems[:20]:
             print("  " + p)

@@ -9,12 +9,13 @@
 #include <mutex>
 #include <vector>
 
-#include "gemm_tile.hpp"
+#include "gemm_p256.hpp"
 
 namespace cake {
 
 // =====================================================================================
-// Persistent GEMM for shapes with many 256 x 256 tiles (the gate/up product): out = a * w^T as above.
+// Persistent GEMM of 256 x 256 tiles, four waves: K ranges of a product, each stored as an output of its own (of the plain
+// products with so many tiles those of short K too; see launch_p256 for the line to the kernel with eight waves).
 //
 // What bounds a 256 x 256 tile on this chip is the LDS port, then the texture addresser: with eight
 // waves of 128 x 64 the operand reads plus the incoming tile data keep the LDS busy for as long as the
@@ -38,16 +39,12 @@ namespace cake {
 //    (448 tiles -> 224 workgroups of two tiles).  Past the end of its tiles a workgroup's loads use an
 //    empty buffer descriptor: they return zeros into slots nobody reads again, which keeps the load count
 //    per phase, and with it the s_waitcnt arithmetic, the same in every iteration.
-// Rows past M are read as zeros and their stores dropped by the buffer bounds checks.
-// SwiGLU: the 256 W rows of a tile alternate between the two matrices in groups of sixteen (even MFMA
-// tiles of a wave hold gate columns, odd ones the same columns of up), so the tile yields 128 output
-// columns and silu(gate) * up is formed in registers.
+// Rows past M are read as zeros and their stores dropped by the buffer bounds checks.  Stores of four bytes, 64 of a row to
+// a store: with 16 bytes to a lane (W as the MFMAs' first operand) 512 rows of 11008 -> 4096 in eight ranges take 60.8 us
+// instead of 57.9, sum included.
 // =====================================================================================
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 constexpr int P_ITEM = 256 * 128, P_SLOTS = 5, P_LDS = P_ITEM * P_SLOTS;
-// Operand fragments are held as four 32-bit words (eight bf16 values along K).
-typedef __attribute__((__vector_size__(4 * sizeof(int)))) int p256_frag_t;
-
 // An MFMA as an asm statement with the accumulator tied to an AGPR tuple: the 64 accumulators of a wave then
 // fill the AGPR file exactly and stay where they are (left to itself the allocator rotates them through
 // misaligned tuples with a hundred register copies per slice, each waiting for the MFMA that wrote its source),
@@ -58,22 +55,11 @@ __device__ __forceinline__ void p256_mfma(f32x4& c, const p256_frag_t& a, const 
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
 }
 
-// Column panels.  The N dimension is cut into panels of 8, 6 or 4 MFMA tiles per wave (256, 192 or 128 rows of
-// W; the widest first), so that the number of work items can be made a whole number of rounds over the CUs where
-// 256-wide panels alone leave some idle (448 items on 256 CUs: 224 workgroups of two; with 64 panels of 256 and
-// 64 of 192 every CU gets one item of each width, 7/8 of the time).  A work item is one panel x one band of 256
-// rows of A (x one K range when K is split, 256-wide panels only).
-struct P256Plan { int n8, n6, n4; };
-
-// SPLIT: the instantiation that runs one K range per item and leaves its accumulators in the workspace (256-wide
-// panels only); kept apart so that each instantiation has a single epilogue path.
-template <int EPI, bool SPLIT>
 __global__ void __launch_bounds__(256)
-gemm_p256_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, const bf16_t* __restrict__ W2,
-                 void* __restrict__ outv, int M, int N, int K, int tiles_m, P256Plan plan, int tiles_per_wg,
-                 float* __restrict__ part, int ksplit) {
+gemm_p256_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, float* __restrict__ out, int M, int N, int K,
+                 int tiles_m, P256Plan plan, int tiles_per_wg, int ksplit) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
-    constexpr int UNIT = EPI == EPI_SWIGLU ? 16 : 32;   // output columns per MFMA tile pair of a wave pair: panel of class c = c * UNIT columns
+    constexpr int UNIT = 32;   // output columns per MFMA tile pair of a wave pair: panel of class c = c * UNIT columns
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1;
@@ -109,11 +95,8 @@ gemm_p256_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, con
     // ---- loads.  Wave-load wl = wave + 4 i of an item covers its rows 8 wl .. 8 wl + 7 (128 B each).
     const int lr = lane >> 3, lpos = lane & 7;
     const unsigned chunk = unsigned((lpos ^ (((wave & 1) << 2) + (lr >> 1))) << 4);
-    const unsigned voff_a = unsigned((8 * wave + lr) * K * 2) + chunk, step_a = unsigned(32 * K * 2);
-    // W rows: plain, item row = panel row; SwiGLU, waves 0 and 1 fetch gate rows, waves 2 and 3 up rows.  The
-    // item always has 256 rows: those past the panel lie outside the descriptor and arrive as zeros.
-    const unsigned voff_w = EPI == EPI_SWIGLU ? unsigned((8 * (wave & 1) + lr) * K * 2) + chunk : voff_a;
-    const unsigned step_w = EPI == EPI_SWIGLU ? unsigned(16 * K * 2) : step_a;
+    const unsigned voff = unsigned((8 * wave + lr) * K * 2) + chunk, step = unsigned(32 * K * 2);
+    // the item always has 256 rows of W: those past the panel lie outside the descriptor and arrive as zeros
     __amdgpu_buffer_rsrc_t ra, rw;
     int ka = 0, ua = 0, kw = 0, uw = 0, slot_a = 1, slot_w = 0, nk_a = 0, nk_w = 0;
     // descriptors start at the item's first row and first K element
@@ -129,8 +112,7 @@ gemm_p256_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, con
         nk_w = slices_of(q / n_tiles);
         int nj, m0, cu;
         tile_geom(q % n_tiles, &nj, &m0, &cu);
-        const bf16_t* base = (EPI == EPI_SWIGLU && (wave >> 1) ? W2 : W) + size_t(cu) * UNIT * K;
-        rw = __builtin_amdgcn_make_buffer_rsrc((void*)(base + kbeg), 0, nj * UNIT * K * 2 - kbeg * 2, 0x00020000);
+        rw = __builtin_amdgcn_make_buffer_rsrc((void*)(W + size_t(cu) * UNIT * K + kbeg), 0, nj * UNIT * K * 2 - kbeg * 2, 0x00020000);
     };
     auto next_a = [&]() {
         slot_a = slot_a >= P_SLOTS - 2 ? slot_a + 2 - P_SLOTS : slot_a + 2;
@@ -220,10 +202,10 @@ gemm_p256_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, con
 
     // prologue: items W0 A0 W1 A1 in flight (dummies past the end of the streams)
     set_a(); set_w();
-    load_item(rw, slot_w, voff_w, kw, step_w); next_w();
-    load_item(ra, slot_a, voff_a, ka, step_a); next_a();
-    load_item(rw, slot_w, voff_w, kw, step_w); next_w();
-    load_item(ra, slot_a, voff_a, ka, step_a); next_a();
+    load_item(rw, slot_w, voff, kw, step); next_w();
+    load_item(ra, slot_a, voff, ka, step); next_a();
+    load_item(rw, slot_w, voff, kw, step); next_w();
+    load_item(ra, slot_a, voff, ka, step); next_a();
     asm volatile("s_waitcnt vmcnt(16)");
     __builtin_amdgcn_s_barrier();
     int sa = 1, sb = 0;   // slots of the slice being consumed
@@ -237,14 +219,12 @@ gemm_p256_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, con
 #pragma unroll
         for (int i = 0; i < 8; ++i) a0[i] = *(const p256_frag_t*)(pa + tile_off(i));
     }
-    constexpr int OUT_ELT = EPI == EPI_SWIGLU ? 2 : 4;
-    __amdgpu_buffer_rsrc_t obuf = __builtin_amdgcn_make_buffer_rsrc(outv, 0, int(size_t(M) * N * OUT_ELT), 0x00020000);
     // The K loop of an item of class nj (a constant at each of the three call sites)
     auto k_loop = [&](const int nj, const int nk, int b_wave, int b_wave_next) __attribute__((always_inline)) {
         for (int kt = 0; kt < nk; ++kt) {
             // phase A: k-step 0; operands of k-step 1; the W item of the slice after next (the weights come from HBM
             // and get the longer run-up: a slice and a half; the activations are L2 hits)
-            phase(nj, a0, b0, a1, b1, sa, sb, 1, b_wave, rw, slot_w, voff_w, kw, step_w);
+            phase(nj, a0, b0, a1, b1, sa, sb, 1, b_wave, rw, slot_w, voff, kw, step);
             next_w();
             // this wave has read all of this slice; the next slice must have landed: only the item just issued may be out
             asm volatile("s_waitcnt vmcnt(8)");
@@ -252,73 +232,22 @@ gemm_p256_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, con
             sa = sa >= P_SLOTS - 2 ? sa + 2 - P_SLOTS : sa + 2;
             sb = sb >= P_SLOTS - 2 ? sb + 2 - P_SLOTS : sb + 2;
             // phase B: k-step 1; first operands of the next slice; the A item of the slice after next into a freed slot
-            phase(nj, a1, b1, a0, b0, sa, sb, 0, kt + 1 == nk ? b_wave_next : b_wave, ra, slot_a, voff_a, ka, step_a);
+            phase(nj, a1, b1, a0, b0, sa, sb, 0, kt + 1 == nk ? b_wave_next : b_wave, ra, slot_a, voff, ka, step);
             next_a();
         }
     };
     // Epilogue of an item of class nj; accumulator (i, j)[v] is row 16 i + 4 lq + v, column 16 j + l16 of the wave's share
     auto epilogue = [&](const int nj, int q, int m0, int col_units) __attribute__((always_inline)) {
-        const int row0 = m0 + wm * 128 + 4 * lq;
-        if constexpr (EPI == EPI_SWIGLU) {
-            // silu(gate) * up from accumulator pairs (even j: gate, odd j: the same columns of up).  The row offsets go
-            // through the scalar offset of the store.
-            const int pitch = N * 2;
-            const unsigned base = unsigned(row0 * N + col_units * UNIT + wn * nj * 8 + l16) * 2u;
+        // a K range is stored as an output of its own
+        const __amdgpu_buffer_rsrc_t obuf = __builtin_amdgcn_make_buffer_rsrc(out + size_t(q / n_tiles) * M * N, 0, int(size_t(M) * N * 4), 0x00020000);
+        const unsigned base = unsigned((m0 + wm * 128 + 4 * lq) * N + col_units * UNIT + wn * nj * 16 + l16) * 4u;
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
+        for (int i = 0; i < 8; ++i)
 #pragma unroll
-                for (int j = 0; j < 8; j += 2)
+            for (int j = 0; j < 8; ++j)
 #pragma unroll
-                    for (int v = 0; v < 4; ++v)
-                        if (j < nj) {
-                            const float g = acc[i][j][v], up = acc[i][j + 1][v];
-                            // the hardware reciprocal (1 ulp) instead of an IEEE division: the result is rounded to bf16
-                            const bf16_t o = bf16_t(g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * up);
-                            unsigned short bits;
-                            __builtin_memcpy(&bits, &o, 2);
-                            __builtin_amdgcn_raw_buffer_store_b16(bits, obuf, base, (i * 16 + v) * pitch + (j >> 1) * 32, 0);
-                        }
-        } else if constexpr (SPLIT) {
-            // This K range's accumulators go to the item's slot of the workspace, in accumulator order (each store
-            // is 4 KB contiguous over the workgroup); a second kernel adds the ranges up and runs the epilogue:
-            // a single workgroup reading a tile's parts back would take longer than the whole K loop.
-            constexpr int TILE_B = 256 * 256 * 4;
-            const __amdgpu_buffer_rsrc_t ws = __builtin_amdgcn_make_buffer_rsrc(part, 0, n_tiles * ksplit * TILE_B, 0x00020000);
-            const unsigned mine = (unsigned(q % n_tiles) * ksplit + unsigned(q / n_tiles)) * TILE_B + unsigned(tid) * 16;
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    u32x4 v = {__float_as_uint(acc[i][j][0]), __float_as_uint(acc[i][j][1]), __float_as_uint(acc[i][j][2]),
-                               __float_as_uint(acc[i][j][3])};
-                    __builtin_amdgcn_raw_buffer_store_b128(v, ws, mine + (i * 8 + j) * 4096, 0, 0);
-                }
-        } else {
-            if constexpr (EPI == EPI_STORE_F32)   // a K range is stored as an output of its own
-                obuf = __builtin_amdgcn_make_buffer_rsrc((float*)outv + size_t(q / n_tiles) * M * N, 0, int(size_t(M) * N * OUT_ELT), 0x00020000);
-            const unsigned base = unsigned(row0 * N + col_units * UNIT + wn * nj * 16 + l16) * 4u;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                float old[8][4];
-                if constexpr (EPI == EPI_RESIDUAL_F32) {   // all loads of a band of 16 rows in flight before the first add
-#pragma unroll
-                    for (int j = 0; j < 8; ++j)
-#pragma unroll
-                        for (int v = 0; v < 4; ++v)
-                            if (j < nj)
-                                old[j][v] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(obuf, base + unsigned((i * 16 + v) * N + j * 16) * 4u, 0, 0));
-                }
-#pragma unroll
-                for (int j = 0; j < 8; ++j)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v)
-                        if (j < nj) {
-                            float x = acc[i][j][v];
-                            if constexpr (EPI == EPI_RESIDUAL_F32) x += old[j][v];
-                            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x), obuf, base + unsigned((i * 16 + v) * N + j * 16) * 4u, 0, 0);
-                        }
-            }
-        }
+                for (int v = 0; v < 4; ++v)
+                    if (j < nj) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[i][j][v]), obuf, base + unsigned((i * 16 + v) * N + j * 16) * 4u, 0, 0);
     };
     for (int u = 0; u < n_mine; ++u) {
         // cleared here and nowhere else, so that no accumulator value lives from one item to the next
@@ -349,42 +278,6 @@ gemm_p256_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, con
         nj_cur = nj_next; m0_cur = m0_next; cu_cur = cu_next;
         // loads and stores complete out of order with respect to each other: nothing is counted across them
         asm volatile("s_waitcnt vmcnt(0)");
-    }
-}
-
-// Second pass of the persistent kernel with K split: workgroup (tile t, band i) adds up, in range order, the
-// `ksplit` parts of the tile's i-th bands of sixteen rows per wave (so the result is the same bits on every
-// launch) and stores them or adds them into the float32 residual stream.  Thread and accumulator layout are
-// the producing kernel's: thread tid = wave (wm, wn) x lane (lq, l16), accumulator (i, j)[e] = row
-// 128 wm + 16 i + 4 lq + e, column 128 wn + 16 j + l16 of the tile.
-template <int EPI>
-__global__ void __launch_bounds__(256)
-gemm_p256_finish_kernel(const float* __restrict__ part, float* __restrict__ out, int M, int N, int tiles_m, int ksplit) {
-    const int t = blockIdx.x >> 3, i = blockIdx.x & 7, tid = threadIdx.x;
-    const int wave = tid >> 6, lane = tid & 63, wm = wave >> 1, wn = wave & 1, l16 = lane & 15, lq = lane >> 4;
-    const int m0 = (t % tiles_m) * 256, c0 = (t / tiles_m) * 256;
-    const float4* src = (const float4*)part + (size_t(t) * ksplit * 64 + i * 8) * 256 + tid;
-    float4 tot[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) tot[j] = src[j * 256];
-    for (int sp = 1; sp < ksplit; ++sp) {
-        float4 p[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) p[j] = src[(size_t(sp) * 64 + j) * 256];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) { tot[j].x += p[j].x; tot[j].y += p[j].y; tot[j].z += p[j].z; tot[j].w += p[j].w; }
-    }
-    const int row = m0 + wm * 128 + 16 * i + 4 * lq, col = c0 + wn * 128 + l16;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        if (row + e >= M) break;
-        float* o = out + size_t(row + e) * N + col;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const float x = e == 0 ? tot[j].x : e == 1 ? tot[j].y : e == 2 ? tot[j].z : tot[j].w;
-            if (EPI == EPI_RESIDUAL_F32) o[16 * j] += x;
-            else o[16 * j] = x;
-        }
     }
 }
 
@@ -450,7 +343,6 @@ enum { GCFG_256x256 = 0, GCFG_256x128 = 1, GCFG_128x128 = 2, GCFG_128x192 = 3, G
        GCFG_192x128 = 7, GCFG_COUNT = 8 };
 static const GemmCfg kGemmCfg[GCFG_COUNT] = {{256, 256}, {256, 128}, {128, 128}, {128, 192}, {128, 64}, {128, 128}, {256, 256}, {192, 128}};
 
-struct P256Plan;
 static P256Plan p256_plan(int epi, int tiles_m, int N);
 static double p256_plan_cost(int tiles_m, int n8, int n6, int n4);
 
@@ -583,35 +475,48 @@ bool gemm_order_fixed(int epi, int max_rows, int N, int K, const GemmSplitWs* ws
     return true;
 }
 
+// Items of 256 rows: on the eight waves in turn (kernels_gemm_pp.hip), but for float32 stores of items of under 56 slices, where
+// its two phases of one group alone weigh more.  us, four waves / in turn, each with the pass that adds the ranges up: 224 slices
+// of 256 items 372 and 369, 128 of 128 items 163 and 157, 112 of 128 items 151 and 143, 72 of 120 items 100.7 and 99.5, 56 of 256
+// items 111.8 and 110.9; 54 of 160 items 84.3 and 85.3, 43 of 128 items 67.0 and 68.2, 28.7 of 192 items 59.3 and 60.7, 16 of 128
+// items 34.2 and 36.5.  Both give the same bits.
+template <int EPI>
+static hipError_t launch_p256(const bf16_t* A, const bf16_t* W, const bf16_t* W2, void* out, int M, int N, int K, const P256Plan& plan,
+                              int ks, hipStream_t st) {
+    if (EPI != EPI_STORE_F32 || K / 64 / ks >= 56) return launch_gemm_pp(EPI, A, W, W2, out, M, N, K, plan, ks, st);
+    const int tiles_m = (M + 255) / 256, nb = tiles_m * (plan.n8 + plan.n6 + plan.n4) * ks;
+    if (nb == 0 || (uintptr_t(out) & 15)) return hipErrorInvalidValue;
+    // a whole number of rounds: every workgroup takes `rounds` items (the last may take one less)
+    const int rounds = (nb + 255) / 256, wgs = (nb + rounds - 1) / rounds;
+    static bool attr_set = false;
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute((const void*)gemm_p256_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    hipLaunchKernelGGL(gemm_p256_kernel, dim3(wgs), dim3(256), P_LDS, st, A, W, (float*)out, M, N, K, tiles_m, plan, rounds, ks);
+    return hipGetLastError();
+}
+
+// K in `ks` ranges (whole slices of 64, as even as they go) on the persistent kernels, each range stored as an output of its
+// own (256-wide panels).
+static hipError_t launch_gemm_p256_parts(const void* a, const void* w, float* part, int M, int N, int K, int ks, hipStream_t st) {
+    if (N % 256 || ks <= 0 || K / 64 < ks || !gemm_cfg_ok(GCFG_P256, EPI_STORE_F32, M, N, K)) return hipErrorInvalidValue;
+    return launch_p256<EPI_STORE_F32>((const bf16_t*)a, (const bf16_t*)w, nullptr, part, M, N, K, P256Plan{N / 256, 0, 0}, ks, st);
+}
+
 template <int EPI>
 static hipError_t gemm_launch_cfg(int cfg, int ks, const GemmSplitWs* ws, const bf16_t* A, const bf16_t* W, const bf16_t* W2,
                                   void* out, int M, int N, int K, hipStream_t st) {
     const long tiles128 = long((M + 127) / 128) * (N / (EPI == EPI_SWIGLU ? 64 : 128)) * ks;
     if (cfg == GCFG_P256) {
-        const int tiles_m = (M + 255) / 256;
-        const P256Plan plan = ks > 1 ? P256Plan{N / 256, 0, 0} : p256_plan(EPI, tiles_m, N);
-        const int panels = plan.n8 + plan.n6 + plan.n4, nb = tiles_m * panels * ks;
-        if (panels == 0) return hipErrorInvalidValue;
-        // a whole number of rounds: every workgroup takes `rounds` items (the last may take one less)
-        const int rounds = (nb + 255) / 256, wgs = (nb + rounds - 1) / rounds;
-        auto kern = gemm_p256_kernel<EPI, false>;
         if constexpr (EPI != EPI_SWIGLU) {
-            if (ks > 1) kern = gemm_p256_kernel<EPI, true>;
+            if (ks > 1) {   // forced only: every range an output of its own, and a pass that adds them up
+                const hipError_t e = launch_gemm_p256_parts(A, W, ws->part, M, N, K, ks, st);
+                return e != hipSuccess ? e : launch_add_parts((float*)out, ws->part, ks, size_t(M) * N, st, EPI == EPI_STORE_F32);
+            }
         }
-        static bool attr_set[2] = {false, false};
-        if (!attr_set[ks > 1]) {
-            hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
-            if (e != hipSuccess) return e;
-            attr_set[ks > 1] = true;
-        }
-        hipLaunchKernelGGL(kern, dim3(wgs), dim3(256), P_LDS, st, A, W, W2, out, M, N, K, tiles_m, plan, rounds,
-                           ks > 1 ? ws->part : nullptr, ks);
-        if (ks > 1) {
-            if constexpr (EPI != EPI_SWIGLU)
-                hipLaunchKernelGGL(gemm_p256_finish_kernel<EPI>, dim3(tiles_m * plan.n8 * 8), dim3(256), 0, st, ws->part, (float*)out,
-                                   M, N, tiles_m, ks);
-        }
-        return hipGetLastError();
+        return launch_p256<EPI>(A, W, W2, out, M, N, K, p256_plan(EPI, (M + 255) / 256, N), 1, st);
     }
     switch (cfg) {
         case GCFG_256x256: return gemm_launch_t<4, 2, 2, 4, 32, 5, EPI>(A, W, W2, out, M, N, K, st, ks, ws);
@@ -645,23 +550,6 @@ static hipError_t gemm_launch_cfg(int cfg, int ks, const GemmSplitWs* ws, const 
             if (tiles128 <= 256 && (K / ks % 64) == 0) return gemm_launch_t<2, 2, 2, 2, 64, 4, EPI>(A, W, W2, out, M, N, K, st, ks, ws);
             return gemm_launch_t<2, 2, 2, 2, 32, 4, EPI>(A, W, W2, out, M, N, K, st, ks, ws);
     }
-}
-
-// K in `ks` ranges (whole slices of 64, as even as they go) on the persistent kernel, each range stored as an output of its
-// own (256-wide panels).
-static hipError_t launch_gemm_p256_parts(const void* a, const void* w, float* part, int M, int N, int K, int ks, hipStream_t st) {
-    if (N % 256 || ks <= 0 || K / 64 < ks || !gemm_cfg_ok(GCFG_P256, EPI_STORE_F32, M, N, K)) return hipErrorInvalidValue;
-    const int tiles_m = (M + 255) / 256, nb = tiles_m * (N / 256) * ks, rounds = (nb + 255) / 256, wgs = (nb + rounds - 1) / rounds;
-    auto kern = gemm_p256_kernel<EPI_STORE_F32, false>;
-    static bool attr_set = false;
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
-        if (e != hipSuccess) return e;
-        attr_set = true;
-    }
-    hipLaunchKernelGGL(kern, dim3(wgs), dim3(256), P_LDS, st, (const bf16_t*)a, (const bf16_t*)w, (const bf16_t*)nullptr, (void*)part, M, N,
-                       K, tiles_m, P256Plan{N / 256, 0, 0}, rounds, (float*)nullptr, ks);
-    return hipGetLastError();
 }
 
 // K in `ks` ranges on the 128-row tiles whose slices two waves divide, each range stored as an output of its own.
@@ -785,7 +673,8 @@ void gemm_mfma_plan(int epi, int M, int N, int K, int cfg_override, const GemmSp
 hipError_t launch_gemm_mfma(int epi, const void* a, const void* w, const void* w2, void* out, int M, int N, int K,
                             hipStream_t st, int cfg_override, const GemmSplitWs* ws, int ksplit_override) {
     const bf16_t *A = (const bf16_t*)a, *W = (const bf16_t*)w, *W2 = (const bf16_t*)w2;
-    const GemmChoice ch = gemm_choose(epi, M, N, K, cfg_override, ws, ksplit_override);
+    GemmChoice ch = gemm_choose(epi, M, N, K, cfg_override, ws, ksplit_override);
+    if (ch.cfg == GCFG_P256 && (uintptr_t(out) & 15)) ch = GemmChoice{GCFG_128x128, 1};   // the persistent kernels store 8 and 16 bytes at once
     if (!gemm_cfg_ok(ch.cfg, epi, M, N, K)) return hipErrorInvalidValue;
     if (epi == EPI_SWIGLU) return gemm_launch_cfg<EPI_SWIGLU>(ch.cfg, 1, ws, A, W, W2, out, M, N, K, st);
     if (epi == EPI_RESIDUAL_F32) return gemm_launch_cfg<EPI_RESIDUAL_F32>(ch.cfg, ch.ksplit, ws, A, W, W2, out, M, N, K, st);

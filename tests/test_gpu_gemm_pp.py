@@ -1,0 +1,76 @@
+"""bf16 products of items of 256 rows on the kernel with eight waves in turn: one slice of K, two and three, the line between it
+and the four-wave kernel (56 slices), panels of every width, ragged rows, several items to a workgroup, K ranges of unequal
+length, and results that are not 16-byte aligned (which a tile kernel forms)."""
+import pytest
+
+import synth_inputs as si
+
+pytestmark = pytest.mark.gpu
+
+
+def _engine(**tuning):
+    import paper_2410_03065_amd as cake
+    eng = cake.Engine(si.ModelShape("gemm-pp", 1, 4096, 32, 8, 128, 512, 64, "bf16"), None, max_tokens=1024, max_chunk=1024, page_tokens=64)
+    eng.set_tuning(gemm_config=7, **tuning)
+    return eng
+
+
+def _operands(eng, M, N, K):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(M * 7 + N + K)
+    mk = lambda r, c, std: (torch.randn(r, c, device="cuda", generator=g) * std).to(eng.tdtype)
+    a, w, w2, x0 = mk(M, K, 1.0), mk(N, K, 0.05), mk(N, K, 0.05), torch.randn(M, N, device="cuda", generator=g)
+    torch.cuda.synchronize()       # the engine's streams do not wait for torch's
+    return a, w, w2, x0
+
+
+def _rel(got, want):
+    return float((got.double() - want).abs().max() / want.abs().max())
+
+
+# Sums: float32 over K, 2e-6 of the largest value up to K = 256 and in proportion beyond.  SwiGLU: one rounding to bf16, and 1e-6
+# of the largest value for the sums in front of it.
+@pytest.mark.parametrize("M,N,K", [
+    (1, 128, 64), (128, 128, 128), (129, 192, 192), (255, 256, 64), (257, 320, 128), (256, 448, 192),
+    (300, 384, 3520), (300, 384, 3584), (511, 640, 3648),                                                # 55, 56 and 57 slices
+    (1000, 16640, 64), (1024, 14336, 128), (700, 33280, 192)])                                           # two rounds and more
+def test_gemm_items_of_256_rows(M, N, K):
+    import torch
+    eng = _engine(gemm_ksplit=1)
+    a, w, w2, x0 = _operands(eng, M, N, K)
+    want = a.double() @ w.double().t().contiguous()
+    tol = 2e-6 * max(1, K / 256)
+    got = eng.op_gemm(a, w)
+    assert _rel(got, want) < tol
+    assert torch.equal(got, eng.op_gemm(a, w))
+    assert _rel(eng.op_gemm_residual(a, w, x0.clone()), x0.double() + want) < tol
+    want = torch.nn.functional.silu(want) * (a.double() @ w2.double().t().contiguous())
+    got = eng.op_gemm_swiglu(a, w, w2).double()
+    assert bool(((got - want).abs() <= 2.0 ** -8 * 1.01 * want.abs() + 1e-6 * want.abs().max()).all())
+
+
+@pytest.mark.parametrize("M,N,K,ranges", [(300, 512, 7168, 2), (257, 256, 7232, 2), (1024, 1024, 14336, 4)])   # 56; 57 and 56; 56
+def test_gemm_k_ranges_of_items_of_256_rows(M, N, K, ranges):
+    eng = _engine(gemm_ksplit=ranges)
+    a, w, _, x0 = _operands(eng, M, N, K)
+    want = a.double() @ w.double().t().contiguous()
+    tol = 2e-6 * max(1, K / 256)
+    assert _rel(eng.op_gemm(a, w), want) < tol
+    assert _rel(eng.op_gemm_residual(a, w, x0.clone()), x0.double() + want) < tol
+
+
+@pytest.mark.parametrize("offset", [1, 2, 4])
+def test_results_off_16_bytes(offset):
+    import torch
+    M, N, K = 1024, 14336, 128     # a shape that goes to this kernel unforced
+    eng = _engine()
+    a, w, w2, _ = _operands(eng, M, N, K)
+    want = eng.op_gemm_swiglu(a, w, w2)
+    buf = torch.zeros(M * N + 16, device="cuda", dtype=eng.tdtype)
+    torch.cuda.synchronize()
+    out = buf[offset:offset + M * N]
+    assert eng.lib.cake_op_gemm_swiglu(eng.ctx, a.data_ptr(), w.data_ptr(), w2.data_ptr(), out.data_ptr(), M, N, K) == 0
+    torch.cuda.synchronize()
+    # 16- instead of 32-deep MFMAs: sums in another order under one rounding to bf16
+    assert float((out.view(M, N).float() - want.float()).abs().max()) <= 2.0 ** -7 * float(want.float().abs().max())
+    assert float(buf[:offset].abs().max()) == 0 and float(buf[offset + M * N:].abs().max()) == 0
