@@ -267,21 +267,36 @@ static int enqueue_prefill(cake_ctx* c, int tok_begin, int rows, const cake_kv* 
     auto product = [&](const GemmPartsPlan& plan, int epi, const void* a, const void* w, float* out, int N, int K) {
         return plan.ksplit ? launch_gemm_parts(plan, a, w, parts, rows, N, K, c->cs) : gemm(c, epi, a, w, nullptr, out, rows, N, K, plan_rows, c->step_free);
     };
+    // A float32 product norms its input itself (not where a test asks for the plain kernels).
+    auto norms_itself = [&](const float* gain, const void* wa, const void* wb) {
+        return m.dtype == CAKE_F32 && c->tun.kernel_path == 0 && ((uintptr_t(gain) | uintptr_t(wa) | uintptr_t(wb)) & 15) == 0;
+    };
+    auto normed_product = [&](int epi, const void* wa, const void* wb, void* out, int N, const float* gain) {
+        return launch_gemm_f32(epi, c->x, (const float*)wa, (const float*)wb, (float*)out, rows, N, int(d), c->cs, {gain, m.rms_eps});
+    };
     for (int l = 0; l < m.n_layers; ++l) {
         const cake_layer_weights& w = c->layers[l];
         KvView view = make_view(c, kv, l);
-        KLAUNCH(c, CAKE_K_RMSNORM, 0, R * d * (4 + e), norm(l > 0 ? p_down : none, w.attn_norm));
-        KLAUNCH(c, CAKE_K_GEMM_QKV, 2 * R * nqkv * d, (R * d + nqkv * d) * e + R * nqkv * 4,
-                product(p_qkv, EPI_STORE_F32, c->h, w.wqkv, c->qkv, nqkv, d));
+        const uint64_t qkv_bytes = (R * d + nqkv * d) * e + R * nqkv * 4, gateup_bytes = (R * d + 2 * ff * d + R * ff) * e;
+        if (norms_itself(w.attn_norm, w.wqkv, nullptr)) {
+            KLAUNCH(c, CAKE_K_GEMM_QKV, 2 * R * nqkv * d, qkv_bytes, normed_product(EPI_STORE_F32, w.wqkv, nullptr, c->qkv, int(nqkv), w.attn_norm));
+        } else {
+            KLAUNCH(c, CAKE_K_RMSNORM, 0, R * d * (4 + e), norm(l > 0 ? p_down : none, w.attn_norm));
+            KLAUNCH(c, CAKE_K_GEMM_QKV, 2 * R * nqkv * d, qkv_bytes, product(p_qkv, EPI_STORE_F32, c->h, w.wqkv, c->qkv, nqkv, d));
+        }
         KLAUNCH(c, CAKE_K_ROPE_KV, 0, R * nqkv * (4 + e),
                 launch_rope_kv_write(m.dtype, p_qkv.ksplit ? parts : c->qkv, c->rope_cs, c->q, m.n_q_heads, tok_begin, rows, view, c->cs,
                                      p_qkv.ksplit ? p_qkv.ksplit : 1));
         KLAUNCH(c, CAKE_K_ATTENTION, attn_flops, attn_bytes, attention(c, c->q, c->ao, tok_begin, rows, view));
         KLAUNCH(c, CAKE_K_GEMM_O, 2 * R * d * hq, (R * hq + d * hq) * e + 2 * R * d * 4,
                 product(p_o, EPI_RESIDUAL_F32, c->ao, w.wo, c->x, d, hq));
-        KLAUNCH(c, CAKE_K_RMSNORM, 0, R * d * (4 + e), norm(p_o, w.ffn_norm));
-        KLAUNCH(c, CAKE_K_GEMM_GATEUP, 4 * R * ff * d, (R * d + 2 * ff * d + R * ff) * e,
-                gemm(c, EPI_SWIGLU, c->h, w.w_gate, w.w_up, c->act, rows, m.ffn_dim, d, plan_rows, c->step_free));
+        if (norms_itself(w.ffn_norm, w.w_gate, w.w_up)) {
+            KLAUNCH(c, CAKE_K_GEMM_GATEUP, 4 * R * ff * d, gateup_bytes, normed_product(EPI_SWIGLU, w.w_gate, w.w_up, c->act, m.ffn_dim, w.ffn_norm));
+        } else {
+            KLAUNCH(c, CAKE_K_RMSNORM, 0, R * d * (4 + e), norm(p_o, w.ffn_norm));
+            KLAUNCH(c, CAKE_K_GEMM_GATEUP, 4 * R * ff * d, gateup_bytes,
+                    gemm(c, EPI_SWIGLU, c->h, w.w_gate, w.w_up, c->act, rows, m.ffn_dim, d, plan_rows, c->step_free));
+        }
         KLAUNCH(c, CAKE_K_GEMM_DOWN, 2 * R * d * ff, (R * ff + d * ff) * e + 2 * R * d * 4,
                 product(p_down, EPI_RESIDUAL_F32, c->act, w.w_down, c->x, d, m.ffn_dim));
     }

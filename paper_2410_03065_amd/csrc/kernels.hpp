@@ -52,8 +52,11 @@ struct AttnWs { float* part; size_t bytes; int range_keys; };
 bool attention_f32_supported(const void* q, const KvView& kv);
 hipError_t launch_attention_f32(const float* q, float* out, int n_q, int tok_begin, int rows, const KvView& kv,
                                 hipStream_t st, const AttnWs& ws);
+// The RMSNorm in front of a product: its input is x / sqrt(mean(x^2) + eps) * gain (gain null: x as it is).
+struct GemvNorm { const float* gain; float eps; };
+// nm.gain: a is normed on the way (store and SwiGLU; gain 16-byte aligned like a, w and w2).
 hipError_t launch_gemm_f32(int epi, const float* a, const float* w, const float* w2, float* out, int M, int N, int K,
-                           hipStream_t st);
+                           hipStream_t st, const GemvNorm& nm = {nullptr, 0.f});
 // Adds up the key ranges of a split attention launch: part[split][head][row][head_dim + 2] (O, reference of
 // the exponentials, row sum) -> out[row][head][head_dim].
 hipError_t launch_attention_merge(int dtype, int head_dim, const float* part, void* out, int n_q, int rows, int splits,
@@ -126,7 +129,6 @@ hipError_t launch_quant_pages(int dtype, void* images, size_t image_bytes, const
 // h = x (gain null: mode 1 only) or its RMSNorm (gain, eps; modes 0, 2, 3): out[n] (mode 0: =, 1: +=) sum_k h[k] w[n][k];
 // mode 2: out[n] = silu(h.w[n]) * (h.w2[n]); mode 3: mode 0 with adjacent rows of a head rotated by cs[head_dim / 2]
 // (cos, sin).  x, out float32.  host (mode 0): null, or pinned memory, 16-byte aligned, for a copy of the result.
-struct GemvNorm { const float* gain; float eps; };
 hipError_t launch_gemv(int dtype, int mode, const GemvNorm& nm, const float* x, const void* w, const void* w2, float* out,
                        int N, int K, hipStream_t st, const double* cs = nullptr, int head_dim = 0, float* host = nullptr);
 // x = row `id` of the embedding table; cs[head_dim / 2] = (cos, sin) of the rotary pairs at position pos.

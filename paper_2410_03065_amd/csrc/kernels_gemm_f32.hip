@@ -19,6 +19,11 @@
 // 256 -> 768 18 -> 7, 256 -> 688 twice with SwiGLU 35 -> 9.5, 688 -> 256 48 -> 5); for large products the float32
 // matrix rate, fed from L2 through tiles of 64 x 64 per wave (1024 x 4096 x 4096: 492 -> 323 us, 106 TFLOP/s, both
 // against the 64 x 64 tiles on the vector ALUs of the generic kernel).
+//
+// NORM: `a` is the residual stream in front of an RMSNorm.  A row's norm is a factor of all its products, so the tile
+// multiplies x by the gain as it reads it, adds up the squares beside the products (the same quarters of K, added in the
+// same order in every tile) and scales its results by the row's factor at the end: no normed copy of the activations, and no
+// launch of 3 us before the product (256 rows of the tiny model, two layers: 127 -> 113 us with the four norms gone).
 #include "kernels.hpp"
 
 namespace cake {
@@ -29,16 +34,17 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 // wave's registers (1024 x 4096 x 4096: spilled 1742 us, in LDS 600).
 constexpr bool f32_lds_total(int t, int sp, int epi) { return sp == 2 && epi == EPI_SWIGLU && t == 4; }
 
-template <int T, int SP, int EPI>
+template <int T, int SP, int EPI, bool NORM>
 __global__ void __launch_bounds__(256)
 gemm_f32_kernel(const float* __restrict__ a, const float* __restrict__ w, const float* __restrict__ w2, float* __restrict__ out,
-                int M, int N, int K, int tiles_m) {
+                int M, int N, int K, int tiles_m, const float* __restrict__ gain, float eps) {
     constexpr int KW = SP == 1 ? 4 : 1;              // waves that divide K
     constexpr int NM = EPI == EPI_SWIGLU ? 2 : 1;    // weight matrices
     constexpr int KB = NM * T > 4 ? 1 : 2;           // 16-deep blocks per trip (one where 64 x 64 twice fill the registers)
     constexpr int BT = 16 * T * SP;                  // rows and columns of the workgroup's tile
     constexpr bool LDS_TOTAL = f32_lds_total(T, SP, EPI);
     __shared__ float4 parts[KW > 1 ? (KW - 1) * NM * T * T * 64 : 1];
+    __shared__ float squares[NORM && KW > 1 ? KW * 16 * T : 1];   // of a row in a quarter of K
     extern __shared__ __attribute__((aligned(16))) float4 total_lds[];   // LDS_TOTAL: [NM][T][T][256]
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int l16 = lane & 15, lq = lane >> 4;
@@ -53,9 +59,10 @@ gemm_f32_kernel(const float* __restrict__ a, const float* __restrict__ w, const 
         if constexpr (NM == 2) wp[1][i] = w2 + size_t(min(n0 + 16 * i + l16, N - 1)) * K + 4 * lq;
     }
     auto ld = [&](const float* p, int k) { return k + 4 * lq < K ? *(const float4*)(p + k) : make_float4(0.f, 0.f, 0.f, 0.f); };
-    auto load = [&](float4 (&av)[T][KB], float4 (&wv)[NM][T][KB], int k0) {
+    auto load = [&](float4 (&av)[T][KB], float4 (&wv)[NM][T][KB], float4 (&gv)[KB], int k0) {
 #pragma unroll
         for (int b = 0; b < KB; ++b) {
+            if constexpr (NORM) gv[b] = ld(gain + 4 * lq, k0 + 16 * b);
 #pragma unroll
             for (int i = 0; i < T; ++i) av[i][b] = ld(ap[i], k0 + 16 * b);
 #pragma unroll
@@ -71,7 +78,20 @@ gemm_f32_kernel(const float* __restrict__ a, const float* __restrict__ w, const 
         for (int i = 0; i < T; ++i)
 #pragma unroll
             for (int j = 0; j < T; ++j) acc[n][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    auto mul = [&](const float4 (&av)[T][KB], const float4 (&wv)[NM][T][KB]) {
+    float sq[T];   // NORM: squares of this lane's elements of row l16 of row tile i, of a quarter of K
+#pragma unroll
+    for (int i = 0; i < T; ++i) sq[i] = 0.f;
+    auto mul = [&](float4 (&av)[T][KB], const float4 (&wv)[NM][T][KB], const float4 (&gv)[KB]) {
+        if constexpr (NORM) {
+#pragma unroll
+            for (int b = 0; b < KB; ++b)
+#pragma unroll
+                for (int i = 0; i < T; ++i) {
+                    float4& x = av[i][b];
+                    sq[i] += x.x * x.x + x.y * x.y + x.z * x.z + x.w * x.w;
+                    x.x *= gv[b].x; x.y *= gv[b].y; x.z *= gv[b].z; x.w *= gv[b].w;
+                }
+        }
 #pragma unroll
         for (int b = 0; b < KB; ++b)
 #pragma unroll
@@ -85,28 +105,43 @@ gemm_f32_kernel(const float* __restrict__ a, const float* __restrict__ w, const 
                             acc[n][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(((const float*)&av[i][b])[e], ((const float*)&wv[n][j][b])[e],
                                                                                 acc[n][i][j], 0, 0, 0);
     };
-    float4 av[2][T][KB], wv[2][NM][T][KB];
+    float4 av[2][T][KB], wv[2][NM][T][KB], gv[2][KB];
     f32x4 total[NM][T][T];   // KW = 1: the finished sums (in LDS where the registers do not hold them as well)
     const int quarter = (K + 127) / 128 * 32;
     auto sum_of = [&](int p) {   // quarter p of K into acc
         constexpr int STEP = 16 * KB;
         const int k_end = min((p + 1) * quarter, K);
         int k = p * quarter;
-        if (k < k_end) load(av[0], wv[0], k);
+        if (k < k_end) load(av[0], wv[0], gv[0], k);
         for (; k < k_end; k += 2 * STEP) {   // two trips unrolled, so that the two register sets alternate without copies
-            if (k + STEP < k_end) load(av[1], wv[1], k + STEP);
-            mul(av[0], wv[0]);
+            if (k + STEP < k_end) load(av[1], wv[1], gv[1], k + STEP);
+            mul(av[0], wv[0], gv[0]);
             if (k + STEP >= k_end) break;
-            if (k + 2 * STEP < k_end) load(av[0], wv[0], k + 2 * STEP);
-            mul(av[1], wv[1]);
+            if (k + 2 * STEP < k_end) load(av[0], wv[0], gv[0], k + 2 * STEP);
+            mul(av[1], wv[1], gv[1]);
+        }
+        if constexpr (NORM) {   // the four lanes of a row
+#pragma unroll
+            for (int i = 0; i < T; ++i) {
+                sq[i] += __shfl_xor(sq[i], 16, 64);
+                sq[i] += __shfl_xor(sq[i], 32, 64);
+            }
         }
     };
+    float sq_total[T];   // KW = 1
     if constexpr (KW > 1) {
         sum_of(kw);
     } else {
 #pragma unroll 1
         for (int p = 0; p < 4; ++p) {
             sum_of(p);
+            if constexpr (NORM) {
+#pragma unroll
+                for (int i = 0; i < T; ++i) {
+                    sq_total[i] = p > 0 ? sq_total[i] + sq[i] : sq[i];
+                    sq[i] = 0.f;
+                }
+            }
 #pragma unroll
             for (int m = 0; m < NM; ++m)
 #pragma unroll
@@ -138,6 +173,12 @@ gemm_f32_kernel(const float* __restrict__ a, const float* __restrict__ w, const 
                         parts[(((wave - 1) * NM + n) * T * T + i * T + j) * 64 + lane] = make_float4(v[0], v[1], v[2], v[3]);
                     }
         }
+        if constexpr (NORM) {
+            if (lq == 0) {
+#pragma unroll
+                for (int i = 0; i < T; ++i) squares[wave * 16 * T + 16 * i + l16] = sq[i];
+            }
+        }
         __syncthreads();
         if (wave > 0) return;
 #pragma unroll
@@ -157,54 +198,71 @@ gemm_f32_kernel(const float* __restrict__ a, const float* __restrict__ w, const 
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int row = m0 + 16 * i + 4 * lq + v;
+            float r = 1.f;
+            if constexpr (NORM) {
+                float total_sq;
+                if constexpr (KW > 1) {
+                    const int t = 16 * i + 4 * lq + v;
+                    total_sq = squares[t] + squares[16 * T + t] + squares[32 * T + t] + squares[48 * T + t];
+                } else {
+                    total_sq = __shfl(sq_total[i], 4 * lq + v, 64);
+                }
+                r = 1.0f / sqrtf(total_sq / float(K) + eps);
+            }
             if (row >= M) continue;
 #pragma unroll
             for (int j = 0; j < T; ++j) {
                 const int col = n0 + 16 * j + l16;
                 if (col >= N) continue;
                 float* o = out + size_t(row) * N + col;
-                const float x = acc[0][i][j][v];
+                const float x = NORM ? acc[0][i][j][v] * r : acc[0][i][j][v];
                 if constexpr (EPI == EPI_STORE_F32) *o = x;
                 else if constexpr (EPI == EPI_RESIDUAL_F32) *o += x;
-                else *o = x / (1.0f + expf(-x)) * acc[1][i][j][v];
+                else *o = x / (1.0f + expf(-x)) * (NORM ? acc[1][i][j][v] * r : acc[1][i][j][v]);
             }
         }
 }
 
-template <int T, int SP, int EPI>
-static hipError_t launch_t(const float* a, const float* w, const float* w2, float* out, int M, int N, int K, hipStream_t st) {
+template <int T, int SP, int EPI, bool NORM>
+static hipError_t launch_t(const float* a, const float* w, const float* w2, float* out, int M, int N, int K, const GemvNorm& nm,
+                           hipStream_t st) {
     constexpr int BT = 16 * T * SP;
     const int tiles_m = (M + BT - 1) / BT, tiles_n = (N + BT - 1) / BT;
     constexpr int LDS = f32_lds_total(T, SP, EPI) ? 2 * T * T * 256 * int(sizeof(float4)) : 0;
     if (LDS > 0) {
         static bool attr_set = false;   // one flag per instantiation
         if (!attr_set) {
-            hipError_t e = hipFuncSetAttribute((const void*)gemm_f32_kernel<T, SP, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+            hipError_t e = hipFuncSetAttribute((const void*)gemm_f32_kernel<T, SP, EPI, NORM>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
             if (e != hipSuccess) return e;
             attr_set = true;
         }
     }
-    hipLaunchKernelGGL((gemm_f32_kernel<T, SP, EPI>), dim3(tiles_m * tiles_n), dim3(256), LDS, st, a, w, w2, out, M, N, K, tiles_m);
+    hipLaunchKernelGGL((gemm_f32_kernel<T, SP, EPI, NORM>), dim3(tiles_m * tiles_n), dim3(256), LDS, st, a, w, w2, out, M, N, K, tiles_m,
+                       nm.gain, nm.eps);
     return hipGetLastError();
 }
 
 // The largest tile whose grid still gives most CUs a workgroup: 128 x 128 (64 x 64 per wave); 64 x 64, 32 x 32 or
 // 16 x 16 with the waves dividing K.  (512 x 4096 x 1024: 58 us on 64 x 64 tiles, 78 on 32 x 32, 72 generic.)
-template <int EPI>
-static hipError_t launch_epi(const float* a, const float* w, const float* w2, float* out, int M, int N, int K, hipStream_t st) {
+template <int EPI, bool NORM>
+static hipError_t launch_epi(const float* a, const float* w, const float* w2, float* out, int M, int N, int K, const GemvNorm& nm,
+                             hipStream_t st) {
     auto tiles = [&](long t) { return ((M + t - 1) / t) * ((N + t - 1) / t); };
-    if (tiles(128) >= 192) return launch_t<4, 2, EPI>(a, w, w2, out, M, N, K, st);
-    if (tiles(64) >= 160) return launch_t<4, 1, EPI>(a, w, w2, out, M, N, K, st);
-    if (tiles(32) >= 160) return launch_t<2, 1, EPI>(a, w, w2, out, M, N, K, st);
-    return launch_t<1, 1, EPI>(a, w, w2, out, M, N, K, st);
+    if (tiles(128) >= 192) return launch_t<4, 2, EPI, NORM>(a, w, w2, out, M, N, K, nm, st);
+    if (tiles(64) >= 160) return launch_t<4, 1, EPI, NORM>(a, w, w2, out, M, N, K, nm, st);
+    if (tiles(32) >= 160) return launch_t<2, 1, EPI, NORM>(a, w, w2, out, M, N, K, nm, st);
+    return launch_t<1, 1, EPI, NORM>(a, w, w2, out, M, N, K, nm, st);
 }
 
-hipError_t launch_gemm_f32(int epi, const float* a, const float* w, const float* w2, float* out, int M, int N, int K, hipStream_t st) {
+hipError_t launch_gemm_f32(int epi, const float* a, const float* w, const float* w2, float* out, int M, int N, int K, hipStream_t st,
+                           const GemvNorm& nm) {
     if (M <= 0 || N <= 0) return hipSuccess;
-    if (K <= 0 || (K & 3)) return hipErrorInvalidValue;
-    if (epi == EPI_STORE_F32) return launch_epi<EPI_STORE_F32>(a, w, w2, out, M, N, K, st);
-    if (epi == EPI_RESIDUAL_F32) return launch_epi<EPI_RESIDUAL_F32>(a, w, w2, out, M, N, K, st);
-    if (epi == EPI_SWIGLU) return launch_epi<EPI_SWIGLU>(a, w, w2, out, M, N, K, st);
+    if (K <= 0 || (K & 3) || (nm.gain && epi == EPI_RESIDUAL_F32)) return hipErrorInvalidValue;
+    if (epi == EPI_STORE_F32)
+        return nm.gain ? launch_epi<EPI_STORE_F32, true>(a, w, w2, out, M, N, K, nm, st) : launch_epi<EPI_STORE_F32, false>(a, w, w2, out, M, N, K, nm, st);
+    if (epi == EPI_RESIDUAL_F32) return launch_epi<EPI_RESIDUAL_F32, false>(a, w, w2, out, M, N, K, nm, st);
+    if (epi == EPI_SWIGLU)
+        return nm.gain ? launch_epi<EPI_SWIGLU, true>(a, w, w2, out, M, N, K, nm, st) : launch_epi<EPI_SWIGLU, false>(a, w, w2, out, M, N, K, nm, st);
     return hipErrorInvalidValue;
 }
 
