@@ -238,8 +238,8 @@ static hipError_t prof_after(cake_ctx* c) {
         HIP_TRY(c, prof_after(c));                          \
     } while (0)
 
-// Enqueues the prefill of [tok_begin, tok_begin+rows); token ids already in c->d_ids.
-static int enqueue_prefill(cake_ctx* c, int tok_begin, int rows, const cake_kv* kv) {
+// Enqueues the prefill of [tok_begin, tok_begin+rows); token ids already in c->d_ids, or (the rows' own) in ids_by_value.
+static int enqueue_prefill(cake_ctx* c, int tok_begin, int rows, const cake_kv* kv, const TokenIds* ids_by_value = nullptr) {
     const cake_model_desc& m = c->m;
     const uint64_t d = m.d_model, hq = uint64_t(m.n_q_heads) * m.head_dim, hkv = uint64_t(m.n_kv_heads) * m.head_dim;
     const uint64_t nqkv = hq + 2 * hkv, ff = m.ffn_dim, R = rows, e = esize(c);
@@ -247,8 +247,16 @@ static int enqueue_prefill(cake_ctx* c, int tok_begin, int rows, const cake_kv* 
     // algorithmic work per launch: flops of the contraction; bytes = operands once + result once
     const uint64_t attn_flops = 4 * hq * (t0 * R + R * (R + 1) / 2);
     const uint64_t attn_bytes = (2 * R * hq + 2 * hkv * (t0 + R)) * e;
-    KLAUNCH(c, CAKE_K_EMBED, 0, R * d * (e + 4), launch_embed(m.dtype, c->embed, c->d_ids + tok_begin, c->x, rows, d, m.vocab, c->cs));
-    HIP_TRY(c, launch_rope_table(c->rope_cs, tok_begin, rows, m.head_dim, m.rope_theta, c->cs));
+    // A float32 product norms its input itself (not where a test asks for the plain kernels).
+    auto norms_itself = [&](const float* gain, const void* wa, const void* wb) {
+        return m.dtype == CAKE_F32 && c->tun.kernel_path == 0 && ((uintptr_t(gain) | uintptr_t(wa) | uintptr_t(wb)) & 15) == 0;
+    };
+    const cake_layer_weights& first = c->layers[0];
+    const bool norm_first = !norms_itself(first.attn_norm, first.wqkv, nullptr);
+    bool normed = false;   // the first layer's input
+    KLAUNCH(c, CAKE_K_EMBED, 0, R * d * (e + 4 + (norm_first ? e : 0)),
+            launch_prefill_begin(m.dtype, {c->embed, c->x, rows, int(d), m.vocab, norm_first ? first.attn_norm : nullptr, c->h, m.rms_eps,
+                                           c->rope_cs, tok_begin, m.head_dim, m.rope_theta}, c->d_ids + tok_begin, ids_by_value, c->cs, &normed));
     // A product may leave its K ranges in the split workspace for the kernel after it, which reads them before anything
     // else is put there: QKV for the rotary step, O and down for the norm (the last layer's down for a sum of its own).
     const bool rope_adds = (uintptr_t(kv->pool) & 15) == 0;
@@ -267,10 +275,6 @@ static int enqueue_prefill(cake_ctx* c, int tok_begin, int rows, const cake_kv* 
     auto product = [&](const GemmPartsPlan& plan, int epi, const void* a, const void* w, float* out, int N, int K) {
         return plan.ksplit ? launch_gemm_parts(plan, a, w, parts, rows, N, K, c->cs) : gemm(c, epi, a, w, nullptr, out, rows, N, K, plan_rows, c->step_free);
     };
-    // A float32 product norms its input itself (not where a test asks for the plain kernels).
-    auto norms_itself = [&](const float* gain, const void* wa, const void* wb) {
-        return m.dtype == CAKE_F32 && c->tun.kernel_path == 0 && ((uintptr_t(gain) | uintptr_t(wa) | uintptr_t(wb)) & 15) == 0;
-    };
     auto normed_product = [&](int epi, const void* wa, const void* wb, void* out, int N, const float* gain) {
         return launch_gemm_f32(epi, c->x, (const float*)wa, (const float*)wb, (float*)out, rows, N, int(d), c->cs, {gain, m.rms_eps});
     };
@@ -281,7 +285,7 @@ static int enqueue_prefill(cake_ctx* c, int tok_begin, int rows, const cake_kv* 
         if (norms_itself(w.attn_norm, w.wqkv, nullptr)) {
             KLAUNCH(c, CAKE_K_GEMM_QKV, 2 * R * nqkv * d, qkv_bytes, normed_product(EPI_STORE_F32, w.wqkv, nullptr, c->qkv, int(nqkv), w.attn_norm));
         } else {
-            KLAUNCH(c, CAKE_K_RMSNORM, 0, R * d * (4 + e), norm(l > 0 ? p_down : none, w.attn_norm));
+            if (l > 0 || !normed) KLAUNCH(c, CAKE_K_RMSNORM, 0, R * d * (4 + e), norm(l > 0 ? p_down : none, w.attn_norm));
             KLAUNCH(c, CAKE_K_GEMM_QKV, 2 * R * nqkv * d, qkv_bytes, product(p_qkv, EPI_STORE_F32, c->h, w.wqkv, c->qkv, nqkv, d));
         }
         KLAUNCH(c, CAKE_K_ROPE_KV, 0, R * nqkv * (4 + e),
@@ -804,6 +808,14 @@ int32_t cake_prefill_chunk(cake_ctx* c, const int32_t* token_ids, int32_t tok_be
     for (int i = 0; i < tok_count; ++i) {
         int id = token_ids[tok_begin + i];
         if (id < 0 || id >= c->m.vocab) return fail(c, CAKE_E_INVAL, "token id %d at %d outside the vocabulary", id, tok_begin + i);
+    }
+    // A short step's ids go with its first launch; in a captured stream they stay a copy that a replay reads anew.
+    hipStreamCaptureStatus capturing;
+    HIP_TRY(c, hipStreamIsCapturing(c->cs, &capturing));
+    if (tok_count <= TokenIds::MAX && capturing == hipStreamCaptureStatusNone) {
+        TokenIds ids = {};
+        memcpy(ids.v, token_ids + tok_begin, size_t(tok_count) * 4);
+        return enqueue_prefill(c, tok_begin, tok_count, kv, &ids);
     }
     HIP_TRY(c, hipMemcpyAsync(c->d_ids + tok_begin, token_ids + tok_begin, size_t(tok_count) * 4, hipMemcpyHostToDevice, c->cs));
     return enqueue_prefill(c, tok_begin, tok_count, kv);

@@ -24,8 +24,16 @@ struct KvView {
 enum GemmEpilogue { EPI_STORE_F32 = 0, EPI_RESIDUAL_F32 = 1, EPI_SWIGLU = 2 };
 
 // ---- generic kernels (any supported shape) ----
-hipError_t launch_embed(int dtype, const void* table, const int32_t* ids, float* x, int rows,
-                        int d, int vocab, hipStream_t st);
+// What a prefill begins with, in one launch: x = the rows' embeddings, cs = the rotary table of positions tok_begin ..; with a
+// gain also h = the RMSNorm of x where d and the alignment allow it (*normed says whether).  ids: device memory, or
+// ids_by_value (at most TokenIds::MAX rows).
+struct TokenIds { static constexpr int MAX = 512; int32_t v[MAX]; };   // 2 KB of a launch's 4 KB of arguments
+struct PrefillBegin {
+    const void* table; float* x; int rows, d, vocab;
+    const float* gain; void* h; float eps;
+    float* cs; int tok_begin, head_dim; float theta;
+};
+hipError_t launch_prefill_begin(int dtype, const PrefillBegin& b, const int32_t* ids, const TokenIds* ids_by_value, hipStream_t st, bool* normed);
 hipError_t launch_rmsnorm(int dtype, const float* x, const float* gain, void* out, int rows, int d,
                           float eps, hipStream_t st);
 hipError_t launch_rope_table(float* cs, int tok_begin, int rows, int head_dim, float theta,

@@ -28,44 +28,6 @@ __device__ __forceinline__ float wave_max(float v) {
     return v;
 }
 
-// ------------------------------------------------------------------ embedding
-template <typename T>
-__global__ void __launch_bounds__(256) embed_kernel(const T* __restrict__ table, const int32_t* __restrict__ ids,
-                                                    float* __restrict__ x, int d, int vocab) {
-    int row = blockIdx.x;
-    int id = ids[row];
-    id = id < 0 ? 0 : (id >= vocab ? vocab - 1 : id);
-    const T* src = table + size_t(id) * d;
-    float* dst = x + size_t(row) * d;
-    for (int c = threadIdx.x; c < d; c += 256) dst[c] = to_f<T>(src[c]);
-}
-
-// bf16 rows of a multiple of 8 elements, 16 bytes of a row per thread (1024 rows of 4096: 15 -> 10 us, 137: 10 -> 4).
-__global__ void __launch_bounds__(256) embed_bf16_vec_kernel(const bf16_t* __restrict__ table, const int32_t* __restrict__ ids,
-                                                             float* __restrict__ x, int d, int vocab) {
-    int id = ids[blockIdx.x];
-    id = id < 0 ? 0 : (id >= vocab ? vocab - 1 : id);
-    const uint4* src = (const uint4*)(table + size_t(id) * d);
-    float4* dst = (float4*)(x + size_t(blockIdx.x) * d);
-    for (int c = threadIdx.x; c < d / 8; c += 256) {
-        const uint4 v = src[c];
-        dst[2 * c] = make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xFFFF0000u), __uint_as_float(v.y << 16),
-                                 __uint_as_float(v.y & 0xFFFF0000u));
-        dst[2 * c + 1] = make_float4(__uint_as_float(v.z << 16), __uint_as_float(v.z & 0xFFFF0000u), __uint_as_float(v.w << 16),
-                                     __uint_as_float(v.w & 0xFFFF0000u));
-    }
-}
-
-hipError_t launch_embed(int dtype, const void* table, const int32_t* ids, float* x, int rows, int d,
-                        int vocab, hipStream_t st) {
-    if (rows <= 0) return hipSuccess;
-    if (dtype == 0) hipLaunchKernelGGL(embed_kernel<float>, dim3(rows), dim3(256), 0, st, (const float*)table, ids, x, d, vocab);
-    else if (d % 8 == 0 && ((uintptr_t(table) | uintptr_t(x)) & 15) == 0)
-        hipLaunchKernelGGL(embed_bf16_vec_kernel, dim3(rows), dim3(256), 0, st, (const bf16_t*)table, ids, x, d, vocab);
-    else hipLaunchKernelGGL(embed_kernel<bf16_t>, dim3(rows), dim3(256), 0, st, (const bf16_t*)table, ids, x, d, vocab);
-    return hipGetLastError();
-}
-
 // ------------------------------------------------------------------ RMSNorm
 // y = x / sqrt(mean(x^2) + eps) * gain ; one 256-thread block per row.
 template <typename T>
@@ -82,6 +44,33 @@ __global__ void __launch_bounds__(256) rmsnorm_kernel(const float* __restrict__ 
     float r = 1.0f / sqrtf(tot / float(d) + eps);
     T* o = out + size_t(blockIdx.x) * d;
     for (int c = threadIdx.x; c < d; c += 256) o[c] = from_f<T>(xr[c] * r * gain[c]);
+}
+
+// The norm of a row that the workgroup's threads hold in pieces, thread t the elements 4 t .. 4 t + 3 of every 1024.
+template <typename T, int NV>
+__device__ __forceinline__ void rmsnorm_row(const float4 (&v)[NV], float* part, const float* __restrict__ gain, T* __restrict__ o, float eps) {
+    constexpr int d = NV * 1024;
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) s += v[i].x * v[i].x + v[i].y * v[i].y + v[i].z * v[i].z + v[i].w * v[i].w;
+    s = wave_sum(s);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
+    __syncthreads();
+    const float tot = part[0] + part[1] + part[2] + part[3];
+    const float r = 1.0f / sqrtf(tot / float(d) + eps);
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        const int c4 = threadIdx.x + 256 * i;
+        const float4 g = ((const float4*)gain)[c4];
+        const float y0 = v[i].x * r * g.x, y1 = v[i].y * r * g.y, y2 = v[i].z * r * g.z, y3 = v[i].w * r * g.w;
+        if constexpr (sizeof(T) == 4) {
+            ((float4*)o)[c4] = make_float4(y0, y1, y2, y3);
+        } else {
+            typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4_t;
+            bf16x4_t w = {from_f<T>(y0), from_f<T>(y1), from_f<T>(y2), from_f<T>(y3)};
+            ((bf16x4_t*)o)[c4] = w;
+        }
+    }
 }
 
 // Rows whose length is a multiple of 1024: every thread keeps its NV float4 pieces of the row in
@@ -110,28 +99,7 @@ __global__ void __launch_bounds__(256) rmsnorm_vec_kernel(float* __restrict__ x,
 #pragma unroll
         for (int i = 0; i < NV; ++i) xr[threadIdx.x + 256 * i] = v[i];
     }
-    float s = 0.f;
-#pragma unroll
-    for (int i = 0; i < NV; ++i) s += v[i].x * v[i].x + v[i].y * v[i].y + v[i].z * v[i].z + v[i].w * v[i].w;
-    s = wave_sum(s);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
-    __syncthreads();
-    const float tot = part[0] + part[1] + part[2] + part[3];
-    const float r = 1.0f / sqrtf(tot / float(d) + eps);
-    T* o = out + size_t(blockIdx.x) * d;
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        const int c4 = threadIdx.x + 256 * i;
-        const float4 g = ((const float4*)gain)[c4];
-        const float y0 = v[i].x * r * g.x, y1 = v[i].y * r * g.y, y2 = v[i].z * r * g.z, y3 = v[i].w * r * g.w;
-        if constexpr (sizeof(T) == 4) {
-            ((float4*)o)[c4] = make_float4(y0, y1, y2, y3);
-        } else {
-            typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4_t;
-            bf16x4_t w = {from_f<T>(y0), from_f<T>(y1), from_f<T>(y2), from_f<T>(y3)};
-            ((bf16x4_t*)o)[c4] = w;
-        }
-    }
+    rmsnorm_row<T, NV>(v, part, gain, out + size_t(blockIdx.x) * d, eps);
 }
 
 template <typename T>
@@ -196,8 +164,7 @@ hipError_t launch_rmsnorm_parts(int dtype, float* x, const float* parts, int n_p
 // ------------------------------------------------------------------ rotary table
 // cs[row][pair] = (cos, sin) of (tok_begin + row) * theta^(-2*pair/head_dim).  The angle is
 // formed in double precision: at position 65535 a float32 angle is off by ~4e-3 rad.
-__global__ void rope_table_kernel(float2* __restrict__ cs, int tok_begin, int rows, int half, double log2_theta) {
-    int idx = blockIdx.x * blockDim.x + threadIdx.x;
+__device__ __forceinline__ void rope_table_entry(float2* __restrict__ cs, int idx, int tok_begin, int rows, int half, double log2_theta) {
     if (idx >= rows * half) return;
     int row = idx / half, pair = idx % half;
     double inv_freq = exp2(-(double(pair) / double(half)) * log2_theta);
@@ -207,12 +174,96 @@ __global__ void rope_table_kernel(float2* __restrict__ cs, int tok_begin, int ro
     cs[idx] = make_float2(float(c), float(s));
 }
 
+__global__ void __launch_bounds__(256) rope_table_kernel(float2* __restrict__ cs, int tok_begin, int rows, int half, double log2_theta) {
+    rope_table_entry(cs, blockIdx.x * 256 + threadIdx.x, tok_begin, rows, half, log2_theta);
+}
+
 hipError_t launch_rope_table(float* cs, int tok_begin, int rows, int head_dim, float theta, hipStream_t st) {
     if (rows <= 0) return hipSuccess;
     int half = head_dim / 2, n = rows * half;
     hipLaunchKernelGGL(rope_table_kernel, dim3((n + 255) / 256), dim3(256), 0, st, (float2*)cs, tok_begin, rows, half,
                        log2(double(theta)));
     return hipGetLastError();
+}
+
+// ------------------------------------------------------------------ what a prefill begins with
+// One launch: the rows' embeddings (x), their first RMSNorm (h; NV 1024-element pieces of a row, NV = 0: no norm) and, by the
+// workgroups after the rows', the rotary table.  They were three launches of 2 to 10 us at the start of a step, when the host
+// is not ahead of the GPU yet.  Token ids: device memory, or (TokenIds) the launch's own arguments, which saves a short step
+// the copy in front of it.  Two layers, us: 137 rows of the Llama3-8B shape 346 -> 335, 512 rows of the small model with heads
+// of 64 313 -> 299, 256 rows of the tiny model 126 -> 119.
+struct IdsInMemory {
+    const int32_t* p;
+    __device__ int32_t operator[](int row) const { return p[row]; }
+};
+struct IdsInArguments {
+    TokenIds t;
+    __device__ int32_t operator[](int row) const { return t.v[row]; }
+};
+template <typename T, int NV, typename Ids>
+__global__ void __launch_bounds__(256)
+prefill_begin_kernel(const T* __restrict__ table, const Ids ids, float* __restrict__ x, int d_any, int vocab, int rows,
+                     const float* __restrict__ gain, T* __restrict__ out, float eps, float2* __restrict__ cs, int tok_begin, int half,
+                     double log2_theta) {
+    __shared__ float part[4];
+    if (int(blockIdx.x) >= rows) {
+        rope_table_entry(cs, (blockIdx.x - rows) * 256 + threadIdx.x, tok_begin, rows, half, log2_theta);
+        return;
+    }
+    int id = ids[blockIdx.x];
+    id = id < 0 ? 0 : (id >= vocab ? vocab - 1 : id);
+    if constexpr (NV == 0) {
+        const T* src = table + size_t(id) * d_any;
+        float* dst = x + size_t(blockIdx.x) * d_any;
+        for (int c = threadIdx.x; c < d_any; c += 256) dst[c] = to_f<T>(src[c]);
+    } else {
+        constexpr int d = NV * 1024;
+        typedef __attribute__((__vector_size__(4 * sizeof(T)))) T vec4_t;
+        const vec4_t* src = (const vec4_t*)(table + size_t(id) * d);
+        float4 v[NV];
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const vec4_t t = src[threadIdx.x + 256 * i];
+            v[i] = make_float4(to_f<T>(t[0]), to_f<T>(t[1]), to_f<T>(t[2]), to_f<T>(t[3]));
+        }
+#pragma unroll
+        for (int i = 0; i < NV; ++i) ((float4*)(x + size_t(blockIdx.x) * d))[threadIdx.x + 256 * i] = v[i];
+        rmsnorm_row<T, NV>(v, part, gain, out + size_t(blockIdx.x) * d, eps);
+    }
+}
+
+template <typename T, int NV, typename Ids>
+static void launch_begin(const PrefillBegin& b, const Ids& ids, hipStream_t st) {
+    const int half = b.head_dim / 2;
+    hipLaunchKernelGGL((prefill_begin_kernel<T, NV, Ids>), dim3(b.rows + (b.rows * half + 255) / 256), dim3(256), 0, st, (const T*)b.table, ids, b.x,
+                       b.d, b.vocab, b.rows, b.gain, (T*)b.h, b.eps, (float2*)b.cs, b.tok_begin, half, log2(double(b.theta)));
+}
+template <typename T, typename Ids>
+static hipError_t launch_begin_any(const PrefillBegin& b, bool norm, const Ids& ids, hipStream_t st) {
+    switch (norm ? b.d / 1024 : 0) {
+        case 1: launch_begin<T, 1>(b, ids, st); break;
+        case 2: launch_begin<T, 2>(b, ids, st); break;
+        case 3: launch_begin<T, 3>(b, ids, st); break;
+        case 4: launch_begin<T, 4>(b, ids, st); break;
+        case 5: launch_begin<T, 5>(b, ids, st); break;
+        case 6: launch_begin<T, 6>(b, ids, st); break;
+        case 7: launch_begin<T, 7>(b, ids, st); break;
+        case 8: launch_begin<T, 8>(b, ids, st); break;
+        default: launch_begin<T, 0>(b, ids, st);
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_prefill_begin(int dtype, const PrefillBegin& b, const int32_t* ids, const TokenIds* ids_by_value, hipStream_t st, bool* normed) {
+    *normed = false;
+    if (b.rows <= 0) return hipSuccess;
+    if (ids_by_value && b.rows > TokenIds::MAX) return hipErrorInvalidValue;
+    // whole pieces of 1024 elements, 16 bytes of x, h and the gains at once (8 of a bf16 table)
+    *normed = b.gain && b.d % 1024 == 0 && b.d <= 8192 && ((uintptr_t(b.table) | uintptr_t(b.x) | uintptr_t(b.gain) | uintptr_t(b.h)) & 15) == 0;
+    if (ids_by_value)
+        return dtype == 0 ? launch_begin_any<float>(b, *normed, IdsInArguments{*ids_by_value}, st)
+                          : launch_begin_any<bf16_t>(b, *normed, IdsInArguments{*ids_by_value}, st);
+    return dtype == 0 ? launch_begin_any<float>(b, *normed, IdsInMemory{ids}, st) : launch_begin_any<bf16_t>(b, *normed, IdsInMemory{ids}, st);
 }
 
 // ------------------------------------------------------------------ rotary + KV page write
