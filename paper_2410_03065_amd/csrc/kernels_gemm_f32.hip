@@ -44,7 +44,7 @@ gemm_f32_kernel(const float* __restrict__ a, const float* __restrict__ w, const 
     constexpr int BT = 16 * T * SP;                  // rows and columns of the workgroup's tile
     constexpr bool LDS_TOTAL = f32_lds_total(T, SP, EPI);
     __shared__ float4 parts[KW > 1 ? (KW - 1) * NM * T * T * 64 : 1];
-    __shared__ float squares[NORM && KW > 1 ? KW * 16 * T : 1];   // of a row in a quarter of K
+    __shared__ float squares[NORM ? 64 * T : 1];   // of a row in a quarter of K
     extern __shared__ __attribute__((aligned(16))) float4 total_lds[];   // LDS_TOTAL: [NM][T][T][256]
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int l16 = lane & 15, lq = lane >> 4;
@@ -193,22 +193,21 @@ gemm_f32_kernel(const float* __restrict__ a, const float* __restrict__ w, const 
                         acc[n][i][j][0] += v.x; acc[n][i][j][1] += v.y; acc[n][i][j][2] += v.z; acc[n][i][j][3] += v.w;
                     }
     }
+    float factor[T];   // NORM: of row l16 of row tile i
+    if constexpr (NORM) {
+#pragma unroll
+        for (int i = 0; i < T; ++i) {
+            const int t = 16 * i + l16;
+            const float s = KW > 1 ? squares[t] + squares[16 * T + t] + squares[32 * T + t] + squares[48 * T + t] : sq_total[i];
+            factor[i] = 1.0f / sqrtf(s / float(K) + eps);
+        }
+    }
 #pragma unroll
     for (int i = 0; i < T; ++i)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int row = m0 + 16 * i + 4 * lq + v;
-            float r = 1.f;
-            if constexpr (NORM) {
-                float total_sq;
-                if constexpr (KW > 1) {
-                    const int t = 16 * i + 4 * lq + v;
-                    total_sq = squares[t] + squares[16 * T + t] + squares[32 * T + t] + squares[48 * T + t];
-                } else {
-                    total_sq = __shfl(sq_total[i], 4 * lq + v, 64);
-                }
-                r = 1.0f / sqrtf(total_sq / float(K) + eps);
-            }
+            const float r = NORM ? __shfl(factor[i], 4 * lq + v, 64) : 1.f;
             if (row >= M) continue;
 #pragma unroll
             for (int j = 0; j < T; ++j) {
@@ -244,13 +243,16 @@ static hipError_t launch_t(const float* a, const float* w, const float* w2, floa
 
 // The largest tile whose grid still gives most CUs a workgroup: 128 x 128 (64 x 64 per wave); 64 x 64, 32 x 32 or
 // 16 x 16 with the waves dividing K.  (512 x 4096 x 1024: 58 us on 64 x 64 tiles, 78 on 32 x 32, 72 generic.)
+// Where K is short, a tile's life is latency and 16 x 16 tiles in threes on a CU hide each other's (us, 16 and 32 square: 192
+// tiles of 32, K 256 5.0 and 5.3, with norm and SwiGLU 7.8 and 9.0; K 688 7.6 and 8.0, 13.7 and 16.0; 256 tiles, K 256 6.0 and 5.4,
+// K 688 9.2 and 8.1; 192 tiles, K 1536 18.7 and 16.0).
 template <int EPI, bool NORM>
 static hipError_t launch_epi(const float* a, const float* w, const float* w2, float* out, int M, int N, int K, const GemvNorm& nm,
                              hipStream_t st) {
     auto tiles = [&](long t) { return ((M + t - 1) / t) * ((N + t - 1) / t); };
     if (tiles(128) >= 192) return launch_t<4, 2, EPI, NORM>(a, w, w2, out, M, N, K, nm, st);
     if (tiles(64) >= 160) return launch_t<4, 1, EPI, NORM>(a, w, w2, out, M, N, K, nm, st);
-    if (tiles(32) >= 160) return launch_t<2, 1, EPI, NORM>(a, w, w2, out, M, N, K, nm, st);
+    if (tiles(32) >= (K <= 1024 ? 224 : 160)) return launch_t<2, 1, EPI, NORM>(a, w, w2, out, M, N, K, nm, st);
     return launch_t<1, 1, EPI, NORM>(a, w, w2, out, M, N, K, nm, st);
 }
 
