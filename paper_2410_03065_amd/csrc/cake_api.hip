@@ -810,8 +810,8 @@ int32_t cake_prefill_chunk(cake_ctx* c, const int32_t* token_ids, int32_t tok_be
         if (id < 0 || id >= c->m.vocab) return fail(c, CAKE_E_INVAL, "token id %d at %d outside the vocabulary", id, tok_begin + i);
     }
     // A short step's ids go with its first launch; in a captured stream they stay a copy that a replay reads anew.
-    hipStreamCaptureStatus capturing;
-    HIP_TRY(c, hipStreamIsCapturing(c->cs, &capturing));
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusActive;
+    if (tok_count <= TokenIds::MAX && hipStreamIsCapturing(c->cs, &capturing) != hipSuccess) (void)hipGetLastError();   // unknown: copy
     if (tok_count <= TokenIds::MAX && capturing == hipStreamCaptureStatusNone) {
         TokenIds ids = {};
         memcpy(ids.v, token_ids + tok_begin, size_t(tok_count) * 4);
