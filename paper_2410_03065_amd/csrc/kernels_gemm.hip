@@ -336,9 +336,9 @@ hipError_t launch_mfma_rate(float* out, int workgroups, int iters, hipStream_t s
 // Tile configurations.  Chosen per GEMM by gemm_pick() from how well the grid fills 256 CUs.
 struct GemmCfg { int bm, bn; };
 // GCFG_128x128K: the 128x128 tile as two 128x64 halves, each shared by two waves that divide K (KW = 2)
-// GCFG_P256: the persistent four-wave kernel (256x256 tiles, several per workgroup)
-// GCFG_192x128: gate/up of 129 to 192 rows in one tile of all rows (137 rows of the Llama3-8B shape 76 -> 58 us, 192 rows
-// 78 -> 61, against the persistent kernel's 256 rows; two bands of 128 take 78)
+// GCFG_P256: items of 256 rows on a persistent kernel (several per workgroup; launch_p256)
+// GCFG_192x128: gate/up of 129 to 192 rows in one tile of all rows (137 rows of the Llama3-8B shape 56 us, 192 rows 58, against
+// 62 and 63 on items of 256 rows; two bands of 128 take 82 and 89)
 enum { GCFG_256x256 = 0, GCFG_256x128 = 1, GCFG_128x128 = 2, GCFG_128x192 = 3, GCFG_128x64 = 4, GCFG_128x128K = 5, GCFG_P256 = 6,
        GCFG_192x128 = 7, GCFG_COUNT = 8 };
 static const GemmCfg kGemmCfg[GCFG_COUNT] = {{256, 256}, {256, 128}, {128, 128}, {128, 192}, {128, 64}, {128, 128}, {256, 256}, {192, 128}};
