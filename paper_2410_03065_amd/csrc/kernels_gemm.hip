@@ -475,15 +475,15 @@ bool gemm_order_fixed(int epi, int max_rows, int N, int K, const GemmSplitWs* ws
     return true;
 }
 
-// Items of 256 rows: on the eight waves in turn (kernels_gemm_pp.hip), but for float32 stores of items of under 56 slices, where
-// its two phases of one group alone weigh more.  us, four waves / in turn, each with the pass that adds the ranges up: 224 slices
-// of 256 items 372 and 369, 128 of 128 items 163 and 157, 112 of 128 items 151 and 143, 72 of 120 items 100.7 and 99.5, 56 of 256
-// items 111.8 and 110.9; 54 of 160 items 84.3 and 85.3, 43 of 128 items 67.0 and 68.2, 28.7 of 192 items 59.3 and 60.7, 16 of 128
-// items 34.2 and 36.5.  Both give the same bits.
+// Items of 256 rows: on the eight waves in turn (kernels_gemm_pp.hip), but for float32 stores of items of under 100 slices, where
+// its two phases of one group alone weigh as much as it gains.  us, four waves / in turn, each with the pass that adds the ranges
+// up: 224 slices of 256 items 359.7 and 357.4, 128 of 128 items 163 and 157, 112 of 256 items 203.5 and 202.2, 108 of 160 items
+// 141.9 and 138.2; 75 of 192 items 111.2 and 110.4, 72 of 240 items 118.1 and 119.0, 64 of 256 items 119.6 and 120.9, 56 of 256
+// items 103.2 and 104.6, 43 of 128 items 67.0 and 68.2, 16 of 128 items 34.2 and 36.5.  Both give the same bits.
 template <int EPI>
 static hipError_t launch_p256(const bf16_t* A, const bf16_t* W, const bf16_t* W2, void* out, int M, int N, int K, const P256Plan& plan,
                               int ks, hipStream_t st) {
-    if (EPI != EPI_STORE_F32 || K / 64 / ks >= 56) return launch_gemm_pp(EPI, A, W, W2, out, M, N, K, plan, ks, st);
+    if (EPI != EPI_STORE_F32 || K / 64 / ks >= 100) return launch_gemm_pp(EPI, A, W, W2, out, M, N, K, plan, ks, st);
     const int tiles_m = (M + 255) / 256, nb = tiles_m * (plan.n8 + plan.n6 + plan.n4) * ks;
     if (nb == 0 || (uintptr_t(out) & 15)) return hipErrorInvalidValue;
     // a whole number of rounds: every workgroup takes `rounds` items (the last may take one less)

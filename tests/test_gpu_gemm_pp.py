@@ -1,5 +1,5 @@
 """bf16 products of items of 256 rows on the kernel with eight waves in turn: one slice of K, two and three, the line between it
-and the four-wave kernel (56 slices), panels of every width, ragged rows, several items to a workgroup, K ranges of unequal
+and the four-wave kernel (100 slices), panels of every width, ragged rows, several items to a workgroup, K ranges of unequal
 length, and results that are not 16-byte aligned (which a tile kernel forms)."""
 import pytest
 
@@ -32,7 +32,7 @@ def _rel(got, want):
 # of the largest value for the sums in front of it.
 @pytest.mark.parametrize("M,N,K", [
     (1, 128, 64), (128, 128, 128), (129, 192, 192), (255, 256, 64), (257, 320, 128), (256, 448, 192),
-    (300, 384, 3520), (300, 384, 3584), (511, 640, 3648),                                                # 55, 56 and 57 slices
+    (300, 384, 6336), (300, 384, 6400), (511, 640, 6464),                                                # 99, 100 and 101 slices
     (1000, 16640, 64), (1024, 14336, 128), (700, 33280, 192)])                                           # two rounds and more
 def test_gemm_items_of_256_rows(M, N, K):
     import torch
@@ -49,7 +49,7 @@ def test_gemm_items_of_256_rows(M, N, K):
     assert bool(((got - want).abs() <= 2.0 ** -8 * 1.01 * want.abs() + 1e-6 * want.abs().max()).all())
 
 
-@pytest.mark.parametrize("M,N,K,ranges", [(300, 512, 7168, 2), (257, 256, 7232, 2), (1024, 1024, 14336, 4)])   # 56; 57 and 56; 56
+@pytest.mark.parametrize("M,N,K,ranges", [(300, 512, 12800, 2), (257, 256, 12864, 2), (1024, 1024, 14336, 4)])   # 100; 101 and 100; 56
 def test_gemm_k_ranges_of_items_of_256_rows(M, N, K, ranges):
     eng = _engine(gemm_ksplit=ranges)
     a, w, _, x0 = _operands(eng, M, N, K)
