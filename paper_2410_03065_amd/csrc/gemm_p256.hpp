@@ -15,7 +15,7 @@ typedef __attribute__((__vector_size__(4 * sizeof(int)))) int p256_frag_t;
 // rows of A (x one K range when K is split).
 struct P256Plan { int n8, n6, n4; };
 
-// kernels_gemm_pp.hip; out: 16-byte aligned.  ks > 1 (float32 store): every K range an output of its own.
+// kernels_gemm_pp.hip; out: on a whole element.  ks > 1 (float32 store): every K range an output of its own.
 hipError_t launch_gemm_pp(int epi, const bf16_t* A, const bf16_t* W, const bf16_t* W2, void* out, int M, int N, int K,
                           const P256Plan& plan, int ks, hipStream_t st);
 

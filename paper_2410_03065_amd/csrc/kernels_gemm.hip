@@ -485,7 +485,7 @@ static hipError_t launch_p256(const bf16_t* A, const bf16_t* W, const bf16_t* W2
                               int ks, hipStream_t st) {
     if (EPI != EPI_STORE_F32 || K / 64 / ks >= 100) return launch_gemm_pp(EPI, A, W, W2, out, M, N, K, plan, ks, st);
     const int tiles_m = (M + 255) / 256, nb = tiles_m * (plan.n8 + plan.n6 + plan.n4) * ks;
-    if (nb == 0 || (uintptr_t(out) & 15)) return hipErrorInvalidValue;
+    if (nb == 0) return hipErrorInvalidValue;
     // a whole number of rounds: every workgroup takes `rounds` items (the last may take one less)
     const int rounds = (nb + 255) / 256, wgs = (nb + rounds - 1) / rounds;
     static bool attr_set = false;
@@ -674,7 +674,8 @@ hipError_t launch_gemm_mfma(int epi, const void* a, const void* w, const void* w
                             hipStream_t st, int cfg_override, const GemmSplitWs* ws, int ksplit_override) {
     const bf16_t *A = (const bf16_t*)a, *W = (const bf16_t*)w, *W2 = (const bf16_t*)w2;
     GemmChoice ch = gemm_choose(epi, M, N, K, cfg_override, ws, ksplit_override);
-    if (ch.cfg == GCFG_P256 && (uintptr_t(out) & 15)) ch = GemmChoice{GCFG_128x128, 1};   // the persistent kernels store 8 and 16 bytes at once
+    if (ch.cfg == GCFG_P256 && (uintptr_t(out) & (epi == EPI_SWIGLU ? 1 : 3))) ch = GemmChoice{GCFG_128x128, 1};   // off whole elements
+    if (ch.cfg == GCFG_P256 && (uintptr_t(out) & 15)) ch.ksplit = 1;   // forced K ranges: the pass that adds them up takes 16 bytes at once
     if (!gemm_cfg_ok(ch.cfg, epi, M, N, K)) return hipErrorInvalidValue;
     if (epi == EPI_SWIGLU) return gemm_launch_cfg<EPI_SWIGLU>(ch.cfg, 1, ws, A, W, W2, out, M, N, K, st);
     if (epi == EPI_RESIDUAL_F32) return gemm_launch_cfg<EPI_RESIDUAL_F32>(ch.cfg, ch.ksplit, ws, A, W, W2, out, M, N, K, st);

@@ -30,6 +30,9 @@
 // them wait for more.
 // SwiGLU: the W rows of a half alternate between the two matrices in groups of sixteen (even MFMA tiles of a wave hold gate
 // columns, odd ones the same columns of up), so an item yields half as many output columns, formed in registers.
+// Stores of 16 bytes need a result on 4 bytes, which every float32 result is; ODD: a bf16 result that starts half-way between
+// two words leaves in pieces of two and four bytes (1024 x 4096 -> 2 x 14336: 174 us on 4 bytes, 184 between two words, on
+// 128 x 128 tiles 311).
 #include <type_traits>
 #include <utility>
 
@@ -59,7 +62,7 @@ template <int N, typename F> __device__ __forceinline__ void pp_each(F f) {
     [&]<int... X>(std::integer_sequence<int, X...>) { (f(std::integral_constant<int, X>{}), ...); }(std::make_integer_sequence<int, N>{});
 }
 
-template <int EPI>
+template <int EPI, bool ODD>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2), amdgpu_num_vgpr(128)))
 gemm_pp_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, const bf16_t* __restrict__ W2,
                  void* __restrict__ outv, int M, int N, int K, int tiles_m, P256Plan plan, int tiles_per_wg, int ksplit) {
@@ -170,7 +173,8 @@ gemm_pp_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, const
     if (grp) __builtin_amdgcn_s_barrier();   // a phase behind
 
     constexpr int OUT_ELT = EPI == EPI_SWIGLU ? 2 : 4;
-    __amdgpu_buffer_rsrc_t obuf = __builtin_amdgcn_make_buffer_rsrc(outv, 0, int(size_t(M) * N * OUT_ELT), 0x00020000);
+    // ODD: from the word that the result's first element shares
+    __amdgpu_buffer_rsrc_t obuf = __builtin_amdgcn_make_buffer_rsrc((char*)outv - (ODD ? 2 : 0), 0, int(size_t(M) * N * OUT_ELT) + (ODD ? 2 : 0), 0x00020000);
     // The K loop of an item of class nj (a constant at each of the three call sites)
     auto k_loop = [&](auto nj_tag, const int nk) __attribute__((always_inline)) {
         constexpr int nj = decltype(nj_tag)::value;
@@ -236,9 +240,19 @@ gemm_pp_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, const
                 const auto r0 = __builtin_amdgcn_permlane16_swap(x[0], y[0], false, false), r1 = __builtin_amdgcn_permlane16_swap(x[1], y[1], false, false);
                 return u32x4{r0[0], r1[0], r0[1], r1[1]};
             };
-            const int col = col_units * UNIT + grp * nj * 8 + 16 * (lq & 1) + 8 * (lq >> 1);
+            const int col0 = col_units * UNIT + grp * nj * 8, col = col0 + 16 * (lq & 1) + 8 * (lq >> 1);
             pp_each<4>([&](auto it) {
                 const int row = m0 + wm * 64 + 16 * it.value;
+                if constexpr (ODD) {
+                    pp_each<nj / 2>([&](auto pt) {
+                        const u32x2 x = pair(it, pt);
+                        const unsigned at = unsigned((row + l16) * N + col0 + 16 * pt.value + 4 * lq) * 2u + 2u;
+                        __builtin_amdgcn_raw_buffer_store_b16((unsigned short)x[0], obuf, at, 0, 0);
+                        __builtin_amdgcn_raw_buffer_store_b32(x[0] >> 16 | x[1] << 16, obuf, at + 2, 0, 0);
+                        __builtin_amdgcn_raw_buffer_store_b16((unsigned short)(x[1] >> 16), obuf, at + 6, 0, 0);
+                    });
+                    return;
+                }
                 const u32x4 x = two(it, std::integral_constant<int, 0>{});
                 if constexpr (nj == 8) {   // whole 128-byte lines: eight rows in one store, the other eight in the next
                     const u32x4 y = two(it, std::integral_constant<int, 2>{});
@@ -254,7 +268,7 @@ gemm_pp_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, const
                     __builtin_amdgcn_raw_buffer_store_b128(x, obuf, unsigned((row + l16) * N + col) * 2u, 0, 0);
                     if constexpr (nj == 6)
                         __builtin_amdgcn_raw_buffer_store_b64(pair(it, std::integral_constant<int, 2>{}), obuf,
-                                                              unsigned((row + l16) * N + col_units * UNIT + grp * nj * 8 + 32 + 4 * lq) * 2u, 0, 0);
+                                                              unsigned((row + l16) * N + col0 + 32 + 4 * lq) * 2u, 0, 0);
                 }
             });
         } else {
@@ -324,26 +338,28 @@ gemm_pp_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, const
 
 
 // A whole number of rounds over the CUs: every workgroup takes `rounds` items (the last may take one less).
-template <int EPI>
+template <int EPI, bool ODD = false>
 static hipError_t launch_pp(const bf16_t* A, const bf16_t* W, const bf16_t* W2, void* out, int M, int N, int K, const P256Plan& plan,
                             int ks, hipStream_t st) {
     const int tiles_m = (M + 255) / 256, nb = tiles_m * (plan.n8 + plan.n6 + plan.n4) * ks;
-    if (nb == 0 || (uintptr_t(out) & 15)) return hipErrorInvalidValue;
+    if (nb == 0 || (uintptr_t(out) & 3) != (ODD ? 2 : 0)) return hipErrorInvalidValue;
     const int rounds = (nb + 255) / 256, wgs = (nb + rounds - 1) / rounds;
     static bool attr_set = false;   // one flag per instantiation
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void*)gemm_pp_kernel<EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, PP_LDS);
+        hipError_t e = hipFuncSetAttribute((const void*)gemm_pp_kernel<EPI, ODD>, hipFuncAttributeMaxDynamicSharedMemorySize, PP_LDS);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    hipLaunchKernelGGL(gemm_pp_kernel<EPI>, dim3(wgs), dim3(512), PP_LDS, st, A, W, W2, out, M, N, K, tiles_m, plan, rounds, ks);
+    hipLaunchKernelGGL((gemm_pp_kernel<EPI, ODD>), dim3(wgs), dim3(512), PP_LDS, st, A, W, W2, out, M, N, K, tiles_m, plan, rounds, ks);
     return hipGetLastError();
 }
 
 hipError_t launch_gemm_pp(int epi, const bf16_t* A, const bf16_t* W, const bf16_t* W2, void* out, int M, int N, int K,
                           const P256Plan& plan, int ks, hipStream_t st) {
     switch (epi) {
-        case EPI_SWIGLU: return launch_pp<EPI_SWIGLU>(A, W, W2, out, M, N, K, plan, 1, st);
+        case EPI_SWIGLU:
+            if (uintptr_t(out) & 2) return launch_pp<EPI_SWIGLU, true>(A, W, W2, out, M, N, K, plan, 1, st);
+            return launch_pp<EPI_SWIGLU>(A, W, W2, out, M, N, K, plan, 1, st);
         case EPI_RESIDUAL_F32: return launch_pp<EPI_RESIDUAL_F32>(A, W, W2, out, M, N, K, plan, 1, st);
         case EPI_STORE_F32: return launch_pp<EPI_STORE_F32>(A, W, W2, out, M, N, K, plan, ks, st);
     }

@@ -1,6 +1,6 @@
 """bf16 products of items of 256 rows on the kernel with eight waves in turn: one slice of K, two and three, the line between it
 and the four-wave kernel (100 slices), panels of every width, ragged rows, several items to a workgroup, K ranges of unequal
-length, and results that are not 16-byte aligned (which a tile kernel forms)."""
+length, and results that are not 16-byte aligned."""
 import pytest
 
 import synth_inputs as si
@@ -59,18 +59,38 @@ def test_gemm_k_ranges_of_items_of_256_rows(M, N, K, ranges):
     assert _rel(eng.op_gemm_residual(a, w, x0.clone()), x0.double() + want) < tol
 
 
-@pytest.mark.parametrize("offset", [1, 2, 4])
-def test_results_off_16_bytes(offset):
+# Results that start on any element: the same bits as on 16 bytes, and nothing beside them.  The first shape goes to these
+# kernels unforced, in panels of 256 and 192; the others have panels of 128 and ragged rows, two rounds of items, and (192 and
+# 128 wide) the 100 slices from which on plain stores are on the eight waves too.
+@pytest.mark.parametrize("M,N,K,forced", [(1024, 14336, 128, False), (300, 384, 192, True), (700, 33280, 64, True), (1024, 10240, 6400, True)])
+@pytest.mark.parametrize("offset", [1, 2, 3, 4])
+def test_results_off_16_bytes(M, N, K, forced, offset):
     import torch
-    M, N, K = 1024, 14336, 128     # a shape that goes to this kernel unforced
     eng = _engine()
-    a, w, w2, _ = _operands(eng, M, N, K)
-    want = eng.op_gemm_swiglu(a, w, w2)
-    buf = torch.zeros(M * N + 16, device="cuda", dtype=eng.tdtype)
-    torch.cuda.synchronize()
-    out = buf[offset:offset + M * N]
-    assert eng.lib.cake_op_gemm_swiglu(eng.ctx, a.data_ptr(), w.data_ptr(), w2.data_ptr(), out.data_ptr(), M, N, K) == 0
-    torch.cuda.synchronize()
-    # 16- instead of 32-deep MFMAs: sums in another order under one rounding to bf16
-    assert float((out.view(M, N).float() - want.float()).abs().max()) <= 2.0 ** -7 * float(want.float().abs().max())
-    assert float(buf[:offset].abs().max()) == 0 and float(buf[offset + M * N:].abs().max()) == 0
+    if not forced:
+        eng.set_tuning()
+    a, w, w2, x0 = _operands(eng, M, N, K)
+    ops = eng.lib
+
+    def swiglu(out):
+        return ops.cake_op_gemm_swiglu(eng.ctx, a.data_ptr(), w.data_ptr(), w2.data_ptr(), out.data_ptr(), M, N, K)
+
+    def residual(out):
+        return ops.cake_op_gemm_residual(eng.ctx, a.data_ptr(), w.data_ptr(), out.data_ptr(), M, N, K)
+
+    def store(out):
+        return ops.cake_op_gemm(eng.ctx, a.data_ptr(), w.data_ptr(), out.data_ptr(), M, N, K)
+
+    for op, dtype, start in ((swiglu, eng.tdtype, None), (residual, torch.float32, x0), (store, torch.float32, None)):
+        got = []
+        for off in (0, offset):
+            buf = torch.full((M * N + 16,), 7.0, device="cuda", dtype=dtype)
+            out = buf[off:off + M * N]
+            if start is not None:
+                out.copy_(start.flatten())
+            torch.cuda.synchronize()
+            assert op(out) == 0
+            eng.sync()
+            got.append(out.clone())
+            assert bool((buf[:off] == 7.0).all()) and bool((buf[off + M * N:] == 7.0).all())
+        assert torch.equal(got[0], got[1]), op.__name__
