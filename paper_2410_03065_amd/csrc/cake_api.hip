@@ -247,12 +247,13 @@ static int enqueue_prefill(cake_ctx* c, int tok_begin, int rows, const cake_kv* 
     // algorithmic work per launch: flops of the contraction; bytes = operands once + result once
     const uint64_t attn_flops = 4 * hq * (t0 * R + R * (R + 1) / 2);
     const uint64_t attn_bytes = (2 * R * hq + 2 * hkv * (t0 + R)) * e;
-    // A float32 product norms its input itself (not where a test asks for the plain kernels).
-    auto norms_itself = [&](const float* gain, const void* wa, const void* wb) {
-        return m.dtype == CAKE_F32 && c->tun.kernel_path == 0 && ((uintptr_t(gain) | uintptr_t(wa) | uintptr_t(wb)) & 15) == 0;
+    // A float32 product norms its input itself where that is shorter (and not where a test asks for the plain kernels).
+    auto norms_itself = [&](int epi, uint64_t N, const float* gain, const void* wa, const void* wb) {
+        return m.dtype == CAKE_F32 && c->tun.kernel_path == 0 && gemm_f32_norms_input(epi, c->max_chunk, int(N), int(d)) &&
+               ((uintptr_t(gain) | uintptr_t(wa) | uintptr_t(wb)) & 15) == 0;
     };
     const cake_layer_weights& first = c->layers[0];
-    const bool norm_first = !norms_itself(first.attn_norm, first.wqkv, nullptr);
+    const bool norm_first = !norms_itself(EPI_STORE_F32, nqkv, first.attn_norm, first.wqkv, nullptr);
     bool normed = false;   // the first layer's input
     KLAUNCH(c, CAKE_K_EMBED, 0, R * d * (e + 4 + (norm_first ? e : 0)),
             launch_prefill_begin(m.dtype, {c->embed, c->x, rows, int(d), m.vocab, norm_first ? first.attn_norm : nullptr, c->h, m.rms_eps,
@@ -282,7 +283,7 @@ static int enqueue_prefill(cake_ctx* c, int tok_begin, int rows, const cake_kv* 
         const cake_layer_weights& w = c->layers[l];
         KvView view = make_view(c, kv, l);
         const uint64_t qkv_bytes = (R * d + nqkv * d) * e + R * nqkv * 4, gateup_bytes = (R * d + 2 * ff * d + R * ff) * e;
-        if (norms_itself(w.attn_norm, w.wqkv, nullptr)) {
+        if (norms_itself(EPI_STORE_F32, nqkv, w.attn_norm, w.wqkv, nullptr)) {
             KLAUNCH(c, CAKE_K_GEMM_QKV, 2 * R * nqkv * d, qkv_bytes, normed_product(EPI_STORE_F32, w.wqkv, nullptr, c->qkv, int(nqkv), w.attn_norm));
         } else {
             if (l > 0 || !normed) KLAUNCH(c, CAKE_K_RMSNORM, 0, R * d * (4 + e), norm(l > 0 ? p_down : none, w.attn_norm));
@@ -294,7 +295,7 @@ static int enqueue_prefill(cake_ctx* c, int tok_begin, int rows, const cake_kv* 
         KLAUNCH(c, CAKE_K_ATTENTION, attn_flops, attn_bytes, attention(c, c->q, c->ao, tok_begin, rows, view));
         KLAUNCH(c, CAKE_K_GEMM_O, 2 * R * d * hq, (R * hq + d * hq) * e + 2 * R * d * 4,
                 product(p_o, EPI_RESIDUAL_F32, c->ao, w.wo, c->x, d, hq));
-        if (norms_itself(w.ffn_norm, w.w_gate, w.w_up)) {
+        if (norms_itself(EPI_SWIGLU, ff, w.ffn_norm, w.w_gate, w.w_up)) {
             KLAUNCH(c, CAKE_K_GEMM_GATEUP, 4 * R * ff * d, gateup_bytes, normed_product(EPI_SWIGLU, w.w_gate, w.w_up, c->act, m.ffn_dim, w.ffn_norm));
         } else {
             KLAUNCH(c, CAKE_K_RMSNORM, 0, R * d * (4 + e), norm(p_o, w.ffn_norm));

@@ -62,7 +62,9 @@ hipError_t launch_attention_f32(const float* q, float* out, int n_q, int tok_beg
                                 hipStream_t st, const AttnWs& ws);
 // The RMSNorm in front of a product: its input is x / sqrt(mean(x^2) + eps) * gain (gain null: x as it is).
 struct GemvNorm { const float* gain; float eps; };
-// nm.gain: a is normed on the way (store and SwiGLU; gain 16-byte aligned like a, w and w2).
+// nm.gain: a is normed on the way (store and SwiGLU, where gemm_f32_norms_input says so for M rows or more; gain 16-byte
+// aligned like a, w and w2).
+bool gemm_f32_norms_input(int epi, int max_rows, int N, int K);
 hipError_t launch_gemm_f32(int epi, const float* a, const float* w, const float* w2, float* out, int M, int N, int K,
                            hipStream_t st, const GemvNorm& nm = {nullptr, 0.f});
 // Adds up the key ranges of a split attention launch: part[split][head][row][head_dim + 2] (O, reference of

@@ -23,7 +23,8 @@
 // NORM: `a` is the residual stream in front of an RMSNorm.  A row's norm is a factor of all its products, so the tile
 // multiplies x by the gain as it reads it, adds up the squares beside the products (the same quarters of K, added in the
 // same order in every tile) and scales its results by the row's factor at the end: no normed copy of the activations, and no
-// launch of 3 us before the product (256 rows of the tiny model, two layers: 127 -> 113 us with the four norms gone).
+// launch of 3 us before the product (256 rows of the tiny model, two layers: 131 -> 126 us).  Every tile does this again for its
+// rows, so it is for products that take less than such a launch more by it (gemm_f32_norms_input), on tiles whose waves divide K.
 #include "kernels.hpp"
 
 namespace cake {
@@ -43,6 +44,7 @@ gemm_f32_kernel(const float* __restrict__ a, const float* __restrict__ w, const 
     constexpr int KB = NM * T > 4 ? 1 : 2;           // 16-deep blocks per trip (one where 64 x 64 twice fill the registers)
     constexpr int BT = 16 * T * SP;                  // rows and columns of the workgroup's tile
     constexpr bool LDS_TOTAL = f32_lds_total(T, SP, EPI);
+    static_assert(!NORM || KW > 1, "a row's squares are added up through LDS");
     __shared__ float4 parts[KW > 1 ? (KW - 1) * NM * T * T * 64 : 1];
     __shared__ float squares[NORM ? 64 * T : 1];   // of a row in a quarter of K
     extern __shared__ __attribute__((aligned(16))) float4 total_lds[];   // LDS_TOTAL: [NM][T][T][256]
@@ -128,20 +130,12 @@ gemm_f32_kernel(const float* __restrict__ a, const float* __restrict__ w, const 
             }
         }
     };
-    float sq_total[T];   // KW = 1
     if constexpr (KW > 1) {
         sum_of(kw);
     } else {
 #pragma unroll 1
         for (int p = 0; p < 4; ++p) {
             sum_of(p);
-            if constexpr (NORM) {
-#pragma unroll
-                for (int i = 0; i < T; ++i) {
-                    sq_total[i] = p > 0 ? sq_total[i] + sq[i] : sq[i];
-                    sq[i] = 0.f;
-                }
-            }
 #pragma unroll
             for (int m = 0; m < NM; ++m)
 #pragma unroll
@@ -198,7 +192,7 @@ gemm_f32_kernel(const float* __restrict__ a, const float* __restrict__ w, const 
 #pragma unroll
         for (int i = 0; i < T; ++i) {
             const int t = 16 * i + l16;
-            const float s = KW > 1 ? squares[t] + squares[16 * T + t] + squares[32 * T + t] + squares[48 * T + t] : sq_total[i];
+            const float s = squares[t] + squares[16 * T + t] + squares[32 * T + t] + squares[48 * T + t];
             factor[i] = 1.0f / sqrtf(s / float(K) + eps);
         }
     }
@@ -241,6 +235,8 @@ static hipError_t launch_t(const float* a, const float* w, const float* w2, floa
     return hipGetLastError();
 }
 
+static long f32_tiles(int t, int M, int N) { return long((M + t - 1) / t) * ((N + t - 1) / t); }
+
 // The largest tile whose grid still gives most CUs a workgroup: 128 x 128 (64 x 64 per wave); 64 x 64, 32 x 32 or
 // 16 x 16 with the waves dividing K.  (512 x 4096 x 1024: 58 us on 64 x 64 tiles, 78 on 32 x 32, 72 generic.)
 // Where K is short, a tile's life is latency and 16 x 16 tiles in threes on a CU hide each other's (us, 16 and 32 square: 192
@@ -249,11 +245,26 @@ static hipError_t launch_t(const float* a, const float* w, const float* w2, floa
 template <int EPI, bool NORM>
 static hipError_t launch_epi(const float* a, const float* w, const float* w2, float* out, int M, int N, int K, const GemvNorm& nm,
                              hipStream_t st) {
-    auto tiles = [&](long t) { return ((M + t - 1) / t) * ((N + t - 1) / t); };
-    if (tiles(128) >= 192) return launch_t<4, 2, EPI, NORM>(a, w, w2, out, M, N, K, nm, st);
+    auto tiles = [&](int t) { return f32_tiles(t, M, N); };
+    if (tiles(128) >= 192) {
+        if constexpr (NORM) return hipErrorInvalidValue;
+        else return launch_t<4, 2, EPI, NORM>(a, w, w2, out, M, N, K, nm, st);
+    }
     if (tiles(64) >= 160) return launch_t<4, 1, EPI, NORM>(a, w, w2, out, M, N, K, nm, st);
     if (tiles(32) >= (K <= 1024 ? 224 : 160)) return launch_t<2, 1, EPI, NORM>(a, w, w2, out, M, N, K, nm, st);
     return launch_t<1, 1, EPI, NORM>(a, w, w2, out, M, N, K, nm, st);
+}
+
+// Whether the products of a context whose chunks have up to max_rows rows norm their input themselves: by the context and not
+// by the chunk, so that a token's bits do not depend on its step.  The norm's launch takes 6.5 to 8 us of a chunk; in
+// front of a plain product the squares and gains cost 10 % of it, more than that from about 3.5 GFLOP on, in front of SwiGLU next to
+// nothing on tiles of 64 and 4 to 6 % on tiles of 128.  us, norm apart and inside: QKV 500 rows of 1024 -> 1536 40 and 35, 256
+// of 2048 -> 3072 60 and 58, 64 of 4096 -> 6144 82 and 81, 500 of 1536 -> 2304 (3.5 GFLOP) 86 and 86, 500 of 2048 -> 3072
+// 106 and 109, 137 of 4096 -> 6144 182 and 193, 1024 of 4096 -> 6144 637 and 680; gate/up 64 rows of 1024 -> 2 x 2816 28 and
+// 25, 1024 of them 186 and 178, 256 of 4096 -> 2 x 11008 553 and 547, on 128: 1024 of 1536 -> 2 x 4096 249 and 256, 1024
+// of 4096 -> 2 x 11008 1781 and 1845.
+bool gemm_f32_norms_input(int epi, int max_rows, int N, int K) {
+    return f32_tiles(128, max_rows, N) < 192 && (epi == EPI_SWIGLU || 2.0 * max_rows * N * K < 3.5e9);
 }
 
 hipError_t launch_gemm_f32(int epi, const float* a, const float* w, const float* w2, float* out, int M, int N, int K, hipStream_t st,
