@@ -1,5 +1,6 @@
 """What a prefill begins with: token ids in the launch's arguments (up to 512 rows) and in device memory, rows whose first norm is
-in that launch (multiples of 1024) and others, float32 and bf16, positions away from 0, a captured step."""
+in that launch (multiples of 1024) and others, in pieces of 16 bytes and off them, float32 and bf16, positions away from 0, a
+captured step."""
 import pytest
 
 import synth_inputs as si
@@ -23,6 +24,30 @@ def test_ids_in_arguments_and_in_memory(shape, rows):
     eng.clear_pool()
     eng.bidirectional_prefill(toks, 640, 0.0, mode="compute_only")
     assert torch.equal(eng.pool, want) and float(want.abs().max()) > 0
+
+
+@pytest.mark.parametrize("d,rows", [(72, 3), (2568, 150), (2048, 150), (9216, 20)])
+def test_embedding_rows_on_and_off_16_bytes(d, rows):
+    """bf16 rows of 9, 321 (two trips, the second short), 256 and 1152 pieces; the table moved by one element and by 16 bytes."""
+    import ctypes
+    import paper_2410_03065_amd as cake
+    import torch
+    shape = si.ModelShape("begin-off", 1, d, 2, 1, 64, 256, 1000, "bf16")
+    eng = cake.Engine(shape, None, max_tokens=192, max_chunk=192, page_tokens=64, seed=2)
+    toks, want = si.make_tokens(rows, shape.vocab, seed=rows), None
+    for offset in (0, 1, 8):
+        table = torch.zeros(shape.vocab * d + 16, device="cuda", dtype=eng.tdtype)
+        table[offset:offset + shape.vocab * d] = eng.embed.flatten()
+        torch.cuda.synchronize()
+        eng.lib.cake_destroy(eng.ctx)
+        eng._weights.embed = table.data_ptr() + 2 * offset
+        desc = cake.model_desc(shape)
+        assert eng.lib.cake_create(ctypes.byref(eng.ctx), ctypes.byref(desc), ctypes.byref(eng._weights), 192, 192,
+                                   eng.compute_stream.cuda_stream, eng.copy_stream.cuda_stream) == 0
+        eng.clear_pool()
+        eng.prefill_chunk(toks, 0, rows)
+        want = eng.pool.clone() if want is None else want
+        assert torch.equal(eng.pool, want) and float(want.abs().max()) > 0
 
 
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: s.name)
