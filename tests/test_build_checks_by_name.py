@@ -1,5 +1,9 @@
 """The build-time check of a kernel that names its accumulators in asm (csrc/check_mfma_hazards.py --by-name): AGPRs as the
-compiler prints an asm statement's operands, and none outside such statements."""
+compiler prints an asm statement's operands, and none outside such statements; and the listings that the build checks are of the
+code that it links."""
+import os
+import sys
+
 import pytest
 
 from test_build_checks import chk
@@ -22,3 +26,23 @@ def test_named_accumulators_keep_their_distance():
     read = "\tv_accvgpr_read_b32 v9, a[0x6d]\n"
     assert chk.check_kernel("k", (mfma + "\n" + read).split("\n"))[1]
     assert not chk.check_kernel("k", (mfma + "\n\ts_nop 15\n\ts_nop 15\n" + read).split("\n"))[1]
+
+
+def test_listings_are_compiled_like_the_objects(monkeypatch):
+    sys.path.insert(0, os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+    import __graft_entry__ as entry
+    ran = []
+    monkeypatch.setattr(entry, "_run", ran.append)
+    for src in ("kernels_gemm.hip", "kernels_gemm_pp.hip"):
+        monkeypatch.setitem(entry.EXTRA_FLAGS, src, ["-DOF_" + src[:-4]])
+    entry.build()                       # every command goes to `ran` instead
+
+    def flags(cmd, how):
+        src = [a for a in cmd if a.endswith(".hip")][0]
+        return os.path.basename(src), [a for a in cmd if a not in how + [src, cmd[cmd.index("-o") + 1]]]
+
+    objects = dict(flags(c, ["-c"]) for c in ran if "-c" in c and any(a.endswith(".hip") for a in c))
+    listings = dict(flags(c, ["-S", "--cuda-device-only"]) for c in ran if "-S" in c)
+    assert sorted(listings) == ["kernels_gemm.hip", "kernels_gemm_pp.hip"]
+    for src, f in listings.items():
+        assert f == objects[src] and "-DOF_" + src[:-4] in f
