@@ -254,10 +254,10 @@ static int enqueue_prefill(cake_ctx* c, int tok_begin, int rows, const cake_kv* 
     };
     const cake_layer_weights& first = c->layers[0];
     const bool norm_first = !norms_itself(EPI_STORE_F32, nqkv, first.attn_norm, first.wqkv, nullptr);
-    bool normed = false;   // the first layer's input
-    KLAUNCH(c, CAKE_K_EMBED, 0, R * d * (e + 4 + (norm_first ? e : 0)),
-            launch_prefill_begin(m.dtype, {c->embed, c->x, rows, int(d), m.vocab, norm_first ? first.attn_norm : nullptr, c->h, m.rms_eps,
-                                           c->rope_cs, tok_begin, m.head_dim, m.rope_theta}, c->d_ids + tok_begin, ids_by_value, c->cs, &normed));
+    const PrefillBegin begin = {c->embed, c->x, rows, int(d), m.vocab, norm_first ? first.attn_norm : nullptr, c->h, m.rms_eps,
+                                c->rope_cs, tok_begin, m.head_dim, m.rope_theta};
+    const bool normed = prefill_begin_norms(begin);   // the first layer's input
+    KLAUNCH(c, CAKE_K_EMBED, 0, R * d * (e + 4 + (normed ? e : 0)), launch_prefill_begin(m.dtype, begin, c->d_ids + tok_begin, ids_by_value, c->cs));
     // A product may leave its K ranges in the split workspace for the kernel after it, which reads them before anything
     // else is put there: QKV for the rotary step, O and down for the norm (the last layer's down for a sum of its own).
     const bool rope_adds = (uintptr_t(kv->pool) & 15) == 0;

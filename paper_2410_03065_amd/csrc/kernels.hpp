@@ -25,7 +25,7 @@ enum GemmEpilogue { EPI_STORE_F32 = 0, EPI_RESIDUAL_F32 = 1, EPI_SWIGLU = 2 };
 
 // ---- generic kernels (any supported shape) ----
 // What a prefill begins with, in one launch: x = the rows' embeddings, cs = the rotary table of positions tok_begin ..; with a
-// gain also h = the RMSNorm of x where d and the alignment allow it (*normed says whether).  ids: device memory, or
+// gain also h = the RMSNorm of x where d and the alignment allow it (prefill_begin_norms).  ids: device memory, or
 // ids_by_value (at most TokenIds::MAX rows).
 struct TokenIds { static constexpr int MAX = 512; int32_t v[MAX]; };   // 2 KB of a launch's 4 KB of arguments
 struct PrefillBegin {
@@ -33,7 +33,8 @@ struct PrefillBegin {
     const float* gain; void* h; float eps;
     float* cs; int tok_begin, head_dim; float theta;
 };
-hipError_t launch_prefill_begin(int dtype, const PrefillBegin& b, const int32_t* ids, const TokenIds* ids_by_value, hipStream_t st, bool* normed);
+bool prefill_begin_norms(const PrefillBegin& b);
+hipError_t launch_prefill_begin(int dtype, const PrefillBegin& b, const int32_t* ids, const TokenIds* ids_by_value, hipStream_t st);
 hipError_t launch_rmsnorm(int dtype, const float* x, const float* gain, void* out, int rows, int d,
                           float eps, hipStream_t st);
 hipError_t launch_rope_table(float* cs, int tok_begin, int rows, int head_dim, float theta,

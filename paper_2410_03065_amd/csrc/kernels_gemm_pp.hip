@@ -240,13 +240,13 @@ gemm_pp_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, const
                 const auto r0 = __builtin_amdgcn_permlane16_swap(x[0], y[0], false, false), r1 = __builtin_amdgcn_permlane16_swap(x[1], y[1], false, false);
                 return u32x4{r0[0], r1[0], r0[1], r1[1]};
             };
-            const int col0 = col_units * UNIT + grp * nj * 8, col = col0 + 16 * (lq & 1) + 8 * (lq >> 1);
+            const int col = col_units * UNIT + grp * nj * 8 + 16 * (lq & 1) + 8 * (lq >> 1);
             pp_each<4>([&](auto it) {
                 const int row = m0 + wm * 64 + 16 * it.value;
                 if constexpr (ODD) {
                     pp_each<nj / 2>([&](auto pt) {
                         const u32x2 x = pair(it, pt);
-                        const unsigned at = unsigned((row + l16) * N + col0 + 16 * pt.value + 4 * lq) * 2u + 2u;
+                        const unsigned at = unsigned((row + l16) * N + col_units * UNIT + grp * nj * 8 + 16 * pt.value + 4 * lq) * 2u + 2u;
                         __builtin_amdgcn_raw_buffer_store_b16((unsigned short)x[0], obuf, at, 0, 0);
                         __builtin_amdgcn_raw_buffer_store_b32(x[0] >> 16 | x[1] << 16, obuf, at + 2, 0, 0);
                         __builtin_amdgcn_raw_buffer_store_b16((unsigned short)(x[1] >> 16), obuf, at + 6, 0, 0);
@@ -268,7 +268,7 @@ gemm_pp_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, const
                     __builtin_amdgcn_raw_buffer_store_b128(x, obuf, unsigned((row + l16) * N + col) * 2u, 0, 0);
                     if constexpr (nj == 6)
                         __builtin_amdgcn_raw_buffer_store_b64(pair(it, std::integral_constant<int, 2>{}), obuf,
-                                                              unsigned((row + l16) * N + col0 + 32 + 4 * lq) * 2u, 0, 0);
+                                                              unsigned((row + l16) * N + col_units * UNIT + grp * nj * 8 + 32 + 4 * lq) * 2u, 0, 0);
                 }
             });
         } else {

@@ -188,10 +188,11 @@ hipError_t launch_rope_table(float* cs, int tok_begin, int rows, int head_dim, f
 
 // ------------------------------------------------------------------ what a prefill begins with
 // One launch: the rows' embeddings (x), their first RMSNorm (h; NV 1024-element pieces of a row, NV = 0: no norm, NV = -1: no
-// norm, bf16 rows read in pieces of 16 bytes; 137 rows of 3584 6.6 -> 4.0 us, 1024 rows 12.7 -> 11.2) and, by the workgroups after the rows', the rotary table.  They were three launches of 2 to 10 us at the start of a step, when the host
-// is not ahead of the GPU yet.  Token ids: device memory, or (TokenIds) the launch's own arguments, which saves a short step
-// the copy in front of it.  Two layers, us: 137 rows of the Llama3-8B shape 346 -> 335, 512 rows of the small model with heads
-// of 64 313 -> 299, 256 rows of the tiny model 126 -> 119.
+// norm, bf16 rows read in pieces of 16 bytes; 137 rows of 3584 6.6 -> 4.0 us, 1024 rows 12.7 -> 11.2) and, by the workgroups
+// after the rows', the rotary table.  They were three launches of 2 to 10 us at the start of a step, when the host is not
+// ahead of the GPU yet.  Token ids: device memory, or (TokenIds) the launch's own arguments, which saves a short step the copy
+// in front of it.  Two layers, us: 137 rows of the Llama3-8B shape 346 -> 335, 512 rows of the small model with heads of 64
+// 313 -> 299, 256 rows of the tiny model 126 -> 119.
 struct IdsInMemory {
     const int32_t* p;
     __device__ int32_t operator[](int row) const { return p[row]; }
@@ -270,16 +271,19 @@ static hipError_t launch_begin_any(const PrefillBegin& b, bool norm, const Ids& 
     return hipGetLastError();
 }
 
-hipError_t launch_prefill_begin(int dtype, const PrefillBegin& b, const int32_t* ids, const TokenIds* ids_by_value, hipStream_t st, bool* normed) {
-    *normed = false;
+// whole pieces of 1024 elements, 16 bytes of x, h and the gains at once (8 of a bf16 table)
+bool prefill_begin_norms(const PrefillBegin& b) {
+    return b.gain && b.d % 1024 == 0 && b.d <= 8192 && ((uintptr_t(b.table) | uintptr_t(b.x) | uintptr_t(b.gain) | uintptr_t(b.h)) & 15) == 0;
+}
+
+hipError_t launch_prefill_begin(int dtype, const PrefillBegin& b, const int32_t* ids, const TokenIds* ids_by_value, hipStream_t st) {
     if (b.rows <= 0) return hipSuccess;
     if (ids_by_value && b.rows > TokenIds::MAX) return hipErrorInvalidValue;
-    // whole pieces of 1024 elements, 16 bytes of x, h and the gains at once (8 of a bf16 table)
-    *normed = b.gain && b.d % 1024 == 0 && b.d <= 8192 && ((uintptr_t(b.table) | uintptr_t(b.x) | uintptr_t(b.gain) | uintptr_t(b.h)) & 15) == 0;
+    const bool norm = prefill_begin_norms(b);
     if (ids_by_value)
-        return dtype == 0 ? launch_begin_any<float>(b, *normed, IdsInArguments{*ids_by_value}, st)
-                          : launch_begin_any<bf16_t>(b, *normed, IdsInArguments{*ids_by_value}, st);
-    return dtype == 0 ? launch_begin_any<float>(b, *normed, IdsInMemory{ids}, st) : launch_begin_any<bf16_t>(b, *normed, IdsInMemory{ids}, st);
+        return dtype == 0 ? launch_begin_any<float>(b, norm, IdsInArguments{*ids_by_value}, st)
+                          : launch_begin_any<bf16_t>(b, norm, IdsInArguments{*ids_by_value}, st);
+    return dtype == 0 ? launch_begin_any<float>(b, norm, IdsInMemory{ids}, st) : launch_begin_any<bf16_t>(b, norm, IdsInMemory{ids}, st);
 }
 
 // ------------------------------------------------------------------ rotary + KV page write

@@ -62,7 +62,7 @@ def test_gemm_k_ranges_of_items_of_256_rows(M, N, K, ranges):
 # Results that start on any element: the same bits as on 16 bytes, and nothing beside them.  The first shape goes to these
 # kernels unforced, in panels of 256 and 192; the others have panels of 128 and ragged rows, two rounds of items, and (192 and
 # 128 wide) the 100 slices from which on plain stores are on the eight waves too.
-@pytest.mark.parametrize("M,N,K,forced", [(1024, 14336, 128, False), (300, 384, 192, True), (700, 33280, 64, True), (1024, 10240, 6400, True)])
+@pytest.mark.parametrize("M,N,K,forced", [(1024, 14336, 1024, False), (300, 384, 192, True), (700, 33280, 64, True), (1024, 10240, 6400, True)])
 @pytest.mark.parametrize("offset", [1, 2, 3, 4])
 def test_results_off_16_bytes(M, N, K, forced, offset):
     import torch

@@ -77,6 +77,21 @@ def test_first_norm_and_rotary_table(shape):
     assert float((got - want).abs().max() / want.abs().max()) < tol
 
 
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: s.name)
+def test_bytes_of_the_first_launch(shape):
+    """The profile counts the normed rows in the launch that writes them: the begin of a bf16 prefill whose rows are whole pieces
+    of 1024, the norm's own launch elsewhere, no launch where the product norms its input (float32)."""
+    import paper_2410_03065_amd as cake
+    eng = cake.Engine(shape, None, max_tokens=128, max_chunk=128, page_tokens=64, seed=2)
+    eng.profile_enable(True)
+    rows, d, e = 100, shape.d_model, shape.elem_bytes
+    eng.prefill_chunk(si.make_tokens(rows, shape.vocab, seed=1), 0, rows)
+    got = eng.profile_read()
+    inside = shape.dtype == "bf16" and d % 1024 == 0
+    assert got["embed"]["bytes"] == rows * d * (e + 4 + (e if inside else 0))
+    assert got["rmsnorm"]["bytes"] == rows * d * (4 + e) * (0 if shape.dtype == "f32" else 1 if inside else 2)
+
+
 def test_captured_step_reads_its_ids_anew():
     """In a captured stream the ids stay a copy: a replay takes what the caller's array then holds."""
     import paper_2410_03065_amd as cake
