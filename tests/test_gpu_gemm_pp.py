@@ -29,10 +29,12 @@ def _rel(got, want):
 
 
 # Sums: float32 over K, 2e-6 of the largest value up to K = 256 and in proportion beyond.  SwiGLU: one rounding to bf16, and 1e-6
-# of the largest value for the sums in front of it.
+# of the largest value for the sums in front of it.  A plain product of under 100 slices is the four-wave kernel's and a residual one
+# the eight waves': the same bits into a result of zeros.  (N of 192, 320 and 448: SwiGLU only, plain ones take the generic kernel.)
 @pytest.mark.parametrize("M,N,K", [
     (1, 128, 64), (128, 128, 128), (129, 192, 192), (255, 256, 64), (257, 320, 128), (256, 448, 192),
     (300, 384, 6336), (300, 384, 6400), (511, 640, 6464),                                                # 99, 100 and 101 slices
+    (1024, 10240, 6400), (1000, 14336, 6464),                              # plain panels of 192 and 128, of 256 and 192 at 100 and 101
     (1000, 16640, 64), (1024, 14336, 128), (700, 33280, 192)])                                           # two rounds and more
 def test_gemm_items_of_256_rows(M, N, K):
     import torch
@@ -44,6 +46,8 @@ def test_gemm_items_of_256_rows(M, N, K):
     assert _rel(got, want) < tol
     assert torch.equal(got, eng.op_gemm(a, w))
     assert _rel(eng.op_gemm_residual(a, w, x0.clone()), x0.double() + want) < tol
+    if N % 128 == 0:
+        assert torch.equal(eng.op_gemm_residual(a, w, torch.zeros_like(x0)), got)
     want = torch.nn.functional.silu(want) * (a.double() @ w2.double().t().contiguous())
     got = eng.op_gemm_swiglu(a, w, w2).double()
     assert bool(((got - want).abs() <= 2.0 ** -8 * 1.01 * want.abs() + 1e-6 * want.abs().max()).all())
