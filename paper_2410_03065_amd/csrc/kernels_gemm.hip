@@ -380,17 +380,18 @@ static bool ksplit_ok(int cfg, int ks, int epi, int M, int N, int K, const GemmS
     return tiles <= ws->n_counters && size_t(tiles) * ks * c.bm * c.bn * sizeof(float) <= ws->part_bytes;
 }
 static GemmChoice gemm_pick(int epi, int M, int N, int K, const GemmSplitWs* ws, double* cost_out = nullptr) {
-    static const double eff[GCFG_COUNT] = {1.0, 0.60, 0.62, 0.80, 0.40, 0.65, 1.11, 0.72};   // measured TFLOP/s per busy CU, relative to 256x256
+    // Measured TFLOP/s per busy CU, relative to 256x256; GCFG_P256 on four waves, which store plain products of under 100 slices.
+    // The eight waves in turn that take the others, gate/up among them, are 5 to 11 % faster over 64 slices, 7 to 20 over 32.
+    static const double eff[GCFG_COUNT] = {1.0, 0.60, 0.62, 0.80, 0.40, 0.65, 1.11, 0.72};
     GemmChoice best{GCFG_128x128, 1};
     double best_cost = 1e30;
     for (int cfg = GCFG_COUNT - 1; cfg >= 0; --cfg) {
         if (!gemm_cfg_ok(cfg, epi, M, N, K)) continue;
         const GemmCfg& c = kGemmCfg[cfg];
         if (cfg == GCFG_P256) {
-            // The persistent kernel needs a grid that fills the chip.  With K split, its parts (256 KB per workgroup)
-            // go through memory to a second kernel, about 45 us for 256 of them: measured 487 us against 443 for the
-            // eight-wave 256 x 256 kernel on 1024 x 8192 x 28672 in two ranges, 155 against 140 for 128 x 128 tiles
-            // on 1024 x 4096 x 14336 in four.  So it is chosen unsplit only (the split path stays for forced use).
+            // The persistent kernels need a grid that fills the chip.  They are chosen unsplit only: with K split each range
+            // becomes an output of its own, and products for which that pays go there by gemm_parts_plan (the path here
+            // stays for forced use).
             const int tiles_m = (M + 255) / 256;
             const P256Plan plan = p256_plan(epi, tiles_m, N);
             const long items = long(tiles_m) * (plan.n8 + plan.n6 + plan.n4);
@@ -419,7 +420,7 @@ static GemmChoice gemm_pick(int epi, int M, int N, int K, const GemmSplitWs* ws,
 // Panel widths of the persistent kernel for N columns and `tiles_m` row bands: counts of 8-, 6- and 4-tile panels
 // with 8 n8 + 6 n6 + 4 n4 = N / unit that minimise the time of the busiest workgroup: items go out widest first,
 // one per workgroup and round, so workgroup 0 takes the widest item of every round.  A narrow item is not
-// faster in proportion (measured, 256 items over K = 4096: 108 us at 256 wide, 86 to 100 at 192, 70 to 74 at 128,
+// faster in proportion (measured on four waves, 256 items over K = 4096: 108 us at 256 wide, 86 to 100 at 192, 70 to 74 at 128,
 // and 1.2 us per slice at 128 wide over a long K against 1.46 at 256: the loads, reads and barriers of a slice
 // stay the same), and every item costs an epilogue.
 static double p256_plan_cost(int tiles_m, int n8, int n6, int n4) {
@@ -476,10 +477,13 @@ bool gemm_order_fixed(int epi, int max_rows, int N, int K, const GemmSplitWs* ws
 }
 
 // Items of 256 rows: on the eight waves in turn (kernels_gemm_pp.hip), but for float32 stores of items of under 100 slices, where
-// its two phases of one group alone weigh as much as it gains.  us, four waves / in turn, each with the pass that adds the ranges
-// up: 224 slices of 256 items 359.7 and 357.4, 128 of 128 items 163 and 157, 112 of 256 items 203.5 and 202.2, 108 of 160 items
-// 141.9 and 138.2; 75 of 192 items 111.2 and 110.4, 72 of 240 items 118.1 and 119.0, 64 of 256 items 119.6 and 120.9, 56 of 256
-// items 103.2 and 104.6, 43 of 128 items 67.0 and 68.2, 16 of 128 items 34.2 and 36.5.  Both give the same bits.
+// its two phases of one group alone weigh as much as it gains.  Residual products and SwiGLU gain at every length.  us, four
+// waves / in turn: residual 1024 rows -> 8192 over 1 slice 23.5 and 13.6, 16 slices 35 and 27, 32 slices 48 and 41; -> 16384 over 64
+// slices 125 and 112, 128 slices 222 and 203; SwiGLU 1024 rows -> 14336 over 1 slice 23.5 and 14.4, 16 slices 64 and 53, 64
+// slices 182 and 171.  Stores, each with the pass that adds the ranges up: 224 slices of 256 items 359.7 and 357.4, 128 of 128
+// items 163 and 157, 112 of 256 items 203.5 and 202.2, 108 of 160 items 141.9 and 138.2; 75 of 192 items 111.2 and 110.4, 72 of
+// 240 items 118.1 and 119.0, 64 of 256 items 119.6 and 120.9, 56 of 256 items 103.2 and 104.6,
+// 43 of 128 items 67.0 and 68.2, 16 of 128 items 34.2 and 36.5.  Both give the same bits.
 template <int EPI>
 static hipError_t launch_p256(const bf16_t* A, const bf16_t* W, const bf16_t* W2, void* out, int M, int N, int K, const P256Plan& plan,
                               int ks, hipStream_t st) {
@@ -576,7 +580,7 @@ static double plain_launch_us(const GemmChoice& ch, int epi, int M, int N, int K
                                                {{0.693, 4.1, 0.0, 0.18}, {0.946, 0.0, 10.7, 0.49}},   // 128 x 192
                                                {{0.435, 3.5, 0.0, 1.02}, {0.401, 0.0, 9.4, 4.13}},    // 128 x 64
                                                {{0.566, 2.0, 0.0, 0.45}, {0.634, 0.0, 10.9, 0.82}},   // 128 x 128, waves along K
-                                               {{0.853, 7.5, 0.0, 0.48}, {0.853, 7.5, 45.0, 0.48}},   // persistent
+                                               {{0.853, 7.5, 0.0, 0.48}, {}},                         // persistent (four waves); gemm_pick leaves it unsplit
                                                {{0.693, 4.1, 0.0, 0.18}, {0.946, 0.0, 10.7, 0.49}}};  // 192 x 128 (gate/up only)
     const GemmCfg& c = kGemmCfg[ch.cfg];
     const Price& p = price[ch.cfg][ch.ksplit > 1];

@@ -199,7 +199,8 @@ gemm_pp_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, const
             }
             next(st[0], 0); next(st[1], 1);
             q4 = ring(q4 + 4);
-            // the operands are here, and for the next phase group 1's half of A two loads back
+            // The operands are here.  For the next phase: what group 0 requested a slice ago for group 1 (younger than that are
+            // the other half of those eight requests and this phase's), and group 1's requests of a slice ago.
             asm volatile("s_cmp_eq_u32 %0, 0\n\ts_cbranch_scc1 .Lpp_r%=\n\ts_waitcnt vmcnt(8)\n.Lpp_r%=:\n\ts_waitcnt vmcnt(12) lgkmcnt(0)\n\ts_barrier" ::"s"(grp) : "memory", "scc");
             __builtin_amdgcn_sched_barrier(0);
             // product phase
@@ -207,9 +208,9 @@ gemm_pp_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, const
                 constexpr int ks = n.value / (4 * nj), i = n.value / nj % 4, j = n.value % nj;
                 pp_mfma<8 * i + j>(b[ks][j], a[ks][i]);
             });
-            // For the next phase: group 0's requests of this slice but for the half of W two slices ahead, group 1's older
-            // ones.  One statement with the barrier (none after an item's last slice): as branches of the loop these
-            // would be laid out with copies of it.
+            // For the next phase: group 0's own half of W, the last of its requests of a slice ago (group 1 has waited for its
+            // own by now).  One statement with the barrier (none after an item's last slice): as branches of the loop
+            // these would be laid out with copies of it.
             asm volatile("s_cmp_lg_u32 %0, 0\n\ts_cbranch_scc1 .Lpp_w%=\n\ts_waitcnt vmcnt(8)\n.Lpp_w%=:\n\t"
                          "s_cmp_eq_u32 %1, 0\n\ts_cbranch_scc1 .Lpp_b%=\n\ts_barrier\n.Lpp_b%=:" ::"s"(grp), "s"(left - 1) : "memory", "scc");
             __builtin_amdgcn_sched_barrier(0);
